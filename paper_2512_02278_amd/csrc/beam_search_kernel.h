@@ -90,7 +90,8 @@ struct BeamSearch {
     static constexpr int G = Row::G;
     static constexpr int NCH = Row::NCH;
     static constexpr int RPS = 64 / G;                                // rows per gather step
-    static constexpr int U = NCH >= 8 ? 1 : (NCH >= 4 ? 2 : (NCH >= 2 ? 3 : 4));  // gather steps in flight
+    static constexpr int U = NCH >= 8 ? 1 : (NCH >= 4 ? 2 : NCH >= 2 ? 3 : G == 32 ? 8 : 4);  // gather steps in flight
+    static constexpr int UP = U <= 1 ? 1 : U <= 2 ? 2 : U <= 4 ? 4 : 8;                       // U or the next power of two
     static constexpr int BR = LPL >= 2 ? 2 : 1;                       // registers of a sort batch
     static constexpr int kInsertMax = 8;                // at most this many new keys are inserted one by one
 
@@ -256,13 +257,32 @@ struct BeamSearch {
             // one filter, one ballot and one store then serve all U steps (G >= U for every row variant).
             static_assert(G >= U, "one lane of a group per gather step");
             uint64_t mine = kInfKey;  // is not below `worst`, whatever that is
+            if constexpr (Row::kDtype == kU8) {
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                if (j0 + u * RPS >= m) break;
-                const int j = j0 + u * RPS + grp;
-                const uint32_t okey = row.key(x[u], lane);
-                const uint64_t packed = ((uint64_t)okey << 32) | (uint64_t)(id[u] << 1);  // ids are below 2^31
-                mine = (row.lg == u && j < m) ? packed : mine;
+                for (int u = 0; u < U; ++u) {
+                    if (j0 + u * RPS >= m) break;
+                    const int j = j0 + u * RPS + grp;
+                    const uint32_t okey = row.key(x[u], lane);
+                    const uint64_t packed = ((uint64_t)okey << 32) | (uint64_t)(id[u] << 1);  // ids are below 2^31
+                    mine = (row.lg == u && j < m) ? packed : mine;
+                }
+            } else {
+                // the U sums meet in one register: a float key ends in log2(G) additions and four instructions that
+                // make it ordered
+                float part[UP];
+                uint32_t my_id = 0;
+#pragma unroll
+                for (int u = 0; u < UP; ++u) part[u] = 0.0f;
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    if (j0 + u * RPS >= m) break;
+                    part[u] = row.partial(x[u]);
+                    asm volatile("" : "+v"(part[u]));  // here, not at its use: there it would keep every product's operands
+                    my_id = row.lg == u ? id[u] : my_id;
+                }
+                const uint32_t okey = Row::ordered(group_sums<G>(part, lane));
+                const int j = j0 + row.lg * RPS + grp;
+                if (row.lg < U && j < m) mine = ((uint64_t)okey << 32) | (uint64_t)(my_id << 1);
             }
             const bool keep = mine < worst;
             const uint64_t b = __ballot(keep);

@@ -36,6 +36,18 @@ __device__ __forceinline__ float ordered_to_float(uint32_t u) {
     return __builtin_bit_cast(float, u);
 }
 
+// a - b of the low (H = 0) or high halves, rounded once to fp32: what converting both and subtracting gives, in one
+// instruction instead of three (an fp16 L2 key is 4 instructions per pair of elements, from 8).
+template <int H>
+__device__ __forceinline__ float half_difference(uint32_t a, uint32_t b) {
+    float d;
+    if constexpr (H == 0)
+        asm("v_fma_mix_f32 %0, %1, 1.0, -%2 op_sel:[0,0,0] op_sel_hi:[1,0,1]" : "=v"(d) : "v"(a), "v"(b));
+    else
+        asm("v_fma_mix_f32 %0, %1, 1.0, -%2 op_sel:[1,0,1] op_sel_hi:[1,0,1]" : "=v"(d) : "v"(a), "v"(b));
+    return d;
+}
+
 template <int DT, int METRIC, int G_, int NCH_>
 struct RowOps {
     static constexpr int G = G_;
@@ -144,47 +156,38 @@ struct RowOps {
                 int32_t s = group_sum<G>((int32_t)qx, lane);
                 return (uint32_t)(-s) ^ 0x80000000u;  // signed order -> unsigned order
             }
-        } else if constexpr (DT == kF32) {
-            float acc = 0.0f;
-#pragma unroll
-            for (int c = 0; c < NCH; ++c) {
-                const uint32_t xs[4] = {x[c].x, x[c].y, x[c].z, x[c].w};
-                const uint32_t qs[4] = {q[c].x, q[c].y, q[c].z, q[c].w};
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const float a = __builtin_bit_cast(float, qs[i]), b = __builtin_bit_cast(float, xs[i]);
-                    if constexpr (METRIC == kL2) {
-                        const float d = a - b;
-                        acc = __builtin_fmaf(d, d, acc);
-                    } else {
-                        acc = __builtin_fmaf(a, b, acc);
-                    }
-                }
-            }
-            acc = group_sum<G>(acc, lane);
-            return float_to_ordered(METRIC == kL2 ? acc : -acc);
         } else {
-            float acc = 0.0f;
-#pragma unroll
-            for (int c = 0; c < NCH; ++c) {
-                const uint32_t xs[4] = {x[c].x, x[c].y, x[c].z, x[c].w};
-                const uint32_t qs[4] = {q[c].x, q[c].y, q[c].z, q[c].w};
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const half2_t a = __builtin_bit_cast(half2_t, qs[i]), b = __builtin_bit_cast(half2_t, xs[i]);
-                    if constexpr (METRIC == kL2) {
-                        const float d0 = (float)a.x - (float)b.x, d1 = (float)a.y - (float)b.y;
-                        acc = __builtin_fmaf(d0, d0, acc);
-                        acc = __builtin_fmaf(d1, d1, acc);
-                    } else {
-                        acc = __builtin_amdgcn_fdot2(a, b, acc, false);  // fp16 products, fp32 accumulate
-                    }
-                }
-            }
-            acc = group_sum<G>(acc, lane);
-            return float_to_ordered(METRIC == kL2 ? acc : -acc);
+            return ordered(group_sum<G>(partial(x), lane));
         }
     }
+
+    // Float types: acc plus what one dword of a query and of a row adds to the key.
+    static __device__ __forceinline__ float step(float acc, uint32_t qs, uint32_t xs) {
+        if constexpr (DT == kF32) {
+            const float a = __builtin_bit_cast(float, qs), b = __builtin_bit_cast(float, xs);
+            const float d = a - b;
+            return METRIC == kL2 ? __builtin_fmaf(d, d, acc) : __builtin_fmaf(a, b, acc);
+        } else if constexpr (METRIC == kL2) {
+            const float d0 = half_difference<0>(qs, xs), d1 = half_difference<1>(qs, xs);
+            return __builtin_fmaf(d1, d1, __builtin_fmaf(d0, d0, acc));
+        } else {
+            // fp16 products, fp32 accumulate
+            return __builtin_amdgcn_fdot2(__builtin_bit_cast(half2_t, qs), __builtin_bit_cast(half2_t, xs), acc, false);
+        }
+    }
+
+    // Float types: this lane's share of the key of a row whose pieces are in x, before the group's sum.
+    __device__ __forceinline__ float partial(const u32x4 (&x)[NCH]) const {
+        float acc = 0.0f;
+#pragma unroll
+        for (int c = 0; c < NCH; ++c)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) acc = step(acc, q[c][i], x[c][i]);
+        return acc;
+    }
+
+    // Float types: the ordered key of a group's sum.
+    static __device__ __forceinline__ uint32_t ordered(float sum) { return float_to_ordered(METRIC == kL2 ? sum : -sum); }
 
     // Ordered key -> the value written to out_dists (bit pattern of int32 or float).
     static __device__ __forceinline__ uint32_t key_to_output(uint32_t okey) {

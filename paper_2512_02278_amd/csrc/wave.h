@@ -82,6 +82,26 @@ __device__ __forceinline__ T group_sum(T v, int lane) {
     }
 }
 
+// Sums of Q values (a power of two) over groups of G lanes, in group_sum's order: every lane ends up with the sum
+// of value number lane % Q.  A lane keeps half of the values at each of the first log2(Q) levels, so a value costs
+// about three instructions instead of log2(G) and more.
+template <int G, int M = 1, class T, int Q>
+__device__ __forceinline__ T group_sums(const T (&v)[Q], int lane) {
+    if constexpr (Q == 1) {
+        return group_sum<G, M>(v[0], lane);
+    } else {
+        static_assert(Q <= G, "a lane keeps one value");
+        T w[Q / 2];
+        const bool odd = (lane & M) != 0;
+#pragma unroll
+        for (int i = 0; i < Q / 2; ++i) {
+            const T keep = odd ? v[2 * i + 1] : v[2 * i], send = odd ? v[2 * i] : v[2 * i + 1];
+            w[i] = keep + __builtin_bit_cast(T, xor_lane_dpp<M>(__builtin_bit_cast(uint32_t, send), lane));
+        }
+        return group_sums<G, M * 2>(w, lane);
+    }
+}
+
 __device__ __forceinline__ void order2(uint64_t& lo, uint64_t& hi) {
     uint64_t a = lo, b = hi;
     lo = a < b ? a : b;

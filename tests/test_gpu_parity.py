@@ -866,3 +866,17 @@ def test_text_like_config_at_full_size_sampled_against_oracle(oracle, torch_cuda
     torch = torch_cuda
     full_size_float_config(oracle, torch, torch.float16, "f16", 1, 20_000_000, 8192, 768, 64, 50_000, 100, 256, 8, 200,
                            sample=300, recall_floor=0.95)
+
+
+@pytest.mark.parametrize("dt,dims", [("f16", (136, 200, 256, 264, 512, 520)), ("f32", (100, 128, 132, 256, 260))])
+@pytest.mark.parametrize("metric", [0, 1])
+def test_float_rows_at_the_edges_of_the_32_lane_variants(oracle, torch_cuda, dt, dims, metric):
+    """Rows just above 256 bytes, and on both sides of 512 and 1024 bytes: the variants of one, two and three (four)
+    pieces per lane, with partly empty and with full last pieces."""
+    for dim in dims:
+        rng = np.random.default_rng(dim + metric)
+        x, _, _ = clustered(rng, 1500, dim, dt)
+        if metric == 1:
+            x = (x.astype(np.float64) / np.linalg.norm(x.astype(np.float64), axis=1, keepdims=True)).astype(NP_DT[dt])
+        check_float(oracle, torch_cuda, x, knn_graph(x, 16, metric), queries_near(rng, x, 60, dt), 10, 64, 3, 60, TOL[dt],
+                    MIN_IDENTICAL[dt], metric=metric, n_entry=32, seed=4)
