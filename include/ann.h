@@ -128,7 +128,12 @@ int ann_index_set_option(ann_index_t* handle, int option, int64_t value);
  * int32 for the cluster-grouped execution order) is allocated and released on `stream`; the
  * runtime may hold the calling thread in that allocation until the previous call on the stream has
  * finished (no wrong result follows from it; ann_search_static does not allocate).  On an
- * argument error nothing is launched and the outputs are untouched.  Calls on
+ * argument error nothing is launched and the outputs are untouched.  Batches over float rows with
+ * at least 8 to 16 queries per cluster (route_c == 1) are also grouped by cluster and may score whole
+ * clusters ahead of the search: the table of those keys lives in device memory of the handle,
+ * allocated by the first call that needs it (at most four blocks of 1 GiB, one per call in flight;
+ * given back by ann_free; no such block under stream capture or where none can be had: the search then
+ * gathers the rows, with the same results).  Calls on
  * different streams may share a handle.  A route id outside [0, n_clusters) (only possible
  * through ann_search_routed) names no cluster: it gives no entries, and a query whose routes
  * all do so returns padding.

@@ -12,6 +12,7 @@
 #include "ann.h"
 #include "combine.h"
 #include "graph_build.h"
+#include "key_table.h"
 #include "route_mfma.h"
 #include "route_mfma_u8.h"
 #include "schedule.h"
@@ -58,6 +59,87 @@ constexpr int64_t kMaxQueriesPerLaunch = 1 << 22;
 constexpr int kDefaultWindowBits = 8192, kMaxWindowBits = 1 << 17;
 // From this batch size on, a routed batch is executed grouped by cluster (schedule.hip).
 constexpr int64_t kMinQueriesForClusterOrder = 16384;
+// Bytes of key table one launch works on.
+constexpr int64_t kTableBytes = 1ll << 30;
+
+}  // namespace ann
+
+namespace ann {
+
+// Device memory for the key tables of a handle's calls, kept from call to call: allocated and released per call, even
+// from a pool that stays mapped, 300 MB held the calling thread for 0.5 ms.  At most kMost blocks of at most kTableBytes,
+// given back with the handle.  Any number of threads and streams: a block belongs to one call from take() to
+// give_back(), and a call waits on its own stream for the work of the block's previous user.
+struct TableBlocks {
+    static constexpr int kMost = 4;
+    struct Block {
+        void* memory = nullptr;
+        size_t bytes = 0;
+        hipEvent_t done = nullptr;     // after the last user's work
+        hipStream_t stream = nullptr;  // of the last user
+        bool taken = false;
+    };
+    std::mutex mutex;
+    Block blocks[kMost];
+
+    // A block of at least `bytes`, or null if there is no memory.
+    Block* take(size_t bytes, hipStream_t stream) {
+        std::lock_guard<std::mutex> lock(mutex);
+        Block *idle = nullptr, *same_stream = nullptr, *busy = nullptr, *replace = nullptr;
+        for (Block& b : blocks) {
+            if (b.taken) continue;
+            const bool done = !b.memory || hipEventQuery(b.done) == hipSuccess;
+            if (b.memory && b.bytes >= bytes) (done ? idle : b.stream == stream ? same_stream : busy) = &b;
+            else if (done && (!replace || b.bytes < replace->bytes)) replace = &b;  // an empty place before a block that is too small
+        }
+        (void)hipGetLastError();  // "not ready" is no error
+        Block* b = idle ? idle : same_stream;
+        if (!b && replace && grow(replace, bytes)) b = replace;
+        if (!b) b = busy;
+        if (!b || hipStreamWaitEvent(stream, b->done, 0) != hipSuccess) {
+            (void)hipGetLastError();
+            return nullptr;
+        }
+        b->taken = true;
+        return b;
+    }
+
+    // The call's work on the block has been enqueued on `stream`.
+    void give_back(Block* b, hipStream_t stream) {
+        std::lock_guard<std::mutex> lock(mutex);
+        // without the event nobody could tell when the work has ended: wait for it here
+        if (hipEventRecord(b->done, stream) != hipSuccess) (void)hipStreamSynchronize(stream);
+        b->stream = stream;
+        b->taken = false;
+    }
+
+    void release() {
+        for (Block& b : blocks) {
+            if (b.memory) (void)hipFree(b.memory);  // waits for searches still running
+            if (b.done) (void)hipEventDestroy(b.done);
+            b = Block();
+        }
+    }
+
+   private:
+    static bool grow(Block* b, size_t bytes) {
+        size_t rounded = size_t(16) << 20;
+        while (rounded < bytes) rounded *= 2;
+        if (b->memory) (void)hipFree(b->memory);
+        b->memory = nullptr;
+        b->bytes = 0;
+        if (!b->done && hipEventCreateWithFlags(&b->done, hipEventDisableTiming) != hipSuccess) {
+            b->done = nullptr;
+            return false;
+        }
+        if (hipMalloc(&b->memory, rounded) != hipSuccess) {
+            b->memory = nullptr;
+            return false;
+        }
+        b->bytes = rounded;
+        return true;
+    }
+};
 
 }  // namespace ann
 
@@ -74,6 +156,7 @@ struct ann_index {
     bool matrix_core_routing;
     int32_t* centroid_bias;  // DEVICE, owned: per-centroid term of the uint8 d=128 matrix-core routing, or null
     void* route_bias;        // DEVICE, owned: the same for the general matrix-core routing, or null
+    ann::TableBlocks tables;  // DEVICE, owned: memory for key tables
 };
 
 using namespace ann;
@@ -177,6 +260,7 @@ extern "C" int ann_free(ann_index_t* h) {
     h->magic = 0;
     if (h->centroid_bias) (void)hipFree(h->centroid_bias);
     if (h->route_bias) (void)hipFree(h->route_bias);
+    h->tables.release();
     delete h;
     return ANN_OK;
 }
@@ -313,13 +397,18 @@ size_t route_scratch_bytes(const ann_index_t* h, int64_t nq) {
     return slices > 1 ? padded256(sizeof(uint64_t) * (size_t)nq * slices * h->d.route_c) : 0;
 }
 
+bool grouped_order(const ann_index_t* h, int64_t nq, int table_stride) {
+    return h->d.entry_mode == ANN_ENTRY_ROUTED && h->cluster_order_min >= 0 && (nq >= h->cluster_order_min || table_stride > 0) &&
+           nq <= 2147483647ll;
+}
+
 // Bytes of temporaries a whole search call of nq queries takes (what Workspace::take hands out): the routes and
 // the routing's own temporaries unless the caller brings the routes, and the execution order of a large batch.
-size_t search_scratch_bytes(const ann_index_t* h, int64_t nq, bool routes_given) {
+size_t search_scratch_bytes(const ann_index_t* h, int64_t nq, bool routes_given, int table_stride) {
     if (h->d.entry_mode != ANN_ENTRY_ROUTED || nq <= 0) return 0;
     size_t need = 0;
     if (!routes_given) need += padded256(sizeof(int32_t) * (size_t)nq * h->d.route_c) + route_scratch_bytes(h, nq);
-    if (h->cluster_order_min >= 0 && nq >= h->cluster_order_min) need += padded256(sizeof(int32_t) * ((size_t)nq + h->d.n_clusters));
+    if (grouped_order(h, nq, table_stride)) need += padded256(sizeof(int32_t) * ((size_t)nq + h->d.n_clusters));
     return need;
 }
 
@@ -383,10 +472,42 @@ int default_team(const ann_index_t* h, int64_t nq) {
     return 1;                                         // 128-byte rows: a round's gathers are one instruction group
 }
 
+// Keys per query of the key table (key_table.h) this call searches with, 0 for a search that gathers every row.
+//
+// The table costs a product of every query with every row of its cluster; it saves the rows the search would gather,
+// about eight per list entry and at most the cluster.  Measured over rows of 256 to 1536 bytes, clusters of 300 to
+// 2 441 rows and lists of 64 to 256 entries, time without / with:
+//   * with 16 queries per cluster (8 for rows of 1 KB) and gathered bytes >= 0.8 x vector instructions of the products,
+//     0.85 .. 1.4 at 256 bytes, 1.2 .. 1.6 at 384 bytes, 1.2 .. 3.4 above;
+//   * with 4 queries per cluster 0.8 .. 1.1, and where few rows of large clusters are gathered (768-byte L2 rows, list of
+//     64, clusters of 2 441) 0.6 .. 0.8 at any batch size.
+// Rows below 256 bytes and clusters below 256 rows were not measured.
+int table_stride(const ann_index_t* h, int64_t nq, int itopk, int width, int max_iters, hipStream_t stream) {
+    if (h->d.entry_mode != ANN_ENTRY_ROUTED || h->d.route_c != 1 || h->d.dtype == ANN_U8 || h->row_bytes < 256) return 0;
+    // a fixed team, an order that is never grouped and a hash without bitmap ask for the search they describe
+    if (h->team != 0 || h->cluster_order_min < 0 || h->window_bits == 0) return 0;
+    const int64_t mean = h->d.n / h->d.n_clusters;
+    if (mean < 256 || nq > 2147483647ll || nq / h->d.n_clusters < (h->row_bytes >= 1024 ? 8 : 16)) return 0;
+    const int64_t parents = (int64_t)width * max_iters < itopk ? (int64_t)width * max_iters : itopk;
+    const int64_t gathered = 8 * parents < mean ? 8 * parents : mean;
+    const int64_t twice_products = (int64_t)h->d.dim * (h->d.dtype == ANN_F16 && h->d.metric == ANN_IP ? 1 : 4);
+    if (10 * gathered * h->row_bytes < 4 * twice_products * mean) return 0;
+    // half as long again as the mean cluster: rows beyond are gathered
+    int64_t stride = (mean + mean / 2 + 127) / 64 * 64;
+    if (stride > h->window_bits) stride = h->window_bits;
+    // a captured call keeps to what it would have allocated without a table
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &capture) != hipSuccess) {
+        (void)hipGetLastError();
+        return 0;
+    }
+    return capture == hipStreamCaptureStatusNone ? (int)stride : 0;
+}
+
 // Checks the arguments of a search and launches it; `route` is null for uniform entries.
 int search_impl(ann_index_t* h, const void* queries, int64_t nq, const int32_t* route, bool route_given, int k,
                 int itopk, int width, int max_iters, int32_t* out_ids, void* out_dists, int32_t* out_counters,
-                Workspace& ws) {
+                Workspace& ws, int stride) {
     hipStream_t stream = ws.stream;
     if (nq < 0) return fail(ANN_EINVAL, "ann_search: nq = %lld", (long long)nq);
     if (k < 1 || k > itopk) return fail(ANN_EINVAL, "ann_search: k = %d outside 1..itopk (%d)", k, itopk);
@@ -410,17 +531,28 @@ int search_impl(ann_index_t* h, const void* queries, int64_t nq, const int32_t* 
     }
     // routed batches that are large enough run grouped by cluster, for cache reuse
     int32_t* order = nullptr;
-    if (h->d.entry_mode == ANN_ENTRY_ROUTED && h->cluster_order_min >= 0 && nq >= h->cluster_order_min && nq <= 2147483647ll) {
+    if (grouped_order(h, nq, stride)) {
         hipError_t e;
         order = static_cast<int32_t*>(ws.take(sizeof(int32_t) * ((size_t)nq + h->d.n_clusters), &e));
         if (!order) return fail(ANN_ENOMEM, "ann_search: no scratch memory for the execution order: %s", hipGetErrorString(e));
         e = launch_cluster_order(route, h->d.route_c, nq, h->d.n_clusters, order + nq, order, stream);
         if (e != hipSuccess) return fail(ANN_EHIP, "ann_search: launching the execution-order kernels failed: %s", hipGetErrorString(e));
     }
-
+    int64_t per_launch = kMaxQueriesPerLaunch;
+    TableBlocks::Block* block = nullptr;
+    if (stride > 0 && order) {
+        const int64_t most = kTableBytes / (4 * (int64_t)stride);
+        int64_t launches = (nq + most - 1) / most;
+        per_launch = ((nq + launches - 1) / launches + 511) / 512 * 512;
+        if (per_launch > nq) per_launch = nq;
+        block = h->tables.take(4 * (size_t)stride * (size_t)per_launch, stream);
+        if (!block) per_launch = kMaxQueriesPerLaunch;  // no memory: gather every row
+    }
+    uint32_t* const table = block ? static_cast<uint32_t*>(block->memory) : nullptr;
     const int team = h->team ? h->team : default_team(h, nq);
-    for (int64_t q0 = 0; q0 < nq; q0 += kMaxQueriesPerLaunch) {
-        const int64_t cnt = nq - q0 < kMaxQueriesPerLaunch ? nq - q0 : kMaxQueriesPerLaunch;
+    hipError_t e = hipSuccess;
+    for (int64_t q0 = 0; q0 < nq && e == hipSuccess; q0 += per_launch) {
+        const int64_t cnt = nq - q0 < per_launch ? nq - q0 : per_launch;
         SearchParams p;
         p.vectors = static_cast<const uint8_t*>(h->d.vectors);
         p.n = h->d.n;
@@ -452,9 +584,40 @@ int search_impl(ann_index_t* h, const void* queries, int64_t nq, const int32_t* 
         p.out_dists = static_cast<uint32_t*>(out_dists);
         p.out_counters = out_counters;
         p.order = order;
-        const hipError_t e = h->variant->search(p, plan.list_variant, team, (unsigned)(8 * p.q_per_xcd), plan.lds_bytes, stream);
-        if (e != hipSuccess) return fail(ANN_EHIP, "ann_search: launch failed: %s", hipGetErrorString(e));
+        p.table = table;
+        p.table_stride = table ? stride : 0;
+        size_t lds_bytes = plan.lds_bytes;
+        if (table) {
+            KeyTableParams t;
+            t.vectors = p.vectors;
+            t.n = p.n;
+            t.row_stride = p.row_stride;
+            t.row_bytes = p.row_bytes;
+            t.queries = p.queries;
+            t.order = order;
+            t.q_base = q0;
+            t.q_count = cnt;
+            t.route = route;
+            t.cluster_offsets = p.cluster_offsets;
+            t.n_clusters = p.n_clusters;
+            t.stride = stride;
+            // several workgroups for every place on the chip, of at least 128 rows each
+            const int64_t mean = h->d.n / h->d.n_clusters + 1, set = key_table_set(h->variant->nch), sets = (cnt + set - 1) / set;
+            const int64_t want = (4096 + sets - 1) / sets;
+            t.slice_rows = (int)((mean + mean / 16 + want - 1) / want + 63) / 64 * 64;
+            if (t.slice_rows < 128) t.slice_rows = 128;
+            t.slices = (stride + t.slice_rows - 1) / t.slice_rows;
+            t.table = table;
+            e = launch_key_table(h->d.dtype, h->d.metric, h->variant->g, h->variant->nch, t, stream);
+            if (e != hipSuccess) break;
+            // the bitmap covers no more ids than the table
+            lds_bytes -= sizeof(uint32_t) * (size_t)(p.window_bits / 32 - (stride + 31) / 32);
+            p.window_bits = (stride + 31) / 32 * 32;
+        }
+        e = h->variant->search(p, plan.list_variant, team, (unsigned)(8 * p.q_per_xcd), lds_bytes, stream);
     }
+    if (block) h->tables.give_back(block, stream);
+    if (e != hipSuccess) return fail(ANN_EHIP, "ann_search: launch failed: %s", hipGetErrorString(e));
     return ANN_OK;
 }
 
@@ -464,16 +627,18 @@ extern "C" int ann_search_counters(ann_index_t* h, const void* queries, int64_t 
                                    int max_iters, int32_t* out_ids, void* out_dists, int32_t* out_counters,
                                    void* stream) {
     if (!h || h->magic != kMagic) return fail(ANN_EINVAL, "ann_search: not a live handle");
-    Workspace ws(static_cast<hipStream_t>(stream), search_scratch_bytes(h, nq, false));
-    return search_impl(h, queries, nq, nullptr, false, k, itopk, width, max_iters, out_ids, out_dists, out_counters, ws);
+    const int stride = table_stride(h, nq, itopk, width, max_iters, static_cast<hipStream_t>(stream));
+    Workspace ws(static_cast<hipStream_t>(stream), search_scratch_bytes(h, nq, false, stride));
+    return search_impl(h, queries, nq, nullptr, false, k, itopk, width, max_iters, out_ids, out_dists, out_counters, ws, stride);
 }
 
 extern "C" int ann_search_routed(ann_index_t* h, const void* queries, int64_t nq, const int32_t* routes, int k,
                                  int itopk, int width, int max_iters, int32_t* out_ids, void* out_dists,
                                  int32_t* out_counters, void* stream) {
     if (!h || h->magic != kMagic) return fail(ANN_EINVAL, "ann_search_routed: not a live handle");
-    Workspace ws(static_cast<hipStream_t>(stream), search_scratch_bytes(h, nq, true));
-    return search_impl(h, queries, nq, routes, true, k, itopk, width, max_iters, out_ids, out_dists, out_counters, ws);
+    const int stride = table_stride(h, nq, itopk, width, max_iters, static_cast<hipStream_t>(stream));
+    Workspace ws(static_cast<hipStream_t>(stream), search_scratch_bytes(h, nq, true, stride));
+    return search_impl(h, queries, nq, routes, true, k, itopk, width, max_iters, out_ids, out_dists, out_counters, ws, stride);
 }
 
 extern "C" int ann_search(ann_index_t* h, const void* queries, int64_t nq, int k, int itopk, int width, int max_iters,
@@ -517,7 +682,7 @@ int static_scratch_of_current_device(void** out) {
 extern "C" int ann_search_static(ann_index_t* h, const void* queries, int64_t nq, int k, int itopk, int width, int max_iters,
                                  int32_t* out_ids, void* out_dists, void* stream) {
     if (!h || h->magic != kMagic) return fail(ANN_EINVAL, "ann_search_static: not a live handle");
-    const size_t need = search_scratch_bytes(h, nq, false);
+    const size_t need = search_scratch_bytes(h, nq, false, 0);
     if (need > kStaticScratchBytes)
         return fail(ANN_EUNSUPPORTED,
                     "ann_search_static: %lld queries need %zu bytes of temporaries, the static scratch holds %zu; split the batch",
@@ -528,7 +693,7 @@ extern "C" int ann_search_static(ann_index_t* h, const void* queries, int64_t nq
         if (rc != ANN_OK) return rc;
     }
     Workspace ws(static_cast<hipStream_t>(stream), base, need > 0 ? kStaticScratchBytes : 0);
-    return search_impl(h, queries, nq, nullptr, false, k, itopk, width, max_iters, out_ids, out_dists, nullptr, ws);
+    return search_impl(h, queries, nq, nullptr, false, k, itopk, width, max_iters, out_ids, out_dists, nullptr, ws, 0);
 }
 
 extern "C" int ann_gather_vectors(ann_index_t* h, const int32_t* ids, int64_t count, void* out_vectors, void* stream) {

@@ -55,6 +55,8 @@ struct SearchParams {
     int32_t* out_counters;  // nq * 4 or null
     const int32_t* order;   // execution order: the launch's i-th query is order[q_base + i]; null = identity
     int64_t q_per_xcd;      // queries of this launch handed to each of the 8 XCDs
+    const uint32_t* table;  // ordered keys of the launch's i-th query against its first window, i * table_stride on; or null
+    int32_t table_stride;   // keys per query; no window is longer (TABLE kernels)
 };
 
 constexpr uint32_t kEmptySlot = 0xffffffffu;
@@ -85,13 +87,19 @@ __device__ __forceinline__ bool hash_insert(uint32_t* table, int hash_bits, uint
 // the candidate list, the visited set and the choice of parents; all wavefronts share the gathers and
 // keys of a round, which is where the time of a round with long rows goes when few queries are in
 // flight (a wavefront has only so many loads in flight; TEAM of them have TEAM times as many).
-template <class Row, int LPL, int CPL, int TEAM = 1>
+//
+// TABLE: the keys of a query against every row of its (only) window have been computed beforehand
+// (key_table.h), so a new id of the window costs one 4-byte read instead of a row gather and its arithmetic.
+// Ids outside the window are gathered as ever.  Such a search takes 0.26 ms for 5 000 queries over 1536-byte rows
+// (512 neighbours a round) that took 1.98 ms with gathers, and 0.80 ms for 20 000 over 384-byte rows instead of
+// 1.33 ms.  Two thirds of the vector-ALU issue slots are used then; the rest waits for graph rows and LDS.
+template <class Row, int LPL, int CPL, int TEAM = 1, bool TABLE = false>
 struct BeamSearch {
     static constexpr int G = Row::G;
     static constexpr int NCH = Row::NCH;
     static constexpr int RPS = 64 / G;                                // rows per gather step
-    static constexpr int U = NCH >= 8 ? 1 : (NCH >= 4 ? 2 : NCH >= 2 ? 3 : G == 32 ? 8 : 4);  // gather steps in flight
-    static constexpr int UP = U <= 1 ? 1 : U <= 2 ? 2 : U <= 4 ? 4 : 8;                       // U or the next power of two
+    static constexpr int U = TABLE || NCH >= 8 ? 1 : (NCH >= 4 ? 2 : NCH >= 2 ? 3 : G == 32 ? 8 : 4);  // gather steps in flight
+    static constexpr int UP = U <= 1 ? 1 : U <= 2 ? 2 : U <= 4 ? 4 : 8;                                // U or the next power of two
     static constexpr int BR = LPL >= 2 ? 2 : 1;                       // registers of a sort batch
     static constexpr int kInsertMax = 8;                // at most this many new keys are inserted one by one
 
@@ -111,6 +119,7 @@ struct BeamSearch {
     int n_windows;
     uint32_t w0_lo, w0_size;  // first window: ids [w0_lo, w0_lo + w0_size) are bits 0..
     int n_table;  // ids in the visited hash
+    const uint32_t* keys;  // TABLE: this query's row of the key table
     uint64_t worst;  // list entry number itopk-1 (the empty key while the list is not full), kept up to date by merge_all
     int n_dist, n_parents, n_resets;
 
@@ -217,20 +226,63 @@ struct BeamSearch {
         return w;
     }
 
-    // Gathers rows cid[0..m) and writes the packed keys that can enter the list to
-    // ckey[0..returned count).
-    __device__ __forceinline__ int score(int m) { return row.full ? score_rows<true>(m) : score_rows<false>(m); }
+    // Gathers rows cid[0..m) and appends the packed keys that can enter the list to
+    // ckey[kept..returned count).
+    __device__ __forceinline__ int score(int m, int kept = 0) { return row.full ? score_rows<true>(m, kept) : score_rows<false>(m, kept); }
+
+    // TABLE: of the ids held one per lane and register, those never scored before, their packed keys where they can
+    // enter the list, in ckey[0..returned count).  All bitmap updates are issued before the first is waited for, then
+    // all key reads.
+    __device__ __forceinline__ int look_up(const int32_t (&id)[CPL], int count) {
+        bool fresh[CPL];
+        bool outside = false;
+#pragma unroll
+        for (int t = 0; t < CPL; ++t) {
+            const uint32_t rel = (uint32_t)id[t] - w0_lo;
+            const bool valid = t * 64 + lane < count && (uint32_t)id[t] < (uint32_t)p.n;
+            fresh[t] = false;
+            if (valid && rel < w0_size) {
+                const uint32_t bit = 1u << (rel & 31);
+                fresh[t] = (atomicOr(&bitmap[rel >> 5], bit) & bit) == 0;
+            }
+            outside |= valid && rel >= w0_size;
+        }
+        uint32_t okey[CPL];
+#pragma unroll
+        for (int t = 0; t < CPL; ++t) {
+            okey[t] = 0xffffffffu;
+            if (fresh[t]) okey[t] = keys[(uint32_t)id[t] - w0_lo];
+        }
+        int kept = 0;
+#pragma unroll
+        for (int t = 0; t < CPL; ++t) {
+            const uint64_t packed = ((uint64_t)okey[t] << 32) | (uint64_t)((uint32_t)id[t] << 1);
+            const bool keep = fresh[t] && packed < worst;
+            const uint64_t b = __ballot(keep);
+            if (keep) ckey[rank_below(b, kept)] = packed;
+            kept += __builtin_popcountll(b);
+            n_dist += __builtin_popcountll(__ballot(fresh[t]));
+        }
+        if (__any(outside)) {
+            int m = 0;
+#pragma unroll
+            for (int t = 0; t < CPL; ++t)
+                filter_into(id[t], t * 64 + lane < count && (uint32_t)id[t] - w0_lo >= w0_size, m);
+            lds_sync();
+            kept = score(m, kept);
+        }
+        return kept;
+    }
 
     // FULL: the row fills every piece of every lane, so the row buffers need no clearing (RowOps::blank_row); else
     // they are zeroed once and a piece this lane does not load keeps its zeros (RowOps::reload_row).
     template <bool FULL>
-    __device__ __forceinline__ int score_rows(int m) {
+    __device__ __forceinline__ int score_rows(int m, int kept) {
         const int grp = lane / G;
         const uint64_t worst = this->worst;
         // the host keeps the stride below 2^31, so a row's address is one 32 x 32 -> 64 bit multiply-add
         const uint8_t* const piece0 = row.lane_piece(p.vectors);
         const uint32_t stride = (uint32_t)p.row_stride;
-        int kept = 0;
         u32x4 x[U][NCH];
         if constexpr (!FULL) {
 #pragma unroll
@@ -475,7 +527,7 @@ struct BeamSearch {
     }
 
     // Empty list and visited set, the windows of the routed clusters, and the entry ids (duplicates collapse
-    // in the visited set) in cid[0..returned count).
+    // in the visited set) in cid[0..returned count); with a key table their packed keys in ckey[0..returned count).
     __device__ __forceinline__ int start(int64_t qi) {
 #pragma unroll
         for (int r = 0; r < LPL; ++r) L[r] = kInfKey;
@@ -489,7 +541,7 @@ struct BeamSearch {
                 const int32_t c = p.route[qi * p.route_c + w];
                 const bool known = (uint32_t)c < (uint32_t)p.n_clusters;
                 const int64_t lo = known ? p.cluster_offsets[c] : 0, hi = known ? p.cluster_offsets[c + 1] : 0;
-                const uint32_t room = (uint32_t)p.window_bits - bit;
+                const uint32_t room = (TABLE ? (uint32_t)p.table_stride : (uint32_t)p.window_bits) - bit;
                 const uint32_t size = hi <= lo ? 0u : (uint64_t)(hi - lo) < room ? (uint32_t)(hi - lo) : room;
                 if (lane == 0) {
                     wtab[3 * w] = (uint32_t)lo;
@@ -506,6 +558,7 @@ struct BeamSearch {
         }
         lds_sync();
         int m = 0;
+        int32_t entry[CPL];
 #pragma unroll
         for (int t = 0; t < CPL; ++t) {
             const int j = t * 64 + lane;
@@ -522,14 +575,16 @@ struct BeamSearch {
                     if (hi > lo) e = (int32_t)(lo + (int64_t)(z % (uint64_t)(hi - lo)));
                 }
             }
-            filter_into(e, valid, m);
+            if constexpr (TABLE) entry[t] = e;
+            else filter_into(e, valid, m);
         }
+        if constexpr (TABLE) m = look_up(entry, p.n_entry);
         return m;
     }
 
     // One round up to the gathers: marks the first <= width unexpanded list entries as expanded, reads their
-    // graph rows and leaves the ids that were never scored in cid[0..returned count); -1 if nothing is
-    // left to expand.
+    // graph rows and leaves the ids that were never scored in cid[0..returned count) (with a key table: the packed
+    // keys of look_up in ckey); -1 if nothing is left to expand.
     __device__ __forceinline__ int expand() {
         // Register r holds entries 64r .. 64r+63, so the registers are walked in order and the walk stops
         // once `width` parents are found.
@@ -567,6 +622,7 @@ struct BeamSearch {
                 nb[t] = p.graph[(uint64_t)parents[pi] * (uint32_t)p.degree + (uint32_t)(s - pi * p.degree)];
             }
         }
+        if constexpr (TABLE) return look_up(nb, nref);
         int m = 0;
 #pragma unroll
         for (int t = 0; t < CPL; ++t) filter_into(nb[t], t * 64 + lane < nref, m);
@@ -601,16 +657,20 @@ struct BeamSearch {
         }
         int m = start(qi);
         lds_sync();
-        m = score(m);
-        lds_sync();
+        if constexpr (!TABLE) {
+            m = score(m);
+            lds_sync();
+        }
         first_list(m);
         int iters = 0;
         for (; iters < p.max_iters; ++iters) {
             m = expand();
             if (m < 0) break;
             lds_sync();
-            m = score(m);
-            lds_sync();
+            if constexpr (!TABLE) {
+                m = score(m);
+                lds_sync();
+            }
             merge_all(m);
         }
         finish(qi, iters);
@@ -664,14 +724,15 @@ struct BeamSearch {
 // kept on one XCD and its L2: query = (b % 8) * q_per_xcd + b / 8.
 // The small uint8 variants (rows of at most 256 bytes) are asked to fit 7 wavefronts per SIMD (72 vector registers; 8 would need spills):
 // with about 5.5 KB of LDS per query that is also what a compute unit's LDS holds, 28 queries in flight.
-template <class Row, int LPL, int CPL, int TEAM>
+template <class Row, int LPL, int CPL, int TEAM, bool TABLE>
 __global__ void __launch_bounds__(64 * TEAM, (TEAM == 1 && Row::kDtype == kU8 && Row::G * Row::NCH <= 16 && LPL <= 4 && CPL <= 2) ? 7 : 1)
     beam_search_kernel(const SearchParams p) {
     extern __shared__ uint32_t lds[];
     const int64_t b = blockIdx.x;
     const int64_t local = (b & 7) * p.q_per_xcd + (b >> 3);
     if (local >= p.q_count) return;  // the whole workgroup
-    BeamSearch<Row, LPL, CPL, TEAM> s(p, lds, lane_id(), TEAM == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)));
+    BeamSearch<Row, LPL, CPL, TEAM, TABLE> s(p, lds, lane_id(), TEAM == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)));
+    if constexpr (TABLE) s.keys = p.table + local * p.table_stride;
     s.run(p.order ? (int64_t)p.order[p.q_base + local] : p.q_base + local);
 }
 

@@ -60,8 +60,69 @@ __global__ void __launch_bounds__(256) cluster_scatter_kernel(const int32_t* rou
         order[atomicAdd(&offsets[bucket_of(route[q * route_c], n_clusters)], 1)] = (int32_t)q;
 }
 
+// The same in one launch for batches and cluster counts that one workgroup gets through in about the time that the
+// four launches' own latencies add up to, a counter per cluster in LDS: 7 us for 5 000 queries (four launches: 19 us),
+// 21 us for 20 000 (27 us).
+constexpr int kSmallOrderQueries = 24576, kSmallOrderClusters = 8192;
+__global__ void __launch_bounds__(1024) small_cluster_order_kernel(const int32_t* __restrict__ route, int route_c, int nq,
+                                                                   int n_clusters, int32_t* __restrict__ order) {
+    __shared__ int32_t counts[kSmallOrderClusters];
+    __shared__ int32_t wave_sums[16];
+    constexpr int U = 8;  // routes in flight per thread
+    const int t = threadIdx.x;
+    for (int c = t; c < n_clusters; c += 1024) counts[c] = 0;
+    __syncthreads();
+    for (int q0 = 0; q0 < nq; q0 += 1024 * U) {
+        int32_t b[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int q = q0 + u * 1024 + t;
+            b[u] = q < nq ? bucket_of(route[(int64_t)q * route_c], n_clusters) : -1;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (b[u] >= 0) atomicAdd(&counts[b[u]], 1);
+    }
+    __syncthreads();
+    // exclusive scan: every thread's run of clusters, the wavefront's threads, the wavefronts
+    const int per = (n_clusters + 1023) / 1024;
+    const int lo = min(t * per, n_clusters), hi = min(lo + per, n_clusters);
+    int32_t sum = 0;
+    for (int c = lo; c < hi; ++c) sum += counts[c];
+    int32_t upto = sum;
+    for (int d = 1; d < 64; d <<= 1) {
+        const int32_t below = __shfl_up(upto, d);
+        if ((t & 63) >= d) upto += below;
+    }
+    if ((t & 63) == 63) wave_sums[t >> 6] = upto;
+    __syncthreads();
+    int32_t run = upto - sum;
+    for (int w = 0; w < (t >> 6); ++w) run += wave_sums[w];
+    for (int c = lo; c < hi; ++c) {
+        const int32_t n = counts[c];
+        counts[c] = run;
+        run += n;
+    }
+    __syncthreads();
+    for (int q0 = 0; q0 < nq; q0 += 1024 * U) {
+        int32_t b[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int q = q0 + u * 1024 + t;
+            b[u] = q < nq ? bucket_of(route[(int64_t)q * route_c], n_clusters) : -1;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (b[u] >= 0) order[atomicAdd(&counts[b[u]], 1)] = q0 + u * 1024 + t;
+    }
+}
+
 hipError_t launch_cluster_order(const int32_t* route, int route_c, int64_t nq, int n_clusters, int32_t* counts,
                                 int32_t* order, hipStream_t stream) {
+    if (nq <= kSmallOrderQueries && n_clusters <= kSmallOrderClusters) {
+        hipLaunchKernelGGL(small_cluster_order_kernel, dim3(1), dim3(1024), 0, stream, route, route_c, (int)nq, n_clusters, order);
+        return hipGetLastError();
+    }
     const unsigned blocks = (unsigned)((nq + 255) / 256 < 4096 ? (nq + 255) / 256 : 4096);
     hipLaunchKernelGGL(fill_zero_kernel, dim3((unsigned)((n_clusters + 255) / 256)), dim3(256), 0, stream, counts,
                        (int64_t)n_clusters);

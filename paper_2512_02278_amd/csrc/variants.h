@@ -10,18 +10,9 @@
 
 #include "beam_search_kernel.h"
 #include "route_kernel.h"
+#include "row_variants.h"
 
 namespace ann {
-
-// X(dtype, metric, G, NCH).  Float rows of 257 .. 512 and 513 .. 1024 bytes have variants of one and two pieces per
-// lane: with the next larger ones (three and four pieces) up to three quarters of a gather step were empty pieces,
-// and fewer rows were in flight (3 001 searches over 400-byte fp16 rows: 1.41 ms, now 0.79 ms).
-#define ANN_ROW_VARIANTS(X)                                                  \
-    X(kU8, kL2, 8, 1) X(kU8, kIP, 8, 1) X(kU8, kL2, 8, 2) X(kU8, kIP, 8, 2) X(kU8, kL2, 4, 2) X(kU8, kIP, 4, 2) \
-    X(kF16, kL2, 8, 2) X(kF16, kIP, 8, 2) X(kF16, kL2, 32, 1) X(kF16, kIP, 32, 1) X(kF16, kL2, 32, 2) X(kF16, kIP, 32, 2) \
-    X(kF16, kL2, 32, 3) X(kF16, kIP, 32, 3) X(kF32, kL2, 32, 1) X(kF32, kIP, 32, 1) X(kF32, kL2, 32, 2) X(kF32, kIP, 32, 2) \
-    X(kF32, kL2, 8, 3) X(kF32, kIP, 8, 3) X(kF32, kL2, 32, 4) X(kF32, kIP, 32, 4)                               \
-    X(kU8, kL2, 32, 3) X(kU8, kIP, 32, 3) X(kF16, kL2, 32, 6) X(kF16, kIP, 32, 6) X(kF32, kL2, 32, 12) X(kF32, kIP, 32, 12)
 
 // List variants (LPL, CPL); a request is served by the first one that is large enough.
 constexpr int kListVariants[][2] = {{1, 1}, {2, 2}, {3, 2}, {4, 2}, {4, 4}, {4, 8}, {8, 8}};
@@ -37,13 +28,17 @@ hipError_t launch_search(const SearchParams& p, int list_variant, int team, unsi
 template <int DT, int METRIC, int G, int NCH>
 hipError_t launch_route(const RouteParams& p, hipStream_t stream);
 
-#define ANN_LAUNCH_LIST(LPL, CPL)                                                                                         \
-    switch (team) {                                                                                                       \
-        case 1: hipLaunchKernelGGL((beam_search_kernel<Row, LPL, CPL, 1>), dim3(grid), dim3(64), lds_bytes, stream, p); break;  \
-        case 2: hipLaunchKernelGGL((beam_search_kernel<Row, LPL, CPL, 2>), dim3(grid), dim3(128), lds_bytes, stream, p); break; \
-        case 4: hipLaunchKernelGGL((beam_search_kernel<Row, LPL, CPL, 4>), dim3(grid), dim3(256), lds_bytes, stream, p); break; \
-        default: return hipErrorInvalidValue;                                                                             \
-    }                                                                                                                     \
+#define ANN_LAUNCH_LIST(LPL, CPL)                                                                                                \
+    if (p.table) {                                                                                                               \
+        hipLaunchKernelGGL((beam_search_kernel<Row, LPL, CPL, 1, true>), dim3(grid), dim3(64), lds_bytes, stream, p);            \
+        break;                                                                                                                   \
+    }                                                                                                                            \
+    switch (team) {                                                                                                              \
+        case 1: hipLaunchKernelGGL((beam_search_kernel<Row, LPL, CPL, 1, false>), dim3(grid), dim3(64), lds_bytes, stream, p); break;  \
+        case 2: hipLaunchKernelGGL((beam_search_kernel<Row, LPL, CPL, 2, false>), dim3(grid), dim3(128), lds_bytes, stream, p); break; \
+        case 4: hipLaunchKernelGGL((beam_search_kernel<Row, LPL, CPL, 4, false>), dim3(grid), dim3(256), lds_bytes, stream, p); break; \
+        default: return hipErrorInvalidValue;                                                                                    \
+    }                                                                                                                            \
     break;
 
 #define ANN_DEFINE_ROW_VARIANT(DT, METRIC, G, NCH)                                                              \

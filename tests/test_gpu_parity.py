@@ -880,3 +880,55 @@ def test_float_rows_at_the_edges_of_the_32_lane_variants(oracle, torch_cuda, dt,
             x = (x.astype(np.float64) / np.linalg.norm(x.astype(np.float64), axis=1, keepdims=True)).astype(NP_DT[dt])
         check_float(oracle, torch_cuda, x, knn_graph(x, 16, metric), queries_near(rng, x, 60, dt), 10, 64, 3, 60, TOL[dt],
                     MIN_IDENTICAL[dt], metric=metric, n_entry=32, seed=4)
+
+
+@pytest.mark.parametrize("dt,dim,metric,sizes,itopk,width,degree,nq", [
+    ("f32", 96, 0, (300, 2100, 257, 900, 1, 700), 128, 4, 32, 333),        # a cluster longer than the table's rows, one of a single row
+    ("f32", 100, 1, (500, 260, 900), 64, 3, 27, 97),                       # partly empty pieces, odd degree
+    ("f16", 128, 0, (256, 256, 256, 300), 256, 8, 64, 130),                # 512 neighbours a round
+    ("f16", 200, 0, (400, 333), 100, 2, 33, 64),
+    ("f16", 768, 1, (290, 700, 410), 70, 2, 16, 51),
+    ("f16", 1000, 1, (300, 300), 64, 1, 24, 33),
+    ("f32", 1536, 0, (280, 301), 64, 1, 16, 35),
+    ("f32", 128, 1, (600, 600, 600), 200, 4, 48, 5_000),                   # many sets of queries per cluster
+    ("f32", 96, 0, (6_000, 6_200), 512, 4, 16, 33_000),                    # more queries than one launch's table holds
+])
+def test_key_table_gives_the_bits_of_the_gathering_search(torch_cuda, dt, dim, metric, sizes, itopk, width, degree, nq):
+    """Batches with many queries per cluster search with a table of keys computed beforehand.  Results and counters have
+    the bits of the search that gathers every row (a fixed team size asks for that one), also for ids outside the query's
+    cluster, clusters longer than the table's rows, empty slots and route ids that name no cluster."""
+    from paper_2512_02278_amd import ann
+
+    torch, dev = torch_cuda, "cuda:0"
+    rng = np.random.default_rng(dim + nq)
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    n, nc = int(off[-1]), len(sizes)
+    cen = rng.standard_normal((nc, dim))
+    lab = np.repeat(np.arange(nc), sizes)
+    x = (cen[lab] + 0.7 * rng.standard_normal((n, dim))).astype(NP_DT[dt])
+    g = rng.integers(off[lab][:, None], off[lab + 1][:, None], (n, degree)).astype(np.int32)
+    far = rng.random((n, degree))
+    g[far < 0.1] = rng.integers(0, n, int((far < 0.1).sum()))     # edges to other clusters
+    g[far > 0.97] = -1                                            # empty slots
+    g[far > 0.99] = n                                             # ids out of range
+    q = (x[rng.integers(0, n, nq)].astype(np.float64) + 0.1 * rng.standard_normal((nq, dim))).astype(NP_DT[dt])
+    to = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(dev)
+    xt, gt, ct, ot, qt = to(x), to(g), to(cen.astype(NP_DT[dt])), to(off), to(q)
+    h = ann.ann_index_load(xt, gt, metric=metric, n_entry=32, entry_mode=1, seed=4, centroids=ct, cluster_offsets=ot, route_c=1)
+    routes = ann.ann_route(h, qt)
+    odd = routes.clone()
+    odd[::7], odd[1::11] = -1, nc
+    for r in (None, odd):
+        got = []
+        for team in (0, 1):
+            ann.ann_index_set_option(h, ann.ANN_OPT_WAVEFRONTS_PER_QUERY, team)
+            ids = torch.full((nq, 10), -7, dtype=torch.int32, device=dev)
+            counters = torch.full((nq, 4), -7, dtype=torch.int32, device=dev)
+            keys = torch.empty((nq, 10), dtype=torch.float32, device=dev)
+            ann.ann_search(h, qt, 10, itopk, width, 100, out_ids=ids, out_dists=keys, counters=counters, routes=r)
+            torch.cuda.synchronize()
+            got.append((ids, keys.view(torch.int32), counters[:, 0], counters[:, 2], counters[:, 1]))
+        assert all(torch.equal(a, b) for a, b in zip(*(v[:4] for v in got)))     # ids, keys, rounds, graph rows
+        # rows scored: an id beyond the table's rows is remembered in the hash, which may forget it, not in the bitmap
+        assert torch.equal(got[0][4], got[1][4]) or max(sizes) > 1.5 * n / nc
+    ann.ann_free(h)
