@@ -16,8 +16,7 @@
 // rows of d_in ids are read per node (16 KB at d_in = 64), a random gather like the search's
 // own, but with rows that mostly sit in the node's own cluster: runs of consecutive nodes stay
 // on one XCD so that its L2 serves the re-reads.  The ids of x's row go into a small LDS table
-// (id -> rank); the ids of every neighbour's row pass a Bloom filter of x's row, and those that
-// survive are looked up in the table and bump an LDS counter.
+// (id -> rank); the ids of every neighbour's row are looked up there and bump an LDS counter.
 // Step 3 is a counting sort by target (histogram - counted by the pruning kernel itself -, scan,
 // scatter of (position, source) words) followed by a selection per node, so that the result does not
 // depend on the order in which the atomics land.
@@ -47,64 +46,27 @@ __device__ __forceinline__ int64_t first_node_of(int64_t b, int64_t runs_per_xcd
 }
 
 // ------------------------------------------------------------------------------------- steps 1 + 2
-// id -> rank table of one row: B buckets of four 32-bit ids (one 16-byte LDS read fetches a bucket)
-// plus one byte of rank per slot.  A bucket fills from slot 0 upwards; an id that finds its bucket
-// full goes to the next one.  With 64*R ids in 128*R buckets a full bucket is met by about one
-// lookup in six hundred, so the lookup is a straight line: one bucket, four compares, and a
-// wave-uniform branch to the rare walk over further buckets.  (A per-lane probing loop would
-// run as long as its slowest lane and cost mostly scalar branch and mask instructions, and the
-// scalar unit is shared by the four SIMDs of a compute unit.)
-constexpr uint32_t kEmptyId = 0xffffffffu;
+// id -> rank table of one row: a byte per slot, rank + 1 or 0 where no id of the row falls, addressed directly by
+// hash(id) = (id ^ (id >> shift)) mod kSlots.  A lookup is one byte read and one comparison with the id that holds the
+// rank; it never walks.  For that no two ids of a row may share a slot: the row tries up to kTries shifts.  The first
+// leaves the low bits of the id, which are distinct whenever the row's neighbours lie within kSlots consecutive ids, as
+// they do in a cluster; 64 ids drawn at random fit at a try with probability 0.6, 128 with 0.14.  Ids that still find
+// their slot taken (after the last try; 1 row in 40 of 64 random ids, and about one id per row of 128) are compared
+// one by one.
+constexpr int kSlots = 4096, kTries = 8;
+constexpr int kNever = 1 << 20;  // a rank above all others
+constexpr int kAhead = 64;       // ranks beyond the last that are asked for by loads in flight
 
-template <int B>
-__device__ __forceinline__ uint32_t bucket_of(uint32_t id) {
-    return (id * 0x9E3779B1u) >> (32 - __builtin_ctz(B));
-}
-
-// Slot index of `id` in bucket `b`, or -1.
-__device__ __forceinline__ int match_in(const uint4 t, uint32_t id) {
-    return t.x == id ? 0 : t.y == id ? 1 : t.z == id ? 2 : t.w == id ? 3 : -1;
-}
-
-template <int B>
-__device__ __forceinline__ void rank_table_insert(uint32_t* tid, uint8_t* trk, uint32_t id, int rank) {
-    uint32_t b = bucket_of<B>(id);
-    for (;;) {  // ends: the row's ids fill at most an eighth of the slots
-        for (int s = 0; s < 4; ++s) {
-            const uint32_t old = atomicCAS(&tid[4 * b + s], kEmptyId, id);
-            if (old == kEmptyId) {
-                trk[4 * b + s] = (uint8_t)rank;
-                return;
-            }
-            if (old == id) return;  // a repeated id (not allowed in a row) keeps one of its ranks
-        }
-        b = (b + 1) & (B - 1);
-    }
-}
-
-// Slot of `id` (4 * bucket + position) or -1.  Called by all lanes; lanes with live == false get -1.
-template <int B>
-__device__ __forceinline__ int rank_table_find(const uint32_t* tid, uint32_t id, bool live) {
-    uint32_t b = bucket_of<B>(id);
-    uint4 t = reinterpret_cast<const uint4*>(tid)[b];
-    int s = match_in(t, id);
-    bool more = live && s < 0 && t.w != kEmptyId;  // bucket full and no match: the id may have moved on
-    while (__ballot(more)) {
-        if (more) {
-            b = (b + 1) & (B - 1);
-            t = reinterpret_cast<const uint4*>(tid)[b];
-            s = match_in(t, id);
-            more = s < 0 && t.w != kEmptyId;
-        }
-    }
-    return (live && s >= 0) ? (int)(4 * b) + s : -1;
-}
+__device__ __forceinline__ uint32_t slot_of(uint32_t id, int shift) { return (id ^ (id >> shift)) & (kSlots - 1); }
 
 // R registers per lane: rank j of a row lives in lane j % 64, register j / 64 (d_in <= 64 * R).
 //
-// Only about one id in ten of a neighbour's row is also in x's row (clustered 128-d data), so the
-// ids first pass a one-hash Bloom filter of x's row (2048 * R bits in LDS, one 4-byte read each);
-// the survivors are queued in LDS with the later of their two ranks and looked up 64 at a time.
+// An entry y of rank rr in the row of the neighbour of rank i is a detour of the edge x -> y of rank j if y is in x's row
+// and j is above both i and rr: sixteen table reads are in flight per lane, then sixteen reads of the ids at those ranks.
+// What the entry is needs no test: an absent one equals no id of x's row, and a rank of d_in - 1 is below no other.
+// About 7 vector instructions per 64 lookups (25 with a Bloom filter, a queue and a bucketed table).  1M nodes 64 -> 32:
+// 1.70 ms (3.13 ms before), 590 vector and 211 LDS instructions per node; 250 000 nodes 128 -> 64: 1.79 ms (4.71 ms).
+// Bound by LDS: random byte reads of 64 lanes take a dozen cycles, and the vector ALUs are 0.65 and 0.55 busy.
 //
 // COUNT: the kernel also counts the in-edges of the pruned graph (step 3's histogram) - one returning
 // atomic per pruned edge, whose result is the edge's slot in its target's list.  The atomics are
@@ -113,99 +75,140 @@ template <int R, bool COUNT, bool VEC>
 __global__ void __launch_bounds__(64) graph_prune_kernel(const int32_t* __restrict__ knn, int64_t n, int d_in, int d_out,
                                                          int32_t* __restrict__ pruned, int64_t runs_per_xcd,
                                                          uint32_t* indeg, uint32_t* __restrict__ slot) {
-    constexpr int B = 128 * R, U = 8, kBloomBits = 11 + (R > 1), kQueue = 128;
-    __shared__ __align__(16) uint32_t tid[4 * B];   // ids of x's row, by bucket
-    __shared__ uint8_t trk[4 * B];                  // their ranks
-    __shared__ uint32_t bloom[(1 << kBloomBits) / 32];
-    __shared__ uint64_t queue[kQueue];              // ring of (later rank << 32) | id waiting for a lookup
-    __shared__ uint32_t cnt[64 * R];                // detour count per rank
-    __shared__ __align__(16) uint32_t key[64 * R];  // (count << 8) | rank, all ones where absent
-    __shared__ int32_t nbr[64 * R];                 // x's row, -1 where absent
+    __shared__ __align__(16) uint8_t table[kSlots];
+    __shared__ uint32_t cnt[64 * R + 1];            // detour count per rank + 1
+    __shared__ int32_t at_rank[64 * R + 1];         // id per rank + 1 of x's row, -1 where absent
+    __shared__ int32_t nbr[64 * R + kAhead];        // x's row, -1 where absent and beyond d_in
     __shared__ int32_t orow[64];
+    __shared__ uint8_t extra[64 * R];               // rank + 1 of the ids that have no slot
     const int lane = lane_id();
     const int64_t x0 = first_node_of(blockIdx.x, runs_per_xcd);
     const int64_t x1 = x0 + kNodesPerWave < n ? x0 + kNodesPerWave : n;
+    for (int i = lane; i < kSlots / 16; i += 64) reinterpret_cast<uint4*>(table)[i] = make_uint4(0, 0, 0, 0);
+    if (lane == 0) at_rank[0] = -1;
+    for (int i = lane; i < kAhead; i += 64) nbr[64 * R + i] = -1;
 
-    // looks up queue[head .. head + 64) (the first `live` of them are real) and counts the detours
-    auto drain = [&](int head, int live) {
-        const uint64_t e = queue[(head + lane) & (kQueue - 1)];
-        const int slot = rank_table_find<B>(tid, (uint32_t)e, lane < live);
-        if (slot >= 0) {
-            const int j = trk[slot];
-            if ((int)(e >> 32) < j) atomicAdd(&cnt[j], 1u);  // both hops rank below the edge itself
-        }
+    // the next node's row is read while this one is worked on, and the slot of an edge is stored a node later, when the
+    // atomic that counts it has long returned
+    int32_t coming[R];
+    auto row_of = [&](int64_t x) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) coming[r] = x < x1 && lane + 64 * r < d_in ? knn[x * d_in + lane + 64 * r] : -1;
     };
-
+    bool counted = false;
+    uint32_t counted_slot = 0;
+    row_of(x0);
     for (int64_t x = x0; x < x1; ++x) {
         int32_t mine[R];
         bool have[R];
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             const int j = lane + 64 * r;
-            mine[r] = j < d_in ? knn[x * d_in + j] : -1;
+            mine[r] = coming[r];
             have[r] = is_present(mine[r], n, x);
-            nbr[j] = have[r] ? mine[r] : -1;
-            cnt[j] = 0u;
+            nbr[j] = at_rank[j + 1] = have[r] ? mine[r] : -1;
+            cnt[j + 1] = 0u;
         }
-        for (int i = lane; i < B; i += 64) reinterpret_cast<uint4*>(tid)[i] = make_uint4(kEmptyId, kEmptyId, kEmptyId, kEmptyId);
-        for (int i = lane; i < (1 << kBloomBits) / 32; i += 64) bloom[i] = 0u;
+        row_of(x + 1);
         wave_lds_sync();
+        int shift = 31, n_extra = 0;  // wave-uniform
+        for (int attempt = 0;; ++attempt) {
+            // 31: the id itself (ids are below 2^31); then the low bits stirred with others
+            shift = attempt == 0 ? 31 : attempt == 1 ? 12 : attempt == 2 ? 5 : attempt == 3 ? 8 : attempt == 4 ? 3 : attempt == 5 ? 10 : attempt == 6 ? 7 : 14;
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-            if (have[r]) {
-                rank_table_insert<B>(tid, trk, (uint32_t)mine[r], lane + 64 * r);
-                const uint32_t hb = ((uint32_t)mine[r] * 0x9E3779B1u) >> (32 - kBloomBits);
-                atomicOr(&bloom[hb >> 5], 1u << (hb & 31));
+            for (int r = 0; r < R; ++r)
+                if (have[r]) table[slot_of((uint32_t)mine[r], shift)] = (uint8_t)(lane + 64 * r + 1);
+            wave_lds_sync();
+            bool lost[R], any = false;
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                lost[r] = have[r] && table[slot_of((uint32_t)mine[r], shift)] != (uint8_t)(lane + 64 * r + 1);
+                any |= lost[r];
             }
+            if (!__any(any)) break;
+            if (attempt == kTries - 1) {
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    const uint64_t m = __ballot(lost[r]);
+                    if (lost[r]) extra[rank_below(m, n_extra)] = (uint8_t)(lane + 64 * r + 1);
+                    n_extra += __builtin_popcountll(m);
+                }
+                break;
+            }
+            wave_lds_sync();
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                if (have[r]) table[slot_of((uint32_t)mine[r], shift)] = 0;
+            wave_lds_sync();
         }
         wave_lds_sync();
 
-        // rows of the neighbours at ranks 0 .. d_in-2 (the last one has no edge after it); every id that passes
-        // the Bloom filter is queued with the later of its two ranks
-        int head = 0, queued = 0;  // wave-uniform
-        auto push = [&](int32_t ys, int later) {
-            const uint32_t y = (uint32_t)ys;
-            const uint32_t hb = (y * 0x9E3779B1u) >> (32 - kBloomBits);
-            const bool pass = ys >= 0 && ((bloom[hb >> 5] >> (hb & 31)) & 1u);
-            const uint64_t m = __ballot(pass);
-            if (pass) queue[(head + queued + rank_below(m)) & (kQueue - 1)] = ((uint64_t)(uint32_t)later << 32) | y;
-            queued += __builtin_popcountll(m);
-            if (queued >= 64) {
-                wave_lds_sync();
-                drain(head, 64);
-                head = (head + 64) & (kQueue - 1);
-                queued -= 64;
+        // N entries per lane: y[e] is an entry of rank rr in the row of the neighbour of rank i, later[e] = max(i, rr) + 1;
+        // both hops must rank below the edge itself.  kNever as a rank: not an entry.
+        auto count = [&](const auto& y, const auto& later) {
+            constexpr int N = sizeof(y) / sizeof(y[0]);
+            uint32_t at[N];
+            int32_t id[N];
+#pragma unroll
+            for (int e = 0; e < N; ++e) at[e] = table[slot_of((uint32_t)y[e], shift)];
+#pragma unroll
+            for (int e = 0; e < N; ++e) id[e] = at_rank[at[e]];
+#pragma unroll
+            for (int e = 0; e < N; ++e)
+                if (id[e] == y[e] && (int)at[e] > later[e]) atomicAdd(&cnt[at[e]], 1u);
+            for (int o = 0; o < n_extra; ++o) {
+                const int j = extra[o];
+                const int32_t want = at_rank[j];
+#pragma unroll
+                for (int e = 0; e < N; ++e)
+                    if (y[e] == want && j > later[e]) atomicAdd(&cnt[j], 1u);
             }
         };
+        // rows of the neighbours at ranks 0 .. d_in-2 (the last one has no edge after it)
         if constexpr (VEC) {
-            // rows of d_in % 4 == 0 ids, 16-byte aligned: a lane reads four consecutive ranks, 16 * R lanes
-            // cover a row, so one load instruction fetches 4 / R rows; four of them in flight
-            constexpr int kLanesPerRow = 16 * R, kRowsPerLoad = 64 / kLanesPerRow, UV = 4;
+            // rows of d_in % 4 == 0 ids, 16-byte aligned: a lane reads four consecutive ranks, 16 * R lanes cover a row,
+            // so one load instruction fetches 4 / R rows; the next UV loads are in flight while UV are looked up
+            constexpr int kLanesPerRow = 16 * R, kRowsPerLoad = 64 / kLanesPerRow, UV = 2, kStep = UV * kRowsPerLoad;
             const int quad = lane % kLanesPerRow, sub = lane / kLanesPerRow;
-            for (int i0 = 0; i0 < d_in - 1; i0 += UV * kRowsPerLoad) {
-                int4 v[UV];
+            const int column = min(4 * quad, d_in - 4), rank1 = 4 * quad < d_in ? 4 * quad + 1 : kNever;
+            int4 v[2][UV];
+            int hop1[2][UV];  // rank of the neighbour, + 1
+            auto fetch = [&](int buf, int i0) {
 #pragma unroll
                 for (int u = 0; u < UV; ++u) {
                     const int i = i0 + u * kRowsPerLoad + sub;
-                    const int32_t z = i < d_in - 1 ? nbr[i] : -1;
-                    v[u] = make_int4(-1, -1, -1, -1);
-                    if (z >= 0 && 4 * quad < d_in - 1) v[u] = *reinterpret_cast<const int4*>(knn + (int64_t)z * d_in + 4 * quad);
+                    const int32_t z = nbr[i];
+                    hop1[buf][u] = z >= 0 ? i + 1 : kNever;  // an absent neighbour: row 0 is read for nothing
+                    v[buf][u] = *reinterpret_cast<const int4*>(knn + (uint64_t)(uint32_t)max(z, 0) * (uint32_t)d_in + column);
                 }
+            };
+            auto look_up = [&](int buf) {
+                int32_t y[4 * UV];
+                int later[4 * UV];
 #pragma unroll
                 for (int u = 0; u < UV; ++u) {
-                    const int i = i0 + u * kRowsPerLoad + sub;
-                    const int32_t c4[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
+                    y[4 * u] = v[buf][u].x;
+                    y[4 * u + 1] = v[buf][u].y;
+                    y[4 * u + 2] = v[buf][u].z;
+                    y[4 * u + 3] = v[buf][u].w;
 #pragma unroll
-                    for (int c = 0; c < 4; ++c) {
-                        const int rr = 4 * quad + c;
-                        push(rr < d_in - 1 ? c4[c] : -1, max(i, rr));
-                    }
+                    for (int c = 0; c < 4; ++c) later[4 * u + c] = max(hop1[buf][u], rank1 + c);
                 }
+                count(y, later);
+            };
+            fetch(0, 0);
+            for (int i0 = 0; i0 < d_in - 1; i0 += 2 * kStep) {
+                fetch(1, i0 + kStep);
+                look_up(0);
+                fetch(0, i0 + 2 * kStep);
+                look_up(1);
             }
         } else {
             // any d_in: a lane reads rank lane (+ 64) of one row per load, U rows in flight
+            constexpr int U = 8;
             for (int i0 = 0; i0 < d_in - 1; i0 += U) {
-                int32_t v[U][R];
+                int32_t y[U * R];
+                int later[U * R];
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
                     const int i = i0 + u;
@@ -213,53 +216,82 @@ __global__ void __launch_bounds__(64) graph_prune_kernel(const int32_t* __restri
 #pragma unroll
                     for (int r = 0; r < R; ++r) {
                         const int rr = lane + 64 * r;
-                        v[u][r] = (z >= 0 && rr < d_in - 1) ? knn[(int64_t)z * d_in + rr] : -1;
+                        y[u * R + r] = (z >= 0 && rr < d_in - 1) ? knn[(int64_t)z * d_in + rr] : -1;
+                        later[u * R + r] = max(i, rr) + 1;
                     }
                 }
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-#pragma unroll
-                    for (int r = 0; r < R; ++r) push(v[u][r], max(i0 + u, lane + 64 * r));
-                }
+                count(y, later);
             }
         }
         wave_lds_sync();
-        if (queued > 0) drain(head, queued);
-        wave_lds_sync();
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            if (have[r]) table[slot_of((uint32_t)mine[r], shift)] = 0;
 
-        // position of every present edge in ascending (count, rank)
-        uint32_t mykey[R];
+        // position of every present edge in ascending (count, rank): the edges whose count is lower, bit by bit from the
+        // top - among the edges that agree with this one so far, those with a 0 where it has a 1 - and of the rest those
+        // of lower rank.  About 55 instructions for 64 edges; comparing every pair of them took 128 and 16 LDS reads.
+        uint32_t same[R][2 * R];  // the edges (a bit each, 32 to a word) that agree with this lane's edge of register r
+        int c[R], pos[R];
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const int j = lane + 64 * r;
-            mykey[r] = have[r] ? ((cnt[j] << 8) | (uint32_t)j) : 0xffffffffu;
-            key[j] = mykey[r];
+        for (int q = 0; q < R; ++q) {
+            const uint64_t m = __ballot(have[q]);
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                same[r][2 * q] = (uint32_t)m;
+                same[r][2 * q + 1] = (uint32_t)(m >> 32);
+            }
+            c[q] = (int)cnt[lane + 64 * q + 1];
+            pos[q] = 0;
         }
-        wave_lds_sync();
-        int pos[R];
+        // counts are below 64 R: there are fewer ranks than that below an edge's
 #pragma unroll
-        for (int r = 0; r < R; ++r) pos[r] = 0;
-        // fully unrolled, the 32 reads of two registers per lane would all be in flight and take 128 VGPRs
-        constexpr int kRankUnroll = R == 1 ? 16 : 4;
-#pragma unroll kRankUnroll
-        for (int t = 0; t < 16 * R; ++t) {
-            const uint4 k4 = reinterpret_cast<const uint4*>(key)[t];
+        for (int bit = R == 1 ? 5 : 6; bit >= 0; --bit) {
+            uint64_t ones[R], any = 0;
 #pragma unroll
-            for (int r = 0; r < R; ++r)
-                pos[r] += (k4.x < mykey[r]) + (k4.y < mykey[r]) + (k4.z < mykey[r]) + (k4.w < mykey[r]);
+            for (int q = 0; q < R; ++q) {
+                ones[q] = __ballot((c[q] >> bit) & 1);
+                any |= ones[q];
+            }
+            if (any) {  // uniform
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    const uint32_t set = (uint32_t)(-((c[r] >> bit) & 1));
+#pragma unroll
+                    for (int h = 0; h < 2 * R; ++h) {
+                        const uint32_t o = (uint32_t)(ones[h / 2] >> (32 * (h % 2)));
+                        pos[r] += __builtin_popcount(__builtin_amdgcn_bitop3_b32(same[r][h], o, set, 0x20));  // same & ~o & set
+                        same[r][h] = __builtin_amdgcn_bitop3_b32(same[r][h], o, set, 0x90);                   // same & ~(o ^ set)
+                    }
+                }
+            }
         }
+        const uint64_t below = (1ull << lane) - 1;
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int h = 0; h <= 2 * r + 1; ++h)
+                pos[r] += __builtin_popcount(same[r][h] & (h / 2 < r ? ~0u : (uint32_t)(below >> (32 * (h % 2)))));
         orow[lane] = -1;
         wave_lds_sync();
 #pragma unroll
         for (int r = 0; r < R; ++r)
             if (have[r] && pos[r] < d_out) orow[pos[r]] = mine[r];
         wave_lds_sync();
+        if constexpr (COUNT) {
+            if (counted) slot[(x - 1) * d_out + lane] = counted_slot;
+        }
+        counted = false;
         if (lane < d_out) {
             const int32_t y = orow[lane];  // a present id or -1
             pruned[x * d_out + lane] = y;
-            if (COUNT && y >= 0) slot[x * d_out + lane] = atomicAdd(&indeg[y], 1u);
+            counted = y >= 0;
+            if (COUNT && counted) counted_slot = atomicAdd(&indeg[y], 1u);
         }
         wave_lds_sync();
+    }
+    if constexpr (COUNT) {
+        if (counted) slot[(x1 - 1) * d_out + lane] = counted_slot;
     }
 }
 

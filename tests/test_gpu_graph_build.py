@@ -187,3 +187,28 @@ def test_search_on_the_graph_the_gpu_built(oracle, torch_cuda):
     assert np.array_equal(cnt[:, 0].cpu().numpy(), oc["iters"])
     truth = inputs.ground_truth(part, q, 10)
     assert inputs.recall(ids, truth) > 0.95
+
+
+@pytest.mark.parametrize("n,d_in,d_out,spread", [
+    (3000, 64, 32, 0),        # ids at random: rows that need several tries for a table without collisions
+    (3000, 128, 64, 0),       # most rows keep ids without a slot
+    (900, 128, 64, 4096),     # ids that agree in their low twelve bits: no try but the stirred ones can tell them apart
+    (700, 100, 50, 4096),
+    (500, 90, 45, 4096),      # rows that do not start on 16 bytes
+    (5, 4, 2, 0), (3, 3, 3, 0),
+])
+def test_rows_whose_ids_collide_in_the_rank_table(oracle, torch_cuda, n, d_in, d_out, spread):
+    """Rows whose ids share slots of the pruning kernel's rank table (4096, addressed by the ids' low bits first)."""
+    from paper_2512_02278_amd import ann
+
+    rng = np.random.default_rng(n + d_in)
+    total = n if spread == 0 else 128 * spread
+    ids = np.arange(n) if spread == 0 else (np.arange(n) % 128) * spread + np.arange(n) // 128
+    knn = np.full((total, d_in), -1, np.int32)
+    for x in ids:
+        row = rng.permutation(ids)[: d_in + 1]
+        row = row[row != x][:d_in]
+        knn[x, : len(row)] = row
+    got = ann.ann_graph_optimize(torch_cuda.from_numpy(knn).to("cuda:0"), d_out)
+    torch_cuda.cuda.synchronize()
+    assert np.array_equal(got.cpu().numpy(), oracle.graph_optimize(knn, d_out))
