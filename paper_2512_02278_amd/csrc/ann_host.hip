@@ -154,7 +154,7 @@ struct ann_index {
     int64_t cluster_order_min;  // batches of at least this many queries run grouped by cluster; < 0: never
     int team;                   // wavefronts per query; 0: chosen per call from the batch size and the row length
     bool matrix_core_routing;
-    int32_t* centroid_bias;  // DEVICE, owned: per-centroid term of the uint8 d=128 matrix-core routing, or null
+    void* centroid_bias;     // DEVICE, owned: RouteU8Block of the uint8 d=128 matrix-core routing, or null
     void* route_bias;        // DEVICE, owned: the same for the general matrix-core routing, or null
     ann::TableBlocks tables;  // DEVICE, owned: memory for key tables
 };
@@ -236,12 +236,10 @@ extern "C" int ann_index_load(const ann_index_desc_t* desc, ann_index_t** out_ha
         }
     }
     if (mfma_route && d.dtype == ANN_U8 && d.dim == 128) {
-        // routing runs on the matrix cores; its per-centroid term is computed once, here
-        hipError_t e = hipMalloc(reinterpret_cast<void**>(&h->centroid_bias),
-                                 sizeof(int32_t) * (size_t)route_mfma_u8_padded(d.n_clusters));
+        // routing runs on the matrix cores; what it reads of the centroids is laid out once, here
+        hipError_t e = hipMalloc(&h->centroid_bias, RouteU8Block(d.n_clusters).bytes);
         if (e == hipSuccess)
-            e = launch_centroid_bias_u8(d.metric, static_cast<const uint8_t*>(d.centroids), d.n_clusters,
-                                        h->centroid_bias, nullptr);
+            e = launch_route_u8_block(d.metric, static_cast<const uint8_t*>(d.centroids), d.n_clusters, h->centroid_bias, nullptr);
         if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
         if (e != hipSuccess) {
             if (h->centroid_bias) (void)hipFree(h->centroid_bias);

@@ -37,6 +37,7 @@ namespace ann {
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));
 
+constexpr int kMinNearestTiles = 128;  // see launch_rc
 constexpr int kPadScore = 0x03ffffff;  // score of the padding rows: above every real one, and score*16 fits
 
 template <int METRIC>
@@ -214,38 +215,295 @@ __global__ void __launch_bounds__(256) route_mfma_u8_kernel(const uint8_t* __res
     }
 }
 
+// Where a centroid goes among the tiles (see RouteU8Block): one workgroup.
 template <int METRIC>
-static hipError_t launch_rc(int rc, const uint8_t* centroids, const int32_t* bias, int n_clusters,
+__global__ void __launch_bounds__(1024) route_u8_order_kernel(const int32_t* bias, int n_clusters, int max_tiles, int32_t* shape,
+                                                              int32_t* half, int32_t* map) {
+    __shared__ int32_t wave_even[16];
+    const int t = threadIdx.x, wave = t >> 6;
+    for (int i = t; i < max_tiles * 32; i += 1024) {
+        half[i] = 0x1fffffff;  // padding never wins
+        map[i] = 0x7fffffff;
+    }
+    auto even_at = [&](int c) { return c < n_clusters && (METRIC != 0 || ((bias[c] >> 4) & 1) == 0); };
+    // even centroids in front of this wavefront's, and in the whole block of 1024
+    auto count = [&](bool even, int* before) {
+        const uint64_t m = __ballot(even);
+        if ((t & 63) == 0) wave_even[wave] = __builtin_popcountll(m);
+        __syncthreads();
+        int all = 0;
+        *before = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+        for (int w = 0; w < 16; ++w) {
+            if (w < wave) *before += wave_even[w];
+            all += wave_even[w];
+        }
+        __syncthreads();
+        return all;
+    };
+    int total = 0, before;
+    for (int c0 = 0; c0 < n_clusters; c0 += 1024) total += count(even_at(c0 + t), &before);
+    const int even_tiles = (total + 31) / 32, odd_tiles = (n_clusters - total + 31) / 32;
+    if (t == 0) {
+        shape[0] = even_tiles;
+        shape[1] = even_tiles + odd_tiles;
+    }
+    int even_run = 0;
+    for (int c0 = 0; c0 < n_clusters; c0 += 1024) {
+        const int c = c0 + t;
+        const bool even = even_at(c);
+        const int all = count(even, &before);
+        if (c < n_clusters) {
+            const int at = even ? even_run + before : even_tiles * 32 + (c0 - even_run) + (t - before);
+            half[at] = METRIC == 0 ? bias[c] >> 5 : bias[c] >> 4;
+            map[at] = c;
+        }
+        even_run += all;
+    }
+}
+
+// One thread per 16-byte unit of the tiles.
+__global__ void __launch_bounds__(256) route_u8_rows_kernel(const uint8_t* centroids, int n_clusters, int64_t units, const int32_t* map, v4i* rows) {
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= units) return;
+    const int tile = (int)(i >> 8), piece = (int)(i >> 5) & 7, row = (int)i & 31;
+    const int c = map[tile * 32 + row];
+    rows[i] = (uint32_t)c < (uint32_t)n_clusters ? *reinterpret_cast<const v4i*>(centroids + (int64_t)c * 128 + piece * 16) ^ (int)0x80808080
+                                                 : v4i{0, 0, 0, 0};
+}
+
+// The nearest cluster of each query (route_c = 1), for many centroids.
+//
+// As route_mfma_u8_kernel, but nothing is packed: the accumulators start at half the bias, so a result is the score
+// itself (IP) or half of it without its lowest bit (L2), which is the same for all rows of a tile; a tile costs a lane
+// eight three-way minima and four instructions for the running best and its tile.  Which row of the tile it was is found
+// once, at the end: the wavefront computes the 32 scores of each query's best tile again and looks for the equal one.
+// Among equal scores the lowest cluster wins: they lie in one class of tiles, whose order is that of the clusters, and a
+// lane keeps the first; the two lanes of a query meet in the final search.
+// 500 000 queries x 16 384 centroids: 1.07 ms where route_mfma_u8_kernel takes 1.34 ms.  The matrix cores are busy half of
+// the time, the vector ALUs a third, at 1.8 GHz: the clock gives way under this load.
+template <int METRIC, int kTiles>
+__global__ void __launch_bounds__(256) route_nearest_u8_kernel(const v4i* __restrict__ rows, const int32_t* __restrict__ half_bias,
+                                                               const int32_t* __restrict__ map, const int32_t* __restrict__ shape,
+                                                               const uint8_t* __restrict__ queries, int64_t nq,
+                                                               int32_t* __restrict__ out, uint64_t* __restrict__ partial,
+                                                               int tiles_per_slice) {
+    constexpr int NQS = 2;  // query sets of 32 per wavefront
+    __shared__ v4i atile[2][kTiles * 256];  // [tile][piece][row] 16-byte units; in the end 16 queries of each wavefront
+    __shared__ v4i btile[2][kTiles * 8];    // the tiles' half biases
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int col = lane & 31, half = lane >> 5;
+    const int64_t q0 = ((int64_t)blockIdx.x * 4 + wave) * (NQS * 32);  // may lie beyond nq: such wavefronts only help loading
+    const int even_tiles = shape[0];
+    const int tile0 = blockIdx.y * tiles_per_slice;
+    const int n_tiles = min(shape[1], tile0 + tiles_per_slice);
+    if (tile0 >= n_tiles) {  // the whole workgroup; only the last slice can be empty (a tile more or less of padding)
+        const int64_t q = q0 + lane;
+        if (q < nq) partial[q * gridDim.y + blockIdx.y] = ~0ull;
+        return;
+    }
+
+    v4i b[NQS][4];
+#pragma unroll
+    for (int s = 0; s < NQS; ++s) {
+        int64_t q = q0 + s * 32 + col;
+        if (q >= nq) q = nq - 1;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            b[s][t] = *reinterpret_cast<const v4i*>(queries + q * 128 + (2 * t + half) * 16) ^ (int)0x7f7f7f7f;  // u = 127 - q
+        }
+    }
+    int32_t best[NQS], best_tile[NQS];
+#pragma unroll
+    for (int s = 0; s < NQS; ++s) {
+        best[s] = 0x7fffffff;
+        best_tile[s] = tile0;
+    }
+    const v4i* bias4 = reinterpret_cast<const v4i*>(half_bias);
+    // a step is kTiles tiles: one barrier for all of them (the arrays hold whole steps beyond the last tile)
+    v4i next[kTiles], next_bias;
+    auto fetch = [&](int ct) {
+#pragma unroll
+        for (int i = 0; i < kTiles; ++i) next[i] = rows[(int64_t)(ct + i) * 256 + threadIdx.x];
+        if (threadIdx.x < 8 * kTiles) next_bias = bias4[(int64_t)ct * 8 + threadIdx.x];
+    };
+    auto stage = [&](int buf) {
+#pragma unroll
+        for (int i = 0; i < kTiles; ++i) atile[buf][i * 256 + threadIdx.x] = next[i];
+        if (threadIdx.x < 8 * kTiles) btile[buf][threadIdx.x] = next_bias;
+    };
+    fetch(tile0);
+    stage(0);
+    __syncthreads();
+    int buf = 0;
+    for (int ct0 = tile0; ct0 < n_tiles; ct0 += kTiles, buf ^= 1) {
+        if (ct0 + kTiles < n_tiles) fetch(ct0 + kTiles);
+#pragma unroll
+        for (int i = 0; i < kTiles; ++i) {
+            const int ct = ct0 + i;
+            if (ct >= n_tiles) break;
+            v4i a[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) a[t] = atile[buf][i * 256 + (2 * t + half) * 32 + col];
+            v16i c;
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const v4i bs = btile[buf][i * 8 + 2 * g + half];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) c[4 * g + k] = bs[k];
+            }
+            const int odd = METRIC == 0 && ct >= even_tiles ? 1 : 0;
+            v16i accs[NQS];
+#pragma unroll
+            for (int s = 0; s < NQS; ++s) {
+                accs[s] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[0], b[s][0], c, 0, 0, 0);
+#pragma unroll
+                for (int t = 1; t < 4; ++t) accs[s] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[t], b[s][t], accs[s], 0, 0, 0);
+            }
+#pragma unroll
+            for (int s = 0; s < NQS; ++s) {
+                const v16i v = accs[s];
+                const int32_t m0 = min(min(v[0], v[1]), v[2]), m1 = min(min(v[3], v[4]), v[5]), m2 = min(min(v[6], v[7]), v[8]);
+                const int32_t m3 = min(min(v[9], v[10]), v[11]), m4 = min(min(v[12], v[13]), v[14]);
+                const int32_t m = min(min(min(m0, m1), min(m2, m3)), min(m4, v[15]));
+                const int32_t score = METRIC == 0 ? (m << 1) | odd : m;
+                best_tile[s] = score < best[s] ? ct : best_tile[s];
+                best[s] = min(best[s], score);
+            }
+        }
+        if (ct0 + kTiles < n_tiles) stage(buf ^ 1);
+        __syncthreads();
+    }
+
+    // The 16 rows of the better half's tile, four lanes (32 bytes each) per row; both halves' if their scores are equal.
+    const int row16 = lane >> 2, part = lane & 3;
+    int32_t cluster = 0, score_of = 0;
+    v4i* const uq = &atile[0][0] + wave * 128;
+#pragma unroll
+    for (int s = 0; s < NQS; ++s) {
+        for (int c0 = 0; c0 < 32; c0 += 4) {
+            if ((c0 & 15) == 0) {  // this wavefront's next 16 queries
+                __builtin_amdgcn_wave_barrier();
+                if ((col & 16) == c0) {
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) uq[(col & 15) * 8 + 2 * t + half] = b[s][t];
+                }
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            }
+            int32_t best2[4][2], tile2[4][2];
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    best2[u][h] = __builtin_amdgcn_readlane(best[s], c0 + u + 32 * h);
+                    tile2[u][h] = __builtin_amdgcn_readlane(best_tile[s], c0 + u + 32 * h);
+                }
+            v4i x[4][2];
+            int32_t hb[4], id[4];
+            auto load = [&](int u, int h) {
+                const int32_t tile = h ? tile2[u][1] : tile2[u][0];
+                const int row = 8 * (row16 >> 2) + 4 * h + (row16 & 3);
+#pragma unroll
+                for (int k = 0; k < 2; ++k) x[u][k] = rows[(int64_t)tile * 256 + (part * 2 + k) * 32 + row];
+                hb[u] = half_bias[tile * 32 + row];
+                id[u] = map[tile * 32 + row];
+            };
+            // lowest cluster whose score is `want`
+            auto find = [&](int u, int32_t want, int tile) {
+                int32_t dot = 0;
+#pragma unroll
+                for (int k = 0; k < 2; ++k) {
+                    const v4i q = uq[((c0 & 15) + u) * 8 + part * 2 + k];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) dot = __builtin_amdgcn_sdot4(q[i], x[u][k][i], dot, false);
+                }
+                dot += __builtin_amdgcn_update_dpp(0, dot, 0xB1, 0xf, 0xf, true);  // quad_perm [1,0,3,2]
+                dot += __builtin_amdgcn_update_dpp(0, dot, 0x4E, 0xf, 0xf, true);  // quad_perm [2,3,0,1]
+                const int32_t m = hb[u] + dot;
+                uint64_t hit = __ballot((METRIC == 0 ? 2 * m + (tile >= even_tiles ? 1 : 0) : m) == want);
+                int32_t found = 0x7fffffff;
+                while (hit) {  // one row, but for equal scores
+                    const int l = __builtin_ctzll(hit);
+                    found = min(found, __builtin_amdgcn_readlane(id[u], l));
+                    hit &= ~(0xfull << (l & ~3));
+                }
+                return found;
+            };
+            int pick[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {  // four queries' rows in flight
+                pick[u] = best2[u][1] < best2[u][0] ? 1 : 0;
+                load(u, pick[u]);
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int32_t want = pick[u] ? best2[u][1] : best2[u][0];
+                int32_t found = find(u, want, pick[u] ? tile2[u][1] : tile2[u][0]);
+                if (best2[u][0] == best2[u][1]) {  // uniform
+                    load(u, 1);
+                    found = min(found, find(u, want, tile2[u][1]));
+                }
+                const bool my = lane == s * 32 + c0 + u;
+                cluster = my ? found : cluster;
+                score_of = my ? want : score_of;
+            }
+        }
+    }
+    const int64_t q = q0 + lane;
+    if (q < nq) {
+        if (gridDim.y == 1) out[q] = cluster;
+        else partial[q * gridDim.y + blockIdx.y] = ((uint64_t)((uint32_t)score_of ^ 0x80000000u) << 32) | (uint32_t)cluster;
+    }
+}
+
+template <int METRIC>
+static hipError_t launch_rc(int rc, const uint8_t* centroids, const char* block, int n_clusters,
                             const uint8_t* queries, int64_t nq, int32_t* out, uint64_t* partial, int slices,
                             hipStream_t stream) {
+    const RouteU8Block at(n_clusters);
+    const int32_t* bias = reinterpret_cast<const int32_t*>(block + at.bias);
     const int all_tiles = (n_clusters + 31) / 32;
     const int tiles_per_slice = (all_tiles + slices - 1) / slices;
+    // the final search of route_nearest_u8_kernel takes as long as some eighty tiles: 500 000 queries x 16 384 / 8 192 /
+    // 4 096 / 2 048 centroids in 1.07 / 0.59 / 0.36 / 0.24 ms, the other kernel's 1.34 / 0.71 / 0.37 / 0.19 ms
+    if (rc == 1 && tiles_per_slice >= kMinNearestTiles) {
+        // with both classes padded there may be a tile more than that
+        const int per = (all_tiles + slices) / slices;
+        slices = (all_tiles + per) / per;
+        hipLaunchKernelGGL((route_nearest_u8_kernel<METRIC, kRouteU8StepTiles>), dim3((unsigned)((nq + 255) / 256), (unsigned)slices), dim3(256), 0, stream,
+                           reinterpret_cast<const v4i*>(block + at.rows), reinterpret_cast<const int32_t*>(block + at.half),
+                           reinterpret_cast<const int32_t*>(block + at.map), reinterpret_cast<const int32_t*>(block + at.shape),
+                           queries, nq, out, partial, per);
+        if (slices > 1) return launch_route_merge(rc, partial, slices, nq, out, stream);
+        return hipGetLastError();
+    }
     slices = (all_tiles + tiles_per_slice - 1) / tiles_per_slice;  // no slice may start beyond the last tile
-    const dim3 grid((unsigned)((nq + 255) / 256), (unsigned)slices), block(256);
+    const dim3 grid((unsigned)((nq + 255) / 256), (unsigned)slices), threads(256);
     switch (rc) {
         case 1:
-            hipLaunchKernelGGL((route_mfma_u8_kernel<METRIC, 1>), grid, block, 0, stream, centroids, bias, n_clusters, queries, nq, out, partial, tiles_per_slice);
+            hipLaunchKernelGGL((route_mfma_u8_kernel<METRIC, 1>), grid, threads, 0, stream, centroids, bias, n_clusters, queries, nq, out, partial, tiles_per_slice);
             break;
         case 2:
-            hipLaunchKernelGGL((route_mfma_u8_kernel<METRIC, 2>), grid, block, 0, stream, centroids, bias, n_clusters, queries, nq, out, partial, tiles_per_slice);
+            hipLaunchKernelGGL((route_mfma_u8_kernel<METRIC, 2>), grid, threads, 0, stream, centroids, bias, n_clusters, queries, nq, out, partial, tiles_per_slice);
             break;
         case 3:
-            hipLaunchKernelGGL((route_mfma_u8_kernel<METRIC, 3>), grid, block, 0, stream, centroids, bias, n_clusters, queries, nq, out, partial, tiles_per_slice);
+            hipLaunchKernelGGL((route_mfma_u8_kernel<METRIC, 3>), grid, threads, 0, stream, centroids, bias, n_clusters, queries, nq, out, partial, tiles_per_slice);
             break;
         case 4:
-            hipLaunchKernelGGL((route_mfma_u8_kernel<METRIC, 4>), grid, block, 0, stream, centroids, bias, n_clusters, queries, nq, out, partial, tiles_per_slice);
+            hipLaunchKernelGGL((route_mfma_u8_kernel<METRIC, 4>), grid, threads, 0, stream, centroids, bias, n_clusters, queries, nq, out, partial, tiles_per_slice);
             break;
         case 5:
-            hipLaunchKernelGGL((route_mfma_u8_kernel<METRIC, 5>), grid, block, 0, stream, centroids, bias, n_clusters, queries, nq, out, partial, tiles_per_slice);
+            hipLaunchKernelGGL((route_mfma_u8_kernel<METRIC, 5>), grid, threads, 0, stream, centroids, bias, n_clusters, queries, nq, out, partial, tiles_per_slice);
             break;
         case 6:
-            hipLaunchKernelGGL((route_mfma_u8_kernel<METRIC, 6>), grid, block, 0, stream, centroids, bias, n_clusters, queries, nq, out, partial, tiles_per_slice);
+            hipLaunchKernelGGL((route_mfma_u8_kernel<METRIC, 6>), grid, threads, 0, stream, centroids, bias, n_clusters, queries, nq, out, partial, tiles_per_slice);
             break;
         case 7:
-            hipLaunchKernelGGL((route_mfma_u8_kernel<METRIC, 7>), grid, block, 0, stream, centroids, bias, n_clusters, queries, nq, out, partial, tiles_per_slice);
+            hipLaunchKernelGGL((route_mfma_u8_kernel<METRIC, 7>), grid, threads, 0, stream, centroids, bias, n_clusters, queries, nq, out, partial, tiles_per_slice);
             break;
         case 8:
-            hipLaunchKernelGGL((route_mfma_u8_kernel<METRIC, 8>), grid, block, 0, stream, centroids, bias, n_clusters, queries, nq, out, partial, tiles_per_slice);
+            hipLaunchKernelGGL((route_mfma_u8_kernel<METRIC, 8>), grid, threads, 0, stream, centroids, bias, n_clusters, queries, nq, out, partial, tiles_per_slice);
             break;
         default: return hipErrorInvalidValue;
     }
@@ -253,24 +511,34 @@ static hipError_t launch_rc(int rc, const uint8_t* centroids, const int32_t* bia
     return hipGetLastError();
 }
 
-hipError_t launch_centroid_bias_u8(int metric, const uint8_t* centroids, int n_clusters, int32_t* bias,
-                                   hipStream_t stream) {
-    const int padded = route_mfma_u8_padded(n_clusters);
-    const dim3 grid((unsigned)((padded + 255) / 256)), block(256);
-    if (metric == 0)
-        hipLaunchKernelGGL((centroid_bias_kernel<0>), grid, block, 0, stream, centroids, n_clusters, padded, bias);
-    else
-        hipLaunchKernelGGL((centroid_bias_kernel<1>), grid, block, 0, stream, centroids, n_clusters, padded, bias);
+template <int METRIC>
+static hipError_t fill_block(const uint8_t* centroids, int n_clusters, char* block, hipStream_t stream) {
+    const RouteU8Block at(n_clusters);
+    const int padded = route_mfma_u8_padded(n_clusters), max_tiles = padded / 32 + kRouteU8StepTiles;
+    int32_t* const bias = reinterpret_cast<int32_t*>(block + at.bias);
+    int32_t* const map = reinterpret_cast<int32_t*>(block + at.map);
+    hipLaunchKernelGGL((centroid_bias_kernel<METRIC>), dim3((unsigned)((padded + 255) / 256)), dim3(256), 0, stream, centroids, n_clusters,
+                       padded, bias);
+    hipLaunchKernelGGL((route_u8_order_kernel<METRIC>), dim3(1), dim3(1024), 0, stream, bias, n_clusters, max_tiles,
+                       reinterpret_cast<int32_t*>(block + at.shape), reinterpret_cast<int32_t*>(block + at.half), map);
+    hipLaunchKernelGGL(route_u8_rows_kernel, dim3((unsigned)max_tiles), dim3(256), 0, stream, centroids, n_clusters, (int64_t)max_tiles * 256, map,
+                       reinterpret_cast<v4i*>(block + at.rows));
     return hipGetLastError();
+}
+
+hipError_t launch_route_u8_block(int metric, const uint8_t* centroids, int n_clusters, void* block, hipStream_t stream) {
+    char* const to = static_cast<char*>(block);
+    return metric == 0 ? fill_block<0>(centroids, n_clusters, to, stream) : fill_block<1>(centroids, n_clusters, to, stream);
 }
 
 int route_mfma_u8_slices(int n_clusters, int64_t nq) { return route_slices((n_clusters + 31) / 32, 8, nq); }
 
-hipError_t launch_route_mfma_u8(int metric, int route_c, const uint8_t* centroids, const int32_t* bias, int n_clusters,
+hipError_t launch_route_mfma_u8(int metric, int route_c, const uint8_t* centroids, const void* block, int n_clusters,
                                 const uint8_t* queries, int64_t nq, int32_t* out, uint64_t* partial, int slices,
                                 hipStream_t stream) {
-    return metric == 0 ? launch_rc<0>(route_c, centroids, bias, n_clusters, queries, nq, out, partial, slices, stream)
-                       : launch_rc<1>(route_c, centroids, bias, n_clusters, queries, nq, out, partial, slices, stream);
+    const char* const from = static_cast<const char*>(block);
+    return metric == 0 ? launch_rc<0>(route_c, centroids, from, n_clusters, queries, nq, out, partial, slices, stream)
+                       : launch_rc<1>(route_c, centroids, from, n_clusters, queries, nq, out, partial, slices, stream);
 }
 
 }  // namespace ann

@@ -932,3 +932,34 @@ def test_key_table_gives_the_bits_of_the_gathering_search(torch_cuda, dt, dim, m
         # rows scored: an id beyond the table's rows is remembered in the hash, which may forget it, not in the bitmap
         assert torch.equal(got[0][4], got[1][4]) or max(sizes) > 1.5 * n / nc
     ann.ann_free(h)
+
+
+@pytest.mark.parametrize("metric", [0, 1])
+@pytest.mark.parametrize("n_clusters,nq,levels", [
+    (4096, 66_000, 256),    # one slice of whole tiles
+    (4097, 66_001, 256),    # a last tile of one centroid, a batch that ends inside a wavefront
+    (4100, 66_000, 3),      # three values per byte: many equal scores within and across tiles
+    (5000, 66_000, 1),      # all centroids the same
+    (16_400, 30_000, 256),  # several slices
+])
+def test_uint8_nearest_centroid_among_many(torch_cuda, metric, n_clusters, nq, levels):
+    """The routing of large batches to the nearest of many centroids, against the plain routing kernel."""
+    from paper_2512_02278_amd import ann
+
+    torch, dev = torch_cuda, "cuda:0"
+    g = torch.Generator(device=dev).manual_seed(n_clusters + levels)
+    make = lambda n, top: torch.randint(0, top, (n, 128), generator=g, device=dev, dtype=torch.int32)
+    cen = (make(n_clusters, levels) * (255 // max(levels - 1, 1)) if levels < 256 else make(n_clusters, 256)).to(torch.uint8)
+    if levels == 3:
+        cen[1::2] = cen[0::2]                       # every centroid twice
+    q = make(nq, 256).to(torch.uint8)
+    q[: nq // 2] = cen[torch.randint(0, n_clusters, (nq // 2,), generator=g, device=dev)]
+    off = torch.arange(n_clusters + 1, device=dev)
+    graph = torch.full((n_clusters, 1), -1, dtype=torch.int32, device=dev)
+    h = ann.ann_index_load(cen, graph, metric=metric, entry_mode=1, centroids=cen, cluster_offsets=off, route_c=1)
+    got = ann.ann_route(h, q)
+    ann.ann_index_set_option(h, ann.ANN_OPT_MATRIX_CORE_ROUTING, 0)
+    want = ann.ann_route(h, q)
+    torch.cuda.synchronize()
+    ann.ann_free(h)
+    assert torch.equal(got, want)
