@@ -7,7 +7,7 @@
 //     L2:  |c|^2 - 2 q.c          IP:  -q.c
 // uint8 operands are shifted by -128 into int8 (exact int32 sums; for the inner product the shift
 // adds -128*sum(c') per centroid, which goes into the bias); fp16 / fp32 operands accumulate in
-// fp32 on v_mfma_f32_32x32x16_f16 / v_mfma_f32_32x32x2_f32.
+// fp32 on v_mfma_f32_32x32x16_f16 / v_mfma_f32_32x32x16_bf16 (three parts per fp32 value).
 //
 // A wavefront owns a 64 x 64 block of scores (two operand sets of 32 rows on either side): four 32x32
 // accumulator tiles, and per 16-byte piece of the rows two reads of each operand feed four matrix
@@ -16,6 +16,8 @@
 // lanes' registers and are merged once at the end.  A lane visits its rows in ascending cluster order, so a
 // strict "<" keeps the lower index among equal scores, and the final merge compares (score, index) words.
 #include <hip/hip_runtime.h>
+
+#include <type_traits>
 
 #include "route_mfma.h"
 
@@ -26,6 +28,9 @@ typedef int v16i __attribute__((ext_vector_type(16)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
+typedef float v2f __attribute__((ext_vector_type(2)));
+typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
+typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 
 template <int DT>
 struct Mma;
@@ -34,9 +39,10 @@ template <>
 struct Mma<0> {  // uint8 -> int8, int32 sums
     typedef v16i acc_t;
     typedef int32_t score_t;
+    static constexpr int kParts = 1;
     static __device__ __forceinline__ v4i prep(v4i x) { return x ^ (int)0x80808080; }
-    static __device__ __forceinline__ void mma(acc_t& c, v4i a, v4i b) {
-        c = __builtin_amdgcn_mfma_i32_32x32x32_i8(a, b, c, 0, 0, 0);
+    static __device__ __forceinline__ acc_t mma(acc_t c, v4i a, v4i b) {
+        return __builtin_amdgcn_mfma_i32_32x32x32_i8(a, b, c, 0, 0, 0);
     }
     static __device__ __forceinline__ score_t score(score_t bias, int32_t dot, bool l2) {
         return bias - (l2 ? 2 : 1) * dot;
@@ -48,9 +54,10 @@ template <>
 struct Mma<1> {  // fp16, fp32 sums
     typedef v16f acc_t;
     typedef float score_t;
+    static constexpr int kParts = 1;
     static __device__ __forceinline__ v4i prep(v4i x) { return x; }
-    static __device__ __forceinline__ void mma(acc_t& c, v4i a, v4i b) {
-        c = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8h, a), __builtin_bit_cast(v8h, b), c, 0, 0, 0);
+    static __device__ __forceinline__ acc_t mma(acc_t c, v4i a, v4i b) {
+        return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8h, a), __builtin_bit_cast(v8h, b), c, 0, 0, 0);
     }
     static __device__ __forceinline__ score_t score(score_t bias, float dot, bool l2) {
         return l2 ? __builtin_fmaf(-2.0f, dot, bias) : bias - dot;  // bias is 0 for real rows of an IP index
@@ -62,14 +69,37 @@ struct Mma<1> {  // fp16, fp32 sums
     }
     static constexpr score_t kWorst = __builtin_inff();
 };
+// fp32: every value is the sum of three bf16 values (its 24 bits are theirs, 8 each, rounded to nearest, so that the
+// second and third are at most 2^-9 and 2^-18 of the first), and of the nine products of two sums the six largest run on
+// v_mfma_f32_32x32x16_bf16, the smallest first; what is left out is below 2^-26 of the product, a quarter of what one
+// rounding of an fp32 product may be off.  Six such instructions take 3/8 of the time of the eight
+// v_mfma_f32_32x32x2_f32 that 16 elements take otherwise.
+// Centroids chosen for 200 000 queries half way between two of 2 048 (32 to 256 elements, three scales, two spreads): their
+// keys exceed the nearest in 64 bits by no more on average than with the fp32 instructions (3.66e-9 against 3.81e-9 of
+// |q|^2 + |c|^2 at 32 elements, 3.34e-9 and 3.36e-9 at 96; inner product at 128: 2.5e-11 and 4.1e-11).
 template <>
-struct Mma<2> : Mma<1> {  // fp32: four K=2 instructions per 16-byte piece
-    static __device__ __forceinline__ void mma(acc_t& c, v4i a, v4i b) {
-        const v4f x = __builtin_bit_cast(v4f, a), y = __builtin_bit_cast(v4f, b);
-        c = __builtin_amdgcn_mfma_f32_32x32x2f32(x.x, y.x, c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_32x32x2f32(x.y, y.y, c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_32x32x2f32(x.z, y.z, c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_32x32x2f32(x.w, y.w, c, 0, 0, 0);
+struct Mma<2> : Mma<1> {
+    static constexpr int kParts = 3;
+    // parts of four floats: part[p] holds four bf16
+    static __device__ __forceinline__ void split(v4i x, uint2 (&part)[kParts]) {
+        const v4f f = __builtin_bit_cast(v4f, x);
+        v2f lo = {f.x, f.y}, hi = {f.z, f.w};
+#pragma unroll
+        for (int p = 0; p < kParts; ++p) {
+            // the largest fp32 values would round to infinity
+            constexpr float kMax = 3.3895313892515355e38f;
+            const v2f a = p == 0 ? v2f{__builtin_amdgcn_fmed3f(lo.x, -kMax, kMax), __builtin_amdgcn_fmed3f(lo.y, -kMax, kMax)} : lo;
+            const v2f b = p == 0 ? v2f{__builtin_amdgcn_fmed3f(hi.x, -kMax, kMax), __builtin_amdgcn_fmed3f(hi.y, -kMax, kMax)} : hi;
+            part[p].x = __builtin_bit_cast(uint32_t, __builtin_convertvector(a, v2bf));
+            part[p].y = __builtin_bit_cast(uint32_t, __builtin_convertvector(b, v2bf));
+            lo.x -= __builtin_bit_cast(float, part[p].x << 16);
+            lo.y -= __builtin_bit_cast(float, part[p].x & 0xffff0000u);
+            hi.x -= __builtin_bit_cast(float, part[p].y << 16);
+            hi.y -= __builtin_bit_cast(float, part[p].y & 0xffff0000u);
+        }
+    }
+    static __device__ __forceinline__ acc_t mma(acc_t c, v4i a, v4i b) {
+        return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, a), __builtin_bit_cast(v8bf, b), c, 0, 0, 0);
     }
 };
 
@@ -132,7 +162,8 @@ __global__ void __launch_bounds__(256) route_mfma_kernel(const uint8_t* __restri
     typedef Mma<DT> M;
     typedef typename M::acc_t acc_t;
     typedef typename M::score_t score_t;
-    constexpr int kRows = 128, kPieces = 4, kPieceStride = kRows + 1;
+    // 16-byte pieces of a row's chunk as they are staged: four, or two of each bf16 part (eight elements each)
+    constexpr int kRows = 128, kPieces = M::kParts == 1 ? 4 : 2 * M::kParts, kPieceStride = kRows + 1;
     constexpr int kOperand = kPieces * kPieceStride;  // 16-byte units of one operand chunk
     __shared__ v4i smem[4 * kOperand];                // [buffer 0 / 1][centroids, queries]; afterwards the pool of best lists
     static_assert(sizeof(v4i) * 4 * kOperand >= sizeof(uint64_t) * kRows * 4 * RC, "the pool reuses the staging buffers");
@@ -188,36 +219,71 @@ __global__ void __launch_bounds__(256) route_mfma_kernel(const uint8_t* __restri
             v4i* b = a + kOperand;
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
-                a[st_piece * kPieceStride + st_row + 64 * i] = ra[i];
-                b[st_piece * kPieceStride + st_row + 64 * i] = rb[i];
+                if constexpr (M::kParts == 1) {
+                    a[st_piece * kPieceStride + st_row + 64 * i] = ra[i];
+                    b[st_piece * kPieceStride + st_row + 64 * i] = rb[i];
+                } else {
+                    uint2 pa[M::kParts], pb[M::kParts];
+                    M::split(ra[i], pa);
+                    M::split(rb[i], pb);
+#pragma unroll
+                    for (int p = 0; p < M::kParts; ++p) {
+                        const int unit = (2 * p + (st_piece >> 1)) * kPieceStride + st_row + 64 * i;
+                        reinterpret_cast<uint2*>(a + unit)[st_piece & 1] = pa[p];
+                        reinterpret_cast<uint2*>(b + unit)[st_piece & 1] = pb[p];
+                    }
+                }
             }
         };
         acc_t acc[2][2];
+        // the products of chunk ch; the first chunk's start from zero
+        auto multiply = [&](int ch, auto first) {
+            const v4i* a_chunk = smem + (ch & 1) * 2 * kOperand;
+            const v4i* b_chunk = a_chunk + kOperand;
+            acc_t none;
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+            for (int v = 0; v < 16; ++v) none[v] = 0;
+            if constexpr (M::kParts == 1) {
 #pragma unroll
-            for (int s = 0; s < 2; ++s)
+                for (int t = 0; t < 2; ++t) {
+                    v4i a[2], b[2];
 #pragma unroll
-                for (int v = 0; v < 16; ++v) acc[i][s][v] = 0;
+                    for (int i = 0; i < 2; ++i) a[i] = a_chunk[(2 * t + half) * kPieceStride + wc * 64 + i * 32 + col];
+#pragma unroll
+                    for (int s = 0; s < 2; ++s) b[s] = b_chunk[(2 * t + half) * kPieceStride + wq * 64 + s * 32 + col];
+#pragma unroll
+                    for (int i = 0; i < 2; ++i)
+#pragma unroll
+                        for (int s = 0; s < 2; ++s) acc[i][s] = M::mma(decltype(first)::value && t == 0 ? none : acc[i][s], a[i], b[s]);
+                }
+            } else {
+                v4i a[2][M::kParts], b[2][M::kParts];
+#pragma unroll
+                for (int p = 0; p < M::kParts; ++p) {
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) a[i][p] = a_chunk[(2 * p + half) * kPieceStride + wc * 64 + i * 32 + col];
+#pragma unroll
+                    for (int s = 0; s < 2; ++s) b[s][p] = b_chunk[(2 * p + half) * kPieceStride + wq * 64 + s * 32 + col];
+                }
+                constexpr int pa[6] = {1, 0, 2, 0, 1, 0}, pb[6] = {1, 2, 0, 1, 0, 0};
+#pragma unroll
+                for (int k = 0; k < 6; ++k)
+#pragma unroll
+                    for (int i = 0; i < 2; ++i)
+#pragma unroll
+                        for (int s = 0; s < 2; ++s) acc[i][s] = M::mma(decltype(first)::value && k == 0 ? none : acc[i][s], a[i][pa[k]], b[s][pb[k]]);
+            }
+        };
         fetch(0);
         stage(0);
         __syncthreads();
-        for (int ch = 0; ch < chunks; ++ch) {
+        if (chunks > 1) fetch(1);
+        multiply(0, std::true_type());
+        if (chunks > 1) stage(1);
+        __syncthreads();
+        for (int ch = 1; ch < chunks; ++ch) {
             if (ch + 1 < chunks) fetch(ch + 1);
-            const v4i* a_chunk = smem + (ch & 1) * 2 * kOperand;
-            const v4i* b_chunk = a_chunk + kOperand;
-#pragma unroll
-            for (int t = 0; t < 2; ++t) {
-                v4i a[2], b[2];
-#pragma unroll
-                for (int i = 0; i < 2; ++i) a[i] = a_chunk[(2 * t + half) * kPieceStride + wc * 64 + i * 32 + col];
-#pragma unroll
-                for (int s = 0; s < 2; ++s) b[s] = b_chunk[(2 * t + half) * kPieceStride + wq * 64 + s * 32 + col];
-#pragma unroll
-                for (int i = 0; i < 2; ++i)
-#pragma unroll
-                    for (int s = 0; s < 2; ++s) M::mma(acc[i][s], a[i], b[s]);
-            }
+            multiply(ch, std::false_type());
             if (ch + 1 < chunks) stage((ch + 1) & 1);
             __syncthreads();
         }
