@@ -152,7 +152,7 @@ int ann_search(ann_index_t* handle, const void* queries, int64_t nq, int k, int 
  * call outside any capture first.
  * Limit: the temporaries of one call, each rounded up to 256 bytes -
  *     4*nq*route_c                       routes
- *   + 8*nq*slices*route_c                routing partials of small batches (slices <= 64, nq*slices <= 131072)
+ *   + 8*nq*slices*route_c                routing partials (slices <= 64; nq*slices <= 131072, or at most 8 MiB in all)
  *   + 4*(nq + n_clusters)                execution order, for batches that run grouped by cluster
  * - must fit: e.g. 1M queries at route_c = 1 take 8.1 MB.  A larger batch gives ANN_EUNSUPPORTED
  * and launches nothing; an index with uniform entries needs no temporaries at all.
@@ -176,8 +176,8 @@ int ann_search_counters(ann_index_t* handle, const void* queries, int64_t nq, in
  * The routing step alone (routed indices only): for each query the route_c nearest
  * clusters under (key(query, centroid), cluster index), ascending.
  *   out_clusters  DEVICE, nq*route_c int32
- * Small batches split the centroids over more workgroups and use a stream-ordered scratch of
- * at most nq*64*route_c uint64.
+ * Batches that would not fill the GPU evenly split the centroids over more workgroups and use a
+ * stream-ordered scratch of at most nq*64*route_c uint64.
  */
 int ann_route(ann_index_t* handle, const void* queries, int64_t nq, int32_t* out_clusters, void* stream);
 

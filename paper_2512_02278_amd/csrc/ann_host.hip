@@ -391,7 +391,8 @@ size_t padded256(size_t n) { return (n + 255) / 256 * 256; }
 // Bytes of temporaries the routing of nq queries takes.
 size_t route_scratch_bytes(const ann_index_t* h, int64_t nq) {
     if (nq <= 0 || !(h->matrix_core_routing && (h->centroid_bias || h->route_bias))) return 0;
-    const int slices = h->centroid_bias ? route_mfma_u8_slices(h->d.n_clusters, nq) : route_mfma_slices(h->d.n_clusters, nq);
+    const int slices = h->centroid_bias ? route_mfma_u8_slices(h->d.n_clusters, nq)
+                                        : route_mfma_slices(h->d.dtype, h->d.n_clusters, h->row_bytes, h->d.route_c, nq);
     return slices > 1 ? padded256(sizeof(uint64_t) * (size_t)nq * slices * h->d.route_c) : 0;
 }
 
@@ -414,7 +415,8 @@ int route_impl(ann_index_t* h, const void* queries, int64_t nq, int32_t* out_clu
     hipStream_t st = ws.stream;
     if (h->matrix_core_routing && (h->centroid_bias || h->route_bias)) {
         // matrix-core routing; small batches cut the centroid range into slices and merge them
-        const int slices = h->centroid_bias ? route_mfma_u8_slices(h->d.n_clusters, nq) : route_mfma_slices(h->d.n_clusters, nq);
+        const int slices = h->centroid_bias ? route_mfma_u8_slices(h->d.n_clusters, nq)
+                                        : route_mfma_slices(h->d.dtype, h->d.n_clusters, h->row_bytes, h->d.route_c, nq);
         uint64_t* partial = nullptr;
         if (slices > 1) {
             hipError_t e;

@@ -24,7 +24,7 @@ inline int route_slices(int steps, int min_steps, int64_t nq) {
     if (s > 64) s = 64;
     return s < 1 ? 1 : (int)s;
 }
-int route_mfma_slices(int n_clusters, int64_t nq);
+int route_mfma_slices(int dtype, int n_clusters, int row_bytes, int route_c, int64_t nq);
 
 // Each slice leaves its best (ordered score << 32 | cluster) words in partial[q][slice][route_c],
 // ascending; this picks the route_c smallest per query.

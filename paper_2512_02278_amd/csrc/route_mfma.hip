@@ -144,8 +144,8 @@ __global__ void __launch_bounds__(256) route_bias_kernel(const uint8_t* centroid
 }
 
 // One workgroup: 128 queries against 128 centroids at a time, four wavefronts in a 2 x 2 arrangement, each
-// owning a 64 x 64 block of scores (2 x 2 result tiles of 32 x 32).  The rows are walked in chunks of 64 bytes;
-// a chunk of both operands (128 rows x 64 bytes each) is staged in LDS once per workgroup, piece-major
+// owning a 64 x 64 block of scores (2 x 2 result tiles of 32 x 32).  The rows are walked in chunks of 128 bytes
+// (fp32: 64); a chunk of both operands is staged in LDS once per workgroup, piece-major
 // ([16-byte piece][row], one unit of padding per piece so that the staging writes spread over the banks),
 // which is the order the matrix instruction consumes: lane (row % 32, half) reads consecutive 16-byte units.
 // The next chunk travels from L2 to registers while the current one is multiplied; two LDS buffers, one
@@ -162,8 +162,9 @@ __global__ void __launch_bounds__(256) route_mfma_kernel(const uint8_t* __restri
     typedef Mma<DT> M;
     typedef typename M::acc_t acc_t;
     typedef typename M::score_t score_t;
-    // 16-byte pieces of a row's chunk as they are staged: four, or two of each bf16 part (eight elements each)
-    constexpr int kRows = 128, kPieces = M::kParts == 1 ? 4 : 2 * M::kParts, kPieceStride = kRows + 1;
+    // bytes of a row per chunk, and its 16-byte pieces as they are staged: eight, or two of each bf16 part
+    constexpr int kChunk = M::kParts == 1 ? 128 : 64;
+    constexpr int kRows = 128, kPieces = M::kParts == 1 ? 8 : 2 * M::kParts, kPieceStride = kRows + 1;
     constexpr int kOperand = kPieces * kPieceStride;  // 16-byte units of one operand chunk
     __shared__ v4i smem[4 * kOperand];                // [buffer 0 / 1][centroids, queries]; afterwards the pool of best lists
     static_assert(sizeof(v4i) * 4 * kOperand >= sizeof(uint64_t) * kRows * 4 * RC, "the pool reuses the staging buffers");
@@ -173,14 +174,16 @@ __global__ void __launch_bounds__(256) route_mfma_kernel(const uint8_t* __restri
     const int col = lane & 31, half = lane >> 5;
     const int64_t q0 = (int64_t)blockIdx.x * kRows;
 
-    // staging: thread x moves piece x % 4 of rows x / 4 and x / 4 + 64 (four threads read 64 contiguous bytes)
-    const int st_piece = threadIdx.x & 3, st_row = threadIdx.x >> 2;
-    const uint8_t* qsrc[2];
+    // staging: thread x moves piece x % kMoved of rows x / kMoved + i * kStageRows (the threads of a row read contiguous bytes)
+    constexpr int kMoved = kChunk / 16, kStageRows = 256 / kMoved, kStage = kRows / kStageRows;
+    const int st_piece = threadIdx.x % kMoved, st_row = threadIdx.x / kMoved;
+    const uint8_t* const qbase = queries + q0 * row_bytes + st_piece * 16;
+    int qoff[kStage];
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        int64_t q = q0 + st_row + 64 * i;
-        if (q >= nq) q = nq - 1;
-        qsrc[i] = queries + q * row_bytes + st_piece * 16;
+    for (int i = 0; i < kStage; ++i) {
+        const int64_t left = nq - 1 - q0;  // the last query again beyond the batch's end
+        const int r = st_row + kStageRows * i;
+        qoff[i] = (r < left ? r : (int)left) * row_bytes;
     }
     score_t best_s[2][RC];
     int32_t best_i[2][RC];
@@ -192,43 +195,43 @@ __global__ void __launch_bounds__(256) route_mfma_kernel(const uint8_t* __restri
             best_i[s][r] = 0x7fffffff;
         }
 
-    const int chunks = (row_bytes + 63) / 64;
+    const int chunks = (row_bytes + kChunk - 1) / kChunk;
     const int all_tiles = (n_clusters + kRows - 1) / kRows;
     const int tile_end = min(all_tiles, (int)(blockIdx.y + 1) * tiles_per_slice);
     const v4i zero = v4i{0, 0, 0, 0};
     for (int ct = blockIdx.y * tiles_per_slice; ct < tile_end; ++ct) {
-        const uint8_t* csrc[2];
+        const uint8_t* const cbase = centroids + (int64_t)ct * kRows * row_bytes + st_piece * 16;
+        int coff[kStage];
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            int r = ct * kRows + st_row + 64 * i;
-            if (r >= n_clusters) r = n_clusters - 1;  // its bias never wins
-            csrc[i] = centroids + (int64_t)r * row_bytes + st_piece * 16;
+        for (int i = 0; i < kStage; ++i) {
+            const int r = st_row + kStageRows * i, last = n_clusters - 1 - ct * kRows;
+            coff[i] = (r < last ? r : last) * row_bytes;  // beyond the last: its bias never wins
         }
-        v4i ra[2], rb[2];
+        v4i ra[kStage], rb[kStage];
         auto fetch = [&](int ch) {
-            const int off = ch * 64;
-            const bool ok = off + st_piece * 16 < row_bytes;  // rows are multiples of 32 bytes: the last chunk may be half empty
+            const int off = ch * kChunk;
+            const bool ok = off + st_piece * 16 < row_bytes;  // the last chunk may be partly empty
 #pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                ra[i] = ok ? M::prep(*reinterpret_cast<const v4i*>(csrc[i] + off)) : zero;
-                rb[i] = ok ? M::prep(*reinterpret_cast<const v4i*>(qsrc[i] + off)) : zero;
+            for (int i = 0; i < kStage; ++i) {
+                ra[i] = ok ? M::prep(*reinterpret_cast<const v4i*>(cbase + coff[i] + off)) : zero;
+                rb[i] = ok ? M::prep(*reinterpret_cast<const v4i*>(qbase + qoff[i] + off)) : zero;
             }
         };
         auto stage = [&](int buf) {
             v4i* a = smem + buf * 2 * kOperand;
             v4i* b = a + kOperand;
 #pragma unroll
-            for (int i = 0; i < 2; ++i) {
+            for (int i = 0; i < kStage; ++i) {
                 if constexpr (M::kParts == 1) {
-                    a[st_piece * kPieceStride + st_row + 64 * i] = ra[i];
-                    b[st_piece * kPieceStride + st_row + 64 * i] = rb[i];
+                    a[st_piece * kPieceStride + st_row + kStageRows * i] = ra[i];
+                    b[st_piece * kPieceStride + st_row + kStageRows * i] = rb[i];
                 } else {
                     uint2 pa[M::kParts], pb[M::kParts];
                     M::split(ra[i], pa);
                     M::split(rb[i], pb);
 #pragma unroll
                     for (int p = 0; p < M::kParts; ++p) {
-                        const int unit = (2 * p + (st_piece >> 1)) * kPieceStride + st_row + 64 * i;
+                        const int unit = (2 * p + (st_piece >> 1)) * kPieceStride + st_row + kStageRows * i;
                         reinterpret_cast<uint2*>(a + unit)[st_piece & 1] = pa[p];
                         reinterpret_cast<uint2*>(b + unit)[st_piece & 1] = pb[p];
                     }
@@ -245,7 +248,7 @@ __global__ void __launch_bounds__(256) route_mfma_kernel(const uint8_t* __restri
             for (int v = 0; v < 16; ++v) none[v] = 0;
             if constexpr (M::kParts == 1) {
 #pragma unroll
-                for (int t = 0; t < 2; ++t) {
+                for (int t = 0; t < kPieces / 2; ++t) {
                     v4i a[2], b[2];
 #pragma unroll
                     for (int i = 0; i < 2; ++i) a[i] = a_chunk[(2 * t + half) * kPieceStride + wc * 64 + i * 32 + col];
@@ -391,15 +394,25 @@ hipError_t launch_route_merge(int route_c, const uint64_t* partial, int slices, 
     return hipGetLastError();
 }
 
-// Small batches leave most CUs idle when every workgroup walks all centroids, so the centroid range is cut into
-// slices (grid.y): about 512 workgroups of 128 queries, each slice at least two tiles of 128 centroids, at most 64.
-int route_mfma_slices(int n_clusters, int64_t nq) {
+// Slices of the centroid range (grid.y).  512 workgroups are resident (two per compute unit, for their registers); the
+// slices are chosen so that the last round of workgroups is as full as can be: a workgroup costs its tiles, in chunks of
+// their rows, and about two chunks besides.  25 000 queries x 8 192 centroids of 1536 bytes in five slices: 0.51 ms, in two
+// (as many as fill the chip at all) 0.54 ms.
+// At most 64, at least two tiles each, and partial results of at most 8 MB beyond nq * slices = 131 072.
+int route_mfma_slices(int dtype, int n_clusters, int row_bytes, int route_c, int64_t nq) {
     const int64_t groups = (nq + 127) / 128;
-    const int tiles = (n_clusters + 127) / 128;
-    int64_t s = 512 / groups;
-    if (s > tiles / 2) s = tiles / 2;
-    if (s > 64) s = 64;
-    return s < 1 ? 1 : (int)s;
+    const int tiles = (n_clusters + 127) / 128, chunk = dtype == 2 ? 64 : 128, chunks = (row_bytes + chunk - 1) / chunk;
+    int best = 1;
+    int64_t best_cost = 0;
+    for (int s = 1; s <= 64 && s <= (tiles > 1 ? tiles / 2 : 1); ++s) {
+        if (s > 1 && nq * s > 131072 && nq * s * route_c * 8 > (8 << 20)) break;
+        const int64_t cost = (groups * s + 511) / 512 * ((int64_t)((tiles + s - 1) / s) * chunks + 2);
+        if (s == 1 || cost < best_cost) {
+            best = s;
+            best_cost = cost;
+        }
+    }
+    return best;
 }
 
 template <int DT, int METRIC>
