@@ -963,3 +963,48 @@ def test_uint8_nearest_centroid_among_many(torch_cuda, metric, n_clusters, nq, l
     torch.cuda.synchronize()
     ann.ann_free(h)
     assert torch.equal(got, want)
+
+
+@pytest.mark.parametrize("per_query", [1, 7, 16, 17, 32, 33, 64, 65, 80, 128, 129, 256, 257, 511])
+def test_merge_topk_at_the_edges_of_its_variants(oracle, torch_cuda, per_query):
+    """Lanes per query, registers per lane and lengths of the sorted runs change with per_query and k."""
+    from paper_2512_02278_amd import ann
+
+    rng = np.random.default_rng(per_query)
+    for nq in (1, 17, 130):
+        ids = np.stack([rng.permutation(5000)[:per_query] for _ in range(nq)]).astype(np.int32)
+        ids[rng.random(ids.shape) < 0.2] = -1
+        for keys in (rng.integers(-20, 20, ids.shape).astype(np.int32), np.round(rng.standard_normal(ids.shape), 1).astype(np.float32)):
+            for k in sorted({1, 10, 16, 17, 32, 33, 64, 65, per_query} & set(range(1, per_query + 1))):
+                want = oracle.merge_topk(ids, keys, k)
+                got = ann.ann_merge_topk(torch_cuda.from_numpy(ids).cuda(), torch_cuda.from_numpy(keys).cuda(), k)
+                torch_cuda.cuda.synchronize()
+                assert all(np.array_equal(g.cpu().numpy(), w) for g, w in zip(got, want)), (nq, k)
+
+
+@pytest.mark.parametrize("dt,dims", [("f32", (8, 24, 40, 96, 104)), ("f16", (16, 48, 80, 768)), ("u8", (32, 96, 160))])
+@pytest.mark.parametrize("metric,n_clusters,nq,route_c", [(0, 130, 700, 1), (1, 700, 9_000, 3), (0, 1_500, 40_000, 1)])
+def test_matrix_core_routing_of_partly_empty_chunks_and_uneven_slices(torch_cuda, dt, dims, metric, n_clusters, nq, route_c):
+    """Rows that end inside a chunk, centroid ranges that the slices do not divide; the keys of the chosen clusters are, rank
+    by rank, the smallest in 64 bits up to the rounding of fp32 sums (exact for uint8)."""
+    from paper_2512_02278_amd import ann
+
+    torch, dev = torch_cuda, "cuda:0"
+    for dim in dims:
+        g = torch.Generator(device=dev).manual_seed(dim + n_clusters)
+        make = lambda n: (torch.randint(0, 256, (n, dim), generator=g, device=dev) if dt == "u8" else
+                          torch.randn((n, dim), generator=g, device=dev)).to(getattr(torch, {"u8": "uint8", "f16": "float16", "f32": "float32"}[dt]))
+        cen, q = make(n_clusters), make(nq)
+        h = ann.ann_index_load(cen, torch.full((n_clusters, 1), -1, dtype=torch.int32, device=dev), metric=metric, entry_mode=1,
+                               centroids=cen, cluster_offsets=torch.arange(n_clusters + 1, device=dev), route_c=route_c)
+        got = ann.ann_route(h, q).long()
+        torch.cuda.synchronize()
+        ann.ann_free(h)
+        x, y = q.double(), cen.double()
+        key = -(x @ y.T) if metric else (y * y).sum(1) - 2 * (x @ y.T)
+        want = torch.topk(key, route_c, dim=1, largest=False, sorted=True).values
+        norm = (x * x).sum(1, keepdim=True) + (y * y).sum(1).max()
+        # 2^-24 per rounding of a term, at most 1.5 * dim roundings, of which the square root is seen
+        tol = 0.0 if dt == "u8" else 4 * 2.0 ** -24 * dim ** 0.5
+        assert bool(((key.gather(1, got) - want).abs() <= tol * norm).all())
+        assert route_c == 1 or bool((got.sort(dim=1).values.diff(dim=1) > 0).all())
