@@ -66,6 +66,14 @@ constexpr int64_t kTableBytes = 1ll << 30;
 
 namespace ann {
 
+// Lets the calling thread allocate and query events while another thread captures a stream: that neither fails nor
+// invalidates the other's capture (this call's own stream is not being captured, or it would not be here).
+struct RelaxedCapture {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+};
+
 // Device memory for the key tables of a handle's calls, kept from call to call: allocated and released per call, even
 // from a pool that stays mapped, 300 MB held the calling thread for 0.5 ms.  At most kMost blocks of at most kTableBytes,
 // given back with the handle.  Any number of threads and streams: a block belongs to one call from take() to
@@ -85,6 +93,7 @@ struct TableBlocks {
     // A block of at least `bytes`, or null if there is no memory.
     Block* take(size_t bytes, hipStream_t stream) {
         std::lock_guard<std::mutex> lock(mutex);
+        RelaxedCapture relaxed;
         Block *idle = nullptr, *same_stream = nullptr, *busy = nullptr, *replace = nullptr;
         for (Block& b : blocks) {
             if (b.taken) continue;
@@ -123,8 +132,7 @@ struct TableBlocks {
 
    private:
     static bool grow(Block* b, size_t bytes) {
-        size_t rounded = size_t(16) << 20;
-        while (rounded < bytes) rounded *= 2;
+        const size_t step = size_t(32) << 20, rounded = (bytes + step - 1) / step * step;
         if (b->memory) (void)hipFree(b->memory);
         b->memory = nullptr;
         b->bytes = 0;
