@@ -472,12 +472,16 @@ extern "C" int ann_route(ann_index_t* h, const void* queries, int64_t nq, int32_
 namespace {
 
 // Wavefronts per query when the caller has not fixed them.  A team pays where a round's gathers are the
-// long pole and the chip is not full anyway: long rows (a wavefront covers few of them per instruction and
-// has a bounded number of loads in flight) and a batch that leaves most wavefront slots empty.
+// long pole (long rows: a wavefront covers few of them per instruction and has a bounded number of loads in flight) and the
+// chip is not full anyway: up to 1 024 queries its 1 024 SIMDs hold a wavefront each.  1 / 4 wavefronts per query, us:
+// 1 000 queries over 768-byte rows 214 / 167, 1 024 bytes 274 / 209, 1 536 bytes 276 / 250, but 384 bytes 131 / 146 and 400
+// bytes 212 / 230; 1 500 queries over 384 bytes 143 / 256, 1 024 bytes 416 / 562, 1 536 bytes 671 / 787; 4 800 queries over
+// 1 536 bytes 1 977 / 2 033.  Large batches of long rows are bound by bytes in flight again: 6 000 queries over 1 024 bytes
+// (uniform entries) 3 738 / 3 355, over 1 536 bytes 4 588 / 4 333; 50 000 over 1 536 bytes 33 819 / 33 323.
 int default_team(const ann_index_t* h, int64_t nq) {
-    if (h->row_bytes >= 1024) return 4;               // 1536-byte rows: +15 % even at 50 000 queries per launch
-    if (h->row_bytes >= 256 && nq <= 2048) return 4;  // 384-byte rows: a few percent, small batches only
-    return 1;                                         // 128-byte rows: a round's gathers are one instruction group
+    if (h->row_bytes >= 1024) return nq <= 1024 || nq >= 6000 ? 4 : 1;
+    if (h->row_bytes >= 512) return nq <= 1024 ? 4 : 1;
+    return 1;
 }
 
 // Keys per query of the key table (key_table.h) this call searches with, 0 for a search that gathers every row.
