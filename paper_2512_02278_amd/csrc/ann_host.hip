@@ -231,7 +231,7 @@ extern "C" int ann_index_load(const ann_index_desc_t* desc, ann_index_t** out_ha
     h->route_bias = nullptr;
     const bool mfma_route = d.entry_mode == ANN_ENTRY_ROUTED;
     if (mfma_route && !(d.dtype == ANN_U8 && d.dim == 128) && row_bytes % 32 == 0) {
-        hipError_t e = hipMalloc(&h->route_bias, 4 * (size_t)route_mfma_padded(d.n_clusters));
+        hipError_t e = hipMalloc(&h->route_bias, route_mfma_bias_bytes(d.n_clusters));
         if (e == hipSuccess)
             e = launch_route_bias(d.dtype, d.metric, static_cast<const uint8_t*>(d.centroids), d.n_clusters,
                                   (int)row_bytes, h->route_bias, nullptr);

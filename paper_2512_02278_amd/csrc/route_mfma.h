@@ -7,10 +7,14 @@
 namespace ann {
 
 // Entries of the per-centroid bias array: n_clusters rounded up to whole tiles of 128 rows.
-inline int route_mfma_padded(int n_clusters) { return (n_clusters + 127) / 128 * 128; }
+constexpr int route_mfma_padded(int n_clusters) { return (n_clusters + 127) / 128 * 128; }
+
+// Bytes of what launch_route_bias fills: the array, and for fp32 a word behind it.
+inline size_t route_mfma_bias_bytes(int n_clusters) { return 4 * ((size_t)route_mfma_padded(n_clusters) + 1); }
 
 // bias (4 bytes per entry: int32 for uint8 data, float otherwise): the per-centroid term of the
-// score; padding entries get a value that never wins.
+// score; padding entries get a value that never wins.  fp32: the word behind the array is 0 if every centroid is in the
+// range of the bf16 parts (route_mfma.hip), else 1.
 hipError_t launch_route_bias(int dtype, int metric, const uint8_t* centroids, int n_clusters, int row_bytes, void* bias,
                              hipStream_t stream);
 

@@ -39,7 +39,7 @@ template <>
 struct Mma<0> {  // uint8 -> int8, int32 sums
     typedef v16i acc_t;
     typedef int32_t score_t;
-    static constexpr int kParts = 1;
+    static constexpr int kParts = 1, kChunk = 128;
     static __device__ __forceinline__ v4i prep(v4i x) { return x ^ (int)0x80808080; }
     static __device__ __forceinline__ acc_t mma(acc_t c, v4i a, v4i b) {
         return __builtin_amdgcn_mfma_i32_32x32x32_i8(a, b, c, 0, 0, 0);
@@ -54,7 +54,7 @@ template <>
 struct Mma<1> {  // fp16, fp32 sums
     typedef v16f acc_t;
     typedef float score_t;
-    static constexpr int kParts = 1;
+    static constexpr int kParts = 1, kChunk = 128;
     static __device__ __forceinline__ v4i prep(v4i x) { return x; }
     static __device__ __forceinline__ acc_t mma(acc_t c, v4i a, v4i b) {
         return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8h, a), __builtin_bit_cast(v8h, b), c, 0, 0, 0);
@@ -77,21 +77,27 @@ struct Mma<1> {  // fp16, fp32 sums
 // Centroids chosen for 200 000 queries half way between two of 2 048 (32 to 256 elements, three scales, two spreads): their
 // keys exceed the nearest in 64 bits by no more on average than with the fp32 instructions (3.66e-9 against 3.81e-9 of
 // |q|^2 + |c|^2 at 32 elements, 3.34e-9 and 3.36e-9 at 96; inner product at 128: 2.5e-11 and 4.1e-11).
+//
+// A sum of parts is what the fp32 instruction gives only while no product of two parts overflows (the parts of a large
+// value differ in sign: infinity minus infinity) and none that counts underflows.  Rows whose largest magnitude lies
+// outside [2^-40, 2^57) are therefore ranked by the fp32 instruction (Mma<3>): within it a sum of 1 536 products stays
+// below 2^126, and of the largest product of two rows (2^-80 at least) 46 bits lie above the smallest normal value.
 template <>
 struct Mma<2> : Mma<1> {
-    static constexpr int kParts = 3;
+    static constexpr int kParts = 3, kChunk = 64;
+    // whether the row whose largest magnitude has these bits (0: a row of zeros) is not for this instruction
+    static __device__ __forceinline__ bool apart(uint32_t peak) {
+        return peak != 0u && (peak < __builtin_bit_cast(uint32_t, 0x1p-40f) || peak >= __builtin_bit_cast(uint32_t, 0x1p57f));
+    }
+    static __device__ __forceinline__ uint32_t magnitude(uint32_t bits) { return bits & 0x7fffffffu; }
     // parts of four floats: part[p] holds four bf16
     static __device__ __forceinline__ void split(v4i x, uint2 (&part)[kParts]) {
         const v4f f = __builtin_bit_cast(v4f, x);
         v2f lo = {f.x, f.y}, hi = {f.z, f.w};
 #pragma unroll
         for (int p = 0; p < kParts; ++p) {
-            // the largest fp32 values would round to infinity
-            constexpr float kMax = 3.3895313892515355e38f;
-            const v2f a = p == 0 ? v2f{__builtin_amdgcn_fmed3f(lo.x, -kMax, kMax), __builtin_amdgcn_fmed3f(lo.y, -kMax, kMax)} : lo;
-            const v2f b = p == 0 ? v2f{__builtin_amdgcn_fmed3f(hi.x, -kMax, kMax), __builtin_amdgcn_fmed3f(hi.y, -kMax, kMax)} : hi;
-            part[p].x = __builtin_bit_cast(uint32_t, __builtin_convertvector(a, v2bf));
-            part[p].y = __builtin_bit_cast(uint32_t, __builtin_convertvector(b, v2bf));
+            part[p].x = __builtin_bit_cast(uint32_t, __builtin_convertvector(lo, v2bf));
+            part[p].y = __builtin_bit_cast(uint32_t, __builtin_convertvector(hi, v2bf));
             lo.x -= __builtin_bit_cast(float, part[p].x << 16);
             lo.y -= __builtin_bit_cast(float, part[p].x & 0xffff0000u);
             hi.x -= __builtin_bit_cast(float, part[p].y << 16);
@@ -102,9 +108,22 @@ struct Mma<2> : Mma<1> {
         return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, a), __builtin_bit_cast(v8bf, b), c, 0, 0, 0);
     }
 };
+template <>
+struct Mma<3> : Mma<1> {  // fp32, the values as they are: four K = 2 instructions per 16-byte piece
+    static constexpr int kChunk = 64;
+    static __device__ __forceinline__ acc_t mma(acc_t c, v4i a, v4i b) {
+        const v4f x = __builtin_bit_cast(v4f, a), y = __builtin_bit_cast(v4f, b);
+        c = __builtin_amdgcn_mfma_f32_32x32x2f32(x.x, y.x, c, 0, 0, 0);
+        c = __builtin_amdgcn_mfma_f32_32x32x2f32(x.y, y.y, c, 0, 0, 0);
+        c = __builtin_amdgcn_mfma_f32_32x32x2f32(x.z, y.z, c, 0, 0, 0);
+        return __builtin_amdgcn_mfma_f32_32x32x2f32(x.w, y.w, c, 0, 0, 0);
+    }
+};
+
+__global__ void route_no_centroid_apart_kernel(uint32_t* flag) { *flag = 0u; }
 
 // bias[c]: the per-centroid term of the score; rows beyond n_clusters (padding up to a multiple
-// of 64) get a value that never wins.
+// of 128) get a value that never wins.  fp32: the word behind them becomes 1 if any centroid is not for the bf16 parts.
 template <int DT, int METRIC>
 __global__ void __launch_bounds__(256) route_bias_kernel(const uint8_t* centroids, int n_clusters, int padded,
                                                          int row_bytes, void* bias_out) {
@@ -131,15 +150,18 @@ __global__ void __launch_bounds__(256) route_bias_kernel(const uint8_t* centroid
             return;
         }
         float acc = 0.0f;
-        if (METRIC == 0) {
+        uint32_t peak = 0u;
+        if (METRIC == 0 || DT == 2) {
             const int n = row_bytes / (DT == 1 ? 2 : 4);
             for (int i = 0; i < n; ++i) {
                 const float v = DT == 1 ? (float)reinterpret_cast<const _Float16*>(row)[i]
                                         : reinterpret_cast<const float*>(row)[i];
-                acc = __builtin_fmaf(v, v, acc);
+                if (METRIC == 0) acc = __builtin_fmaf(v, v, acc);
+                if (DT == 2) peak = max(peak, Mma<2>::magnitude(__builtin_bit_cast(uint32_t, v)));
             }
         }
         bias[c] = acc;
+        if (DT == 2 && Mma<2>::apart(peak)) reinterpret_cast<uint32_t*>(bias)[padded] = 1u;
     }
 }
 
@@ -151,22 +173,27 @@ __global__ void __launch_bounds__(256) route_bias_kernel(const uint8_t* centroid
 // The next chunk travels from L2 to registers while the current one is multiplied; two LDS buffers, one
 // barrier per chunk.  (Streaming the operands straight from L1/L2 in the instruction's layout - 32 rows x 32
 // bytes per load - left this kernel at a twelfth of the fp16 matrix rate.)
-template <int DT, int METRIC, int RC>
-__global__ void __launch_bounds__(256) route_mfma_kernel(const uint8_t* __restrict__ centroids,
-                                                         const void* __restrict__ bias_in, int n_clusters,
-                                                         int row_bytes, const uint8_t* __restrict__ queries,
-                                                         int64_t nq, int32_t* __restrict__ out,
-                                                         uint64_t* __restrict__ partial, int tiles_per_slice) {
+template <int I>
+constexpr int route_operand_units() {  // 16-byte units of one operand chunk in LDS
+    return (Mma<I>::kParts == 1 ? Mma<I>::kChunk / 16 : 2 * Mma<I>::kParts) * (128 + 1);
+}
+
+// I: how the products are taken (Mma<I>).  The bits of apart[] (fp32 only, else null) are the rows of the workgroup's 128
+// queries that the bf16 parts are not for: Mma<2> sets them and leaves those rows out, Mma<3> writes them only.
+template <int I, int METRIC, int RC>
+__device__ __forceinline__ void route_queries(v4i* smem, uint32_t* apart, const uint8_t* __restrict__ centroids,
+                                              const void* __restrict__ bias_in, int n_clusters, int row_bytes,
+                                              const uint8_t* __restrict__ queries, int64_t nq, int32_t* __restrict__ out,
+                                              uint64_t* __restrict__ partial, int tiles_per_slice) {
     // blockIdx.y = slice of the 128-centroid tiles this workgroup walks; with several slices the best words
     // of a slice go to partial[q][slice][RC] and route_merge_kernel finishes the job
-    typedef Mma<DT> M;
+    typedef Mma<I> M;
     typedef typename M::acc_t acc_t;
     typedef typename M::score_t score_t;
-    // bytes of a row per chunk, and its 16-byte pieces as they are staged: eight, or two of each bf16 part
-    constexpr int kChunk = M::kParts == 1 ? 128 : 64;
-    constexpr int kRows = 128, kPieces = M::kParts == 1 ? 8 : 2 * M::kParts, kPieceStride = kRows + 1;
-    constexpr int kOperand = kPieces * kPieceStride;  // 16-byte units of one operand chunk
-    __shared__ v4i smem[4 * kOperand];                // [buffer 0 / 1][centroids, queries]; afterwards the pool of best lists
+    // bytes of a row per chunk, and its 16-byte pieces as they are staged: all of them, or two of each bf16 part
+    constexpr int kChunk = M::kChunk;
+    constexpr int kRows = 128, kPieces = M::kParts == 1 ? kChunk / 16 : 2 * M::kParts, kPieceStride = kRows + 1;
+    constexpr int kOperand = route_operand_units<I>();
     static_assert(sizeof(v4i) * 4 * kOperand >= sizeof(uint64_t) * kRows * 4 * RC, "the pool reuses the staging buffers");
     const score_t* bias = static_cast<const score_t*>(bias_in);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -185,6 +212,9 @@ __global__ void __launch_bounds__(256) route_mfma_kernel(const uint8_t* __restri
         const int r = st_row + kStageRows * i;
         qoff[i] = (r < left ? r : (int)left) * row_bytes;
     }
+    uint32_t peak[kStage];  // of this thread's share of its rows
+#pragma unroll
+    for (int i = 0; i < kStage; ++i) peak[i] = 0u;
     score_t best_s[2][RC];
     int32_t best_i[2][RC];
 #pragma unroll
@@ -199,7 +229,8 @@ __global__ void __launch_bounds__(256) route_mfma_kernel(const uint8_t* __restri
     const int all_tiles = (n_clusters + kRows - 1) / kRows;
     const int tile_end = min(all_tiles, (int)(blockIdx.y + 1) * tiles_per_slice);
     const v4i zero = v4i{0, 0, 0, 0};
-    for (int ct = blockIdx.y * tiles_per_slice; ct < tile_end; ++ct) {
+    const int tile0 = blockIdx.y * tiles_per_slice;
+    for (int ct = tile0; ct < tile_end; ++ct) {
         const uint8_t* const cbase = centroids + (int64_t)ct * kRows * row_bytes + st_piece * 16;
         int coff[kStage];
 #pragma unroll
@@ -220,6 +251,14 @@ __global__ void __launch_bounds__(256) route_mfma_kernel(const uint8_t* __restri
         auto stage = [&](int buf) {
             v4i* a = smem + buf * 2 * kOperand;
             v4i* b = a + kOperand;
+            if constexpr (I == 2) {
+                if (ct == tile0) {
+#pragma unroll
+                    for (int i = 0; i < kStage; ++i)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) peak[i] = max(peak[i], M::magnitude((uint32_t)rb[i][e]));
+                }
+            }
 #pragma unroll
             for (int i = 0; i < kStage; ++i) {
                 if constexpr (M::kParts == 1) {
@@ -323,6 +362,19 @@ __global__ void __launch_bounds__(256) route_mfma_kernel(const uint8_t* __restri
         }
     }
 
+    if constexpr (I == 2) {
+        // the kMoved threads of a row are neighbours; the barrier below is before the bits are read
+        static_assert(kMoved == 4, "a quad of lanes per row");
+#pragma unroll
+        for (int i = 0; i < kStage; ++i) {
+            uint32_t top = peak[i];
+            top = max(top, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)top, 0xB1, 0xf, 0xf, true));  // quad_perm [1,0,3,2]
+            top = max(top, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)top, 0x4E, 0xf, 0xf, true));  // quad_perm [2,3,0,1]
+            const int r = st_row + kStageRows * i;
+            if (st_piece == 0 && M::apart(top)) atomicOr(&apart[r >> 5], 1u << (r & 31));
+        }
+    }
+
     // A query's candidates sit in four ascending lists: two lanes (halves) in each of the two wavefronts that
     // hold its row of the tile.  They meet in LDS (the staging buffers are free now) and one thread per
     // query merges them.
@@ -335,7 +387,9 @@ __global__ void __launch_bounds__(256) route_mfma_kernel(const uint8_t* __restri
                 ((uint64_t)M::ordered(best_s[s][r]) << 32) | (uint32_t)best_i[s][r];
     __syncthreads();
     const int64_t q = q0 + threadIdx.x;
-    if (threadIdx.x < kRows && q < nq) {
+    bool wanted = threadIdx.x < kRows && q < nq;
+    if constexpr (I >= 2) wanted = wanted && (apart[(threadIdx.x >> 5) & 3] >> (threadIdx.x & 31) & 1u) == (I == 3 ? 1u : 0u);
+    if (wanted) {
         const uint64_t* mine = pool + threadIdx.x * 4 * RC;
         int at[4] = {0, 0, 0, 0};
         for (int r = 0; r < RC; ++r) {
@@ -356,6 +410,29 @@ __global__ void __launch_bounds__(256) route_mfma_kernel(const uint8_t* __restri
             else
                 partial[(q * gridDim.y + blockIdx.y) * RC + r] = best;
         }
+    }
+}
+
+template <int DT, int METRIC, int RC>
+__global__ void __launch_bounds__(256) route_mfma_kernel(const uint8_t* __restrict__ centroids,
+                                                         const void* __restrict__ bias, int n_clusters,
+                                                         int row_bytes, const uint8_t* __restrict__ queries,
+                                                         int64_t nq, int32_t* __restrict__ out,
+                                                         uint64_t* __restrict__ partial, int tiles_per_slice) {
+    // [buffer 0 / 1][centroids, queries]; afterwards the pool of best lists
+    __shared__ v4i smem[4 * (DT == 2 && route_operand_units<3>() > route_operand_units<DT>() ? route_operand_units<3>() : route_operand_units<DT>())];
+    if constexpr (DT != 2) {
+        route_queries<DT, METRIC, RC>(smem, nullptr, centroids, bias, n_clusters, row_bytes, queries, nq, out, partial, tiles_per_slice);
+    } else {
+        // an extreme centroid counts for every query, an extreme query for itself: which queries share a workgroup
+        // changes no result
+        __shared__ uint32_t apart[4];
+        const bool all = static_cast<const uint32_t*>(bias)[route_mfma_padded(n_clusters)] != 0u;
+        if (threadIdx.x < 4) apart[threadIdx.x] = all ? ~0u : 0u;
+        if (!all) route_queries<2, METRIC, RC>(smem, apart, centroids, bias, n_clusters, row_bytes, queries, nq, out, partial, tiles_per_slice);
+        __syncthreads();
+        if (__builtin_amdgcn_readfirstlane((int)(apart[0] | apart[1] | apart[2] | apart[3])))
+            route_queries<3, METRIC, RC>(smem, apart, centroids, bias, n_clusters, row_bytes, queries, nq, out, partial, tiles_per_slice);
     }
 }
 
@@ -440,6 +517,7 @@ static hipError_t launch_rc(int rc, const uint8_t* centroids, const void* bias, 
 template <int DT, int METRIC>
 static hipError_t launch_bias(const uint8_t* centroids, int n_clusters, int row_bytes, void* bias, hipStream_t stream) {
     const int padded = route_mfma_padded(n_clusters);
+    if (DT == 2) hipLaunchKernelGGL(route_no_centroid_apart_kernel, dim3(1), dim3(1), 0, stream, static_cast<uint32_t*>(bias) + padded);
     hipLaunchKernelGGL((route_bias_kernel<DT, METRIC>), dim3((unsigned)((padded + 255) / 256)), dim3(256), 0, stream,
                        centroids, n_clusters, padded, row_bytes, bias);
     return hipGetLastError();

@@ -1008,3 +1008,60 @@ def test_matrix_core_routing_of_partly_empty_chunks_and_uneven_slices(torch_cuda
         tol = 0.0 if dt == "u8" else 4 * 2.0 ** -24 * dim ** 0.5
         assert bool(((key.gather(1, got) - want).abs() <= tol * norm).all())
         assert route_c == 1 or bool((got.sort(dim=1).values.diff(dim=1) > 0).all())
+
+
+def routes_to_centroids(torch, q, cen, metric, route_c):
+    """ann_route over an index whose vectors are the centroids."""
+    from paper_2512_02278_amd import ann
+
+    n = cen.shape[0]
+    h = ann.ann_index_load(cen, torch.full((n, 1), -1, dtype=torch.int32, device=cen.device), metric=metric, entry_mode=1,
+                           centroids=cen, cluster_offsets=torch.arange(n + 1, device=cen.device), route_c=route_c)
+    got = ann.ann_route(h, q).cpu().numpy()
+    ann.ann_free(h)
+    return got
+
+
+@pytest.mark.parametrize("metric", [0, 1])
+@pytest.mark.parametrize("nq,n_clusters,route_c", [(300, 200, 1), (5_000, 700, 3), (70_000, 300, 1)])
+def test_fp32_routing_of_extreme_values(torch_cuda, metric, nq, n_clusters, route_c):
+    """Infinite components, products beyond the largest and near the smallest fp32 numbers, among ordinary queries: the
+    extreme ones are ranked by what an fp32 product gives them, the others as if they were alone."""
+    torch, dim = torch_cuda, 96
+    rng = np.random.default_rng(n_clusters + metric)
+    cen = rng.standard_normal((n_clusters, dim)).astype(np.float32)
+    ordinary = rng.standard_normal((nq, dim)).astype(np.float32)
+    q = ordinary.copy()
+    inf, big, small = (np.sort(rng.choice(nq, (3, nq // 30), replace=False), axis=1))
+    at = rng.integers(0, dim, (2, nq // 30))
+    q[inf, at[0]] = np.where(rng.random(nq // 30) < 0.5, np.inf, -np.inf)
+    q[big] = 0                                              # one product per score, which overflows for some centroids
+    q[big, at[1]] = np.where(rng.random(nq // 30) < 0.5, 3e38, -3e38)
+    a, b = rng.integers(0, n_clusters, (2, nq // 30))
+    q[small] = ((cen[a].astype(np.float64) + cen[b]) * 1e-36).astype(np.float32)    # about half way between two centroids
+    to = lambda v: torch.from_numpy(v).cuda()
+    got = routes_to_centroids(torch, to(q), to(cen), metric, route_c)
+    assert got.min() >= 0 and got.max() < n_clusters
+    bias = (cen.astype(np.float64) ** 2).sum(1) if metric == 0 else np.zeros(n_clusters)
+    with np.errstate(over="ignore"):
+        for rows, col in ((inf, at[0]), (big, at[1])):
+            dot = (q[rows, col].astype(np.float64)[:, None] * cen[:, col].T).astype(np.float32)
+            score = (bias - (2.0 if metric == 0 else 1.0) * dot.astype(np.float64)).astype(np.float32)
+            want = np.argsort(score, axis=1, kind="stable")[:, :route_c]
+            assert np.array_equal(got[rows], want)
+    x, y = q[small].astype(np.float64), cen.astype(np.float64)
+    key = bias - (2.0 if metric == 0 else 1.0) * (x @ y.T)
+    # 2^-24 of the terms' sizes for each of dim roundings, 2^-150 where a product or a sum is subnormal
+    bound = dim * (2.0 ** -24 * (bias + 2 * np.abs(x) @ np.abs(y).T).max(1, keepdims=True) + 2.0 ** -150)
+    assert (np.take_along_axis(key, got[small], 1) - np.sort(key, axis=1)[:, :route_c] <= 2 * bound).all()
+    # the others
+    rest = np.setdiff1d(np.arange(nq), np.concatenate([inf, big, small]))
+    assert np.array_equal(got[rest], routes_to_centroids(torch, to(ordinary), to(cen), metric, route_c)[rest])
+    # an extreme centroid
+    cen[5] *= 1e25
+    cen[7, :] = 0
+    got = routes_to_centroids(torch, to(ordinary), to(cen), metric, route_c)
+    x, y = ordinary.astype(np.float64), cen.astype(np.float64)
+    key = ((y * y).sum(1) if metric == 0 else 0) - (2.0 if metric == 0 else 1.0) * (x @ y.T)
+    size = np.take_along_axis((y * y).sum(1) + (x * x).sum(1)[:, None], got, 1)
+    assert (np.take_along_axis(key, got, 1) - np.sort(key, axis=1)[:, :route_c] <= dim * 2.0 ** -23 * size).all()
