@@ -598,7 +598,6 @@ int search_impl(ann_index_t* h, const void* queries, int64_t nq, const int32_t* 
         p.order = order;
         p.table = table;
         p.table_stride = table ? stride : 0;
-        size_t lds_bytes = plan.lds_bytes;
         if (table) {
             KeyTableParams t;
             t.vectors = p.vectors;
@@ -622,11 +621,8 @@ int search_impl(ann_index_t* h, const void* queries, int64_t nq, const int32_t* 
             t.table = table;
             e = launch_key_table(h->d.dtype, h->d.metric, h->variant->g, h->variant->nch, t, stream);
             if (e != hipSuccess) break;
-            // the bitmap covers no more ids than the table
-            lds_bytes -= sizeof(uint32_t) * (size_t)(p.window_bits / 32 - (stride + 31) / 32);
-            p.window_bits = (stride + 31) / 32 * 32;
         }
-        e = h->variant->search(p, plan.list_variant, team, (unsigned)(8 * p.q_per_xcd), lds_bytes, stream);
+        e = h->variant->search(p, plan.list_variant, team, (unsigned)(8 * p.q_per_xcd), plan.lds_bytes, stream);
     }
     if (block) h->tables.give_back(block, stream);
     if (e != hipSuccess) return fail(ANN_EHIP, "ann_search: launch failed: %s", hipGetErrorString(e));

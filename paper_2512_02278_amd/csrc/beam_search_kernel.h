@@ -56,7 +56,7 @@ struct SearchParams {
     const int32_t* order;   // execution order: the launch's i-th query is order[q_base + i]; null = identity
     int64_t q_per_xcd;      // queries of this launch handed to each of the 8 XCDs
     const uint32_t* table;  // ordered keys of the launch's i-th query against its first window, i * table_stride on; or null
-    int32_t table_stride;   // keys per query; no window is longer (TABLE kernels)
+    int32_t table_stride;   // keys per query
 };
 
 constexpr uint32_t kEmptySlot = 0xffffffffu;
@@ -88,9 +88,9 @@ __device__ __forceinline__ bool hash_insert(uint32_t* table, int hash_bits, uint
 // keys of a round, which is where the time of a round with long rows goes when few queries are in
 // flight (a wavefront has only so many loads in flight; TEAM of them have TEAM times as many).
 //
-// TABLE: the keys of a query against every row of its (only) window have been computed beforehand
-// (key_table.h), so a new id of the window costs one 4-byte read instead of a row gather and its arithmetic.
-// Ids outside the window are gathered as ever.  Such a search takes 0.26 ms for 5 000 queries over 1536-byte rows
+// TABLE: the keys of a query against the first table_stride rows of its (only) window have been computed beforehand
+// (key_table.h), so a new id among them costs one 4-byte read instead of a row gather and its arithmetic.
+// Other ids are gathered as ever, and the visited set is the same as without a table.  Such a search takes 0.26 ms for 5 000 queries over 1536-byte rows
 // (512 neighbours a round) that took 1.98 ms with gathers, and 0.80 ms for 20 000 over 384-byte rows instead of
 // 1.33 ms.  Two thirds of the vector-ALU issue slots are used then; the rest waits for graph rows and LDS.
 template <class Row, int LPL, int CPL, int TEAM = 1, bool TABLE = false>
@@ -119,7 +119,8 @@ struct BeamSearch {
     int n_windows;
     uint32_t w0_lo, w0_size;  // first window: ids [w0_lo, w0_lo + w0_size) are bits 0..
     int n_table;  // ids in the visited hash
-    const uint32_t* keys;  // TABLE: this query's row of the key table
+    const uint32_t* keys;  // TABLE: this query's row of the key table, the keys of ids [w0_lo, w0_lo + n_keys)
+    uint32_t n_keys;
     uint64_t worst;  // list entry number itopk-1 (the empty key while the list is not full), kept up to date by merge_all
     int n_dist, n_parents, n_resets;
 
@@ -141,7 +142,7 @@ struct BeamSearch {
         bitmap = team + kTeamWords;
         table = bitmap + (p.window_bits >> 5);
         n_windows = n_table = n_dist = n_parents = n_resets = 0;
-        w0_lo = w0_size = 0;
+        w0_lo = w0_size = n_keys = 0;
     }
 
     // Orders this wavefront's LDS accesses: what it wrote before is what its lanes read after.  A lone
@@ -241,11 +242,11 @@ struct BeamSearch {
             const uint32_t rel = (uint32_t)id[t] - w0_lo;
             const bool valid = t * 64 + lane < count && (uint32_t)id[t] < (uint32_t)p.n;
             fresh[t] = false;
-            if (valid && rel < w0_size) {
+            if (valid && rel < n_keys) {
                 const uint32_t bit = 1u << (rel & 31);
                 fresh[t] = (atomicOr(&bitmap[rel >> 5], bit) & bit) == 0;
             }
-            outside |= valid && rel >= w0_size;
+            outside |= valid && rel >= n_keys;
         }
         uint32_t okey[CPL];
 #pragma unroll
@@ -267,7 +268,7 @@ struct BeamSearch {
             int m = 0;
 #pragma unroll
             for (int t = 0; t < CPL; ++t)
-                filter_into(id[t], t * 64 + lane < count && (uint32_t)id[t] - w0_lo >= w0_size, m);
+                filter_into(id[t], t * 64 + lane < count && (uint32_t)id[t] - w0_lo >= n_keys, m);
             lds_sync();
             kept = score(m, kept);
         }
@@ -541,7 +542,7 @@ struct BeamSearch {
                 const int32_t c = p.route[qi * p.route_c + w];
                 const bool known = (uint32_t)c < (uint32_t)p.n_clusters;
                 const int64_t lo = known ? p.cluster_offsets[c] : 0, hi = known ? p.cluster_offsets[c + 1] : 0;
-                const uint32_t room = (TABLE ? (uint32_t)p.table_stride : (uint32_t)p.window_bits) - bit;
+                const uint32_t room = (uint32_t)p.window_bits - bit;
                 const uint32_t size = hi <= lo ? 0u : (uint64_t)(hi - lo) < room ? (uint32_t)(hi - lo) : room;
                 if (lane == 0) {
                     wtab[3 * w] = (uint32_t)lo;
@@ -551,6 +552,7 @@ struct BeamSearch {
                 if (w == 0) {
                     w0_lo = (uint32_t)lo;
                     w0_size = size;
+                    if constexpr (TABLE) n_keys = size < (uint32_t)p.table_stride ? size : (uint32_t)p.table_stride;
                 }
                 bit += size;
             }
