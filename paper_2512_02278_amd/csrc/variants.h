@@ -29,9 +29,11 @@ template <int DT, int METRIC, int G, int NCH>
 hipError_t launch_route(const RouteParams& p, hipStream_t stream);
 
 #define ANN_LAUNCH_LIST(LPL, CPL)                                                                                                \
-    if (p.table) {                                                                                                               \
-        hipLaunchKernelGGL((beam_search_kernel<Row, LPL, CPL, 1, true>), dim3(grid), dim3(64), lds_bytes, stream, p);            \
-        break;                                                                                                                   \
+    if constexpr (Row::kDtype != kU8) { /* no uint8 index has a table */                                                         \
+        if (p.table) {                                                                                                           \
+            hipLaunchKernelGGL((beam_search_kernel<Row, LPL, CPL, 1, true>), dim3(grid), dim3(64), lds_bytes, stream, p);        \
+            break;                                                                                                               \
+        }                                                                                                                        \
     }                                                                                                                            \
     switch (team) {                                                                                                              \
         case 1: hipLaunchKernelGGL((beam_search_kernel<Row, LPL, CPL, 1, false>), dim3(grid), dim3(64), lds_bytes, stream, p); break;  \
