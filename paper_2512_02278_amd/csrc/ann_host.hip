@@ -471,17 +471,36 @@ extern "C" int ann_route(ann_index_t* h, const void* queries, int64_t nq, int32_
 
 namespace {
 
-// Wavefronts per query when the caller has not fixed them.  A team pays where a round's gathers are the
-// long pole (long rows: a wavefront covers few of them per instruction and has a bounded number of loads in flight) and the
-// chip is not full anyway: up to 1 024 queries its 1 024 SIMDs hold a wavefront each.  1 / 4 wavefronts per query, us:
-// 1 000 queries over 768-byte rows 214 / 167, 1 024 bytes 274 / 209, 1 536 bytes 276 / 250, but 384 bytes 131 / 146 and 400
-// bytes 212 / 230; 1 500 queries over 384 bytes 143 / 256, 1 024 bytes 416 / 562, 1 536 bytes 671 / 787; 4 800 queries over
-// 1 536 bytes 1 977 / 2 033.  Large batches of long rows are bound by bytes in flight again: 6 000 queries over 1 024 bytes
-// (uniform entries) 3 738 / 3 355, over 1 536 bytes 4 588 / 4 333; 50 000 over 1 536 bytes 33 819 / 33 323.
-int default_team(const ann_index_t* h, int64_t nq) {
-    if (h->row_bytes >= 1024) return nq <= 1024 || nq >= 6000 ? 4 : 1;
-    if (h->row_bytes >= 512) return nq <= 1024 ? 4 : 1;
-    return 1;
+// Wavefronts per query when the caller has not fixed them.  A team pays where a round's gathers are the long pole (rows of 256
+// bytes and more: a wavefront covers few of them per instruction and has a bounded number of loads in flight) and the chip is
+// not full anyway: up to 1 024 queries its 1 024 SIMDs hold all wavefronts of teams of four at once.
+// 1 / 2 / 4 wavefronts per query, us, uniform entries, list of 100, 81 neighbours a round:
+//     queries     50             1 000             1 500             3 001             6 000
+//   256 bytes   335/291/262    438/383/342       455/409/369       561/508/618       702/747/1 019
+//   384         328/299/270    452/419/378       462/425/463       571/655/745       962/921/1 183
+//   400         467/377/307    697/560/466       699/575/575       796/781/840     1 237/1 153/1 373
+//   512         433/343/282    573/463/390       587/487/546       771/705/762     1 238/1 156/1 263
+//   768         574/442/356    893/666/542       905/687/584     1 105/959/952     1 781/1 653/1 594
+//   1 024       943/667/506  1 015/726/572     1 040/789/675   1 329/1 178/1 148   2 167/2 171/2 082
+//   1 536       672/488/385  1 034/816/713     1 181/989/929   1 789/1 594/1 542   3 080/2 963/2 878
+// In a routed search most neighbours have been seen, and a round has fewer rows to gather.  List of 128, 128 neighbours a
+// round, 1 000 and 1 500 queries: 384 bytes 105/107/105 and 111/115/174, 400 bytes 167/155/147 and 174/167/222, 768 bytes
+// 168/142/130 and 178/160/155, 1 536 bytes 210/196/195 and 261/267/309 (6 000: 914/910/903).  List of 64, 32 neighbours: 256
+// bytes 115/126/126, 384 bytes 119/132/131, 400 bytes 180/178/175, 1 536 bytes 196/189/186 (6 000: 762/765/819).
+// Rounds of few neighbours leave a team little to share: 16 neighbours, uniform entries, 1 000 queries: 256 bytes 548/597/600, 512
+// bytes 581/626/614, 768 bytes 715/648/618.
+// Large batches of long rows are bound by bytes in flight again: 50 000 queries over 1 536 bytes 33 819 / - / 33 323.
+int default_team(const ann_index_t* h, int64_t nq, int width) {
+    const int bytes = h->row_bytes;
+    const int64_t round = (int64_t)width * h->d.degree;
+    if (bytes < 256 || (bytes <= 512 && round < 32)) return 1;
+    if (h->d.entry_mode != ANN_ENTRY_UNIFORM) {
+        if (nq <= 1024) return h->variant->g == 32 || round >= 128 ? 4 : 1;
+        return bytes >= 1024 && nq >= 6000 ? 4 : 1;
+    }
+    if (nq <= 1024 || bytes >= 1024) return 4;
+    if (nq <= 1536 && (bytes <= 256 || bytes > 512)) return 4;
+    return nq <= 2560 ? 2 : 1;  // teams of two are all resident up to there
 }
 
 // Keys per query of the key table (key_table.h) this call searches with, 0 for a search that gathers every row.
@@ -561,7 +580,7 @@ int search_impl(ann_index_t* h, const void* queries, int64_t nq, const int32_t* 
         if (!block) per_launch = kMaxQueriesPerLaunch;  // no memory: gather every row
     }
     uint32_t* const table = block ? static_cast<uint32_t*>(block->memory) : nullptr;
-    const int team = h->team ? h->team : default_team(h, nq);
+    const int team = h->team ? h->team : default_team(h, nq, width);
     hipError_t e = hipSuccess;
     for (int64_t q0 = 0; q0 < nq && e == hipSuccess; q0 += per_launch) {
         const int64_t cnt = nq - q0 < per_launch ? nq - q0 : per_launch;

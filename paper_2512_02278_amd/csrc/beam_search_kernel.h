@@ -275,6 +275,11 @@ struct BeamSearch {
         return kept;
     }
 
+    // A team deals the rows out evenly, whole gather steps to a wavefront: with blocks of U steps (16 rows of 400 bytes) one to
+    // three of four wavefronts had work in a round of forty rows (50 queries, uniform entries: 378 us, now 307).  The keys that can enter the list go to ckey
+    // through a counter the team shares; their order in ckey is whatever the atomics give, which the merge does not
+    // depend on (it orders them).
+    //
     // FULL: the row fills every piece of every lane, so the row buffers need no clearing (RowOps::blank_row); else
     // they are zeroed once and a piece this lane does not load keeps its zeros (RowOps::reload_row).
     template <bool FULL>
@@ -291,13 +296,19 @@ struct BeamSearch {
 #pragma unroll
                 for (int c = 0; c < NCH; ++c) x[u][c] = u32x4{0, 0, 0, 0};
         }
-        for (int j0 = 0; j0 < m; j0 += RPS * U) {
+        int first = 0, end = m;
+        if constexpr (TEAM > 1) {
+            const int share = RPS * ((m + RPS * TEAM - 1) / (RPS * TEAM));
+            first = wave * share;
+            end = min(m, first + share);
+        }
+        for (int j0 = first; j0 < end; j0 += RPS * U) {
             uint32_t id[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                if (j0 + u * RPS >= m) break;  // whole step beyond the last row
+                if (j0 + u * RPS >= end) break;  // whole step beyond the last row
                 const int j = j0 + u * RPS + grp;
-                const bool live = j < m;
+                const bool live = j < end;
                 id[u] = live ? cid[j] : 0u;
                 if constexpr (FULL) {
                     row.blank_row(x[u]);
@@ -313,11 +324,11 @@ struct BeamSearch {
             if constexpr (Row::kDtype == kU8) {
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
-                    if (j0 + u * RPS >= m) break;
+                    if (j0 + u * RPS >= end) break;
                     const int j = j0 + u * RPS + grp;
                     const uint32_t okey = row.key(x[u], lane);
                     const uint64_t packed = ((uint64_t)okey << 32) | (uint64_t)(id[u] << 1);  // ids are below 2^31
-                    mine = (row.lg == u && j < m) ? packed : mine;
+                    mine = (row.lg == u && j < end) ? packed : mine;
                 }
             } else {
                 // the U sums meet in one register: a float key ends in log2(G) additions and four instructions that
@@ -328,88 +339,29 @@ struct BeamSearch {
                 for (int u = 0; u < UP; ++u) part[u] = 0.0f;
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
-                    if (j0 + u * RPS >= m) break;
+                    if (j0 + u * RPS >= end) break;
                     part[u] = row.partial(x[u]);
                     asm volatile("" : "+v"(part[u]));  // here, not at its use: there it would keep every product's operands
                     my_id = row.lg == u ? id[u] : my_id;
                 }
                 const uint32_t okey = Row::ordered(group_sums<G>(part, lane));
                 const int j = j0 + row.lg * RPS + grp;
-                if (row.lg < U && j < m) mine = ((uint64_t)okey << 32) | (uint64_t)(my_id << 1);
+                if (row.lg < U && j < end) mine = ((uint64_t)okey << 32) | (uint64_t)(my_id << 1);
             }
             const bool keep = mine < worst;
             const uint64_t b = __ballot(keep);
-            if (keep) ckey[rank_below(b, kept)] = mine;
-            kept += __builtin_popcountll(b);
-        }
-        n_dist += m;
-        return kept;
-    }
-
-    // The same for a team: wavefront w takes the blocks of RPS * U rows number w, w + TEAM, ...  The keys
-    // that can enter the list are appended to ckey through a counter the team shares; their order in ckey
-    // is whatever the atomics give, which the merge does not depend on (it orders them).
-    __device__ __forceinline__ void score_team(int m) {
-        if (row.full) score_team_rows<true>(m);
-        else score_team_rows<false>(m);
-    }
-
-    template <bool FULL>
-    __device__ __forceinline__ void score_team_rows(int m) {
-        const int grp = lane / G;
-        const uint64_t worst = this->worst;
-        const uint8_t* const piece0 = row.lane_piece(p.vectors);
-        const uint32_t stride = (uint32_t)p.row_stride;
-        u32x4 x[U][NCH];
-        if constexpr (!FULL) {
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-#pragma unroll
-                for (int c = 0; c < NCH; ++c) x[u][c] = u32x4{0, 0, 0, 0};
-        }
-        for (int j0 = wave * (RPS * U); j0 < m; j0 += RPS * U * TEAM) {
-            uint32_t id[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                if (j0 + u * RPS >= m) break;
-                const int j = j0 + u * RPS + grp;
-                const bool live = j < m;
-                id[u] = live ? cid[j] : 0u;
-                if constexpr (FULL) {
-                    row.blank_row(x[u]);
-                    row.load_full_row(x[u], piece0 + (uint64_t)id[u] * stride, live);
-                } else {
-                    row.reload_row(x[u], piece0 + (uint64_t)id[u] * stride, live);
-                }
-            }
-            uint64_t packed[U], b[U];
-            bool keep[U];
-            int cnt = 0;
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                b[u] = 0;
-                keep[u] = false;
-                packed[u] = 0;
-                if (j0 + u * RPS < m) {
-                    const int j = j0 + u * RPS + grp;
-                    const uint32_t okey = row.key(x[u], lane);
-                    packed[u] = ((uint64_t)okey << 32) | (uint64_t)(id[u] << 1);
-                    keep[u] = j < m && row.lg == 0 && packed[u] < worst;
-                    b[u] = __ballot(keep[u]);
-                    cnt += __builtin_popcountll(b[u]);
-                }
-            }
-            if (cnt > 0) {  // uniform
+            if constexpr (TEAM == 1) {
+                if (keep) ckey[rank_below(b, kept)] = mine;
+                kept += __builtin_popcountll(b);
+            } else if (b) {  // uniform
                 int base = 0;
-                if (lane == 0) base = (int)atomicAdd(&team[kTeamKept], (uint32_t)cnt);
+                if (lane == 0) base = (int)atomicAdd(&team[kTeamKept], (uint32_t)__builtin_popcountll(b));
                 base = __builtin_amdgcn_readfirstlane(base);
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    if (keep[u]) ckey[rank_below(b[u], base)] = packed[u];
-                    base += __builtin_popcountll(b[u]);
-                }
+                if (keep) ckey[rank_below(b, base)] = mine;
             }
         }
+        if constexpr (TEAM == 1) n_dist += m;
+        return kept;
     }
 
     // list <- itopk smallest of list U ckey[base .. base + 64*R), R registers per lane;
@@ -706,7 +658,7 @@ struct BeamSearch {
             const int m = (int)team[kTeamM];
             if (team[kTeamDone] != 0u) break;
             worst = ((uint64_t)team[kTeamWorst + 1] << 32) | team[kTeamWorst];
-            score_team(m);
+            score(m);
             __syncthreads();
             if (leader) {
                 n_dist += m;

@@ -1064,3 +1064,26 @@ def test_fp32_routing_of_extreme_values(torch_cuda, metric, nq, n_clusters, rout
     key = ((y * y).sum(1) if metric == 0 else 0) - (2.0 if metric == 0 else 1.0) * (x @ y.T)
     size = np.take_along_axis((y * y).sum(1) + (x * x).sum(1)[:, None], got, 1)
     assert (np.take_along_axis(key, got, 1) - np.sort(key, axis=1)[:, :route_c] <= dim * 2.0 ** -23 * size).all()
+
+
+@pytest.mark.parametrize("dt,dim", [("f32", 96), ("f16", 128), ("f16", 200), ("f32", 128), ("f16", 384), ("f16", 520), ("f32", 1536),
+                                    ("u8", 256), ("u8", 272)])
+@pytest.mark.parametrize("itopk,width,degree", [(64, 1, 3), (100, 3, 27), (128, 8, 64)])
+def test_teams_deal_out_any_number_of_rows(torch_cuda, dt, dim, itopk, width, degree):
+    """Rounds of one row to 512 rows: fewer than a team has wavefronts, no multiple of a gather step, several iterations."""
+    from paper_2512_02278_amd import ann
+
+    torch, n, nq = torch_cuda, 4_000, 70
+    rng = np.random.default_rng(dim + degree)
+    x = (rng.integers(0, 256, (n, dim)) if dt == "u8" else rng.standard_normal((n, dim))).astype(NP_DT[dt])
+    to = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    h = ann.ann_index_load(to(x), to(rng.integers(0, n, (n, degree)).astype(np.int32)), n_entry=33, seed=2)
+    q, got = to(x[rng.integers(0, n, nq)]), []
+    for team in (1, 2, 4, 0):
+        ann.ann_index_set_option(h, ann.ANN_OPT_WAVEFRONTS_PER_QUERY, team)
+        counters = torch.zeros((nq, 4), dtype=torch.int32, device="cuda")
+        ids, keys = ann.ann_search(h, q, 10, itopk, width, 60, counters=counters)
+        torch.cuda.synchronize()
+        got.append((ids, keys.view(torch.int32), counters))
+    ann.ann_free(h)
+    assert all(torch.equal(a, b) for other in got[1:] for a, b in zip(got[0], other))
