@@ -108,7 +108,8 @@ enum {
     ANN_OPT_LANES_PER_ROW = 4,             /* lanes that share one vector row in the gather, among the built
                                               variants (4, 8 or 32); 0 = the default choice */
     ANN_OPT_WAVEFRONTS_PER_QUERY = 5       /* 1, 2 or 4 wavefronts work on one query (the leader keeps the list, all
-                                              share a round's gathers); 0 = chosen per call (default) */
+                                              share a round's gathers; rows are always gathered, see ann_search);
+                                              0 = chosen per call (default) */
 };
 int ann_index_set_option(ann_index_t* handle, int option, int64_t value);
 
@@ -131,10 +132,12 @@ int ann_index_set_option(ann_index_t* handle, int option, int64_t value);
  * finished (no wrong result follows from it; ann_search_static does not allocate).  On an
  * argument error nothing is launched and the outputs are untouched.  Batches over float rows with
  * at least 8 to 16 queries per cluster (route_c == 1) are also grouped by cluster and may score whole
- * clusters ahead of the search: the table of those keys lives in device memory of the handle,
- * allocated by the first call that needs it (at most four blocks of 1 GiB, one per call in flight;
- * given back by ann_free; no such block under stream capture or where none can be had: the search then
- * gathers the rows, with the same results).  Calls on
+ * clusters ahead of the search: the table of those keys lives in device memory of the handle, stream-ordered
+ * allocations made by the first call that needs them (at most four blocks of at most 1 GiB, one for each such call in
+ * flight; a later call that needs more replaces one; ann_free gives them back).  No table under stream capture, where no
+ * block can be had without waiting for another stream, or where one of ANN_OPT_CLUSTER_ORDER_MIN_QUERIES < 0,
+ * ANN_OPT_VISITED_WINDOW_BITS = 0 and ANN_OPT_WAVEFRONTS_PER_QUERY != 0 asks for a search that has none: the search then
+ * gathers the rows, with the same results, and keeps no memory.  Calls on
  * different streams may share a handle.  A route id outside [0, n_clusters) (only possible
  * through ann_search_routed) names no cluster: it gives no entries, and a query whose routes
  * all do so returns padding.
@@ -166,8 +169,8 @@ int ann_search_static(ann_index_t* handle, const void* queries, int64_t nq, int 
 
 /*
  * Same as ann_search, and additionally writes four int32 per query to
- * out_counters (DEVICE, nq*4, may be NULL): expansion rounds, keys computed
- * (vector rows gathered), graph rows read, visited-table resets.
+ * out_counters (DEVICE, nq*4, may be NULL): expansion rounds, rows scored (their vectors gathered, or
+ * their keys read from a table of keys, see ann_search), graph rows read, visited-table resets.
  */
 int ann_search_counters(ann_index_t* handle, const void* queries, int64_t nq, int k, int itopk, int width,
                         int max_iters, int32_t* out_ids, void* out_dists, int32_t* out_counters, void* stream);

@@ -59,7 +59,6 @@ constexpr int64_t kMaxQueriesPerLaunch = 1 << 22;
 constexpr int kDefaultWindowBits = 8192, kMaxWindowBits = 1 << 17;
 // From this batch size on, a routed batch is executed grouped by cluster (schedule.hip).
 constexpr int64_t kMinQueriesForClusterOrder = 16384;
-// Bytes of key table one launch works on.
 constexpr int64_t kTableBytes = 1ll << 30;
 
 }  // namespace ann
@@ -76,8 +75,10 @@ struct RelaxedCapture {
 
 // Device memory for the key tables of a handle's calls, kept from call to call: allocated and released per call, even
 // from a pool that stays mapped, 300 MB held the calling thread for 0.5 ms.  At most kMost blocks of at most kTableBytes,
-// given back with the handle.  Any number of threads and streams: a block belongs to one call from take() to
-// give_back(), and a call waits on its own stream for the work of the block's previous user.
+// one for each call in flight; given back with the handle.  Any number of threads and streams: a block belongs to one call
+// from take() to give_back(), and then to the stream of that call until its work has ended.  A block that is too small is
+// replaced, in the order of the call's stream: nothing waits for the device.  A call that finds no block for itself searches
+// without a table: it never waits for another stream's work, and no thread waits for another one's allocation.
 struct TableBlocks {
     static constexpr int kMost = 4;
     struct Block {
@@ -90,58 +91,76 @@ struct TableBlocks {
     std::mutex mutex;
     Block blocks[kMost];
 
-    // A block of at least `bytes`, or null if there is no memory.
+    // A block of at least `bytes` for a call on `stream`, or null.
     Block* take(size_t bytes, hipStream_t stream) {
-        std::lock_guard<std::mutex> lock(mutex);
         RelaxedCapture relaxed;
-        Block *idle = nullptr, *same_stream = nullptr, *busy = nullptr, *replace = nullptr;
-        for (Block& b : blocks) {
-            if (b.taken) continue;
-            const bool done = !b.memory || hipEventQuery(b.done) == hipSuccess;
-            if (b.memory && b.bytes >= bytes) (done ? idle : b.stream == stream ? same_stream : busy) = &b;
-            else if (done && (!replace || b.bytes < replace->bytes)) replace = &b;  // an empty place before a block that is too small
+        Block *fits = nullptr, *small = nullptr, *empty = nullptr;
+        Block* b;
+        {
+            std::lock_guard<std::mutex> lock(mutex);
+            for (Block& c : blocks) {
+                if (c.taken) continue;
+                if (!c.memory) empty = &c;
+                else if (c.stream == stream || idle(c)) (c.bytes >= bytes ? fits : small) = &c;
+            }
+            b = fits ? fits : small ? small : empty;
+            if (!b) return nullptr;
+            b->taken = true;
         }
-        (void)hipGetLastError();  // "not ready" is no error
-        Block* b = idle ? idle : same_stream;
-        if (!b && replace && grow(replace, bytes)) b = replace;
-        if (!b) b = busy;
-        if (!b || hipStreamWaitEvent(stream, b->done, 0) != hipSuccess) {
-            (void)hipGetLastError();
-            return nullptr;
+        // what the stream does from here on comes after the last user's work (which is of this stream, unless this is a new
+        // stream at a destroyed one's address, or has ended)
+        bool ready = !b->memory || hipStreamWaitEvent(stream, b->done, 0) == hipSuccess;
+        if (ready && b->bytes < bytes) {
+            drop(b, stream);
+            ready = allocate(b, bytes, stream);
+            if (!ready) {
+                std::lock_guard<std::mutex> lock(mutex);
+                for (Block& c : blocks)
+                    if (!c.taken && c.memory && idle(c)) drop(&c, stream);
+                ready = allocate(b, bytes, stream);
+            }
         }
-        b->taken = true;
-        return b;
+        if (ready) return b;
+        (void)hipGetLastError();
+        std::lock_guard<std::mutex> lock(mutex);
+        b->taken = false;
+        return nullptr;
     }
 
     // The call's work on the block has been enqueued on `stream`.
     void give_back(Block* b, hipStream_t stream) {
         std::lock_guard<std::mutex> lock(mutex);
-        // without the event nobody could tell when the work has ended: wait for it here
-        if (hipEventRecord(b->done, stream) != hipSuccess) (void)hipStreamSynchronize(stream);
         b->stream = stream;
-        b->taken = false;
+        // without the event nobody could tell when the work has ended: the block is not handed out again
+        b->taken = hipEventRecord(b->done, stream) != hipSuccess;
     }
 
     void release() {
         for (Block& b : blocks) {
-            if (b.memory) (void)hipFree(b.memory);  // waits for searches still running
+            if (b.memory) (void)(b.taken ? hipDeviceSynchronize() : hipEventSynchronize(b.done));  // searches still running
+            if (b.memory) (void)hipFree(b.memory);
             if (b.done) (void)hipEventDestroy(b.done);
             b = Block();
         }
     }
 
    private:
-    static bool grow(Block* b, size_t bytes) {
-        const size_t step = size_t(32) << 20, rounded = (bytes + step - 1) / step * step;
-        if (b->memory) (void)hipFree(b->memory);
+    static bool idle(const Block& b) {
+        const bool ended = hipEventQuery(b.done) == hipSuccess;
+        if (!ended) (void)hipGetLastError();  // "not ready" is no error
+        return ended;
+    }
+    static void drop(Block* b, hipStream_t stream) {
+        if (b->memory) (void)hipFreeAsync(b->memory, stream);
         b->memory = nullptr;
         b->bytes = 0;
-        if (!b->done && hipEventCreateWithFlags(&b->done, hipEventDisableTiming) != hipSuccess) {
-            b->done = nullptr;
-            return false;
-        }
-        if (hipMalloc(&b->memory, rounded) != hipSuccess) {
+    }
+    static bool allocate(Block* b, size_t bytes, hipStream_t stream) {
+        const size_t step = size_t(32) << 20, rounded = (bytes + step - 1) / step * step;
+        if (!b->done && hipEventCreateWithFlags(&b->done, hipEventDisableTiming) != hipSuccess) b->done = nullptr;
+        if (!b->done || hipMallocAsync(&b->memory, rounded, stream) != hipSuccess) {
             b->memory = nullptr;
+            (void)hipGetLastError();
             return false;
         }
         b->bytes = rounded;
@@ -572,9 +591,11 @@ int search_impl(ann_index_t* h, const void* queries, int64_t nq, const int32_t* 
     int64_t per_launch = kMaxQueriesPerLaunch;
     TableBlocks::Block* block = nullptr;
     if (stride > 0 && order) {
-        const int64_t most = kTableBytes / (4 * (int64_t)stride);
-        int64_t launches = (nq + most - 1) / most;
-        per_launch = ((nq + launches - 1) / launches + 511) / 512 * 512;
+        int64_t most = kTableBytes / (4 * (int64_t)stride);
+        if (most > 512) most = most / 512 * 512;
+        const int64_t launches = (nq + most - 1) / most, even = (nq + launches - 1) / launches;
+        per_launch = (even + 511) / 512 * 512;
+        if (per_launch > most) per_launch = most;
         if (per_launch > nq) per_launch = nq;
         block = h->tables.take(4 * (size_t)stride * (size_t)per_launch, stream);
         if (!block) per_launch = kMaxQueriesPerLaunch;  // no memory: gather every row

@@ -1087,3 +1087,140 @@ def test_teams_deal_out_any_number_of_rows(torch_cuda, dt, dim, itopk, width, de
         got.append((ids, keys.view(torch.int32), counters))
     ann.ann_free(h)
     assert all(torch.equal(a, b) for other in got[1:] for a, b in zip(got[0], other))
+
+
+@pytest.fixture(scope="module")
+def float_clusters(torch_cuda):
+    """An index over fp32 rows whose batches of 16 queries per cluster and more search with a key table, and queries."""
+    torch, dim, nc, mean, degree = torch_cuda, 128, 8, 500, 32
+    rng = np.random.default_rng(77)
+    n, off = nc * mean, np.arange(nc + 1, dtype=np.int64) * mean
+    cen = rng.standard_normal((nc, dim))
+    lab = np.repeat(np.arange(nc), mean)
+    x = (cen[lab] + 0.7 * rng.standard_normal((n, dim))).astype(np.float32)
+    g = rng.integers(off[lab][:, None], off[lab + 1][:, None], (n, degree)).astype(np.int32)
+    q = (x[rng.integers(0, n, 24_000)] + 0.1 * rng.standard_normal((24_000, dim))).astype(np.float32)
+    to = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    return to(x), to(g), to(cen.astype(np.float32)), to(off), to(q)
+
+
+FLOAT_SEARCH = (10, 128, 4, 60)
+
+
+def float_clusters_handle(float_clusters):
+    from paper_2512_02278_amd import ann
+
+    x, g, cen, off, _ = float_clusters
+    return ann.ann_index_load(x, g, n_entry=32, entry_mode=1, seed=9, centroids=cen, cluster_offsets=off, route_c=1)
+
+
+def gathered_results(torch, float_clusters, sizes):
+    """The first k of the first m queries for every m, searched one after the other without a table (a fixed team)."""
+    from paper_2512_02278_amd import ann
+
+    h = float_clusters_handle(float_clusters)
+    ann.ann_index_set_option(h, ann.ANN_OPT_WAVEFRONTS_PER_QUERY, 1)
+    want = {m: ann.ann_search(h, float_clusters[4][:m], *FLOAT_SEARCH) for m in sizes}
+    torch.cuda.synchronize()
+    ann.ann_free(h)
+    return want
+
+
+def test_key_table_memory_is_taken_kept_within_bounds_and_given_back(torch_cuda, float_clusters):
+    """A batch with many queries per cluster takes device memory for its table (so a table is what it searched with), a
+    longer one replaces it, shorter ones share it, and ann_free gives it back."""
+    from paper_2512_02278_amd import ann
+
+    torch, q = torch_cuda, float_clusters[4]
+    sizes = (100, 2_000, 8_000, 24_000, 3_000)
+    want = gathered_results(torch, float_clusters, sizes)
+
+    def used():
+        torch.cuda.synchronize()
+        return start - torch.cuda.mem_get_info()[0]
+
+    h = float_clusters_handle(float_clusters)
+    out = {m: (torch.empty((m, 10), dtype=torch.int32, device="cuda"), torch.empty((m, 10), device="cuda")) for m in sizes}
+    stride = 4 * 832                                    # bytes per query: clusters of 500 rows, half as many again, whole 64s
+    ann.ann_index_set_option(h, ann.ANN_OPT_WAVEFRONTS_PER_QUERY, 1)
+    ann.ann_search(h, q, *FLOAT_SEARCH, *out[24_000])  # loads the kernels, without a table
+    ann.ann_index_set_option(h, ann.ANN_OPT_WAVEFRONTS_PER_QUERY, 0)
+    torch.cuda.synchronize()
+    start = torch.cuda.mem_get_info()[0]
+    for m in sizes:
+        ann.ann_search(h, q[:m], *FLOAT_SEARCH, *out[m])
+        longest = max(s for s in sizes[:sizes.index(m) + 1])
+        assert (used() >= longest * stride) == (m >= 2_000), (m, used())
+        assert used() < longest * stride + (34 << 20) + (34 << 20), (m, used())   # one block, and one step of what others share
+        assert torch.equal(out[m][0], want[m][0]) and torch.equal(out[m][1].view(torch.int32), want[m][1].view(torch.int32))
+    ann.ann_free(h)
+    assert used() < 34 << 20
+
+
+def test_key_tables_of_calls_in_flight_on_several_streams_and_host_threads(torch_cuda, float_clusters):
+    """Six threads, each on a stream of its own, share a handle that has four blocks at most: batches with and without a
+    table, growing and shrinking, none waited for before the next; all have the bits of searches one after the other."""
+    import threading
+
+    from paper_2512_02278_amd import ann
+
+    torch, q = torch_cuda, float_clusters[4]
+    sizes = (2_000, 64, 9_000, 300, 24_000, 5_000)
+    want = gathered_results(torch, float_clusters, sizes)
+    h = float_clusters_handle(float_clusters)
+    streams = [torch.cuda.Stream() for _ in range(6)]
+    outs, errors = {}, []
+    for t in range(6):
+        for i in range(2 * len(sizes)):
+            m = sizes[(i + t) % len(sizes)]
+            outs[t, i] = (m, torch.full((m, 10), -7, dtype=torch.int32, device="cuda"), torch.full((m, 10), -7.0, device="cuda"))
+    torch.cuda.synchronize()
+
+    def work(t):
+        try:
+            for i in range(2 * len(sizes)):
+                m, ids, keys = outs[t, i]
+                ann.ann_search(h, q[:m], *FLOAT_SEARCH, ids, keys, stream=streams[t])
+        except Exception as e:  # noqa: BLE001 - reported below
+            errors.append(e)
+
+    threads = [threading.Thread(target=work, args=(t,)) for t in range(6)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    torch.cuda.synchronize()
+    ann.ann_free(h)
+    assert not errors, errors
+    for m, ids, keys in outs.values():
+        assert torch.equal(ids, want[m][0]) and torch.equal(keys.view(torch.int32), want[m][1].view(torch.int32)), m
+
+
+def test_a_captured_search_gathers_and_keeps_its_results_over_replays(torch_cuda, float_clusters):
+    """Under stream capture there is no table; the replays give what the eager call (with a table) gives, also between
+    eager calls that use the handle's block."""
+    from paper_2512_02278_amd import ann
+
+    torch, m = torch_cuda, 3_000
+    q = float_clusters[4][:m].contiguous()
+    h = float_clusters_handle(float_clusters)
+    routes = ann.ann_route(h, q)
+    ids = torch.empty((m, 10), dtype=torch.int32, device="cuda")
+    keys = torch.empty((m, 10), device="cuda")
+    ann.ann_search(h, q, *FLOAT_SEARCH, ids, keys, routes=routes)
+    torch.cuda.synchronize()
+    want = ids.clone(), keys.clone()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        ann.ann_search(h, q, *FLOAT_SEARCH, ids, keys, routes=routes)
+    for _ in range(4):
+        ids.fill_(-7)
+        keys.fill_(-7.0)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(ids, want[0]) and torch.equal(keys.view(torch.int32), want[1].view(torch.int32))
+        eager = ann.ann_search(h, q, *FLOAT_SEARCH)
+        torch.cuda.synchronize()
+        assert torch.equal(eager[0], want[0])
+    del graph
+    ann.ann_free(h)
