@@ -2,6 +2,7 @@
 // Declarations and the meaning of every argument: include/ann.h.
 #include <hip/hip_runtime.h>
 
+#include <cmath>
 #include <cstdarg>
 #include <cstdio>
 #include <cstdlib>
@@ -522,13 +523,42 @@ int default_team(const ann_index_t* h, int64_t nq, int width) {
     return nq <= 2560 ? 2 : 1;  // teams of two are all resident up to there
 }
 
+// Share of a cluster's rows that a search is expected to score: a parent brings 4 + degree / 4 new rows, at most 12, and
+// fewer the more of the cluster has been seen.  Measured against it at lists of 64 to 256 entries, degrees 16 to 64, clusters of
+// 300 to 2 441: 0.23 / 0.27 (list 64, degree 16, 2 441 rows), 0.47 / 0.51, 0.68 / 0.72, 0.71 / 0.60, 0.94 / 0.97.
+double scored_share(const ann_index_t* h, int64_t parents, int64_t mean) {
+    const double fresh = h->d.degree < 32 ? 4.0 + h->d.degree / 4.0 : 12.0;
+    return 1.0 - std::exp(-std::pow((double)parents * fresh / (double)mean, 0.75));
+}
+
+// Share from which a table of keys pays.  Time without / with (300 000 rows; share scored in brackets):
+//   * A batch long enough to run grouped by cluster gathers from the caches as it is.  Below 1 KB the table then pays for nearly
+//     whole clusters only: 256 bytes L2 0.71 [0.47], 0.86 [0.68], 1.03 [0.92], products 0.89 [0.47], 1.04 [0.76]; 384 bytes
+//     0.85 [0.47], 0.97 [0.68], 1.05 [0.76], 1.07 [0.94]; 512 bytes products 0.92 [0.47], 1.07 [0.50], 1.17 [0.76]; 768 bytes L2 0.57
+//     [0.46], 0.84 [0.75], 1.16 [0.92], with clusters of 300 0.92 [0.93], 1.08 [0.99].  From 1 KB on earlier: fp16 L2 0.94 [0.46], 1.00 [0.48],
+//     1.07 [0.57]; products and fp32 1.16 .. 1.18 [0.30].
+//   * A short batch pays for the table kernel's own length: 2 000 to 4 000 queries over 256 bytes 0.82 [0.23], 1.10 [0.40] (L2 0.97 at
+//     [0.83]), 384 to 768 bytes 0.75 [0.23], 0.92 [0.35], 1.02 [0.39]; 1 000 to 1 500 queries over 1 536 bytes 0.73 [0.23], 1.20 [0.48].
+double table_share(const ann_index_t* h, int64_t nq, int64_t mean) {
+    const int bytes = h->row_bytes;
+    const bool f16_l2 = h->d.dtype == ANN_F16 && h->d.metric == ANN_L2;  // the most instructions per byte
+    if (nq >= h->cluster_order_min) {
+        if (bytes >= 1024) return f16_l2 ? 0.48 : 0.25;
+        if (f16_l2) return mean < 512 ? 0.98 : 0.86;
+        return bytes < 512 ? 0.8 : 0.52;
+    }
+    if (bytes >= 1024) return nq < 1536 ? 0.4 : 0.0;
+    if (nq >= 4096) return 0.0;
+    return bytes > 256 ? 0.36 : f16_l2 ? 0.9 : 0.4;
+}
+
 // Keys per query of the key table (key_table.h) this call searches with, 0 for a search that gathers every row.
 //
-// The table costs a product of every query with every row of its cluster; it saves the rows the search would gather,
-// about eight per list entry and at most the cluster.  Measured over rows of 256 to 1536 bytes, clusters of 300 to
-// 2 441 rows and lists of 64 to 256 entries, time without / with:
-//   * with 16 queries per cluster (8 for rows of 1 KB) and gathered bytes >= 0.8 x vector instructions of the products,
-//     0.85 .. 1.4 at 256 bytes, 1.2 .. 1.6 at 384 bytes, 1.2 .. 3.4 above;
+// The table costs a product of every query with every row of its cluster; it saves the rows the search would gather.
+// Measured over rows of 256 to 1536 bytes, clusters of 300 to 2 441 rows and lists of 64 to 256 entries, time without / with,
+// batches that are not grouped otherwise:
+//   * with 16 queries per cluster (8 for rows of 1 KB), about eight rows per parent x row bytes >= 0.8 x vector instructions of the
+//     products, and the shares above: 0.97 .. 1.4 at 256 bytes, 1.0 .. 2.0 at 384 bytes, 1.0 .. 4.2 above;
 //   * with 4 queries per cluster 0.8 .. 1.1, and where few rows of large clusters are gathered (768-byte L2 rows, list of
 //     64, clusters of 2 441) 0.6 .. 0.8 at any batch size.
 // Rows below 256 bytes and clusters below 256 rows were not measured.
@@ -541,7 +571,7 @@ int table_stride(const ann_index_t* h, int64_t nq, int itopk, int width, int max
     const int64_t parents = (int64_t)width * max_iters < itopk ? (int64_t)width * max_iters : itopk;
     const int64_t gathered = 8 * parents < mean ? 8 * parents : mean;
     const int64_t twice_products = (int64_t)h->d.dim * (h->d.dtype == ANN_F16 && h->d.metric == ANN_IP ? 1 : 4);
-    if (10 * gathered * h->row_bytes < 4 * twice_products * mean) return 0;
+    if (10 * gathered * h->row_bytes < 4 * twice_products * mean || scored_share(h, parents, mean) < table_share(h, nq, mean)) return 0;
     // half as long again as the mean cluster: rows beyond are gathered
     int64_t stride = (mean + mean / 2 + 127) / 64 * 64;
     if (stride > h->window_bits) stride = h->window_bits;
