@@ -506,7 +506,8 @@ namespace {
 // In a routed search most neighbours have been seen, and a round has fewer rows to gather.  List of 128, 128 neighbours a
 // round, 1 000 and 1 500 queries: 384 bytes 105/107/105 and 111/115/174, 400 bytes 167/155/147 and 174/167/222, 768 bytes
 // 168/142/130 and 178/160/155, 1 536 bytes 210/196/195 and 261/267/309 (6 000: 914/910/903).  List of 64, 32 neighbours: 256
-// bytes 115/126/126, 384 bytes 119/132/131, 400 bytes 180/178/175, 1 536 bytes 196/189/186 (6 000: 762/765/819).
+// bytes 115/126/126, 384 bytes 119/132/131, 400 bytes 180/178/175, 1 536 bytes 196/189/186 (6 000: 762/765/819).  256 neighbours, 4 400
+// queries: 1 024 bytes 521/517/539, 1 536 bytes 781/764/751.
 // Rounds of few neighbours leave a team little to share: 16 neighbours, uniform entries, 1 000 queries: 256 bytes 548/597/600, 512
 // bytes 581/626/614, 768 bytes 715/648/618.
 // Large batches of long rows are bound by bytes in flight again: 50 000 queries over 1 536 bytes 33 819 / - / 33 323.
@@ -516,7 +517,7 @@ int default_team(const ann_index_t* h, int64_t nq, int width) {
     if (bytes < 256 || (bytes <= 512 && round < 32)) return 1;
     if (h->d.entry_mode != ANN_ENTRY_UNIFORM) {
         if (nq <= 1024) return h->variant->g == 32 || round >= 128 ? 4 : 1;
-        return bytes >= 1024 && nq >= 6000 ? 4 : 1;
+        return (bytes >= 1024 && nq >= 6000) || (bytes >= 1536 && nq >= 4096 && round >= 128) ? 4 : 1;
     }
     if (nq <= 1024 || bytes >= 1024) return 4;
     if (nq <= 1536 && (bytes <= 256 || bytes > 512)) return 4;
