@@ -155,10 +155,11 @@ int ann_search(ann_index_t* handle, const void* queries, int64_t nq, int k, int 
  * call outside any capture first.
  * Limit: the temporaries of one call, each rounded up to 256 bytes -
  *     4*nq*route_c                       routes
- *   + 8*nq*slices*route_c                routing partials (slices <= 64; nq*slices <= 131072, or at most 8 MiB in all)
  *   + 4*(nq + n_clusters)                execution order, for batches that run grouped by cluster
- * - must fit: e.g. 1M queries at route_c = 1 take 8.1 MB.  A larger batch gives ANN_EUNSUPPORTED
- * and launches nothing; an index with uniform entries needs no temporaries at all.
+ * - must fit: e.g. 1M queries at route_c = 1 take 8 MB.  A larger batch gives ANN_EUNSUPPORTED
+ * and launches nothing; an index with uniform entries needs no temporaries at all.  (What is left holds
+ * the routing's partial results, 8*nq*slices*route_c: at most 64 slices and nq*slices <= 131072 or 8 MiB in all,
+ * fewer slices where there is no room for them.)
  * All calls on one GPU share the array: calls that overlap in time on one GPU (different streams or
  * threads) race and give wrong results; calls on one stream are safe.  The array keeps the last
  * call's contents; everything that must start at zero is cleared by the call itself.

@@ -385,6 +385,7 @@ struct Workspace {
     size_t bytes = 0, used = 0;
     size_t reserve = 0;  // > 0: the block is this call's own allocation (made on first use)
     bool owned = false;
+    size_t routing_room = SIZE_MAX;  // bytes of it that the routing's own temporaries may take
 
     Workspace(hipStream_t s, size_t reserve_bytes) : stream(s), reserve(reserve_bytes) {}
     Workspace(hipStream_t s, void* buffer, size_t buffer_bytes) : stream(s), base(static_cast<char*>(buffer)), bytes(buffer_bytes) {}
@@ -416,11 +417,19 @@ struct Workspace {
 
 size_t padded256(size_t n) { return (n + 255) / 256 * 256; }
 
+// Slices of the centroid range the matrix-core routing of nq queries is cut into, with partial results of at most `room` bytes.
+int routing_slices(const ann_index_t* h, int64_t nq, size_t room) {
+    const int slices = h->centroid_bias ? route_mfma_u8_slices(h->d.n_clusters, nq)
+                                        : route_mfma_slices(h->d.dtype, h->d.n_clusters, h->row_bytes, h->d.route_c, nq);
+    if (slices <= 1) return 1;
+    const size_t most = room / (sizeof(uint64_t) * (size_t)nq * h->d.route_c);
+    return most >= (size_t)slices ? slices : most > 1 ? (int)most : 1;
+}
+
 // Bytes of temporaries the routing of nq queries takes.
 size_t route_scratch_bytes(const ann_index_t* h, int64_t nq) {
     if (nq <= 0 || !(h->matrix_core_routing && (h->centroid_bias || h->route_bias))) return 0;
-    const int slices = h->centroid_bias ? route_mfma_u8_slices(h->d.n_clusters, nq)
-                                        : route_mfma_slices(h->d.dtype, h->d.n_clusters, h->row_bytes, h->d.route_c, nq);
+    const int slices = routing_slices(h, nq, SIZE_MAX);
     return slices > 1 ? padded256(sizeof(uint64_t) * (size_t)nq * slices * h->d.route_c) : 0;
 }
 
@@ -443,8 +452,7 @@ int route_impl(ann_index_t* h, const void* queries, int64_t nq, int32_t* out_clu
     hipStream_t st = ws.stream;
     if (h->matrix_core_routing && (h->centroid_bias || h->route_bias)) {
         // matrix-core routing; small batches cut the centroid range into slices and merge them
-        const int slices = h->centroid_bias ? route_mfma_u8_slices(h->d.n_clusters, nq)
-                                        : route_mfma_slices(h->d.dtype, h->d.n_clusters, h->row_bytes, h->d.route_c, nq);
+        const int slices = routing_slices(h, nq, ws.routing_room);
         uint64_t* partial = nullptr;
         if (slices > 1) {
             hipError_t e;
@@ -761,7 +769,9 @@ int static_scratch_of_current_device(void** out) {
 extern "C" int ann_search_static(ann_index_t* h, const void* queries, int64_t nq, int k, int itopk, int width, int max_iters,
                                  int32_t* out_ids, void* out_dists, void* stream) {
     if (!h || h->magic != kMagic) return fail(ANN_EINVAL, "ann_search_static: not a live handle");
-    const size_t need = search_scratch_bytes(h, nq, false, 0);
+    // routes and execution order have to fit; the routing cuts the centroids into as many slices as there is room for
+    const bool routed = h->d.entry_mode == ANN_ENTRY_ROUTED && nq > 0;
+    const size_t need = routed ? padded256(sizeof(int32_t) * (size_t)nq * h->d.route_c) + search_scratch_bytes(h, nq, true, 0) : 0;
     if (need > kStaticScratchBytes)
         return fail(ANN_EUNSUPPORTED,
                     "ann_search_static: %lld queries need %zu bytes of temporaries, the static scratch holds %zu; split the batch",
@@ -772,6 +782,7 @@ extern "C" int ann_search_static(ann_index_t* h, const void* queries, int64_t nq
         if (rc != ANN_OK) return rc;
     }
     Workspace ws(static_cast<hipStream_t>(stream), base, need > 0 ? kStaticScratchBytes : 0);
+    ws.routing_room = kStaticScratchBytes - need;
     return search_impl(h, queries, nq, nullptr, false, k, itopk, width, max_iters, out_ids, out_dists, nullptr, ws, 0);
 }
 

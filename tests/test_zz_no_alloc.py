@@ -65,3 +65,25 @@ def test_static_scratch_search_equals_ann_search_on_consecutive_calls():
     torch.cuda.synchronize()
     assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
     ann.ann_free(h)
+
+
+def test_static_scratch_takes_fewer_slices_where_the_order_leaves_no_room_for_more():
+    """6.4 million clusters: routes and order take 26.7 of 33.6 MB, the partial results of the seven slices that ann_search cuts the
+    centroids into 7.8 MB.  The batch is accepted, with fewer slices and the same results."""
+    import torch
+
+    from paper_2512_02278_amd import ann
+
+    n, nq, dev = 6_400_000, 140_000, "cuda:0"
+    g = torch.Generator(device=dev).manual_seed(1)
+    x = torch.randint(0, 256, (n, 32), generator=g, device=dev, dtype=torch.uint8)
+    h = ann.ann_index_load(x, torch.full((n, 1), -1, dtype=torch.int32, device=dev), n_entry=1, entry_mode=ann.ANN_ENTRY_ROUTED,
+                           centroids=x, cluster_offsets=torch.arange(n + 1, device=dev), route_c=1)
+    at = torch.randint(0, n, (nq,), generator=g, device=dev)
+    q = x[at]
+    want = ann.ann_search(h, q, 1, 8, 1, 1)
+    got = ann.ann_search_static(h, q, 1, 8, 1, 1, torch.full_like(want[0], -7), torch.full_like(want[1], -7))
+    torch.cuda.synchronize()
+    ann.ann_free(h)
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+    assert int(got[1].max()) == 0  # every query is a centroid
