@@ -70,13 +70,18 @@ struct Mma<1> {  // fp16, fp32 sums
     static constexpr score_t kWorst = __builtin_inff();
 };
 // fp32: every value is the sum of three bf16 values (its 24 bits are theirs, 8 each, rounded to nearest, so that the
-// second and third are at most 2^-9 and 2^-18 of the first), and of the nine products of two sums the six largest run on
-// v_mfma_f32_32x32x16_bf16, the smallest first; what is left out is below 2^-26 of the product, a quarter of what one
-// rounding of an fp32 product may be off.  Six such instructions take 3/8 of the time of the eight
-// v_mfma_f32_32x32x2_f32 that 16 elements take otherwise.
-// Centroids chosen for 200 000 queries half way between two of 2 048 (32 to 256 elements, three scales, two spreads): their
-// keys exceed the nearest in 64 bits by no more on average than with the fp32 instructions (3.66e-9 against 3.81e-9 of
-// |q|^2 + |c|^2 at 32 elements, 3.34e-9 and 3.36e-9 at 96; inner product at 128: 2.5e-11 and 4.1e-11).
+// second and third are at most 2^-8 and 2^-17 of it), and of the nine products of two sums the six largest run on
+// v_mfma_f32_32x32x16_bf16, the smallest first.  What is left out is at most 2^-24 of a product, as much as one rounding of
+// an fp32 product may be off (two factors of 1.00388), and 2^-27 on average.  Six such instructions take 3/8 of the time of
+// the eight v_mfma_f32_32x32x2_f32 that 16 elements take otherwise, and they round six sums where those round sixteen.
+// Against 64 bits, what the key of the chosen centroid exceeds the nearest one's by, fp32 instructions / parts, in units of
+// |q|^2 + |c|^2 or |q||c|; mean and worst of 100 000 queries to 1 024 centroids:
+//   half way between two Gaussian centroids, L2: 8 elements 1.7e-10 and 5e-8 / 1.7e-10 and 4e-8, 32 1.7e-9 and 3e-8 / 1.7e-9
+//     and 3e-8, 96 1.35e-9 and 2.0e-8 / 1.35e-9 and 1.6e-8, 256 8.4e-10 and 1e-8 / 8.5e-10 and 1e-8;
+//   all mantissas within 2^-16 of the worst one, all products of one sign (inner product): 8 elements 1.0e-8 and 1.5e-7 / 0, 32
+//     4.2e-9 and 3.0e-7 / 8.6e-11 and 3.7e-9, 96 7.1e-8 and 7.8e-7 / 5.9e-8 and 1.1e-7, 256 1.5e-7 and 9.4e-7 / 5.4e-8 and
+//     1.3e-7; every second centroid with any mantissas instead: 32 2.7e-8 and 3.5e-7 / 3.7e-8 and 5.6e-8, 96 9.2e-8 and 7.4e-7 /
+//     8.2e-8 and 9.5e-8, 256 1.8e-7 and 9.9e-7 / 2.1e-8 and 4.8e-7.
 //
 // A sum of parts is what the fp32 instruction gives only while no product of two parts overflows (the parts of a large
 // value differ in sign: infinity minus infinity) and none that counts underflows.  Rows whose largest magnitude lies

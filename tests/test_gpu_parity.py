@@ -1224,3 +1224,46 @@ def test_a_captured_search_gathers_and_keeps_its_results_over_replays(torch_cuda
         assert torch.equal(eager[0], want[0])
     del graph
     ann.ann_free(h)
+
+
+def bf16_parts(x):
+    """x (fp32) as the sum of three bf16 values, each rounded to nearest."""
+    parts, rest = [], x.astype(np.float32)
+    for _ in range(3):
+        bits = rest.view(np.uint32).astype(np.uint64)
+        part = ((bits + 0x7FFF + ((bits >> 16) & 1)) & 0xFFFF0000).astype(np.uint32).view(np.float32)
+        parts.append(part.astype(np.float64))
+        rest = rest - part
+    return parts
+
+
+@pytest.mark.parametrize("dim", [8, 32, 96])
+@pytest.mark.parametrize("parts_win", [True, False])
+def test_fp32_routing_uses_every_part_of_its_values(torch_cuda, dim, parts_win):
+    """Two centroids whose products with the query differ by 2^-17.5 of their size, which is more than all roundings of the sum
+    of the six products of parts may amount to: the elements of one (and the query's) have the mantissa whose second and third
+    parts are largest, 2^-8 and 2^-17 of it, those of the other have one part.  Without products that a kernel might leave out
+    the wrong one would win."""
+    torch = torch_cuda
+    rng = np.random.default_rng(dim)
+    nq, n_clusters = 300, 500
+    value = np.array([0x3F807F40], np.uint32).view(np.float32)[0]         # 1.00388
+    sign = rng.choice([-1.0, 1.0], dim)
+    q = np.repeat((value * sign)[None].astype(np.float32), nq, axis=0)
+    many, one = np.full(dim, value, np.float64), np.where(np.arange(dim) < dim // 2, 1.0, 1.0078125)
+    size = float(value) * many.sum()
+    one[-1] += size * (1 + (-1 if parts_win else 1) * 2.0 ** -17.5) / float(value) - one.sum()
+    cen = np.repeat((-many * sign)[None], n_clusters, axis=0)
+    slots = rng.permutation(n_clusters)[:2]
+    cen[slots] = [many * sign, one * sign] if parts_win else [one * sign, many * sign]
+    cen = cen.astype(np.float32)
+    # left out of the six: at most 2^-24 of the size; roundings: six instructions per 16 elements, 2^-24 of the sum so far each
+    dots = cen[slots].astype(np.float64) @ q[0].astype(np.float64)
+    assert dots[0] - dots[1] > (1 + 6 * -(-dim // 16)) * 2.0 ** -24 * size
+    pc, pq = bf16_parts(cen[slots]), bf16_parts(q[0])
+    six = {(1, 1), (0, 2), (2, 0), (0, 1), (1, 0), (0, 0)}
+    for left_out in [{(1, 1)}, {(1, 0)}, {(2, 0)}, {(0, 2), (2, 0)}] if parts_win else [{(0, 1)}]:
+        dots = sum(pc[a] @ pq[b] for a, b in six - left_out)
+        assert dots[0] < dots[1], left_out
+    got = routes_to_centroids(torch, torch.from_numpy(q).cuda(), torch.from_numpy(cen).cuda(), 1, 1)
+    assert (got == slots[0]).all()
