@@ -39,7 +39,7 @@ template <>
 struct Mma<0> {  // uint8 -> int8, int32 sums
     typedef v16i acc_t;
     typedef int32_t score_t;
-    static constexpr int kParts = 1, kChunk = 128;
+    static constexpr int kParts = 1;
     static __device__ __forceinline__ v4i prep(v4i x) { return x ^ (int)0x80808080; }
     static __device__ __forceinline__ acc_t mma(acc_t c, v4i a, v4i b) {
         return __builtin_amdgcn_mfma_i32_32x32x32_i8(a, b, c, 0, 0, 0);
@@ -54,7 +54,7 @@ template <>
 struct Mma<1> {  // fp16, fp32 sums
     typedef v16f acc_t;
     typedef float score_t;
-    static constexpr int kParts = 1, kChunk = 128;
+    static constexpr int kParts = 1;
     static __device__ __forceinline__ v4i prep(v4i x) { return x; }
     static __device__ __forceinline__ acc_t mma(acc_t c, v4i a, v4i b) {
         return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8h, a), __builtin_bit_cast(v8h, b), c, 0, 0, 0);
@@ -89,7 +89,7 @@ struct Mma<1> {  // fp16, fp32 sums
 // below 2^126, and of the largest product of two rows (2^-80 at least) 46 bits lie above the smallest normal value.
 template <>
 struct Mma<2> : Mma<1> {
-    static constexpr int kParts = 3, kChunk = 64;
+    static constexpr int kParts = 3;
     // whether the row whose largest magnitude has these bits (0: a row of zeros) is not for this instruction
     static __device__ __forceinline__ bool apart(uint32_t peak) {
         return peak != 0u && (peak < __builtin_bit_cast(uint32_t, 0x1p-40f) || peak >= __builtin_bit_cast(uint32_t, 0x1p57f));
@@ -115,7 +115,6 @@ struct Mma<2> : Mma<1> {
 };
 template <>
 struct Mma<3> : Mma<1> {  // fp32, the values as they are: four K = 2 instructions per 16-byte piece
-    static constexpr int kChunk = 64;
     static __device__ __forceinline__ acc_t mma(acc_t c, v4i a, v4i b) {
         const v4f x = __builtin_bit_cast(v4f, a), y = __builtin_bit_cast(v4f, b);
         c = __builtin_amdgcn_mfma_f32_32x32x2f32(x.x, y.x, c, 0, 0, 0);
@@ -171,21 +170,21 @@ __global__ void __launch_bounds__(256) route_bias_kernel(const uint8_t* centroid
 }
 
 // One workgroup: 128 queries against 128 centroids at a time, four wavefronts in a 2 x 2 arrangement, each
-// owning a 64 x 64 block of scores (2 x 2 result tiles of 32 x 32).  The rows are walked in chunks of 128 bytes
-// (fp32: 64); a chunk of both operands is staged in LDS once per workgroup, piece-major
+// owning a 64 x 64 block of scores (2 x 2 result tiles of 32 x 32).  The rows are walked in chunks of 64 or 128
+// bytes (route_mfma_chunk); a chunk of both operands is staged in LDS once per workgroup, piece-major
 // ([16-byte piece][row], one unit of padding per piece so that the staging writes spread over the banks),
 // which is the order the matrix instruction consumes: lane (row % 32, half) reads consecutive 16-byte units.
 // The next chunk travels from L2 to registers while the current one is multiplied; two LDS buffers, one
 // barrier per chunk.  (Streaming the operands straight from L1/L2 in the instruction's layout - 32 rows x 32
 // bytes per load - left this kernel at a twelfth of the fp16 matrix rate.)
-template <int I>
+template <int I, int CHUNK>
 constexpr int route_operand_units() {  // 16-byte units of one operand chunk in LDS
-    return (Mma<I>::kParts == 1 ? Mma<I>::kChunk / 16 : 2 * Mma<I>::kParts) * (128 + 1);
+    return (Mma<I>::kParts == 1 ? CHUNK / 16 : 2 * Mma<I>::kParts) * (128 + 1);
 }
 
 // I: how the products are taken (Mma<I>).  The bits of apart[] (fp32 only, else null) are the rows of the workgroup's 128
 // queries that the bf16 parts are not for: Mma<2> sets them and leaves those rows out, Mma<3> writes them only.
-template <int I, int METRIC, int RC>
+template <int I, int CHUNK, int METRIC, int RC>
 __device__ __forceinline__ void route_queries(v4i* smem, uint32_t* apart, const uint8_t* __restrict__ centroids,
                                               const void* __restrict__ bias_in, int n_clusters, int row_bytes,
                                               const uint8_t* __restrict__ queries, int64_t nq, int32_t* __restrict__ out,
@@ -196,9 +195,9 @@ __device__ __forceinline__ void route_queries(v4i* smem, uint32_t* apart, const 
     typedef typename M::acc_t acc_t;
     typedef typename M::score_t score_t;
     // bytes of a row per chunk, and its 16-byte pieces as they are staged: all of them, or two of each bf16 part
-    constexpr int kChunk = M::kChunk;
+    constexpr int kChunk = CHUNK;
     constexpr int kRows = 128, kPieces = M::kParts == 1 ? kChunk / 16 : 2 * M::kParts, kPieceStride = kRows + 1;
-    constexpr int kOperand = route_operand_units<I>();
+    constexpr int kOperand = route_operand_units<I, CHUNK>();
     static_assert(sizeof(v4i) * 4 * kOperand >= sizeof(uint64_t) * kRows * 4 * RC, "the pool reuses the staging buffers");
     const score_t* bias = static_cast<const score_t*>(bias_in);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -418,26 +417,27 @@ __device__ __forceinline__ void route_queries(v4i* smem, uint32_t* apart, const 
     }
 }
 
-template <int DT, int METRIC, int RC>
+template <int DT, int CHUNK, int METRIC, int RC>
 __global__ void __launch_bounds__(256) route_mfma_kernel(const uint8_t* __restrict__ centroids,
                                                          const void* __restrict__ bias, int n_clusters,
                                                          int row_bytes, const uint8_t* __restrict__ queries,
                                                          int64_t nq, int32_t* __restrict__ out,
                                                          uint64_t* __restrict__ partial, int tiles_per_slice) {
     // [buffer 0 / 1][centroids, queries]; afterwards the pool of best lists
-    __shared__ v4i smem[4 * (DT == 2 && route_operand_units<3>() > route_operand_units<DT>() ? route_operand_units<3>() : route_operand_units<DT>())];
+    __shared__ v4i smem[4 * route_operand_units<DT, CHUNK>()];
+    static_assert(DT != 2 || route_operand_units<3, CHUNK>() <= route_operand_units<2, CHUNK>(), "the fp32 instruction's operands fit");
     if constexpr (DT != 2) {
-        route_queries<DT, METRIC, RC>(smem, nullptr, centroids, bias, n_clusters, row_bytes, queries, nq, out, partial, tiles_per_slice);
+        route_queries<DT, CHUNK, METRIC, RC>(smem, nullptr, centroids, bias, n_clusters, row_bytes, queries, nq, out, partial, tiles_per_slice);
     } else {
         // an extreme centroid counts for every query, an extreme query for itself: which queries share a workgroup
         // changes no result
         __shared__ uint32_t apart[4];
         const bool all = static_cast<const uint32_t*>(bias)[route_mfma_padded(n_clusters)] != 0u;
         if (threadIdx.x < 4) apart[threadIdx.x] = all ? ~0u : 0u;
-        if (!all) route_queries<2, METRIC, RC>(smem, apart, centroids, bias, n_clusters, row_bytes, queries, nq, out, partial, tiles_per_slice);
+        if (!all) route_queries<2, CHUNK, METRIC, RC>(smem, apart, centroids, bias, n_clusters, row_bytes, queries, nq, out, partial, tiles_per_slice);
         __syncthreads();
         if (__builtin_amdgcn_readfirstlane((int)(apart[0] | apart[1] | apart[2] | apart[3])))
-            route_queries<3, METRIC, RC>(smem, apart, centroids, bias, n_clusters, row_bytes, queries, nq, out, partial, tiles_per_slice);
+            route_queries<3, CHUNK, METRIC, RC>(smem, apart, centroids, bias, n_clusters, row_bytes, queries, nq, out, partial, tiles_per_slice);
     }
 }
 
@@ -481,9 +481,23 @@ hipError_t launch_route_merge(int route_c, const uint64_t* partial, int slices, 
 // their rows, and about two chunks besides.  25 000 queries x 8 192 centroids of 1536 bytes in five slices: 0.51 ms, in two
 // (as many as fill the chip at all) 0.54 ms.
 // At most 64, at least two tiles each, and partial results of at most 8 MB beyond nq * slices = 131 072.
+// Bytes of a row per chunk.  128 halve the barriers and the rounds to L2, which counts where there are no more workgroups than
+// places (65 536 queries); 64 pad rows less and halve the LDS, which counts in long batches, most for uint8, whose products take
+// half the time.  64 / 128, us: 200 000 queries x 500 centroids, uint8 rows of 192 bytes 55 / 72, 512 124 / 157, 1 536 401 / 567, fp16
+// rows of 192 40 / 51, 448 85 / 88, 704 122 / 126, 1 024 160 / 156, 1 536 282 / 244; 400 000 x 117, 32 bytes: uint8 17 / 25, fp16 13 / 19;
+// 20 000 x 8 000 (nearest four) uint8 192 149 / 157, 448 296 / 278, 704 459 / 423, 1 536 722 / 821, fp16 192 194 / 198, 448 266 / 234, 1 536
+// 508 / 449; 60 000 x 1 000 fp16 96 20.1 / 18.8, 256 31.6 / 29.7.
+static int route_mfma_chunk(int dtype, int row_bytes, int64_t nq) {
+    if (dtype == 2) return 64;
+    const int rest = row_bytes % 128;
+    const bool half_empty = rest > 0 && rest <= 64;  // the last chunk of 128
+    if (nq > 65536) return dtype == 0 || row_bytes < 512 || half_empty ? 64 : 128;
+    return (half_empty && row_bytes < 448) || (dtype == 0 && row_bytes >= 768) ? 64 : 128;
+}
+
 int route_mfma_slices(int dtype, int n_clusters, int row_bytes, int route_c, int64_t nq) {
     const int64_t groups = (nq + 127) / 128;
-    const int tiles = (n_clusters + 127) / 128, chunk = dtype == 2 ? 64 : 128, chunks = (row_bytes + chunk - 1) / chunk;
+    const int tiles = (n_clusters + 127) / 128, chunk = route_mfma_chunk(dtype, row_bytes, nq), chunks = (row_bytes + chunk - 1) / chunk;
     int best = 1;
     int64_t best_cost = 0;
     for (int s = 1; s <= 64 && s <= (tiles > 1 ? tiles / 2 : 1); ++s) {
@@ -497,7 +511,7 @@ int route_mfma_slices(int dtype, int n_clusters, int row_bytes, int route_c, int
     return best;
 }
 
-template <int DT, int METRIC>
+template <int DT, int CHUNK, int METRIC>
 static hipError_t launch_rc(int rc, const uint8_t* centroids, const void* bias, int n_clusters, int row_bytes,
                             const uint8_t* queries, int64_t nq, int32_t* out, uint64_t* partial, int slices,
                             hipStream_t stream) {
@@ -507,7 +521,7 @@ static hipError_t launch_rc(int rc, const uint8_t* centroids, const void* bias, 
     const dim3 grid((unsigned)((nq + 127) / 128), (unsigned)slices), block(256);
 #define ANN_RC(N)                                                                                                 \
     case N:                                                                                                       \
-        hipLaunchKernelGGL((route_mfma_kernel<DT, METRIC, N>), grid, block, 0, stream, centroids, bias, n_clusters, \
+        hipLaunchKernelGGL((route_mfma_kernel<DT, CHUNK, METRIC, N>), grid, block, 0, stream, centroids, bias, n_clusters, \
                            row_bytes, queries, nq, out, partial, tiles_per_slice);                                \
         break;
     switch (rc) {
@@ -549,7 +563,10 @@ hipError_t launch_route_bias(int dtype, int metric, const uint8_t* centroids, in
 hipError_t launch_route_mfma(int dtype, int metric, int route_c, const uint8_t* centroids, const void* bias,
                              int n_clusters, int row_bytes, const uint8_t* queries, int64_t nq, int32_t* out,
                              uint64_t* partial, int slices, hipStream_t stream) {
-#define ANN_CALL(D, M) launch_rc<D, M>(route_c, centroids, bias, n_clusters, row_bytes, queries, nq, out, partial, slices, stream)
+    const bool half = route_mfma_chunk(dtype, row_bytes, nq) == 64;
+#define ANN_CALL(D, M)                                                                                                          \
+    (D == 2 || half ? launch_rc<D, 64, M>(route_c, centroids, bias, n_clusters, row_bytes, queries, nq, out, partial, slices, stream) \
+                    : launch_rc<D, D == 2 ? 64 : 128, M>(route_c, centroids, bias, n_clusters, row_bytes, queries, nq, out, partial, slices, stream))
     ANN_DISPATCH(ANN_CALL)
 #undef ANN_CALL
 }

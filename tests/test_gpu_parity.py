@@ -1267,3 +1267,33 @@ def test_fp32_routing_uses_every_part_of_its_values(torch_cuda, dim, parts_win):
         assert dots[0] < dots[1], left_out
     got = routes_to_centroids(torch, torch.from_numpy(q).cuda(), torch.from_numpy(cen).cuda(), 1, 1)
     assert (got == slots[0]).all()
+
+
+@pytest.mark.parametrize("dt", ["u8", "f16"])
+@pytest.mark.parametrize("row_bytes", [32, 64, 96, 160, 448, 512, 768])
+@pytest.mark.parametrize("nq", [65_536, 65_537])
+def test_routing_chunks_of_both_lengths(torch_cuda, dt, row_bytes, nq):
+    """Long and short batches walk the rows in chunks of different lengths: routes as the plain routing kernel gives them, for fp16
+    up to near ties."""
+    from paper_2512_02278_amd import ann
+
+    torch, dim, n_clusters = torch_cuda, row_bytes // NP_DT[dt]().itemsize, 261
+    rng = np.random.default_rng(row_bytes)
+    draw = lambda n: (rng.integers(0, 256, (n, dim)) if dt == "u8" else rng.standard_normal((n, dim))).astype(NP_DT[dt])
+    cen, q = draw(n_clusters), draw(nq)
+    ct, qt = torch.from_numpy(cen).cuda(), torch.from_numpy(q).cuda()
+    h = ann.ann_index_load(ct, torch.full((n_clusters, 1), -1, dtype=torch.int32, device="cuda"), entry_mode=1, centroids=ct,
+                           cluster_offsets=torch.arange(n_clusters + 1, device="cuda"), route_c=2)
+    got = ann.ann_route(h, qt)
+    ann.ann_index_set_option(h, ann.ANN_OPT_MATRIX_CORE_ROUTING, 0)
+    want = ann.ann_route(h, qt)
+    torch.cuda.synchronize()
+    ann.ann_free(h)
+    if dt == "u8":
+        assert torch.equal(got, want)
+    else:
+        x, y = qt.double(), ct.double()
+        key = (y * y).sum(1) - 2 * (x @ y.T)
+        size = (x * x).sum(1, keepdim=True) + (y * y).sum(1).max()
+        # both round a sum of dim terms to fp32 dim times, 2^-24 of its size each
+        assert bool(((key.gather(1, got.long()) - key.gather(1, want.long())).abs() <= 2 * dim * 2.0 ** -24 * size).all())
