@@ -279,8 +279,8 @@ __global__ void __launch_bounds__(256) route_u8_rows_kernel(const uint8_t* centr
 // once, at the end: the wavefront computes the 32 scores of each query's best tile again and looks for the equal one.
 // Among equal scores the lowest cluster wins: they lie in one class of tiles, whose order is that of the clusters, and a
 // lane keeps the first; the two lanes of a query meet in the final search.
-// 500 000 queries x 16 384 centroids: 1.07 ms where route_mfma_u8_kernel takes 1.34 ms.  The matrix cores are busy half of
-// the time, the vector ALUs a third, at 1.8 GHz: the clock gives way under this load.
+// 500 000 queries x 16 384 centroids: 0.93 to 1.00 ms from box to box, where route_mfma_u8_kernel takes 1.16 to 1.24 ms on the
+// same ones.
 template <int METRIC, int kTiles>
 __global__ void __launch_bounds__(256) route_nearest_u8_kernel(const v4i* __restrict__ rows, const int32_t* __restrict__ half_bias,
                                                                const int32_t* __restrict__ map, const int32_t* __restrict__ shape,
@@ -465,8 +465,8 @@ static hipError_t launch_rc(int rc, const uint8_t* centroids, const char* block,
     const int32_t* bias = reinterpret_cast<const int32_t*>(block + at.bias);
     const int all_tiles = (n_clusters + 31) / 32;
     const int tiles_per_slice = (all_tiles + slices - 1) / slices;
-    // the final search of route_nearest_u8_kernel takes as long as some eighty tiles: 500 000 queries x 16 384 / 8 192 /
-    // 4 096 / 2 048 centroids in 1.07 / 0.59 / 0.36 / 0.24 ms, the other kernel's 1.34 / 0.71 / 0.37 / 0.19 ms
+    // the final search of route_nearest_u8_kernel takes as long as some eighty tiles: 500 000 queries x 16 384 / 8 192 / 4 096
+    // centroids in 1.00 / 0.54 / 0.31 ms, the other kernel's 1.24 / 0.62 / 0.32 ms (100 000: 255 / 143 / 91 and 346 / 175 / 89 us)
     if (rc == 1 && tiles_per_slice >= kMinNearestTiles) {
         // with both classes padded there may be a tile more than that
         const int per = (all_tiles + slices) / slices;
