@@ -515,7 +515,7 @@ namespace {
 // round, 1 000 and 1 500 queries: 384 bytes 105/107/105 and 111/115/174, 400 bytes 167/155/147 and 174/167/222, 768 bytes
 // 168/142/130 and 178/160/155, 1 536 bytes 210/196/195 and 261/267/309 (6 000: 914/910/903).  List of 64, 32 neighbours: 256
 // bytes 115/126/126, 384 bytes 119/132/131, 400 bytes 180/178/175, 1 536 bytes 196/189/186 (6 000: 762/765/819).  256 neighbours, 4 400
-// queries: 1 024 bytes 521/517/539, 1 536 bytes 781/764/751.
+// queries: 1 024 bytes 521/517/539, 1 536 bytes 781/764/751; 512 neighbours, 3 465 queries: 1 024 bytes 728/-/653.
 // Rounds of few neighbours leave a team little to share: 16 neighbours, uniform entries, 1 000 queries: 256 bytes 548/597/600, 512
 // bytes 581/626/614, 768 bytes 715/648/618.
 // Large batches of long rows are bound by bytes in flight again: 50 000 queries over 1 536 bytes 33 819 / - / 33 323.
@@ -525,38 +525,40 @@ int default_team(const ann_index_t* h, int64_t nq, int width) {
     if (bytes < 256 || (bytes <= 512 && round < 32)) return 1;
     if (h->d.entry_mode != ANN_ENTRY_UNIFORM) {
         if (nq <= 1024) return h->variant->g == 32 || round >= 128 ? 4 : 1;
-        return (bytes >= 1024 && nq >= 6000) || (bytes >= 1536 && nq >= 4096 && round >= 128) ? 4 : 1;
+        return (bytes >= 1024 && (nq >= 6000 || round >= 512)) || (bytes >= 1536 && nq >= 4096 && round >= 128) ? 4 : 1;
     }
     if (nq <= 1024 || bytes >= 1024) return 4;
     if (nq <= 1536 && (bytes <= 256 || bytes > 512)) return 4;
     return nq <= 2560 ? 2 : 1;  // teams of two are all resident up to there
 }
 
-// Share of a cluster's rows that a search is expected to score: a parent brings 4 + degree / 4 new rows, at most 12, and
-// fewer the more of the cluster has been seen.  Measured against it at lists of 64 to 256 entries, degrees 16 to 64, clusters of
-// 300 to 2 441: 0.23 / 0.27 (list 64, degree 16, 2 441 rows), 0.47 / 0.51, 0.68 / 0.72, 0.71 / 0.60, 0.94 / 0.97.
+// Share of a cluster's rows that a search is expected to score: a parent brings 3 + degree / 4 new rows, at most 15, and
+// fewer the more of the cluster has been seen.  Measured / expected: list 64, degree 16, clusters of 2 441 rows 0.23 / 0.24, of 800
+// 0.47 / 0.48; 112, 24, 800 0.68 / 0.70; 64, 32, 2 441 0.35 / 0.33; 128, 32, 800 0.76 / 0.78; 184, 64, 2 441 0.71 / 0.67; 256, 64, 1 600 0.85 / 0.85.
 double scored_share(const ann_index_t* h, int64_t parents, int64_t mean) {
-    const double fresh = h->d.degree < 32 ? 4.0 + h->d.degree / 4.0 : 12.0;
+    const double fresh = h->d.degree < 48 ? 3.0 + h->d.degree / 4.0 : 15.0;
     return 1.0 - std::exp(-std::pow((double)parents * fresh / (double)mean, 0.75));
 }
 
-// Share from which a table of keys pays.  Time without / with (300 000 rows; share scored in brackets):
-//   * A batch long enough to run grouped by cluster gathers from the caches as it is.  Below 1 KB the table then pays for nearly
-//     whole clusters only: 256 bytes L2 0.71 [0.47], 0.86 [0.68], 1.03 [0.92], products 0.89 [0.47], 1.04 [0.76]; 384 bytes
-//     0.85 [0.47], 0.97 [0.68], 1.05 [0.76], 1.07 [0.94]; 512 bytes products 0.92 [0.47], 1.07 [0.50], 1.17 [0.76]; 768 bytes L2 0.57
-//     [0.46], 0.84 [0.75], 1.16 [0.92], with clusters of 300 0.92 [0.93], 1.08 [0.99].  From 1 KB on earlier: fp16 L2 0.94 [0.46], 1.00 [0.48],
-//     1.07 [0.57]; products and fp32 1.16 .. 1.18 [0.30].
-//   * A short batch pays for the table kernel's own length: 2 000 to 4 000 queries over 256 bytes 0.82 [0.23], 1.10 [0.40] (L2 0.97 at
-//     [0.83]), 384 to 768 bytes 0.75 [0.23], 0.92 [0.35], 1.02 [0.39]; 1 000 to 1 500 queries over 1 536 bytes 0.73 [0.23], 1.20 [0.48].
-double table_share(const ann_index_t* h, int64_t nq, int64_t mean) {
+// Share from which a table of keys pays.  Time without / with, share expected in brackets; the lines lie between what gained and
+// what lost of 1 930 pairs over 100 to 460 MB of rows:
+//   * A batch long enough to run grouped by cluster gathers from the caches as it is, and the table pays for most of a cluster only:
+//     256 bytes L2 0.92 [0.78], 1.04 [0.92], products 0.96 [0.60] (with 64 rounds 1.10), 1.07 [0.67]; 384 bytes 0.88 [0.48], 1.05 [0.60],
+//     1.07 [0.67]; 400 bytes L2 0.88 [0.60], 1.04 [0.67]; 512 bytes fp16 0.95 [0.48], 1.1 [0.60], fp32 0.83 [0.32], 1.05 [0.48]; 768 bytes
+//     L2 0.89 [0.78], 1.06 [0.96], with 512 neighbours a round 1.05 [0.67], 1.12 [0.78]; 1 536 bytes L2 0.82 [0.48], 1.35 [0.67], products
+//     0.88 [0.24], 1.1 [0.32].
+//   * A short batch pays for the table kernel's own length: 2 000 to 4 000 queries over 256 bytes 0.82 [0.24], 1.1 [0.40] (L2 0.97 at
+//     [0.78]), 384 to 768 bytes 0.75 [0.24], 0.92 [0.33], 1.02 [0.40]; 1 000 to 1 500 queries over 1 536 bytes 0.73 [0.24], 1.20 [0.48].
+double table_share(const ann_index_t* h, int64_t nq, int64_t parents, int width) {
     const int bytes = h->row_bytes;
-    const bool f16_l2 = h->d.dtype == ANN_F16 && h->d.metric == ANN_L2;  // the most instructions per byte
+    const bool f32 = h->d.dtype == ANN_F32, f16_l2 = !f32 && h->d.metric == ANN_L2;  // f16_l2: the most instructions per byte
     if (nq >= h->cluster_order_min) {
-        if (bytes >= 1024) return f16_l2 ? 0.48 : 0.25;
-        if (f16_l2) return mean < 512 ? 0.98 : 0.86;
-        return bytes < 512 ? 0.8 : 0.52;
+        if (bytes >= 1024) return f16_l2 ? 0.5 : 0.3;
+        if (bytes >= 512) return f16_l2 ? ((int64_t)width * h->d.degree >= 512 ? 0.66 : 0.96) : f32 ? 0.45 : 0.49;
+        if (bytes > 256) return f32 ? 0.59 : 0.65;
+        return f16_l2 ? 0.86 : parents >= 48 * (int64_t)width ? 0.59 : 0.65;
     }
-    if (bytes >= 1024) return nq < 1536 ? 0.4 : 0.0;
+    if (bytes >= 1024) return nq < 1536 ? 0.38 : 0.0;
     if (nq >= 4096) return 0.0;
     return bytes > 256 ? 0.36 : f16_l2 ? 0.9 : 0.4;
 }
@@ -580,7 +582,7 @@ int table_stride(const ann_index_t* h, int64_t nq, int itopk, int width, int max
     const int64_t parents = (int64_t)width * max_iters < itopk ? (int64_t)width * max_iters : itopk;
     const int64_t gathered = 8 * parents < mean ? 8 * parents : mean;
     const int64_t twice_products = (int64_t)h->d.dim * (h->d.dtype == ANN_F16 && h->d.metric == ANN_IP ? 1 : 4);
-    if (10 * gathered * h->row_bytes < 4 * twice_products * mean || scored_share(h, parents, mean) < table_share(h, nq, mean)) return 0;
+    if (10 * gathered * h->row_bytes < 4 * twice_products * mean || scored_share(h, parents, mean) < table_share(h, nq, parents, width)) return 0;
     // half as long again as the mean cluster: rows beyond are gathered
     int64_t stride = (mean + mean / 2 + 127) / 64 * 64;
     if (stride > h->window_bits) stride = h->window_bits;
