@@ -185,6 +185,7 @@ struct ann_index {
     void* centroid_bias;     // DEVICE, owned: RouteU8Block of the uint8 d=128 matrix-core routing, or null
     void* route_bias;        // DEVICE, owned: the same for the general matrix-core routing, or null
     ann::TableBlocks tables;  // DEVICE, owned: memory for key tables
+    int64_t longest_cluster;  // rows of the longest cluster, or a bound on it
 };
 
 using namespace ann;
@@ -203,6 +204,32 @@ static const RowVariant* pick_variant(int dtype, int metric, int64_t row_bytes, 
 static bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
 extern "C" const char* ann_last_error(void) { return g_error; }
+
+namespace {
+
+// Whether any call on the handle can search with a key table (table_stride).
+bool may_use_table(const ann_index_t* h) {
+    return h->d.entry_mode == ANN_ENTRY_ROUTED && h->d.route_c == 1 && h->d.dtype != ANN_U8 && h->row_bytes >= 256 && h->d.n / h->d.n_clusters >= 256;
+}
+
+// The visited bitmap of a search with a key table need not be longer than the longest cluster: of 11 to 12 KB of LDS per query
+// with 512 neighbours a round it takes one.  46 239 queries over 512-byte rows, clusters of 450: 477 us, with the whole bitmap 494;
+// 5 000 over 1 536-byte rows 649 and 656.  Read with the routing's preparations, where the device is waited for anyhow.
+hipError_t find_longest_cluster(ann_index_t* h) {
+    const size_t count = (size_t)h->d.n_clusters + 1;
+    int64_t* const off = new (std::nothrow) int64_t[count];
+    if (!off) return hipErrorOutOfMemory;
+    const hipError_t e = hipMemcpy(off, h->d.cluster_offsets, count * sizeof(int64_t), hipMemcpyDeviceToHost);
+    if (e == hipSuccess) {
+        h->longest_cluster = 0;
+        for (size_t c = 0; c + 1 < count; ++c)
+            if (off[c + 1] - off[c] > h->longest_cluster) h->longest_cluster = off[c + 1] - off[c];
+    }
+    delete[] off;
+    return e;
+}
+
+}  // namespace
 
 extern "C" int ann_index_load(const ann_index_desc_t* desc, ann_index_t** out_handle) {
     if (!desc || !out_handle) return fail(ANN_EINVAL, "ann_index_load: null argument");
@@ -249,6 +276,7 @@ extern "C" int ann_index_load(const ann_index_desc_t* desc, ann_index_t** out_ha
     h->matrix_core_routing = true;
     h->centroid_bias = nullptr;
     h->route_bias = nullptr;
+    h->longest_cluster = d.n;
     const bool mfma_route = d.entry_mode == ANN_ENTRY_ROUTED;
     if (mfma_route && !(d.dtype == ANN_U8 && d.dim == 128) && row_bytes % 32 == 0) {
         hipError_t e = hipMalloc(&h->route_bias, route_mfma_bias_bytes(d.n_clusters));
@@ -256,6 +284,7 @@ extern "C" int ann_index_load(const ann_index_desc_t* desc, ann_index_t** out_ha
             e = launch_route_bias(d.dtype, d.metric, static_cast<const uint8_t*>(d.centroids), d.n_clusters,
                                   (int)row_bytes, h->route_bias, nullptr);
         if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
+        if (e == hipSuccess && may_use_table(h)) e = find_longest_cluster(h);
         if (e != hipSuccess) {
             if (h->route_bias) (void)hipFree(h->route_bias);
             delete h;
@@ -574,11 +603,11 @@ double table_share(const ann_index_t* h, int64_t nq, int64_t parents, int width)
 //     64, clusters of 2 441) 0.6 .. 0.8 at any batch size.
 // Rows below 256 bytes and clusters below 256 rows were not measured.
 int table_stride(const ann_index_t* h, int64_t nq, int itopk, int width, int max_iters, hipStream_t stream) {
-    if (h->d.entry_mode != ANN_ENTRY_ROUTED || h->d.route_c != 1 || h->d.dtype == ANN_U8 || h->row_bytes < 256) return 0;
+    if (!may_use_table(h)) return 0;
     // a fixed team, an order that is never grouped and a hash without bitmap ask for the search they describe
     if (h->team != 0 || h->cluster_order_min < 0 || h->window_bits == 0) return 0;
     const int64_t mean = h->d.n / h->d.n_clusters;
-    if (mean < 256 || nq > 2147483647ll || nq / h->d.n_clusters < (h->row_bytes >= 1024 ? 8 : 16)) return 0;
+    if (nq > 2147483647ll || nq / h->d.n_clusters < (h->row_bytes >= 1024 ? 8 : 16)) return 0;
     const int64_t parents = (int64_t)width * max_iters < itopk ? (int64_t)width * max_iters : itopk;
     const int64_t gathered = 8 * parents < mean ? 8 * parents : mean;
     const int64_t twice_products = (int64_t)h->d.dim * (h->d.dtype == ANN_F16 && h->d.metric == ANN_IP ? 1 : 4);
@@ -679,6 +708,7 @@ int search_impl(ann_index_t* h, const void* queries, int64_t nq, const int32_t* 
         p.order = order;
         p.table = table;
         p.table_stride = table ? stride : 0;
+        size_t lds_bytes = plan.lds_bytes;
         if (table) {
             KeyTableParams t;
             t.vectors = p.vectors;
@@ -702,8 +732,13 @@ int search_impl(ann_index_t* h, const void* queries, int64_t nq, const int32_t* 
             t.table = table;
             e = launch_key_table(h->d.dtype, h->d.metric, h->variant->g, h->variant->nch, t, stream);
             if (e != hipSuccess) break;
+            const int64_t longest = (h->longest_cluster + 31) / 32 * 32;
+            if (longest < p.window_bits) {
+                lds_bytes -= sizeof(uint32_t) * (size_t)((p.window_bits - longest) / 32);
+                p.window_bits = (int)longest;
+            }
         }
-        e = h->variant->search(p, plan.list_variant, team, (unsigned)(8 * p.q_per_xcd), plan.lds_bytes, stream);
+        e = h->variant->search(p, plan.list_variant, team, (unsigned)(8 * p.q_per_xcd), lds_bytes, stream);
     }
     if (block) h->tables.give_back(block, stream);
     if (e != hipSuccess) return fail(ANN_EHIP, "ann_search: launch failed: %s", hipGetErrorString(e));

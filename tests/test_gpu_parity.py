@@ -892,6 +892,7 @@ def test_float_rows_at_the_edges_of_the_32_lane_variants(oracle, torch_cuda, dt,
     ("f32", 1536, 0, (280, 301), 64, 1, 16, 35),
     ("f32", 128, 1, (600, 600, 600), 200, 4, 48, 5_000),                   # many sets of queries per cluster
     ("f32", 96, 0, (6_000, 6_200), 512, 4, 16, 33_000),                    # more queries than one launch's table holds
+    ("f32", 128, 0, (9_500, 0, 600, 900), 128, 8, 64, 400),                # a cluster longer than the visited bitmap, an empty one
 ])
 def test_key_table_gives_the_bits_of_the_gathering_search(torch_cuda, dt, dim, metric, sizes, itopk, width, degree, nq):
     """Batches with many queries per cluster search with a table of keys computed beforehand.  Results and counters have
