@@ -298,7 +298,7 @@ def main() -> int:
     cm = counters.double().mean(0).tolist()
     actual_bq = metrics.algorithmic_bytes_per_query(cm[1], cm[2], row_bytes, degree, row_bytes, k)
     log(f"stages: route {route_ms:.3f} ms, order + beam search {search_ms:.3f} ms (drawn order {drawn_ms:.3f} ms); per query: "
-        f"rounds {cm[0]:.1f}, rows gathered {cm[1]:.0f}, graph rows {cm[2]:.0f}, table resets {cm[3]:.2f}")
+        f"rounds {cm[0]:.1f}, rows scored {cm[1]:.0f}, graph rows {cm[2]:.0f}, table resets {cm[3]:.2f}")
 
     # ------------------------------------------------------------------ stage 1 of the next batch under stage 3 of this one
     # (two streams; the single-GPU shadow of the paper's two-microbatch pipeline, Sec. 3.2)
@@ -483,6 +483,10 @@ def main() -> int:
     if roofline.get("drawn_order"):
         roofline["drawn_order"]["vs_random_row_gather"] = round(roofline["drawn_order"]["achieved"] / gather_gbps, 4)
 
+    # a float batch with many queries per cluster may score its rows from a table of keys (include/ann.h): the counters do not
+    # tell, and no vector is then gathered for the row
+    scored_note = {} if dt == "u8" else {"note": "gathered = bytes of the rows scored; a batch that searches with a table of keys reads "
+                                                 "four bytes of it per row instead, and every cluster once per eight of its queries"}
     line = {
         "metric": f"queries/sec at recall@{k}>=0.95 on 1 MI355X", "value": round(qps, 1), "unit": "queries/s",
         "n_gpus": 1, "steps": args.steps, "warmup": args.warmup, "ms_per_step": round(ms_per_step, 3),
@@ -493,7 +497,7 @@ def main() -> int:
         "recall_at_k": round(rec, 4), "recall_se": round(rec_se, 4), "recall_queries": n_gt, "k": k,
         "recall_rule": f"smallest itopk of the sweep whose recall - 2 standard errors >= {RECALL_TARGET}",
         "recall_target_met": target_met, "recall_by_itopk": recall_by_itopk,
-        "bytes_per_query": {"algorithmic": None if algo_bytes is None else round(algo_bytes / nq), "gathered": round(actual_bq)},
+        "bytes_per_query": {"algorithmic": None if algo_bytes is None else round(algo_bytes / nq), "gathered": round(actual_bq), **scored_note},
         "per_query": {"rounds": round(cm[0], 2), "rows_gathered": round(cm[1], 1), "graph_rows": round(cm[2], 1),
                       "rows_scored_by_oracle": algo["n_dist"]},
         "stage_ms": {"route": round(route_ms, 3), "order_and_beam_search": round(search_ms, 3)},
@@ -589,11 +593,10 @@ def prune_roofline(workload: str, sha: str, n: int, d_in: int, degree: int, prun
                     "traffic": traffic,
                     "hbm": {"traffic": traffic, "achieved": round(traffic / prune_ms / 1e6, 1), "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                             "frac": round(traffic / prune_ms / 1e6 / HBM_PEAK_GBPS, 4)},
-                    "note": "vector instructions issued x 64 lanes / time against 4 cycles per instruction on every SIMD.  Much of this "
-                            "kernel runs with half of a wavefront's lanes switched off, and such instructions leave the SIMD after 2 "
-                            "cycles, so the count can exceed the nominal capacity (issue_rate_over_nominal); achieved and frac are "
-                            "capped at the peak: the vector ALUs are saturated.  Neighbours' rows are re-read from L2 (XCD-local "
-                            "walk), so the algorithmic bytes do not bind (see hbm)"})
+                    "note": "vector instructions issued x 64 lanes / time against 4 cycles per instruction on every SIMD.  What binds is LDS: "
+                            "every id of a neighbour's row costs a random byte read and a dependent read of an id, a dozen cycles per 64 "
+                            "lanes each.  Neighbours' rows are re-read from L2 (XCD-local walk), so the algorithmic bytes do not bind "
+                            "(see hbm)"})
     else:
         out.update({"bound": "alu", "achieved": None, "peak": round(VALU_PEAK_TOPS, 2), "unit": "TOP/s", "frac": None, "traffic": None})
     return out

@@ -82,8 +82,8 @@ typedef struct {
  * The borrowed arrays are not copied, but for what the routing keeps of the centroids: for a routed
  * index whose rows are a multiple of 32 bytes a small device array (4 bytes per cluster; for 128-byte
  * uint8 rows about 140, the centroids in the order the routing reads them) is allocated and filled on the
- * default stream, which is synchronised before returning (for float rows cluster_offsets may be read back then,
- * too); nothing else touches the device.
+ * default stream, which is synchronised before returning; for float rows of 256 bytes and more and route_c == 1
+ * cluster_offsets is read back on that stream; nothing else touches the device.
  * Must be called with the device that owns the arrays current.
  * Errors: ANN_EINVAL, ANN_EUNSUPPORTED, ANN_ENOMEM, ANN_EHIP.
  */

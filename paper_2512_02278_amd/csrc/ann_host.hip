@@ -214,19 +214,21 @@ bool may_use_table(const ann_index_t* h) {
 
 // The visited bitmap of a search with a key table need not be longer than the longest cluster: of 11 to 12 KB of LDS per query
 // with 512 neighbours a round it takes one.  46 239 queries over 512-byte rows, clusters of 450: 477 us, with the whole bitmap 494;
-// 5 000 over 1 536-byte rows 649 and 656.  Read with the routing's preparations, where the device is waited for anyhow.
-hipError_t find_longest_cluster(ann_index_t* h) {
+// 5 000 over 1 536-byte rows 649 and 656; 3 410 over 400-byte rows, all resident at once or not, 166 and 218.
+// Without memory or an answer from the device the bitmap keeps its length.
+void find_longest_cluster(ann_index_t* h) {
+    RelaxedCapture relaxed;
     const size_t count = (size_t)h->d.n_clusters + 1;
     int64_t* const off = new (std::nothrow) int64_t[count];
-    if (!off) return hipErrorOutOfMemory;
-    const hipError_t e = hipMemcpy(off, h->d.cluster_offsets, count * sizeof(int64_t), hipMemcpyDeviceToHost);
-    if (e == hipSuccess) {
+    if (!off) return;
+    if (hipMemcpy(off, h->d.cluster_offsets, count * sizeof(int64_t), hipMemcpyDeviceToHost) == hipSuccess) {
         h->longest_cluster = 0;
         for (size_t c = 0; c + 1 < count; ++c)
             if (off[c + 1] - off[c] > h->longest_cluster) h->longest_cluster = off[c + 1] - off[c];
+    } else {
+        (void)hipGetLastError();
     }
     delete[] off;
-    return e;
 }
 
 }  // namespace
@@ -284,7 +286,6 @@ extern "C" int ann_index_load(const ann_index_desc_t* desc, ann_index_t** out_ha
             e = launch_route_bias(d.dtype, d.metric, static_cast<const uint8_t*>(d.centroids), d.n_clusters,
                                   (int)row_bytes, h->route_bias, nullptr);
         if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
-        if (e == hipSuccess && may_use_table(h)) e = find_longest_cluster(h);
         if (e != hipSuccess) {
             if (h->route_bias) (void)hipFree(h->route_bias);
             delete h;
@@ -305,6 +306,7 @@ extern "C" int ann_index_load(const ann_index_desc_t* desc, ann_index_t** out_ha
                         hipGetErrorString(e));
         }
     }
+    if (may_use_table(h)) find_longest_cluster(h);
     *out_handle = h;
     return ANN_OK;
 }
@@ -546,19 +548,22 @@ namespace {
 // bytes 115/126/126, 384 bytes 119/132/131, 400 bytes 180/178/175, 1 536 bytes 196/189/186 (6 000: 762/765/819).  256 neighbours, 4 400
 // queries: 1 024 bytes 521/517/539, 1 536 bytes 781/764/751; 512 neighbours, 3 465 queries: 1 024 bytes 728/-/653.
 // Rounds of few neighbours leave a team little to share: 16 neighbours, uniform entries, 1 000 queries: 256 bytes 548/597/600, 512
-// bytes 581/626/614, 768 bytes 715/648/618.
+// bytes 581/626/614, 768 bytes 715/648/618; 32 neighbours, 6 000 queries, 1 024 bytes 878/946/1 316 (17 MB of rows) and 1 998/1 943/2 124
+// (200 MB).  Teams that are not all resident wait for each other's places: 384 neighbours, 1 400 and 2 400 queries: 256 bytes
+// 418/345/490 and 457/581/721, 400 bytes 595/453/575 and 664/790/849, 768 bytes 740/537/676 and 872/1 060/1 009.
 // Large batches of long rows are bound by bytes in flight again: 50 000 queries over 1 536 bytes 33 819 / - / 33 323.
 int default_team(const ann_index_t* h, int64_t nq, int width) {
     const int bytes = h->row_bytes;
     const int64_t round = (int64_t)width * h->d.degree;
     if (bytes < 256 || (bytes <= 512 && round < 32)) return 1;
     if (h->d.entry_mode != ANN_ENTRY_UNIFORM) {
-        if (nq <= 1024) return h->variant->g == 32 || round >= 128 ? 4 : 1;
+        if (h->variant->g == 32 ? nq <= (round > 256 ? 1024 : 1280) : nq <= 1024 && round >= 256) return 4;
         return (bytes >= 1024 && (nq >= 6000 || round >= 512)) || (bytes >= 1536 && nq >= 4096 && round >= 128) ? 4 : 1;
     }
-    if (nq <= 1024 || bytes >= 1024) return 4;
-    if (nq <= 1536 && (bytes <= 256 || bytes > 512)) return 4;
-    return nq <= 2560 ? 2 : 1;  // teams of two are all resident up to there
+    if (nq <= 1024) return 4;
+    if (bytes >= 1024) return round >= 64 ? 4 : nq <= 2560 || nq >= 6000 ? 2 : 1;
+    // as long as teams of two are all resident
+    return nq <= (round > 256 || (h->variant->g == 32 && bytes <= 512) ? 2048 : 2560) ? 2 : 1;
 }
 
 // Share of a cluster's rows that a search is expected to score: a parent brings 3 + degree / 4 new rows, at most 15, and
@@ -589,7 +594,7 @@ double table_share(const ann_index_t* h, int64_t nq, int64_t parents, int width)
     }
     if (bytes >= 1024) return nq < 1536 ? 0.38 : 0.0;
     if (nq >= 4096) return 0.0;
-    return bytes > 256 ? 0.36 : f16_l2 ? 0.9 : 0.4;
+    return bytes > 256 ? 0.36 : f16_l2 ? 0.93 : 0.4;
 }
 
 // Keys per query of the key table (key_table.h) this call searches with, 0 for a search that gathers every row.
