@@ -90,9 +90,9 @@ __device__ __forceinline__ bool hash_insert(uint32_t* table, int hash_bits, uint
 //
 // TABLE: the keys of a query against the first table_stride rows of its (only) window have been computed beforehand
 // (key_table.h), so a new id among them costs one 4-byte read instead of a row gather and its arithmetic.
-// Other ids are gathered as ever, and the visited set is the same as without a table.  Such a search takes 0.26 ms for 5 000 queries over 1536-byte rows
-// (512 neighbours a round) that took 1.98 ms with gathers, and 0.80 ms for 20 000 over 384-byte rows instead of
-// 1.33 ms.  Two thirds of the vector-ALU issue slots are used then; the rest waits for graph rows and LDS.
+// Other ids are gathered as ever, and the visited set is the same as without a table.  Such a search takes 0.27 ms for 5 000
+// queries over 1536-byte rows (512 neighbours a round) that took 1.98 ms with gathers, and 0.82 ms for 20 000 over 384-byte rows
+// instead of 1.33 ms.  0.44 and 0.64 of the vector-ALU issue slots are used then; the rest waits for graph rows and LDS.
 template <class Row, int LPL, int CPL, int TEAM = 1, bool TABLE = false>
 struct BeamSearch {
     static constexpr int G = Row::G;

@@ -65,8 +65,9 @@ __device__ __forceinline__ uint32_t slot_of(uint32_t id, int shift) { return (id
 // and j is above both i and rr: sixteen table reads are in flight per lane, then sixteen reads of the ids at those ranks.
 // What the entry is needs no test: an absent one equals no id of x's row, and a rank of d_in - 1 is below no other.
 // About 7 vector instructions per 64 lookups (25 with a Bloom filter, a queue and a bucketed table).  1M nodes 64 -> 32:
-// 1.70 ms (3.13 ms before), 590 vector and 211 LDS instructions per node; 250 000 nodes 128 -> 64: 1.79 ms (4.71 ms).
-// Bound by LDS: random byte reads of 64 lanes take a dozen cycles, and the vector ALUs are 0.65 and 0.55 busy.
+// 1.70 ms (3.13 ms before), 590 vector and 211 LDS instructions per node; 250 000 nodes 128 -> 64: 1.79 ms (4.71 ms), 2 261 and 815.
+// Bound by LDS: its units are 0.84 and 0.80 busy, nearly half of that with bank conflicts of random byte reads; the vector ALUs
+// 0.63 and 0.56.
 //
 // COUNT: the kernel also counts the in-edges of the pruned graph (step 3's histogram) - one returning
 // atomic per pruned edge, whose result is the edge's slot in its target's list.  The atomics are

@@ -4,9 +4,10 @@
 
 namespace ann {
 
-// The queries' pieces in registers, two rows per lane group in flight.  Bound by the vector ALU (0.65 of its issue
-// slots; the products of a key cost what they cost the search) and the three wavefronts per SIMD that 150 registers
-// allow: 20 000 queries x 2 441 rows of 96 floats in 0.36 ms, 5 000 x 2 441 rows of 768 fp16 products in 0.37 ms.
+// The queries' pieces in registers, two rows per lane group in flight.  Bound by the vector ALU (0.93 of its issue slots
+// for fp32 rows, 0.59 for fp16 products; the products of a key cost what they cost the search) and the three wavefronts per
+// SIMD that 150 registers allow: 20 000 queries x 2 441 rows of 96 floats in 0.37 ms, 5 000 x 2 441 rows of 768 fp16 products
+// in 0.37 ms.
 // N: queries computed, the run's m of them real; without tests between them their chains of dependent products
 // interleave.  FULL: see RowOps::load_full_row.
 template <class Row, bool FULL, int N>
