@@ -588,17 +588,18 @@ def prune_roofline(workload: str, sha: str, n: int, d_in: int, degree: int, prun
     if fresh:
         valu, traffic = prof["prune.valu_insts"], prof["prune.traffic_bytes"]
         tops = valu * 64 / (prune_ms * 1e-3) / 1e12
-        out.update({"bound": "alu", "achieved": round(min(tops, VALU_PEAK_TOPS), 2), "peak": round(VALU_PEAK_TOPS, 2), "unit": "TOP/s",
+        out.update({"bound": "lds", "achieved": round(min(tops, VALU_PEAK_TOPS), 2), "peak": round(VALU_PEAK_TOPS, 2), "unit": "TOP/s",
                     "frac": round(min(1.0, tops / VALU_PEAK_TOPS), 4), "issue_rate_over_nominal": round(tops / VALU_PEAK_TOPS, 4),
                     "traffic": traffic,
                     "hbm": {"traffic": traffic, "achieved": round(traffic / prune_ms / 1e6, 1), "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                             "frac": round(traffic / prune_ms / 1e6 / HBM_PEAK_GBPS, 4)},
-                    "note": "vector instructions issued x 64 lanes / time against 4 cycles per instruction on every SIMD.  What binds is LDS: "
+                    "note": "achieved / peak: vector instructions issued x 64 lanes / time against 4 cycles per instruction on every SIMD, the "
+                            "nearest counted resource.  What binds is LDS: "
                             "every id of a neighbour's row costs a random byte read and a dependent read of an id, a dozen cycles per 64 "
                             "lanes each.  Neighbours' rows are re-read from L2 (XCD-local walk), so the algorithmic bytes do not bind "
                             "(see hbm)"})
     else:
-        out.update({"bound": "alu", "achieved": None, "peak": round(VALU_PEAK_TOPS, 2), "unit": "TOP/s", "frac": None, "traffic": None})
+        out.update({"bound": "lds", "achieved": None, "peak": round(VALU_PEAK_TOPS, 2), "unit": "TOP/s", "frac": None, "traffic": None})
     return out
 
 
