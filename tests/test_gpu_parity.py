@@ -891,8 +891,8 @@ def test_float_rows_at_the_edges_of_the_32_lane_variants(oracle, torch_cuda, dt,
     ("f16", 1000, 1, (300, 300), 64, 1, 24, 33),
     ("f32", 1536, 0, (280, 301), 64, 1, 16, 35),
     ("f32", 128, 1, (600, 600, 600), 200, 4, 48, 5_000),                   # many sets of queries per cluster
-    ("f32", 96, 0, (6_000, 6_200), 512, 4, 16, 33_000),                    # more queries than one launch's table holds
-    ("f32", 128, 0, (9_500, 0, 600, 900), 128, 8, 64, 400),                # a cluster longer than the visited bitmap, an empty one
+    ("f32", 96, 0, (6_000, 6_200), 512, 4, 64, 33_000),                    # more queries than one launch's table holds
+    ("f32", 128, 0, (9_500, 0, 600, 900), 200, 8, 64, 400),                # a cluster longer than the visited bitmap, an empty one
 ])
 def test_key_table_gives_the_bits_of_the_gathering_search(torch_cuda, dt, dim, metric, sizes, itopk, width, degree, nq):
     """Batches with many queries per cluster search with a table of keys computed beforehand.  Results and counters have
@@ -926,8 +926,12 @@ def test_key_table_gives_the_bits_of_the_gathering_search(torch_cuda, dt, dim, m
             ids = torch.full((nq, 10), -7, dtype=torch.int32, device=dev)
             counters = torch.full((nq, 4), -7, dtype=torch.int32, device=dev)
             keys = torch.empty((nq, 10), dtype=torch.float32, device=dev)
+            torch.cuda.synchronize()
+            free = torch.cuda.mem_get_info()[0]
             ann.ann_search(h, qt, 10, itopk, width, 100, out_ids=ids, out_dists=keys, counters=counters, routes=r)
             torch.cuda.synchronize()
+            if r is None and team == 0:                                          # a table: 32 MB steps of device memory
+                assert free - torch.cuda.mem_get_info()[0] >= 32 << 20
             got.append((ids, keys.view(torch.int32), counters[:, 0], counters[:, 2], counters[:, 1]))
         assert all(torch.equal(a, b) for a, b in zip(*(v[:4] for v in got)))     # ids, keys, rounds, graph rows
         assert torch.equal(got[0][4], got[1][4])                                 # rows scored: the bitmap covers every cluster
