@@ -484,14 +484,15 @@ hipError_t launch_route_merge(int route_c, const uint64_t* partial, int slices, 
 // Bytes of a row per chunk.  128 halve the barriers and the rounds to L2, which counts where there are no more workgroups than
 // places (65 536 queries); 64 pad rows less and halve the LDS, which counts in long batches, most for uint8, whose products take
 // half the time.  64 / 128, us: 200 000 queries x 500 centroids, uint8 rows of 192 bytes 55 / 72, 512 124 / 157, 1 536 401 / 567, fp16
-// rows of 192 40 / 51, 448 85 / 88, 704 122 / 126, 1 024 160 / 156, 1 536 282 / 244; 400 000 x 117, 32 bytes: uint8 17 / 25, fp16 13 / 19;
+// rows of 192 40 / 51, 448 85 / 88, 704 122 / 126, 1 024 160 / 156, 1 536 282 / 244; 107 837 x 3 687 fp16 128 115 / 122, 256 168 / 181, 352
+// 268 / 238, 480 367 / 318; 400 000 x 117, 32 bytes: uint8 17 / 25, fp16 13 / 19;
 // 20 000 x 8 000 (nearest four) uint8 192 149 / 157, 448 296 / 278, 704 459 / 423, 1 536 722 / 821, fp16 192 194 / 198, 448 266 / 234, 1 536
 // 508 / 449; 60 000 x 1 000 fp16 96 20.1 / 18.8, 256 31.6 / 29.7.
 static int route_mfma_chunk(int dtype, int row_bytes, int64_t nq) {
     if (dtype == 2) return 64;
     const int rest = row_bytes % 128;
     const bool half_empty = rest > 0 && rest <= 64;  // the last chunk of 128
-    if (nq > 65536) return dtype == 0 || row_bytes < 512 || half_empty ? 64 : 128;
+    if (nq > 65536) return dtype == 0 || row_bytes <= 256 || half_empty ? 64 : 128;
     return (half_empty && row_bytes < 448) || (dtype == 0 && row_bytes >= 768) ? 64 : 128;
 }
 

@@ -1275,7 +1275,7 @@ def test_fp32_routing_uses_every_part_of_its_values(torch_cuda, dim, parts_win):
 
 
 @pytest.mark.parametrize("dt", ["u8", "f16"])
-@pytest.mark.parametrize("row_bytes", [32, 64, 96, 160, 448, 512, 768])
+@pytest.mark.parametrize("row_bytes", [32, 64, 96, 160, 256, 288, 448, 512, 768])
 @pytest.mark.parametrize("nq", [65_536, 65_537])
 def test_routing_chunks_of_both_lengths(torch_cuda, dt, row_bytes, nq):
     """Long and short batches walk the rows in chunks of different lengths: routes as the plain routing kernel gives them, for fp16
