@@ -580,13 +580,14 @@ bool matrix_routing(const ann_index_t* h, int64_t nq, hipStream_t stream) {
     const double steps = (double)h->d.n_clusters * h->variant->g / 64;
     return steps * (nq > 4000 ? nq / 4000.0 : 1.0) >= 64 + 16 * h->d.route_c && may_allocate_more(stream);
 }
-constexpr int64_t kListedQueries = 65536;  // per launch: lists of 11 are 5.8 MB then
+constexpr int64_t kListedQueries = 65536;  // per launch: lists of 12 are 6.3 MB then
+int listed_words(const ann_index_t* h) { return h->d.route_c + route_spare_words(h->d.dtype == ANN_F32, h->row_bytes, h->d.route_c); }
 int listed_slices(const ann_index_t* h, int64_t nq) {
-    const int slices = route_mfma_slices(h->d.dtype, h->d.n_clusters, h->row_bytes, h->d.route_c + kSpareWords, nq < kListedQueries ? nq : kListedQueries);
+    const int slices = route_mfma_slices(h->d.dtype, h->d.n_clusters, h->row_bytes, listed_words(h), nq < kListedQueries ? nq : kListedQueries);
     return route_mfma_used_slices(h->d.n_clusters, slices);
 }
 size_t listed_bytes(const ann_index_t* h, int64_t nq) {
-    return sizeof(uint64_t) * (size_t)(nq < kListedQueries ? nq : kListedQueries) * listed_slices(h, nq) * (h->d.route_c + kSpareWords);
+    return sizeof(uint64_t) * (size_t)(nq < kListedQueries ? nq : kListedQueries) * listed_slices(h, nq) * listed_words(h);
 }
 
 // Bytes of temporaries the routing of nq queries takes.
@@ -666,7 +667,7 @@ int route_impl(ann_index_t* h, const void* queries, int64_t nq, int32_t* out_clu
         if (words) {
             rp.slices = listed_slices(h, nq);
             rp.largest = static_cast<const float*>(h->route_bias) + route_mfma_padded(h->d.n_clusters) + 1;
-            e = launch_route_mfma(h->d.dtype, h->d.metric, h->d.route_c + kSpareWords, rp.centroids, h->route_bias, rp.n_clusters, rp.row_bytes,
+            e = launch_route_mfma(h->d.dtype, h->d.metric, listed_words(h), rp.centroids, h->route_bias, rp.n_clusters, rp.row_bytes,
                                   rp.queries, rp.nq, nullptr, words, rp.slices, st);
         }
         if (e == hipSuccess) e = h->variant->route(rp, st);

@@ -27,14 +27,16 @@ struct RouteParams {
     int64_t nq;
     int32_t route_c;
     int32_t* out;  // nq * route_c
-    const uint64_t* words;  // [query][slice][route_c + kSpareWords] (ordered score << 32 | cluster), ascending per slice; or null
+    const uint64_t* words;  // [query][slice][route_c + route_spare_words] (ordered score << 32 | cluster), ascending per slice; or null
     int32_t slices;
-    const float* largest;   // the largest |c|^2 (with words)
+    const float* largest;   // the largest |c|^2 (with words); fp32: in front of it a word that is not 0 if there are extreme centroids
 };
 
-// Listed beyond the route_c that are wanted.  With two, one of some thousand queries found the last one too near, and its wavefront's
-// walk over all centroids was the launch: 6 400 fp16 rows of 1 008 bytes, 400 centroids, nearest four: 129 us, with three 59 us.
-constexpr int kSpareWords = 3;
+// Listed beyond the route_c that are wanted.  If even the last one is too near, the query's wavefront walks all centroids, and a few such
+// walks are the launch: with two spare words one of some thousand queries did (6 400 fp16 rows of 1 008 bytes, 400 centroids, nearest
+// four: 129 us, with three 59), and scores of long fp32 rows have to be further apart (settle_route).
+constexpr int kMaxSpareWords = 4;
+__host__ __device__ constexpr int route_spare_words(bool f32, int row_bytes, int route_c) { return f32 && row_bytes > 512 && route_c > 2 ? 4 : 3; }
 constexpr int kMaxRouteSlices = 64;
 
 // What the listed words leave to do: nothing (the first route_c are in list[]), score the listed centroids, or all.
@@ -42,8 +44,8 @@ enum RouteRest { kRouteDone, kRouteListed, kRouteAll };
 
 template <class Row>
 __device__ __forceinline__ RouteRest settle_route(const RouteParams& p, const Row& row, int64_t qi, int lane, uint32_t* list) {
-    const int each = p.route_c + kSpareWords, total = p.slices * each;
-    constexpr int kWords = (kMaxRouteSlices * (kMaxRouteC + kSpareWords) + 63) / 64;
+    const int each = p.route_c + route_spare_words(Row::kDtype == kF32, p.row_bytes, p.route_c), total = p.slices * each;
+    constexpr int kWords = (kMaxRouteSlices * (kMaxRouteC + kMaxSpareWords) + 63) / 64;
     uint64_t w[kWords];
 #pragma unroll
     for (int i = 0; i < kWords; ++i) w[i] = i * 64 + lane < total ? p.words[qi * total + i * 64 + lane] : ~0ull;
@@ -61,11 +63,27 @@ __device__ __forceinline__ RouteRest settle_route(const RouteParams& p, const Ro
                 sum = __builtin_fmaf(f, f, sum);
             }
         }
-    // A score is a sum of dim products and |c|^2, in 32 bits.  Its error and the key's own are about sqrt(dim) roundings of
-    // |q|^2 + |c|^2 (2^-24 each; 3 dim if all were at their worst and of one sign); dim + 64 leave a factor of twenty at 400 elements.
+    // How far apart two scores have to be for the keys to be in their order (u = 2^-24, a rounding to nearest; S = |q|^2 + |c|^2, at
+    // least twice the sum of all |q_i c_i|, and half of |q - c|^2):
+    //   * q.c on the matrix cores.  An instruction takes its sixteen products in two groups of eight: it lines a group up with its
+    //     largest, cuts the others off at 2^-24 of that, and adds the group to the sum with one rounding (so it was found; in 50 million
+    //     trials no instruction was off by more than 5.8 u of its products' and the sum's magnitudes).  The cuts are at most 7 u of all
+    //     products; a rounding is counted as 2 u of the sum of magnitudes, two of them per 16 elements of fp16, twelve of fp32, whose parts'
+    //     products add up to at most 1.02 of theirs and leave u out.  Twice that in the score:
+    //         fp16 u S (0.25 dim + 11), fp32 u S (1.55 dim + 33)
+    //     (where extreme values are left to the fp32 instruction: at most two roundings of 2 u per element, fp32 u S 4 dim)
+    //   * |c|^2, summed in a chain, and the score's own rounding:                             u S (dim + 2)
+    //   * the key: differences, squares, a lane's chain and five levels of the group's sum:   2 u S (elements per lane + 8)
+    // Each of the two scores and of the two keys may be off that way.  1.01 is for products of roundings, and for those of S.
+    // (A bound on ordinary sums, (dim + 64) u S, let rows whose squares all round the same way change places: (1, 0.999 * 2^-12, ..)
+    // and (1, 1.0001 * 2^-12, .., 0, ..) seen from zero, 252 fp32 elements.)
     const float scale = group_sum<Row::G>(sum, lane) + *p.largest;
-    const int dim = p.row_bytes / (Row::kDtype == kF16 ? 2 : 4);
-    const float apart = scale * ((float)(dim + 64) * 0x1p-24f);
+    constexpr bool kHalf = Row::kDtype == kF16;
+    constexpr int kSize = kHalf ? 2 : 4, kPerLane = Row::NCH * 16 / kSize;
+    const float dim = (float)(p.row_bytes / kSize);
+    bool extreme = false;  // (of queries only large ones count: next to |c|^2 the products of tiny ones are nothing)
+    if constexpr (!kHalf) extreme = scale >= 0x1p113f || __builtin_bit_cast(uint32_t, p.largest[-1]) != 0u;
+    const float apart = 1.01f * scale * (2.0f * ((kHalf ? 1.25f : extreme ? 5.0f : 2.55f) * dim + (kHalf ? 14.0f : 36.0f) + 2.0f * (kPerLane + 8)) * 0x1p-24f);
     RouteRest rest = scale >= 0x1p-60f ? kRouteDone : kRouteAll;  // (not a number: all)
     float before = 0.0f, wanted = 0.0f;
     for (int r = 0; r < each; ++r) {
@@ -98,7 +116,7 @@ template <class Row>
 __global__ void __launch_bounds__(64) route_kernel(const RouteParams p) {
     constexpr int PR = (64 / Row::G * kMaxRouteC + 63) / 64;  // registers per lane of the final sort
     __shared__ uint64_t pool[64 * PR];
-    __shared__ uint32_t list[kMaxRouteC + kSpareWords];
+    __shared__ uint32_t list[kMaxRouteC + kMaxSpareWords];
     const int lane = lane_id();
     const int64_t qi = blockIdx.x;
     if (qi >= p.nq) return;
@@ -124,7 +142,7 @@ __global__ void __launch_bounds__(64) route_kernel(const RouteParams p) {
 #pragma unroll
     for (int i = 0; i < kMaxRouteC; ++i) best[i] = kInfKey;
 
-    const int rows = listed ? p.route_c + kSpareWords : p.n_clusters;
+    const int rows = listed ? p.route_c + route_spare_words(Row::kDtype == kF32, p.row_bytes, p.route_c) : p.n_clusters;
     for (int c0 = 0; c0 < rows; c0 += RPS) {
         const int at = c0 + grp;
         const int c = !listed || at >= rows ? at : (int)list[at];

@@ -42,7 +42,7 @@ hipError_t launch_route_merge(int route_c, const uint64_t* partial, int slices, 
 
 // out[q][0..route_c): the nearest clusters of query q under (score, cluster index), ascending.
 // slices > 1 needs `partial`: DEVICE scratch of nq * slices * route_c uint64.  Without `out` the slices' words are all that is
-// wanted, of any number of slices; route_c may then be up to 11.
+// wanted, of any number of slices; route_c may then be up to 11 (fp16) or 12 (fp32).
 hipError_t launch_route_mfma(int dtype, int metric, int route_c, const uint8_t* centroids, const void* bias,
                              int n_clusters, int row_bytes, const uint8_t* queries, int64_t nq, int32_t* out,
                              uint64_t* partial, int slices, hipStream_t stream);

@@ -586,7 +586,15 @@ static hipError_t launch_rc(int rc, const uint8_t* centroids, const void* bias, 
             if constexpr (DT != 0) {  // lists with spare words
                 switch (rc) {
                     ANN_RC(9) ANN_RC(10) ANN_RC(11)
-                    default: return hipErrorInvalidValue;
+                    default:
+                        if constexpr (DT == 2) {
+                            switch (rc) {
+                                ANN_RC(12)
+                                default: return hipErrorInvalidValue;
+                            }
+                            break;
+                        }
+                        return hipErrorInvalidValue;
                 }
                 break;
             }

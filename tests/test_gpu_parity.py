@@ -1074,6 +1074,42 @@ def test_routing_of_rows_of_an_odd_multiple_of_16_bytes_is_the_plain_kernels(tor
             assert torch.equal(got, want), (dim, extreme, (got != want).nonzero()[:5].tolist())
 
 
+def plain_and_listed_routes(torch, q, cen, metric, route_c):
+    """Routes of the plain kernel alone and of the one that settles lists of the matrix cores, and whether the latter ran."""
+    from paper_2512_02278_amd import ann
+
+    n = cen.shape[0]
+    h = ann.ann_index_load(cen, torch.full((n, 1), -1, dtype=torch.int32, device=cen.device), metric=metric, entry_mode=1,
+                           centroids=cen, cluster_offsets=torch.arange(n + 1, device=cen.device), route_c=route_c)
+    out = []
+    names = kernels_of(torch, lambda: out.append(ann.ann_route(h, q)))
+    ann.ann_index_set_option(h, ann.ANN_OPT_MATRIX_CORE_ROUTING, 0)
+    out.append(ann.ann_route(h, q))
+    torch.cuda.synchronize()
+    ann.ann_free(h)
+    return out[1].cpu(), out[0].cpu(), "route_mfma_kernel" in names
+
+
+@pytest.mark.parametrize("dt,dim", [("f32", 100), ("f32", 252), ("f32", 380), ("f32", 1_532), ("f16", 200), ("f16", 504)])
+def test_listed_routes_hold_where_all_squares_round_the_same_way(torch_cuda, dt, dim):
+    """Two centroids whose |c|^2, summed in a chain, stand in the wrong order: next to a one, the squares of the first are all lost
+    and those of the second, the nearer one by its zeros, are all counted double."""
+    torch = torch_cuda
+    kind = torch.float32 if dt == "f32" else torch.float16
+    low, high = (0.999, 1.0001) if dt == "f32" else (1 - 2.0 ** -11, 1 + 2.0 ** -10)
+    g = torch.Generator().manual_seed(dim)
+    cen = torch.randn((400, dim), generator=g, dtype=torch.float64)
+    cen = (cen / cen.norm(dim=1, keepdim=True) * 1.01 ** 0.5).to(kind)
+    cen[20, 0], cen[20, 1:] = 1.0, low * 2.0 ** -12
+    cen[310, 0], cen[310, 1:], cen[310, dim - dim // 8:] = 1.0, high * 2.0 ** -12, 0.0
+    chain = torch.zeros(2, dtype=torch.float64)
+    for i in range(dim):
+        chain = (chain + cen[[20, 310], i].double() ** 2).float().double()
+    assert chain[0] < chain[1] and cen[20].double().square().sum() > cen[310].double().square().sum()
+    want, got, listed = plain_and_listed_routes(torch, torch.zeros((64, dim), dtype=kind, device="cuda"), cen.to("cuda"), 0, 1)
+    assert listed and bool((want == 310).all()) and torch.equal(want, got)
+
+
 @pytest.mark.parametrize("metric", [0, 1])
 @pytest.mark.parametrize("nq,n_clusters,route_c", [(300, 200, 1), (5_000, 700, 3), (70_000, 300, 1)])
 def test_fp32_routing_of_extreme_values(torch_cuda, metric, nq, n_clusters, route_c):
