@@ -84,7 +84,8 @@ __device__ __forceinline__ RouteRest settle_route(const RouteParams& p, const Ro
     bool extreme = false;  // (of queries only large ones count: next to |c|^2 the products of tiny ones are nothing)
     if constexpr (!kHalf) extreme = scale >= 0x1p113f || __builtin_bit_cast(uint32_t, p.largest[-1]) != 0u;
     const float apart = 1.01f * scale * (2.0f * ((kHalf ? 1.25f : extreme ? 5.0f : 2.55f) * dim + (kHalf ? 14.0f : 36.0f) + 2.0f * (kPerLane + 8)) * 0x1p-24f);
-    RouteRest rest = scale >= 0x1p-60f ? kRouteDone : kRouteAll;  // (not a number: all)
+    // (not a number: all; so large that a key may be infinite, where every score is finite: all)
+    RouteRest rest = scale >= 0x1p-60f && scale <= 0x1p125f ? kRouteDone : kRouteAll;
     float before = 0.0f, wanted = 0.0f;
     for (int r = 0; r < each; ++r) {
         uint64_t least = ~0ull;

@@ -1110,6 +1110,18 @@ def test_listed_routes_hold_where_all_squares_round_the_same_way(torch_cuda, dt,
     assert listed and bool((want == 310).all()) and torch.equal(want, got)
 
 
+def test_listed_routes_hold_where_only_the_keys_are_infinite(torch_cuda):
+    """|q - c|^2 beyond the largest float for every centroid, |c|^2 - 2 q.c below it: the keys are equal, the scores are not.
+    (256 centroids: no padding rows, which would win against such scores.)"""
+    torch = torch_cuda
+    a = 0.9e38 ** 0.5
+    cen, q = torch.zeros((256, 100)), torch.zeros((64, 100))
+    cen[:, 0] = -a * torch.linspace(0.99, 0.95, 256)
+    q[:, 0] = a
+    want, got, listed = plain_and_listed_routes(torch, q.to("cuda"), cen.to("cuda"), 0, 2)
+    assert listed and want[0].tolist() == [0, 1] and torch.equal(want, got)
+
+
 @pytest.mark.parametrize("metric", [0, 1])
 @pytest.mark.parametrize("nq,n_clusters,route_c", [(300, 200, 1), (5_000, 700, 3), (70_000, 300, 1)])
 def test_fp32_routing_of_extreme_values(torch_cuda, metric, nq, n_clusters, route_c):
