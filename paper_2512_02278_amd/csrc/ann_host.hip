@@ -213,6 +213,7 @@ static const RowVariant* pick_variant(int dtype, int metric, int64_t row_bytes, 
 }
 
 constexpr int kMaxClusterRowBytes = 256, kSampledClusters = 256;
+constexpr float kMostNormRatio = 8.0f;  // largest |c|^2 to their mean
 
 // A workgroup looks at one row of a cluster and 64 others: counts[0] and [1] get its graph edges and those that leave the cluster,
 // counts[2] the others whose keys are too far above the smallest of them for a word of cluster_search.h.
@@ -295,6 +296,19 @@ void find_longest_cluster(ann_index_t* h) {
     delete[] off;
 }
 
+// Whether the matrix cores only list centroids and the plain kernel settles which are nearest (route_kernel.h): float rows that
+// are an odd multiple of 16 bytes, whose nearest centroids have always been those of the plain kernel's keys.
+bool settled_routing(const ann_index_t* h) { return h->route_bias && h->d.dtype != ANN_U8 && h->row_bytes % 32 != 0; }
+
+// How far apart listed scores have to be grows with the largest |c|^2 of all: where that stands out, most queries would be settled by
+// the plain kernel after all, and the lists be made for nothing.  Waits for the default stream.
+hipError_t norms_allow_listing(const ann_index_t* h, bool* allow) {
+    float norms[2];
+    const hipError_t e = hipMemcpy(norms, static_cast<const float*>(h->route_bias) + route_mfma_padded(h->d.n_clusters) + 1, sizeof(norms), hipMemcpyDeviceToHost);
+    *allow = e == hipSuccess && std::isfinite(norms[0]) && norms[0] <= kMostNormRatio * (norms[1] / (float)h->d.n_clusters);
+    return e;
+}
+
 // Whether searches by whole clusters can be expected to end in them.  A query meets some two hundred rows before its list is
 // full, and an edge that leaves the cluster at any time: of the sampled edges at most one in 1 024 may leave, of the sampled keys one in 4 096 may
 // be too far.  (A query that has to be searched anew costs both searches.)
@@ -375,8 +389,9 @@ extern "C" int ann_index_load(const ann_index_desc_t* desc, ann_index_t** out_ha
         if (e == hipSuccess)
             e = launch_route_bias(d.dtype, d.metric, static_cast<const uint8_t*>(d.centroids), d.n_clusters,
                                   (int)row_bytes, h->route_bias, nullptr);
-        if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
-        if (e != hipSuccess) {
+        bool listing = true;
+        if (e == hipSuccess) e = settled_routing(h) ? norms_allow_listing(h, &listing) : hipStreamSynchronize(nullptr);
+        if (e != hipSuccess || !listing) {
             if (h->route_bias) (void)hipFree(h->route_bias);
             h->route_bias = nullptr;
             if (needed) {
@@ -554,10 +569,6 @@ int routing_slices(const ann_index_t* h, int64_t nq, size_t room) {
     const size_t most = room / (sizeof(uint64_t) * (size_t)nq * h->d.route_c);
     return most >= (size_t)slices ? slices : most > 1 ? (int)most : 1;
 }
-
-// Whether the matrix cores only list centroids and the plain kernel settles which are nearest (route_kernel.h): float rows that
-// are an odd multiple of 16 bytes, whose nearest centroids have always been those of the plain kernel's keys.
-bool settled_routing(const ann_index_t* h) { return h->route_bias && h->d.dtype != ANN_U8 && h->row_bytes % 32 != 0; }
 
 // A captured call keeps to what it would have allocated for a search that gathers rows.
 bool may_allocate_more(hipStream_t stream) {

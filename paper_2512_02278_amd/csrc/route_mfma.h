@@ -9,12 +9,12 @@ namespace ann {
 // Entries of the per-centroid bias array: n_clusters rounded up to whole tiles of 128 rows.
 constexpr int route_mfma_padded(int n_clusters) { return (n_clusters + 127) / 128 * 128; }
 
-// Bytes of what launch_route_bias fills: the array, and for float types two words behind it.
-inline size_t route_mfma_bias_bytes(int n_clusters) { return 4 * ((size_t)route_mfma_padded(n_clusters) + 2); }
+// Bytes of what launch_route_bias fills: the array, and for float types three words behind it.
+inline size_t route_mfma_bias_bytes(int n_clusters) { return 4 * ((size_t)route_mfma_padded(n_clusters) + 3); }
 
 // bias (4 bytes per entry: int32 for uint8 data, float otherwise): the per-centroid term of the
 // score; padding entries get a value that never wins.  Float types: the first word behind the array is 0 unless a centroid of
-// fp32 is out of the range of the bf16 parts (route_mfma.hip), the second the largest |c|^2.
+// fp32 is out of the range of the bf16 parts (route_mfma.hip), the second the largest |c|^2, the third the sum of all.
 hipError_t launch_route_bias(int dtype, int metric, const uint8_t* centroids, int n_clusters, int row_bytes, void* bias,
                              hipStream_t stream);
 

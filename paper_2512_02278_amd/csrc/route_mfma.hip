@@ -127,8 +127,8 @@ struct Mma<3> : Mma<1> {  // fp32, the values as they are: four K = 2 instructio
 __global__ void route_clear_words_kernel(uint32_t* words) { words[threadIdx.x] = 0u; }
 
 // bias[c]: the per-centroid term of the score; rows beyond n_clusters (padding up to a multiple
-// of 128) get a value that never wins.  Float types: of the two words behind them the first becomes 1 if any centroid is not for the
-// bf16 parts (fp32), the second the largest |c|^2 (not a number: something larger than any).
+// of 128) get a value that never wins.  Float types: of the three words behind them the first becomes 1 if any centroid is not for the
+// bf16 parts (fp32), the second the largest |c|^2 (not a number: something larger than any), the third the sum of all.
 template <int DT, int METRIC>
 __global__ void __launch_bounds__(256) route_bias_kernel(const uint8_t* centroids, int n_clusters, int padded,
                                                          int row_bytes, void* bias_out) {
@@ -164,7 +164,11 @@ __global__ void __launch_bounds__(256) route_bias_kernel(const uint8_t* centroid
         if (DT == 2 && Mma<2>::apart(peak)) words[0] = 1u;
         uint32_t largest = __builtin_bit_cast(uint32_t, acc) & 0x7fffffffu;
         for (int d = 1; d < 64; d <<= 1) largest = max(largest, (uint32_t)__shfl_xor((int)largest, d));
-        if ((threadIdx.x & 63) == 0) atomicMax(&words[1], largest);
+        for (int d = 1; d < 64; d <<= 1) acc += __shfl_xor(acc, d);
+        if ((threadIdx.x & 63) == 0) {
+            atomicMax(&words[1], largest);
+            atomicAdd(reinterpret_cast<float*>(&words[2]), acc);
+        }
     }
 }
 
@@ -608,7 +612,7 @@ static hipError_t launch_rc(int rc, const uint8_t* centroids, const void* bias, 
 template <int DT, int METRIC>
 static hipError_t launch_bias(const uint8_t* centroids, int n_clusters, int row_bytes, void* bias, hipStream_t stream) {
     const int padded = route_mfma_padded(n_clusters);
-    if (DT != 0) hipLaunchKernelGGL(route_clear_words_kernel, dim3(1), dim3(2), 0, stream, static_cast<uint32_t*>(bias) + padded);
+    if (DT != 0) hipLaunchKernelGGL(route_clear_words_kernel, dim3(1), dim3(3), 0, stream, static_cast<uint32_t*>(bias) + padded);
     hipLaunchKernelGGL((route_bias_kernel<DT, METRIC>), dim3((unsigned)((padded + 255) / 256)), dim3(256), 0, stream,
                        centroids, n_clusters, padded, row_bytes, bias);
     return hipGetLastError();

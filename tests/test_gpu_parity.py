@@ -1122,6 +1122,19 @@ def test_listed_routes_hold_where_only_the_keys_are_infinite(torch_cuda):
     assert listed and want[0].tolist() == [0, 1] and torch.equal(want, got)
 
 
+@pytest.mark.parametrize("dt", ["f32", "f16"])
+@pytest.mark.parametrize("outlier", [1.0, 40.0, float("inf"), float("nan")])
+def test_routes_are_not_listed_where_one_centroid_stands_out(torch_cuda, dt, outlier):
+    """Every query's scores would be too near each other for the margin that a far centroid asks for."""
+    torch = torch_cuda
+    g = torch.Generator().manual_seed(3)
+    kind = torch.float32 if dt == "f32" else torch.float16
+    cen, q = torch.randn((400, 100 if dt == "f32" else 200), generator=g), torch.randn((500, 100 if dt == "f32" else 200), generator=g)
+    cen[77] *= outlier
+    want, got, listed = plain_and_listed_routes(torch, q.to(kind).to("cuda"), cen.to(kind).to("cuda"), 0, 2)
+    assert listed == (outlier == 1.0) and torch.equal(want, got)
+
+
 @pytest.mark.parametrize("metric", [0, 1])
 @pytest.mark.parametrize("nq,n_clusters,route_c", [(300, 200, 1), (5_000, 700, 3), (70_000, 300, 1)])
 def test_fp32_routing_of_extreme_values(torch_cuda, metric, nq, n_clusters, route_c):
