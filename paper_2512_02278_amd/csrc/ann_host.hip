@@ -522,16 +522,17 @@ namespace {
 // given (the static scratch) or one stream-ordered allocation of `reserve` bytes, made when the first piece
 // is asked for and released on the same stream once the call has enqueued its work.  One allocation per
 // call, not one per temporary: on the host an allocate/release pair costs as much as several kernel launches
-// (with two pairs per call, small batches in flight on four streams reached 11.9 M queries/s, with one 14.8 M).
+// (with two pairs per call, small batches in flight on four streams reached 11.9 M queries/s, with one 14.8 M).  Where `reserve`
+// bytes are not to be had, the block holds `least`, what the call cannot do without.
 struct Workspace {
     hipStream_t stream;
     char* base = nullptr;
     size_t bytes = 0, used = 0;
-    size_t reserve = 0;  // > 0: the block is this call's own allocation (made on first use)
+    size_t reserve = 0, least = 0;  // reserve > 0: the block is this call's own allocation (made on first use)
     bool owned = false;
     size_t routing_room = SIZE_MAX;  // bytes of it that the routing's own temporaries may take
 
-    Workspace(hipStream_t s, size_t reserve_bytes) : stream(s), reserve(reserve_bytes) {}
+    Workspace(hipStream_t s, size_t reserve_bytes, size_t least_bytes) : stream(s), reserve(reserve_bytes), least(least_bytes) {}
     Workspace(hipStream_t s, void* buffer, size_t buffer_bytes) : stream(s), base(static_cast<char*>(buffer)), bytes(buffer_bytes) {}
     Workspace(const Workspace&) = delete;
 
@@ -541,7 +542,17 @@ struct Workspace {
         if (!base && reserve > 0) {
             void* p = nullptr;
             *err = hipMallocAsync(&p, reserve, stream);
-            if (*err != hipSuccess) return nullptr;
+            if (*err != hipSuccess && least > 0 && least < reserve) {
+                (void)hipGetLastError();
+                reserve = least;
+                routing_room = 0;
+                *err = hipMallocAsync(&p, reserve, stream);
+            }
+            if (*err != hipSuccess) {
+                (void)hipGetLastError();
+                reserve = 0;  // later pieces are not had either
+                return nullptr;
+            }
             base = static_cast<char*>(p);
             bytes = reserve;
             owned = true;
@@ -632,17 +643,24 @@ size_t search_scratch_bytes(const ann_index_t* h, int64_t nq, bool routes_given,
     return need;
 }
 
+// Of those, what the call cannot do without: the routes, and the order that a large batch runs in whichever way it is searched.
+size_t search_scratch_needed(const ann_index_t* h, int64_t nq, bool routes_given) {
+    if (h->d.entry_mode != ANN_ENTRY_ROUTED || nq <= 0) return 0;
+    return (routes_given ? 0 : padded256(sizeof(int32_t) * (size_t)nq * h->d.route_c)) +
+           (grouped_order(h, nq, Way()) ? padded256(sizeof(int32_t) * ((size_t)nq + h->d.n_clusters)) : 0);
+}
+
 int route_impl(ann_index_t* h, const void* queries, int64_t nq, int32_t* out_clusters, Workspace& ws) {
     hipStream_t st = ws.stream;
     const bool matrix = matrix_routing(h, nq, st);
     if (matrix && !settled_routing(h)) {
-        // matrix-core routing; small batches cut the centroid range into slices and merge them
-        const int slices = routing_slices(h, nq, ws.routing_room);
+        // matrix-core routing; small batches cut the centroid range into slices and merge them, if there is room for that
+        int slices = routing_slices(h, nq, ws.routing_room);
         uint64_t* partial = nullptr;
         if (slices > 1) {
             hipError_t e;
             partial = static_cast<uint64_t*>(ws.take(sizeof(uint64_t) * (size_t)nq * slices * h->d.route_c, &e));
-            if (!partial) return fail(ANN_ENOMEM, "ann_route: no scratch memory for %d centroid slices: %s", slices, hipGetErrorString(e));
+            if (!partial) slices = 1;
         }
         const uint8_t* cen = static_cast<const uint8_t*>(h->d.centroids);
         const uint8_t* qs = static_cast<const uint8_t*>(queries);
@@ -659,7 +677,6 @@ int route_impl(ann_index_t* h, const void* queries, int64_t nq, int32_t* out_clu
     if (matrix && settled_routing(h) && listed_bytes(h, nq) <= ws.routing_room) {
         hipError_t e;
         words = static_cast<uint64_t*>(ws.take(listed_bytes(h, nq), &e));
-        if (!words) (void)hipGetLastError();
     }
     const int64_t most = words ? kListedQueries : kMaxQueriesPerLaunch;
     for (int64_t q0 = 0; q0 < nq; q0 += most) {
@@ -696,7 +713,7 @@ extern "C" int ann_route(ann_index_t* h, const void* queries, int64_t nq, int32_
     if (nq == 0) return ANN_OK;
     if (!queries || !out_clusters) return fail(ANN_EINVAL, "ann_route: null argument");
     if (!aligned16(queries)) return fail(ANN_EINVAL, "ann_route: queries not 16-byte aligned");
-    Workspace ws(static_cast<hipStream_t>(stream), route_scratch_bytes(h, nq, static_cast<hipStream_t>(stream)));
+    Workspace ws(static_cast<hipStream_t>(stream), route_scratch_bytes(h, nq, static_cast<hipStream_t>(stream)), 0);
     return route_impl(h, queries, nq, out_clusters, ws);
 }
 
@@ -853,8 +870,7 @@ void search_by_clusters(const ann_index_t* h, int64_t nq, int itopk, int width, 
 // Checks the arguments of a search and launches it; `route` is null for uniform entries.
 int search_impl(ann_index_t* h, const void* queries, int64_t nq, const int32_t* route, bool route_given, int k,
                 int itopk, int width, int max_iters, int32_t* out_ids, void* out_dists, int32_t* out_counters,
-                Workspace& ws, const Way& way) {
-    const int stride = way.table_stride;
+                Workspace& ws, Way way) {
     hipStream_t stream = ws.stream;
     if (nq < 0) return fail(ANN_EINVAL, "ann_search: nq = %lld", (long long)nq);
     if (k < 1 || k > itopk) return fail(ANN_EINVAL, "ann_search: k = %d outside 1..itopk (%d)", k, itopk);
@@ -881,10 +897,16 @@ int search_impl(ann_index_t* h, const void* queries, int64_t nq, const int32_t* 
     if (grouped_order(h, nq, way)) {
         hipError_t e;
         order = static_cast<int32_t*>(ws.take(sizeof(int32_t) * ((size_t)nq + h->d.n_clusters), &e));
-        if (!order) return fail(ANN_ENOMEM, "ann_search: no scratch memory for the execution order: %s", hipGetErrorString(e));
-        e = launch_cluster_order(route, h->d.route_c, nq, h->d.n_clusters, order + nq, order, stream);
-        if (e != hipSuccess) return fail(ANN_EHIP, "ann_search: launching the execution-order kernels failed: %s", hipGetErrorString(e));
+        if (order) {
+            e = launch_cluster_order(route, h->d.route_c, nq, h->d.n_clusters, order + nq, order, stream);
+            if (e != hipSuccess) return fail(ANN_EHIP, "ann_search: launching the execution-order kernels failed: %s", hipGetErrorString(e));
+        } else if (grouped_order(h, nq, Way())) {
+            return fail(ANN_ENOMEM, "ann_search: no scratch memory for the execution order: %s", hipGetErrorString(e));
+        } else {
+            way = Way();  // which alone wanted the order: gather
+        }
     }
+    const int stride = way.table_stride;
     int64_t per_launch = kMaxQueriesPerLaunch;
     TableBlocks::Block* block = nullptr;
     if (stride > 0 && order) {
@@ -1005,7 +1027,8 @@ extern "C" int ann_search_counters(ann_index_t* h, const void* queries, int64_t 
                                    void* stream) {
     if (!h || h->magic != kMagic) return fail(ANN_EINVAL, "ann_search: not a live handle");
     const Way way = choose_way(h, nq, itopk, width, max_iters, static_cast<hipStream_t>(stream));
-    Workspace ws(static_cast<hipStream_t>(stream), search_scratch_bytes(h, nq, false, way, static_cast<hipStream_t>(stream)));
+    Workspace ws(static_cast<hipStream_t>(stream), search_scratch_bytes(h, nq, false, way, static_cast<hipStream_t>(stream)),
+                 search_scratch_needed(h, nq, false));
     return search_impl(h, queries, nq, nullptr, false, k, itopk, width, max_iters, out_ids, out_dists, out_counters, ws, way);
 }
 
@@ -1014,7 +1037,8 @@ extern "C" int ann_search_routed(ann_index_t* h, const void* queries, int64_t nq
                                  int32_t* out_counters, void* stream) {
     if (!h || h->magic != kMagic) return fail(ANN_EINVAL, "ann_search_routed: not a live handle");
     const Way way = choose_way(h, nq, itopk, width, max_iters, static_cast<hipStream_t>(stream));
-    Workspace ws(static_cast<hipStream_t>(stream), search_scratch_bytes(h, nq, true, way, static_cast<hipStream_t>(stream)));
+    Workspace ws(static_cast<hipStream_t>(stream), search_scratch_bytes(h, nq, true, way, static_cast<hipStream_t>(stream)),
+                 search_scratch_needed(h, nq, true));
     return search_impl(h, queries, nq, routes, true, k, itopk, width, max_iters, out_ids, out_dists, out_counters, ws, way);
 }
 

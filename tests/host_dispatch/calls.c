@@ -1,0 +1,189 @@
+/* Which kernels libann launches, and on what memory, without a GPU: the HIP functions that it calls are defined here (the program's
+ * symbols come before those of the HIP runtime).  Kernels do not run; their names are noted.  Device memory is host memory whose
+ * ranges are remembered.  argv[1] names the scenario. */
+#define __HIP_PLATFORM_AMD__ 1
+#include <hip/hip_runtime_api.h>
+#include <stdio.h>
+#include <stdlib.h>
+#include <string.h>
+
+#include "ann.h"
+
+/* ---- the runtime ---- */
+#define MAX 4096
+static struct { const void* host; const char* name; } kernels[MAX];
+static int n_kernels;
+static struct { char* at; size_t bytes; } ranges[MAX];
+static int n_ranges;
+static size_t async_limit = (size_t)1 << 40; /* hipMallocAsync refuses more */
+static char launched[1 << 16];
+static int host_reads; /* copies from memory that is no device memory */
+static struct { dim3 grid, block; size_t lds; hipStream_t stream; } config;
+static uint32_t sample_result[3]; /* what the kernel that looks at a sample of an index finds: edges, leaving, far */
+static int sampled, default_stream_free = 1;
+
+static int find(const void* p) {
+    for (int i = 0; i < n_ranges; ++i)
+        if ((const char*)p >= ranges[i].at && (const char*)p < ranges[i].at + ranges[i].bytes) return i;
+    return -1;
+}
+static void* device(size_t bytes) {
+    void* p = aligned_alloc(256, (bytes + 255) / 256 * 256);
+    memset(p, 0, bytes);
+    ranges[n_ranges].at = p;
+    ranges[n_ranges++].bytes = bytes;
+    return p;
+}
+static void release(void* p) {
+    const int i = find(p);
+    if (i < 0) return;
+    free(ranges[i].at);
+    ranges[i] = ranges[--n_ranges];
+}
+
+void** __hipRegisterFatBinary(const void* d) { (void)d; static void* m; return &m; }
+void __hipUnregisterFatBinary(void** m) { (void)m; }
+void __hipRegisterFunction(void** m, const void* host, char* dev, const char* name, unsigned limit, void* t, void* b, dim3* bd, dim3* gd, int* w) {
+    (void)m, (void)dev, (void)limit, (void)t, (void)b, (void)bd, (void)gd, (void)w;
+    kernels[n_kernels].host = host;
+    kernels[n_kernels++].name = name;
+}
+void __hipRegisterVar(void** m, void* var, char* h, char* d, int ext, size_t size, int c, int g) {
+    (void)m, (void)var, (void)h, (void)d, (void)ext, (void)size, (void)c, (void)g;
+}
+hipError_t __hipPushCallConfiguration(dim3 grid, dim3 block, size_t lds, hipStream_t s) {
+    config.grid = grid, config.block = block, config.lds = lds, config.stream = s;
+    return hipSuccess;
+}
+hipError_t __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* lds, hipStream_t* s) {
+    *grid = config.grid, *block = config.block, *lds = config.lds, *s = config.stream;
+    return hipSuccess;
+}
+hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3 block, void** args, size_t lds, hipStream_t s) {
+    (void)grid, (void)block, (void)lds, (void)s;
+    for (int i = 0; i < n_kernels; ++i) {
+        if (kernels[i].host != f) continue;
+        strcat(launched, kernels[i].name);
+        strcat(launched, " ");
+        if (strstr(kernels[i].name, "sample_clusters_kernel")) {
+            sampled = 1;
+            uint32_t* counts = *(uint32_t**)args[3];
+            memcpy(counts, sample_result, sizeof(uint32_t) * 3);
+        }
+    }
+    return hipSuccess;
+}
+hipError_t hipMalloc(void** p, size_t bytes) { *p = device(bytes); return hipSuccess; }
+hipError_t hipFree(void* p) { release(p); return hipSuccess; }
+hipError_t hipMallocAsync(void** p, size_t bytes, hipStream_t s) {
+    (void)s;
+    *p = NULL;
+    if (bytes > async_limit) return hipErrorOutOfMemory;
+    *p = device(bytes);
+    return hipSuccess;
+}
+hipError_t hipFreeAsync(void* p, hipStream_t s) { (void)s; release(p); return hipSuccess; }
+hipError_t hipMemcpy(void* d, const void* s, size_t bytes, hipMemcpyKind k) {
+    if (k == hipMemcpyDeviceToHost && find(s) < 0) {
+        ++host_reads;
+        return hipErrorInvalidValue;
+    }
+    memcpy(d, s, bytes);
+    return hipSuccess;
+}
+hipError_t hipPointerGetAttributes(hipPointerAttribute_t* a, const void* p) {
+    memset(a, 0, sizeof(*a));
+    a->type = find(p) >= 0 ? hipMemoryTypeDevice : hipMemoryTypeUnregistered;
+    return hipSuccess;
+}
+hipError_t hipMemGetAddressRange(hipDeviceptr_t* base, size_t* size, hipDeviceptr_t p) {
+    const int i = find(p);
+    if (i < 0) return hipErrorInvalidValue;
+    *base = ranges[i].at, *size = ranges[i].bytes;
+    return hipSuccess;
+}
+hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus* c) {
+    *c = hipStreamCaptureStatusNone;
+    return s || default_stream_free ? hipSuccess : hipErrorStreamCaptureImplicit;
+}
+hipError_t hipThreadExchangeStreamCaptureMode(hipStreamCaptureMode* m) { (void)m; return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t s) { (void)s; return hipSuccess; }
+hipError_t hipDeviceSynchronize(void) { return hipSuccess; }
+hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
+hipError_t hipGetLastError(void) { return hipSuccess; }
+const char* hipGetErrorString(hipError_t e) { (void)e; return "an error"; }
+hipError_t hipGetSymbolAddress(void** p, const void* s) { (void)s; static void* at; if (!at) at = device(ANN_STATIC_SCRATCH_BYTES); *p = at; return hipSuccess; }
+hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned f) { (void)f; *e = (hipEvent_t)1; return hipSuccess; }
+hipError_t hipEventDestroy(hipEvent_t e) { (void)e; return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) { (void)e, (void)s; return hipSuccess; }
+hipError_t hipEventQuery(hipEvent_t e) { (void)e; return hipSuccess; }
+hipError_t hipEventSynchronize(hipEvent_t e) { (void)e; return hipSuccess; }
+hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned f) { (void)s, (void)e, (void)f; return hipSuccess; }
+
+/* ---- scenarios ---- */
+#define CHECK(x) do { if (!(x)) { printf("line %d: %s (%s) after: %s\n", __LINE__, #x, ann_last_error(), launched); exit(1); } } while (0)
+static int ran(const char* name) { return strstr(launched, name) != NULL; }
+
+/* An index of n_clusters clusters of `mean` rows over device memory. */
+static ann_index_desc_t index_of(int dtype, int dim, int mean, int n_clusters, int degree, int route_c) {
+    const int size = dtype == ANN_U8 ? 1 : dtype == ANN_F16 ? 2 : 4;
+    ann_index_desc_t d;
+    memset(&d, 0, sizeof(d));
+    d.n = (int64_t)mean * n_clusters;
+    d.dim = dim, d.dtype = dtype, d.row_stride_bytes = (int64_t)dim * size, d.metric = ANN_L2;
+    d.vectors = device((size_t)d.n * d.row_stride_bytes);
+    d.graph = device((size_t)d.n * degree * 4);
+    d.degree = degree, d.n_entry = 32, d.entry_mode = ANN_ENTRY_ROUTED, d.seed = 1;
+    d.centroids = device((size_t)n_clusters * dim * size);
+    int64_t* off = device(((size_t)n_clusters + 1) * 8);
+    for (int c = 0; c <= n_clusters; ++c) off[c] = (int64_t)c * mean;
+    d.cluster_offsets = off, d.n_clusters = n_clusters, d.route_c = route_c;
+    return d;
+}
+static ann_index_t* load(const ann_index_desc_t* d) {
+    ann_index_t* h = NULL;
+    CHECK(ann_index_load(d, &h) == ANN_OK && h);
+    return h;
+}
+
+/* What a way of searching or routing wants of scratch memory, and the call can do without, is no reason to refuse the call. */
+static void scratch(void) {
+    sample_result[0] = 1 << 20; /* edges, all within their clusters */
+    ann_index_desc_t d = index_of(ANN_U8, 128, 500, 100, 32, 1);
+    ann_index_t* h = load(&d);
+    const int nq = 2000;
+    void* q = device(nq * 128);
+    int32_t *routes = device(nq * 4), *ids = device(nq * 40), *keys = device(nq * 40);
+    launched[0] = 0;
+    CHECK(ann_search_routed(h, q, nq, routes, 10, 184, 4, 100, ids, keys, NULL, NULL) == ANN_OK && ran("cluster_search_kernel") && ran("cluster_order_kernel"));
+    async_limit = 0;
+    launched[0] = 0;
+    CHECK(ann_search_routed(h, q, nq, routes, 10, 184, 4, 100, ids, keys, NULL, NULL) == ANN_OK && ran("beam_search_kernel") && !ran("cluster_"));
+    CHECK(ann_route(h, q, nq, routes, NULL) == ANN_OK);
+    CHECK(ann_search(h, q, nq, 10, 184, 4, 100, ids, keys, NULL) == ANN_ENOMEM); /* no room for the routes */
+    async_limit = nq * 4 + 255;                                                 /* room for the routes */
+    launched[0] = 0;
+    CHECK(ann_search(h, q, nq, 10, 184, 4, 100, ids, keys, NULL) == ANN_OK && ran("beam_search_kernel") && !ran("cluster_"));
+    ann_free(h);
+    /* rows of an odd multiple of 16 bytes: slices (uint8) and lists (float) */
+    const int types[3] = {ANN_U8, ANN_F16, ANN_F32}, dims[3] = {144, 200, 100};
+    for (int t = 0; t < 3; ++t) {
+        d = index_of(types[t], dims[t], 50, 2000, 16, 2);
+        h = load(&d);
+        void* x = device((size_t)nq * 400);
+        for (int room = 0; room < 2; ++room) {
+            async_limit = room ? nq * 8 + 255 : 0;
+            CHECK(ann_route(h, x, nq, routes = device(nq * 8), NULL) == ANN_OK);
+            CHECK(ann_search(h, x, nq, 10, 64, 2, 100, ids, keys, NULL) == (room ? ANN_OK : ANN_ENOMEM));
+        }
+        ann_free(h);
+    }
+}
+
+int main(int argc, char** argv) {
+    const char* what = argc > 1 ? argv[1] : "";
+    if (!strcmp(what, "scratch")) scratch();
+    else return 2;
+    printf("%s ok\n", what);
+    return 0;
+}
