@@ -81,10 +81,12 @@ typedef struct {
  * Validates `desc`, chooses the kernel variant and returns a handle.
  * The borrowed arrays are not copied, but for what the routing keeps of the centroids: for a routed
  * index a small device array (4 bytes per cluster; for rows of an odd multiple of 16 bytes only if
- * the centroids are known to be device memory and there is room, else they are routed without; for 128-byte
+ * the centroids are known to be device memory and there is room, and not while a stream is captured that the default stream waits for,
+ * else they are routed without; for 128-byte
  * uint8 rows about 140, the centroids in the order the routing reads them) is allocated and filled on the
  * default stream, which is synchronised before returning; with route_c == 1, for float rows of 256 bytes and more and uint8
- * rows of at most 256, cluster_offsets is read back on that stream, and for the latter a sample of graph rows and vectors is
+ * rows of at most 256, cluster_offsets is read back on that stream, and for the latter, where all three arrays are known to be whole in
+ * device memory, a sample of graph rows and vectors is
  * looked at (12 bytes of device memory until the call returns); nothing else touches the device.
  * Must be called with the device that owns the arrays current.
  * Errors: ANN_EINVAL, ANN_EUNSUPPORTED, ANN_ENOMEM, ANN_EHIP.

@@ -258,10 +258,23 @@ static __global__ void __launch_bounds__(64) sample_clusters_kernel(ann_index_de
     }
 }
 
-// Whether HIP knows the address as device memory; clears the error if it does not.
-static bool on_device(const void* p) {
+// Whether HIP knows these bytes as device memory; clears the error if it does not.
+static bool on_device(const void* p, size_t bytes) {
     hipPointerAttribute_t a;
-    if (hipPointerGetAttributes(&a, p) == hipSuccess) return a.type == hipMemoryTypeDevice;
+    hipDeviceptr_t base = nullptr;
+    size_t size = 0;
+    if (hipPointerGetAttributes(&a, p) == hipSuccess && a.type == hipMemoryTypeDevice &&
+        hipMemGetAddressRange(&base, &size, const_cast<void*>(p)) == hipSuccess)
+        return bytes <= size && (size_t)(static_cast<const char*>(p) - static_cast<const char*>(base)) <= size - bytes;
+    (void)hipGetLastError();
+    return false;
+}
+
+// A captured call keeps to what it would have allocated for a search that gathers rows.  (Nor does the default stream, asked for as
+// null, take work while another stream that waits for it is being captured.)
+static bool may_allocate_more(hipStream_t stream) {
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &capture) == hipSuccess) return capture == hipStreamCaptureStatusNone;
     (void)hipGetLastError();
     return false;
 }
@@ -381,10 +394,13 @@ extern "C" int ann_index_load(const ann_index_desc_t* desc, ann_index_t** out_ha
     h->longest_cluster = d.n;
     h->by_clusters = false;
     const bool mfma_route = d.entry_mode == ANN_ENTRY_ROUTED;
-    // Rows of an odd multiple of 16 bytes can do without (matrix_routing): no memory, or centroids that are not known to be on a
-    // device, are no reason to refuse them, and nothing is read then.
+    // Rows of an odd multiple of 16 bytes can do without (matrix_routing): no memory, centroids that are not known to be on a
+    // device, or a default stream that takes no work because of another one's capture, are no reason to refuse them, and nothing
+    // is read then.
     const bool needed = row_bytes % 32 == 0;
-    if (mfma_route && !(d.dtype == ANN_U8 && d.dim == 128) && (needed || on_device(d.centroids))) {
+    RelaxedCapture relaxed;
+    if (mfma_route && !(d.dtype == ANN_U8 && d.dim == 128) &&
+        (needed || (on_device(d.centroids, (size_t)d.n_clusters * row_bytes) && may_allocate_more(nullptr)))) {
         hipError_t e = hipMalloc(&h->route_bias, route_mfma_bias_bytes(d.n_clusters));
         if (e == hipSuccess)
             e = launch_route_bias(d.dtype, d.metric, static_cast<const uint8_t*>(d.centroids), d.n_clusters,
@@ -416,7 +432,11 @@ extern "C" int ann_index_load(const ann_index_desc_t* desc, ann_index_t** out_ha
         }
     }
     if (may_use_table(h)) find_longest_cluster(h);
-    if (d.entry_mode == ANN_ENTRY_ROUTED && d.route_c == 1 && d.dtype == ANN_U8 && row_bytes <= kMaxClusterRowBytes) {
+    // A search by whole clusters is a choice: arrays that are not known to be in place on a device (a handle that only routes may have
+    // stand-ins) are not looked at, and are searched by gathering.
+    if (d.entry_mode == ANN_ENTRY_ROUTED && d.route_c == 1 && d.dtype == ANN_U8 && row_bytes <= kMaxClusterRowBytes &&
+        on_device(d.vectors, (size_t)(d.n - 1) * d.row_stride_bytes + row_bytes) && on_device(d.graph, (size_t)d.n * d.degree * sizeof(int32_t)) &&
+        on_device(d.cluster_offsets, ((size_t)d.n_clusters + 1) * sizeof(int64_t)) && may_allocate_more(nullptr)) {
         find_longest_cluster(h);
         if (h->longest_cluster <= kMaxClusterRows) h->by_clusters = clusters_hold_searches(h);
     }
@@ -579,14 +599,6 @@ int routing_slices(const ann_index_t* h, int64_t nq, size_t room) {
     if (slices <= 1) return 1;
     const size_t most = room / (sizeof(uint64_t) * (size_t)nq * h->d.route_c);
     return most >= (size_t)slices ? slices : most > 1 ? (int)most : 1;
-}
-
-// A captured call keeps to what it would have allocated for a search that gathers rows.
-bool may_allocate_more(hipStream_t stream) {
-    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(stream, &capture) == hipSuccess) return capture == hipStreamCaptureStatusNone;
-    (void)hipGetLastError();
-    return false;
 }
 
 // Whether nq queries are routed on the matrix cores.  Rows of a multiple of 32 bytes always are.  For the others that takes

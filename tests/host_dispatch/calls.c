@@ -180,9 +180,40 @@ static void scratch(void) {
     }
 }
 
+/* A handle of routed uint8 rows is loaded over arrays that are not, or not whole, in device memory; nothing of them is read. */
+static void stand_ins(void) {
+    const int dims[2] = {128, 144};
+    for (int t = 0; t < 2; ++t) {
+        for (int which = 0; which < 6; ++which) {
+            ann_index_desc_t d = index_of(ANN_U8, dims[t], 500, 100, 32, 1);
+            if (which == 0) d.vectors = aligned_alloc(256, 1 << 20);
+            if (which == 1) d.graph = aligned_alloc(256, 1 << 20);
+            if (which == 2) d.cluster_offsets = aligned_alloc(256, 1 << 20);
+            if (which == 3) d.vectors = device((size_t)d.n * dims[t] - 256);
+            if (which == 4) d.graph = device((size_t)d.n * 32 * 4 - 256);
+            if (which == 5) default_stream_free = 0; /* another stream is being captured */
+            sampled = host_reads = 0;
+            ann_index_t* h = load(&d);
+            CHECK(!sampled && !host_reads);
+            default_stream_free = 1;
+            ann_free(h);
+        }
+        ann_index_desc_t d = index_of(ANN_U8, dims[t], 500, 100, 32, 1);
+        sampled = 0;
+        ann_free(load(&d));
+        CHECK(sampled);
+    }
+    ann_index_desc_t d = index_of(ANN_F32, 100, 500, 100, 32, 1);
+    default_stream_free = 0;
+    launched[0] = 0;
+    ann_free(load(&d));
+    CHECK(!launched[0]);
+}
+
 int main(int argc, char** argv) {
     const char* what = argc > 1 ? argv[1] : "";
     if (!strcmp(what, "scratch")) scratch();
+    else if (!strcmp(what, "stand_ins")) stand_ins();
     else return 2;
     printf("%s ok\n", what);
     return 0;
