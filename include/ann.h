@@ -87,7 +87,7 @@ typedef struct {
  * default stream, which is synchronised before returning; with route_c == 1, for float rows of 256 bytes and more and uint8
  * rows of at most 256, cluster_offsets is read back on that stream, and for the latter, where all three arrays are known to be whole in
  * device memory, a sample of graph rows and vectors is
- * looked at (12 bytes of device memory until the call returns); nothing else touches the device.
+ * looked at; nothing else touches the device.
  * Must be called with the device that owns the arrays current.
  * Errors: ANN_EINVAL, ANN_EUNSUPPORTED, ANN_ENOMEM, ANN_EHIP.
  */

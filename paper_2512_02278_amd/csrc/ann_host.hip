@@ -215,14 +215,33 @@ static const RowVariant* pick_variant(int dtype, int metric, int64_t row_bytes, 
 constexpr int kMaxClusterRowBytes = 256, kSampledClusters = 256;
 constexpr float kMostNormRatio = 8.0f;  // largest |c|^2 to their mean
 
-// A workgroup looks at one row of a cluster and 64 others: counts[0] and [1] get its graph edges and those that leave the cluster,
-// counts[2] the others whose keys are too far above the smallest of them for a word of cluster_search.h.
-static __global__ void __launch_bounds__(64) sample_clusters_kernel(ann_index_desc_t d, int row_bytes, int longest, uint32_t* counts) {
+// What ann_index_load finds out about an index whose clusters may be searched whole (DEVICE, behind what the routing keeps).
+struct ClusterSample {
+    unsigned long long longest;  // rows of the longest cluster
+    uint32_t edges, leaving;     // sampled graph edges, and those of them that leave the cluster
+    uint32_t far, unused;        // sampled rows whose keys are too far above the smallest for a word of cluster_search.h
+};
+
+// One workgroup: the longest cluster, and zeros for what sample_clusters_kernel adds up.
+static __global__ void __launch_bounds__(1024) longest_cluster_kernel(const int64_t* off, int n_clusters, ClusterSample* out) {
+    __shared__ unsigned long long longest;
+    if (threadIdx.x == 0) longest = 0;
+    __syncthreads();
+    int64_t most = 0;
+    for (int c = (int)threadIdx.x; c < n_clusters; c += 1024) most = max(most, off[c + 1] - off[c]);
+    atomicMax(&longest, (unsigned long long)most);
+    __syncthreads();
+    if (threadIdx.x == 0) *out = ClusterSample{longest, 0u, 0u, 0u, 0u};
+}
+
+// A workgroup looks at one row of a cluster and 64 others.
+static __global__ void __launch_bounds__(64) sample_clusters_kernel(ann_index_desc_t d, int row_bytes, ClusterSample* sample) {
     const int lane = lane_id();
     const int64_t c = (int64_t)blockIdx.x * d.n_clusters / kSampledClusters;
     const int64_t* const off = static_cast<const int64_t*>(d.cluster_offsets);
+    const unsigned long long longest = sample->longest;
     const int64_t lo = off[c] < 0 ? 0 : off[c], hi = off[c + 1] > d.n ? d.n : off[c + 1];
-    if (hi <= lo) return;
+    if (hi <= lo || longest > (unsigned long long)kMaxClusterRows) return;
     const int64_t size = hi - lo;
     const int64_t row = lo + (int64_t)((blockIdx.x * 0x9E3779B1u) % (uint64_t)size);
     uint32_t edges = 0, out = 0;
@@ -252,9 +271,9 @@ static __global__ void __launch_bounds__(64) sample_clusters_kernel(ann_index_de
     const int sh = 1 + (longest > 1 ? 32 - __builtin_clz((uint32_t)longest - 1u) : 1);
     const uint64_t far = __ballot(key > least && key - least >= (0xffffffffu >> sh));
     if (lane == 0) {
-        atomicAdd(&counts[0], edges);
-        atomicAdd(&counts[1], out);
-        atomicAdd(&counts[2], (uint32_t)__builtin_popcountll(far));
+        atomicAdd(&sample->edges, edges);
+        atomicAdd(&sample->leaving, out);
+        atomicAdd(&sample->far, (uint32_t)__builtin_popcountll(far));
     }
 }
 
@@ -268,6 +287,13 @@ static bool on_device(const void* p, size_t bytes) {
         return bytes <= size && (size_t)(static_cast<const char*>(p) - static_cast<const char*>(base)) <= size - bytes;
     (void)hipGetLastError();
     return false;
+}
+
+static size_t padded256(size_t n) { return (n + 255) / 256 * 256; }
+
+// Where a handle's ClusterSample is: behind the routing's block of `bytes`.
+static ClusterSample* sample_behind(void* block, size_t bytes) {
+    return reinterpret_cast<ClusterSample*>(static_cast<char*>(block) + padded256(bytes));
 }
 
 // A captured call keeps to what it would have allocated for a search that gathers rows.  (Nor does the default stream, asked for as
@@ -322,26 +348,20 @@ hipError_t norms_allow_listing(const ann_index_t* h, bool* allow) {
     return e;
 }
 
-// Whether searches by whole clusters can be expected to end in them.  A query meets some two hundred rows before its list is
-// full, and an edge that leaves the cluster at any time: of the sampled edges at most one in 1 024 may leave, of the sampled keys one in 4 096 may
-// be too far.  (A query that has to be searched anew costs both searches.)
-bool clusters_hold_searches(const ann_index_t* h) {
-    RelaxedCapture relaxed;
-    uint32_t* counts = nullptr;
-    uint32_t got[3] = {0, 0, 0};
-    hipError_t e = hipMalloc(&counts, sizeof(got));
-    if (e == hipSuccess) e = hipMemcpy(counts, got, sizeof(got), hipMemcpyHostToDevice);
-    if (e == hipSuccess) {
-        hipLaunchKernelGGL(sample_clusters_kernel, dim3(kSampledClusters), dim3(64), 0, nullptr, h->d, h->row_bytes, (int)h->longest_cluster, counts);
-        e = hipGetLastError();
-    }
-    if (e == hipSuccess) e = hipMemcpy(got, counts, sizeof(got), hipMemcpyDeviceToHost);
-    if (counts) (void)hipFree(counts);
-    if (e != hipSuccess) {
-        (void)hipGetLastError();
-        return false;
-    }
-    return got[1] <= got[0] / 1024 && got[2] <= 64 * kSampledClusters / 4096;
+// The longest cluster, and whether searches by whole clusters can be expected to end in them.  A query meets some two hundred rows
+// before its list is full, and an edge that leaves the cluster at any time: of the sampled edges at most one in 1 024 may leave, of the
+// sampled keys one in 4 096 may be too far.  (A query that has to be searched anew costs both searches.)  `sample`: DEVICE memory of
+// the handle.  Waits for the default stream.
+hipError_t look_at_clusters(ann_index_t* h, ClusterSample* sample) {
+    hipLaunchKernelGGL(longest_cluster_kernel, dim3(1), dim3(1024), 0, nullptr, static_cast<const int64_t*>(h->d.cluster_offsets), h->d.n_clusters, sample);
+    hipLaunchKernelGGL(sample_clusters_kernel, dim3(kSampledClusters), dim3(64), 0, nullptr, h->d, h->row_bytes, sample);
+    ClusterSample got;
+    hipError_t e = hipGetLastError();
+    if (e == hipSuccess) e = hipMemcpy(&got, sample, sizeof(got), hipMemcpyDeviceToHost);
+    if (e != hipSuccess) return e;
+    h->longest_cluster = (int64_t)got.longest;
+    h->by_clusters = got.longest <= (unsigned long long)kMaxClusterRows && got.leaving <= got.edges / 1024 && got.far <= 64 * kSampledClusters / 4096;
+    return hipSuccess;
 }
 
 }  // namespace
@@ -394,6 +414,13 @@ extern "C" int ann_index_load(const ann_index_desc_t* desc, ann_index_t** out_ha
     h->longest_cluster = d.n;
     h->by_clusters = false;
     const bool mfma_route = d.entry_mode == ANN_ENTRY_ROUTED;
+    // A search by whole clusters is a choice: arrays that are not known to be in place on a device (a handle that only routes may have
+    // stand-ins) are not looked at, and are searched by gathering.  Loading an index of 10 000 rows takes 40 us with that look, 22
+    // without; with the offsets read back, an allocation of its own and two more copies it took 79.
+    const bool look = mfma_route && d.route_c == 1 && d.dtype == ANN_U8 && row_bytes <= kMaxClusterRowBytes &&
+                      on_device(d.vectors, (size_t)(d.n - 1) * d.row_stride_bytes + row_bytes) &&
+                      on_device(d.graph, (size_t)d.n * d.degree * sizeof(int32_t)) &&
+                      on_device(d.cluster_offsets, ((size_t)d.n_clusters + 1) * sizeof(int64_t)) && may_allocate_more(nullptr);
     // Rows of an odd multiple of 16 bytes can do without (matrix_routing): no memory, centroids that are not known to be on a
     // device, or a default stream that takes no work because of another one's capture, are no reason to refuse them, and nothing
     // is read then.
@@ -401,12 +428,13 @@ extern "C" int ann_index_load(const ann_index_desc_t* desc, ann_index_t** out_ha
     RelaxedCapture relaxed;
     if (mfma_route && !(d.dtype == ANN_U8 && d.dim == 128) &&
         (needed || (on_device(d.centroids, (size_t)d.n_clusters * row_bytes) && may_allocate_more(nullptr)))) {
-        hipError_t e = hipMalloc(&h->route_bias, route_mfma_bias_bytes(d.n_clusters));
+        hipError_t e = hipMalloc(&h->route_bias, padded256(route_mfma_bias_bytes(d.n_clusters)) + sizeof(ClusterSample));
         if (e == hipSuccess)
             e = launch_route_bias(d.dtype, d.metric, static_cast<const uint8_t*>(d.centroids), d.n_clusters,
                                   (int)row_bytes, h->route_bias, nullptr);
         bool listing = true;
-        if (e == hipSuccess) e = settled_routing(h) ? norms_allow_listing(h, &listing) : hipStreamSynchronize(nullptr);
+        if (e == hipSuccess) e = look ? look_at_clusters(h, sample_behind(h->route_bias, route_mfma_bias_bytes(d.n_clusters)))
+                              : settled_routing(h) ? norms_allow_listing(h, &listing) : hipStreamSynchronize(nullptr);
         if (e != hipSuccess || !listing) {
             if (h->route_bias) (void)hipFree(h->route_bias);
             h->route_bias = nullptr;
@@ -420,10 +448,10 @@ extern "C" int ann_index_load(const ann_index_desc_t* desc, ann_index_t** out_ha
     }
     if (mfma_route && d.dtype == ANN_U8 && d.dim == 128) {
         // routing runs on the matrix cores; what it reads of the centroids is laid out once, here
-        hipError_t e = hipMalloc(&h->centroid_bias, RouteU8Block(d.n_clusters).bytes);
+        hipError_t e = hipMalloc(&h->centroid_bias, padded256(RouteU8Block(d.n_clusters).bytes) + sizeof(ClusterSample));
         if (e == hipSuccess)
             e = launch_route_u8_block(d.metric, static_cast<const uint8_t*>(d.centroids), d.n_clusters, h->centroid_bias, nullptr);
-        if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
+        if (e == hipSuccess) e = look ? look_at_clusters(h, sample_behind(h->centroid_bias, RouteU8Block(d.n_clusters).bytes)) : hipStreamSynchronize(nullptr);
         if (e != hipSuccess) {
             if (h->centroid_bias) (void)hipFree(h->centroid_bias);
             delete h;
@@ -432,14 +460,6 @@ extern "C" int ann_index_load(const ann_index_desc_t* desc, ann_index_t** out_ha
         }
     }
     if (may_use_table(h)) find_longest_cluster(h);
-    // A search by whole clusters is a choice: arrays that are not known to be in place on a device (a handle that only routes may have
-    // stand-ins) are not looked at, and are searched by gathering.
-    if (d.entry_mode == ANN_ENTRY_ROUTED && d.route_c == 1 && d.dtype == ANN_U8 && row_bytes <= kMaxClusterRowBytes &&
-        on_device(d.vectors, (size_t)(d.n - 1) * d.row_stride_bytes + row_bytes) && on_device(d.graph, (size_t)d.n * d.degree * sizeof(int32_t)) &&
-        on_device(d.cluster_offsets, ((size_t)d.n_clusters + 1) * sizeof(int64_t)) && may_allocate_more(nullptr)) {
-        find_longest_cluster(h);
-        if (h->longest_cluster <= kMaxClusterRows) h->by_clusters = clusters_hold_searches(h);
-    }
     *out_handle = h;
     return ANN_OK;
 }
@@ -589,8 +609,6 @@ struct Workspace {
         if (owned) (void)hipFreeAsync(base, stream);
     }
 };
-
-size_t padded256(size_t n) { return (n + 255) / 256 * 256; }
 
 // Slices of the centroid range the matrix-core routing of nq queries is cut into, with partial results of at most `room` bytes.
 int routing_slices(const ann_index_t* h, int64_t nq, size_t room) {

@@ -65,10 +65,17 @@ hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3 block, void** args, si
         if (kernels[i].host != f) continue;
         strcat(launched, kernels[i].name);
         strcat(launched, " ");
+        if (strstr(kernels[i].name, "longest_cluster_kernel")) {
+            const int64_t* off = *(const int64_t**)args[0];
+            uint64_t longest = 0;
+            for (int c = 0; c < *(int*)args[1]; ++c)
+                if ((uint64_t)(off[c + 1] - off[c]) > longest) longest = off[c + 1] - off[c];
+            memcpy(*(char**)args[2], &longest, sizeof(longest));
+        }
         if (strstr(kernels[i].name, "sample_clusters_kernel")) {
             sampled = 1;
-            uint32_t* counts = *(uint32_t**)args[3];
-            memcpy(counts, sample_result, sizeof(uint32_t) * 3);
+            char* sample = *(char**)args[2]; /* rows of the longest cluster (8 bytes), then the counts */
+            memcpy(sample + 8, sample_result, sizeof(uint32_t) * 3);
         }
     }
     return hipSuccess;
