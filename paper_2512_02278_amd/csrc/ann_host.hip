@@ -196,7 +196,8 @@ struct ann_index {
     void* route_bias;        // DEVICE, owned: the same for the general matrix-core routing, or null
     ann::TableBlocks tables;  // DEVICE, owned: memory for key tables
     int64_t longest_cluster;  // rows of the longest cluster, or a bound on it
-    bool by_clusters;         // whether searches by whole clusters (cluster_search.h) can be expected to stay in them
+    bool by_clusters;         // whether searches by whole clusters (cluster_search.h) were looked at and fit
+    double leaving, far;      // shares of graph edges that leave their cluster, and of keys that are too far, if so
 };
 
 using namespace ann;
@@ -212,14 +213,15 @@ static const RowVariant* pick_variant(int dtype, int metric, int64_t row_bytes, 
     return best;
 }
 
-constexpr int kMaxClusterRowBytes = 256, kSampledClusters = 256;
+constexpr int kMaxClusterRowBytes = 256, kFarRows = 1024;
+constexpr int64_t kSampledEdges = 1ll << 24;
 constexpr float kMostNormRatio = 8.0f;  // largest |c|^2 to their mean
 
 // What ann_index_load finds out about an index whose clusters may be searched whole (DEVICE, behind what the routing keeps).
 struct ClusterSample {
     unsigned long long longest;  // rows of the longest cluster
-    uint32_t edges, leaving;     // sampled graph edges, and those of them that leave the cluster
-    uint32_t far, unused;        // sampled rows whose keys are too far above the smallest for a word of cluster_search.h
+    uint32_t leaving;            // sampled graph edges that leave the cluster
+    uint32_t far;                // sampled keys that are too far above the smallest for a word of cluster_search.h
 };
 
 // One workgroup: the longest cluster, and zeros for what sample_clusters_kernel adds up.
@@ -231,50 +233,77 @@ static __global__ void __launch_bounds__(1024) longest_cluster_kernel(const int6
     for (int c = (int)threadIdx.x; c < n_clusters; c += 1024) most = max(most, off[c + 1] - off[c]);
     atomicMax(&longest, (unsigned long long)most);
     __syncthreads();
-    if (threadIdx.x == 0) *out = ClusterSample{longest, 0u, 0u, 0u, 0u};
+    if (threadIdx.x == 0) *out = ClusterSample{longest, 0u, 0u};
 }
 
-// A workgroup looks at one row of a cluster and 64 others.
-static __global__ void __launch_bounds__(64) sample_clusters_kernel(ann_index_desc_t d, int row_bytes, ClusterSample* sample) {
+// A workgroup takes runs of 64 rows, `step` rows from start to start, and counts the graph edges that leave their cluster.  The first
+// kFarRows workgroups also look at the keys of 64 rows of a cluster as seen from another of its rows.
+static __global__ void __launch_bounds__(64) sample_clusters_kernel(ann_index_desc_t d, int row_bytes, int64_t runs, int64_t step, ClusterSample* sample) {
     const int lane = lane_id();
-    const int64_t c = (int64_t)blockIdx.x * d.n_clusters / kSampledClusters;
     const int64_t* const off = static_cast<const int64_t*>(d.cluster_offsets);
     const unsigned long long longest = sample->longest;
-    const int64_t lo = off[c] < 0 ? 0 : off[c], hi = off[c + 1] > d.n ? d.n : off[c + 1];
-    if (hi <= lo || longest > (unsigned long long)kMaxClusterRows) return;
-    const int64_t size = hi - lo;
-    const int64_t row = lo + (int64_t)((blockIdx.x * 0x9E3779B1u) % (uint64_t)size);
-    uint32_t edges = 0, out = 0;
-    for (int j = lane; j < d.degree; j += 64) {
-        const int32_t id = d.graph[row * d.degree + j];
-        const bool there = id >= 0 && (int64_t)id < d.n;
-        edges += there ? 1u : 0u;
-        out += there && ((int64_t)id < lo || (int64_t)id >= hi) ? 1u : 0u;
+    if (longest > (unsigned long long)kMaxClusterRows) return;
+    uint32_t leaving = 0;
+    for (int64_t run = blockIdx.x; run < runs; run += gridDim.x) {
+        const int64_t row = run * step + lane;
+        int at = 0, end = d.n_clusters;  // the last cluster that starts at or before the row
+        while (end - at > 1) {
+            const int mid = at + (end - at) / 2;
+            if (off[mid] <= row) at = mid;
+            else end = mid;
+        }
+        // the bounds of the row's cluster (a row of none: all ids)
+        int lo = 0, hi = (int)d.n;
+        if (row < d.n && off[at] <= row && row < off[at + 1] && off[at + 1] <= d.n) {
+            lo = off[at] < 0 ? 0 : (int)off[at];
+            hi = (int)off[at + 1];
+        }
+        const int32_t* const edges = d.graph + run * step * d.degree;
+        const int rows = d.n - run * step < 64 ? (int)(d.n - run * step) : 64;
+        int r = lane / d.degree, c = lane % d.degree;
+        const int over_r = 64 / d.degree, over_c = 64 % d.degree;
+        for (int i0 = 0; i0 < d.degree; i0 += 8) {
+            int32_t id[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int at_edge = (i0 + u) * 64 + lane;
+                id[u] = at_edge < rows * d.degree ? edges[at_edge] : -1;
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int from = __shfl(lo, r), to = __shfl(hi, r);  // (r is beyond 63 only past the last edge)
+                leaving += id[u] >= 0 && (int64_t)id[u] < d.n && (id[u] < from || id[u] >= to) ? 1u : 0u;
+                r += over_r;
+                c += over_c;
+                if (c >= d.degree) {
+                    c -= d.degree;
+                    ++r;
+                }
+            }
+        }
+        if (run >= kFarRows) continue;
+        lo = __builtin_amdgcn_readfirstlane(lo);
+        const int size = __builtin_amdgcn_readfirstlane(hi) - lo;
+        if (size > kMaxClusterRows) continue;  // a row of none
+        const int64_t other = lo + (int64_t)size * lane / 64;
+        const uint8_t* const vectors = static_cast<const uint8_t*>(d.vectors);
+        const uint32_t* const x = reinterpret_cast<const uint32_t*>(vectors + run * step * d.row_stride_bytes);
+        const uint32_t* const y = reinterpret_cast<const uint32_t*>(vectors + other * d.row_stride_bytes);
+        uint32_t xx = 0, xy = 0, yy = 0;
+        for (int i = 0; i < row_bytes / 4; ++i) {
+            xx = __builtin_amdgcn_udot4(x[i], x[i], xx, false);
+            xy = __builtin_amdgcn_udot4(x[i], y[i], xy, false);
+            yy = __builtin_amdgcn_udot4(y[i], y[i], yy, false);
+        }
+        const uint32_t key = d.metric == ANN_L2 ? xx + yy - 2u * xy : 0x80000000u - xy;
+        uint32_t least = other == run * step ? 0xffffffffu : key;
+        for (int s = 1; s < 64; s <<= 1) least = min(least, (uint32_t)__shfl_xor(least, s));
+        const int sh = 1 + (longest > 1 ? 32 - __builtin_clz((uint32_t)longest - 1u) : 1);
+        const uint64_t far = __ballot(key > least && key - least >= (0xffffffffu >> sh));
+        if (far && lane == 0) atomicAdd(&sample->far, (uint32_t)__builtin_popcountll(far));
     }
-    const int64_t other = lo + size * lane / 64;
-    const uint8_t* const vectors = static_cast<const uint8_t*>(d.vectors);
-    const uint32_t* const x = reinterpret_cast<const uint32_t*>(vectors + row * d.row_stride_bytes);
-    const uint32_t* const y = reinterpret_cast<const uint32_t*>(vectors + other * d.row_stride_bytes);
-    uint32_t xx = 0, xy = 0, yy = 0;
-    for (int i = 0; i < row_bytes / 4; ++i) {
-        xx = __builtin_amdgcn_udot4(x[i], x[i], xx, false);
-        xy = __builtin_amdgcn_udot4(x[i], y[i], xy, false);
-        yy = __builtin_amdgcn_udot4(y[i], y[i], yy, false);
-    }
-    const uint32_t key = d.metric == ANN_L2 ? xx + yy - 2u * xy : 0x80000000u - xy;
-    uint32_t least = other == row ? 0xffffffffu : key;
-    for (int s = 1; s < 64; s <<= 1) {
-        edges += __shfl_xor(edges, s);
-        out += __shfl_xor(out, s);
-        least = min(least, (uint32_t)__shfl_xor(least, s));
-    }
-    const int sh = 1 + (longest > 1 ? 32 - __builtin_clz((uint32_t)longest - 1u) : 1);
-    const uint64_t far = __ballot(key > least && key - least >= (0xffffffffu >> sh));
-    if (lane == 0) {
-        atomicAdd(&sample->edges, edges);
-        atomicAdd(&sample->leaving, out);
-        atomicAdd(&sample->far, (uint32_t)__builtin_popcountll(far));
-    }
+    for (int s = 1; s < 64; s <<= 1) leaving += __shfl_xor(leaving, s);
+    if (leaving && lane == 0) atomicAdd(&sample->leaving, leaving);
 }
 
 // Whether HIP knows these bytes as device memory; clears the error if it does not.
@@ -348,19 +377,21 @@ hipError_t norms_allow_listing(const ann_index_t* h, bool* allow) {
     return e;
 }
 
-// The longest cluster, and whether searches by whole clusters can be expected to end in them.  A query meets some two hundred rows
-// before its list is full, and an edge that leaves the cluster at any time: of the sampled edges at most one in 1 024 may leave, of the
-// sampled keys one in 4 096 may be too far.  (A query that has to be searched anew costs both searches.)  `sample`: DEVICE memory of
-// the handle.  Waits for the default stream.
+// The longest cluster, and how often searches by whole clusters cannot end in them.  `sample`: DEVICE memory of the handle.  Waits for
+// the default stream.
 hipError_t look_at_clusters(ann_index_t* h, ClusterSample* sample) {
+    const int64_t most = kSampledEdges / (64 * (int64_t)h->d.degree), all = (h->d.n + 63) / 64;
+    const int64_t runs = all <= most ? all : most, step = all <= most ? 64 : h->d.n / runs;
     hipLaunchKernelGGL(longest_cluster_kernel, dim3(1), dim3(1024), 0, nullptr, static_cast<const int64_t*>(h->d.cluster_offsets), h->d.n_clusters, sample);
-    hipLaunchKernelGGL(sample_clusters_kernel, dim3(kSampledClusters), dim3(64), 0, nullptr, h->d, h->row_bytes, sample);
+    hipLaunchKernelGGL(sample_clusters_kernel, dim3((unsigned)(runs < 8192 ? runs : 8192)), dim3(64), 0, nullptr, h->d, h->row_bytes, runs, step, sample);
     ClusterSample got;
     hipError_t e = hipGetLastError();
     if (e == hipSuccess) e = hipMemcpy(&got, sample, sizeof(got), hipMemcpyDeviceToHost);
     if (e != hipSuccess) return e;
     h->longest_cluster = (int64_t)got.longest;
-    h->by_clusters = got.longest <= (unsigned long long)kMaxClusterRows && got.leaving <= got.edges / 1024 && got.far <= 64 * kSampledClusters / 4096;
+    h->by_clusters = got.longest <= (unsigned long long)kMaxClusterRows;
+    h->leaving = got.leaving / (64.0 * (double)runs * h->d.degree);
+    h->far = got.far / (64.0 * (double)(runs < kFarRows ? runs : kFarRows));
     return hipSuccess;
 }
 
@@ -413,6 +444,7 @@ extern "C" int ann_index_load(const ann_index_desc_t* desc, ann_index_t** out_ha
     h->route_bias = nullptr;
     h->longest_cluster = d.n;
     h->by_clusters = false;
+    h->leaving = h->far = 0.0;
     const bool mfma_route = d.entry_mode == ANN_ENTRY_ROUTED;
     // A search by whole clusters is a choice: arrays that are not known to be in place on a device (a handle that only routes may have
     // stand-ins) are not looked at, and are searched by gathering.  Loading an index of 10 000 rows takes 40 us with that look, 22
@@ -866,6 +898,11 @@ int cluster_region_words(const ann_index_t* h, const Plan& plan) {
 //     slowest of them: 44 027, d 144, m 748, l 160, w 2: 1 221 | - / 812 / 884; 9 180, d 256, m 753, l 160, w 1: 448 | - / 273 / 334; 16 893, d 128,
 //     m 931, l 64, w 2: 192 | - / 122 / 125; 40 653, d 128, m 1054, l 64, w 2: 506 | - / 315 / 306; 34 070, d 144, m 1877, l 112, w 4: 671 | - / 480 / 450;
 //     28 938, d 96, m 1839, l 64, w 8: 353 | - / 352 / 326; but 2 298, d 256, m 1646, l 64, w 6: 107 | - / 62 / 83.
+//   * Where edges leave the clusters, some queries are searched anew; 128-byte rows, list of 184, w 4, expected of them in a call
+//     [and share of the queries].  All of a batch of few queries wait for one such: 1 000 queries, m 1000: 115 | 76 with none, 90 [0.0006] 0.6,
+//     150 [0.006] 6, 165 [0.6] 600; 100: 106 | 59 none, 75 [0.006] 0.6, 105 [0.018] 1.8, 130 [0.6] 60.  Large batches hide it up to a share:
+//     100 000, m 2000: 2 037 | 1 626 none, 1 740 [0.006], 1 858 [0.018], 2 178 [0.06], 3 520 [0.6]; 40 000, m 1000: 742 | 438 none, 509 [0.006],
+//     521 [0.018], 576 [0.06], 861 [0.6].
 //     Twelve wavefronts of a compute unit have to find room in LDS: 34 594, d 128, m 2676, l 256, w 8 (twelve): 1 010 | - / 727 / 953; 38 424, d 256,
 //     m 2939 (twelve): 1 225 | - / 995 / 1 255; 7 382, d 128, m 4745 (eight): 307 | - / 429 / -.
 void search_by_clusters(const ann_index_t* h, int64_t nq, int itopk, int width, int max_iters, Way* way) {
@@ -879,11 +916,15 @@ void search_by_clusters(const ann_index_t* h, int64_t nq, int itopk, int width, 
     const size_t head = sizeof(uint32_t) * kClusterHeaderWords, region = sizeof(uint32_t) * (size_t)cluster_region_words(h, plan);
     const size_t stages = sizeof(uint32_t) * (kMaxClusterGroup - 1) * kStageWords;
     const int64_t rounds = ((int64_t)width * max_iters < itopk ? max_iters : (itopk + width - 1) / width);
+    // queries that will have to be searched anew, which costs both searches: an edge that leaves the cluster counts at any time, a key that is too
+    // far until the list is full
+    const int64_t parents = (int64_t)width * max_iters < itopk ? (int64_t)width * max_iters : itopk;
+    const double anew = h->leaving * (double)(parents * h->d.degree) + h->far * (double)(itopk + width * h->d.degree);
     // matrix instructions that the keys of up to sixteen queries take
     const int64_t products = (h->d.n / h->d.n_clusters + 15) / 16 * ((h->row_bytes + 63) / 64), per_cluster = nq / h->d.n_clusters;
     if (nq < 1000 || (nq < 3000 && per_cluster < 5)) {
         const size_t graph = ((size_t)h->longest_cluster * h->d.degree + 1) / 2 * sizeof(uint32_t), each = head + region + stages;
-        if (products > 50 * rounds || each * (size_t)((nq + 255) / 256) > kLdsBytes) return;
+        if (products > 50 * rounds || each * (size_t)((nq + 255) / 256) > kLdsBytes || anew * (double)nq > 0.5) return;
         way->group = 1;
         way->waves = nq <= 384 ? kMaxClusterGroup : 4;
         // a small cluster's graph rows fit beside the table (100 queries, m 100, degree 32: 33.7 without, 31.1 with; 40 KB and more
@@ -891,7 +932,7 @@ void search_by_clusters(const ann_index_t* h, int64_t nq, int itopk, int width, 
         if (nq <= 256 && graph <= 16 * 1024 && each + graph <= kLdsBytes) way->graph_words = (int)(graph / sizeof(uint32_t));
         return;
     }
-    if (products > 45 * rounds * (per_cluster < 1 ? 1 : per_cluster < 4 ? per_cluster : 4)) return;
+    if (anew > 1.0 / 128 || products > 45 * rounds * (per_cluster < 1 ? 1 : per_cluster < 4 ? per_cluster : 4)) return;
     const size_t fours = 4 * (kLdsBytes / (head + 4 * region)), eights = 8 * (kLdsBytes / (head + 8 * region));
     if (fours < 12) return;
     way->group = way->waves = products > 4 * rounds && nq >= 4096 && per_cluster >= 8 && eights >= fours ? 8 : 4;

@@ -6,6 +6,7 @@
 #include <stdio.h>
 #include <stdlib.h>
 #include <string.h>
+#include <sys/mman.h>
 
 #include "ann.h"
 
@@ -19,7 +20,8 @@ static size_t async_limit = (size_t)1 << 40; /* hipMallocAsync refuses more */
 static char launched[1 << 16];
 static int host_reads; /* copies from memory that is no device memory */
 static struct { dim3 grid, block; size_t lds; hipStream_t stream; } config;
-static uint32_t sample_result[3]; /* what the kernel that looks at a sample of an index finds: edges, leaving, far */
+static uint32_t sample_result[2]; /* what the kernel that looks at a sample of an index finds: edges that leave, keys too far */
+static unsigned threads; /* of the last launch's workgroups */
 static int sampled, default_stream_free = 1;
 
 static int find(const void* p) {
@@ -27,9 +29,9 @@ static int find(const void* p) {
         if ((const char*)p >= ranges[i].at && (const char*)p < ranges[i].at + ranges[i].bytes) return i;
     return -1;
 }
-static void* device(size_t bytes) {
-    void* p = aligned_alloc(256, (bytes + 255) / 256 * 256);
-    memset(p, 0, bytes);
+static void* device(size_t bytes) { /* zeros; large ones take no memory until they are touched */
+    void* p = mmap(NULL, bytes, PROT_READ | PROT_WRITE, MAP_PRIVATE | MAP_ANONYMOUS | MAP_NORESERVE, -1, 0);
+    if (p == MAP_FAILED) exit(3);
     ranges[n_ranges].at = p;
     ranges[n_ranges++].bytes = bytes;
     return p;
@@ -37,7 +39,7 @@ static void* device(size_t bytes) {
 static void release(void* p) {
     const int i = find(p);
     if (i < 0) return;
-    free(ranges[i].at);
+    munmap(ranges[i].at, ranges[i].bytes);
     ranges[i] = ranges[--n_ranges];
 }
 
@@ -60,7 +62,8 @@ hipError_t __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* lds, hipSt
     return hipSuccess;
 }
 hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3 block, void** args, size_t lds, hipStream_t s) {
-    (void)grid, (void)block, (void)lds, (void)s;
+    (void)grid, (void)lds, (void)s;
+    threads = block.x;
     for (int i = 0; i < n_kernels; ++i) {
         if (kernels[i].host != f) continue;
         strcat(launched, kernels[i].name);
@@ -74,8 +77,8 @@ hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3 block, void** args, si
         }
         if (strstr(kernels[i].name, "sample_clusters_kernel")) {
             sampled = 1;
-            char* sample = *(char**)args[2]; /* rows of the longest cluster (8 bytes), then the counts */
-            memcpy(sample + 8, sample_result, sizeof(uint32_t) * 3);
+            char* sample = *(char**)args[4]; /* rows of the longest cluster (8 bytes), then the counts */
+            memcpy(sample + 8, sample_result, sizeof(uint32_t) * 2);
         }
     }
     return hipSuccess;
@@ -155,7 +158,6 @@ static ann_index_t* load(const ann_index_desc_t* d) {
 
 /* What a way of searching or routing wants of scratch memory, and the call can do without, is no reason to refuse the call. */
 static void scratch(void) {
-    sample_result[0] = 1 << 20; /* edges, all within their clusters */
     ann_index_desc_t d = index_of(ANN_U8, 128, 500, 100, 32, 1);
     ann_index_t* h = load(&d);
     const int nq = 2000;
@@ -217,10 +219,31 @@ static void stand_ins(void) {
     CHECK(!launched[0]);
 }
 
+/* A search by whole clusters is for indices whose queries will end in it: not one in a small batch, few in a large one. */
+static void searched_anew(void) {
+    const struct { int nq; uint32_t leaving, far; int whole; } calls[] = {
+        /* 16 777 216 edges, 184 * 32 of them a query; 65 536 keys, 184 + 128 of them before the list is full */
+        {100, 0, 0, 1}, {100, 1, 0, 1}, {100, 40, 0, 0}, {100, 0, 1, 1}, {100, 0, 2, 0}, {900, 0, 0, 1}, {900, 1, 0, 1}, {900, 4, 0, 0}, {900, 0, 1, 0},
+        {40000, 0, 0, 1}, {40000, 20, 0, 1}, {40000, 25, 0, 0}, {40000, 0, 1, 1}, {40000, 0, 2, 0}, {40000, 31250, 0, 0}};
+    ann_index_desc_t d = index_of(ANN_U8, 128, 1000, 1000, 32, 1);
+    void* q = device(40000 * 128);
+    int32_t *routes = device(40000 * 4), *ids = device(40000 * 40), *keys = device(40000 * 40);
+    for (unsigned i = 0; i < sizeof(calls) / sizeof(calls[0]); ++i) {
+        sample_result[0] = calls[i].leaving, sample_result[1] = calls[i].far;
+        ann_index_t* h = load(&d);
+        launched[0] = 0;
+        CHECK(ann_search_routed(h, q, calls[i].nq, routes, 10, 184, 4, 200, ids, keys, NULL, NULL) == ANN_OK);
+        if (ran("cluster_search_kernel") != calls[i].whole) printf("call %u\n", i);
+        CHECK(ran("cluster_search_kernel") == calls[i].whole);
+        ann_free(h);
+    }
+}
+
 int main(int argc, char** argv) {
     const char* what = argc > 1 ? argv[1] : "";
     if (!strcmp(what, "scratch")) scratch();
     else if (!strcmp(what, "stand_ins")) stand_ins();
+    else if (!strcmp(what, "searched_anew")) searched_anew();
     else return 2;
     printf("%s ok\n", what);
     return 0;

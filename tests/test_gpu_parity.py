@@ -1438,7 +1438,7 @@ def kernels_of(torch, call):
 def test_search_by_whole_clusters_gives_the_bits_of_the_gathering_search(torch_cuda, metric, dim, sizes, itopk, width, degree, n_entry,
                                                                            nq, far):
     """uint8 rows, one cluster per query: the keys of whole clusters come off the matrix cores.  Results and counters are
-    those of the gathering search (a fixed team size asks for that one), also for edges that leave the cluster, empty slots, ids out of
+    those of the gathering search (a fixed team size asks for that one), which indices with edges that leave their clusters go to, also for empty slots, ids out of
     range, duplicates, a few rows far from all others (their keys do not fit the words of the search), and route ids that name no cluster."""
     from paper_2512_02278_amd import ann
 
@@ -1473,7 +1473,8 @@ def test_search_by_whole_clusters_gives_the_bits_of_the_gathering_search(torch_c
             keys, counters = torch.full_like(ids, -7), torch.full((nq, 4), -7, dtype=torch.int32, device="cuda")
             call = lambda: ann.ann_search(h, qt, min(itopk, 10), itopk, width, 200, out_ids=ids, out_dists=keys, counters=counters, routes=r)
             if r is None:
-                assert ("cluster_search_kernel" in kernels_of(torch, call)) == (team == 0)
+                # (of indices whose edges leave, small batches gather: some query would have to be searched anew)
+                assert ("cluster_search_kernel" in kernels_of(torch, call)) == (team == 0 and far == 0.0)
             else:
                 call()
             torch.cuda.synchronize()
@@ -1508,3 +1509,54 @@ def test_search_by_whole_clusters_leaves_out_indices_it_does_not_suit(torch_cuda
         torch.cuda.synchronize()
         assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
         ann.ann_free(h)
+
+
+def uint8_clusters(torch, rng, dim, sizes, degree, pad=0):
+    """Vectors of clusters of these sizes (rows `pad` bytes longer than they need be), their centroids, a graph within the clusters."""
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    n, nc = int(off[-1]), len(sizes)
+    lab = np.repeat(np.arange(nc), sizes)
+    cen = rng.integers(40, 120, (nc, dim))
+    x = np.zeros((n, dim + pad), np.uint8)
+    x[:, :dim] = np.clip(np.rint(cen[lab] + 12.0 * rng.standard_normal((n, dim))), 0, 255)
+    g = rng.integers(off[lab][:, None], off[lab + 1][:, None], (n, degree)).astype(np.int32)
+    return x, cen.astype(np.uint8), off, lab, g
+
+
+@pytest.mark.parametrize("metric", [0, 1])
+@pytest.mark.parametrize("dim,itopk,width,degree,nq", [(128, 184, 4, 32, 100), (48, 100, 3, 27, 61), (128, 184, 4, 32, 1_003), (128, 64, 2, 32, 5_001),
+                                                       (144, 300, 4, 64, 4_100), (256, 256, 8, 64, 4_097)])
+def test_queries_that_cannot_end_in_their_cluster_are_searched_anew(torch_cuda, metric, dim, itopk, width, degree, nq):
+    """An index of clusters that keep their edges but for one edge of one small cluster, which every query of that cluster meets, and
+    with a few rows whose keys do not fit the words: few enough for searches by whole clusters, one query or several to a
+    workgroup.  Results and counters are those of the gathering search."""
+    from paper_2512_02278_amd import ann
+
+    torch = torch_cuda
+    rng = np.random.default_rng(dim + nq)
+    small = 1 if nq < 1_000 or nq > 4_000 else 6                      # several to a workgroup: also runs of short clusters
+    sizes = (8, 40) + (33, 2, 0, 21, 8)[:small - 1] + (2_000,) * 40
+    x, cen, off, lab, g = uint8_clusters(torch, rng, dim, sizes, degree)
+    n = len(x)
+    g[20, 3] = n - 5
+    for c in range(len(sizes) - 8, len(sizes)):
+        x[off[c] + 1 + rng.integers(0, 30)] = 255                       # not among those that ann_index_load looks at
+    at = np.concatenate([rng.integers(0, off[-41], nq // 3), rng.integers(0, n, nq - nq // 3)])
+    q = np.clip(np.rint(x[rng.permutation(at)] + 9.0 * rng.standard_normal((nq, dim))), 0, 255).astype(np.uint8)
+    to = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    h = ann.ann_index_load(to(x), to(g), metric=metric, n_entry=32, entry_mode=1, seed=4, centroids=to(cen), cluster_offsets=to(off), route_c=1)
+    qt, got = to(q), []
+    # routed to the row's own cluster, as nearest centroids of an inner product need not be
+    routes = to(np.where(rng.random(nq) < 0.4, 1, rng.integers(0, len(sizes), nq)).astype(np.int32))
+    for team in (0, 1):
+        ann.ann_index_set_option(h, ann.ANN_OPT_WAVEFRONTS_PER_QUERY, team)
+        ids = torch.full((nq, 10), -7, dtype=torch.int32, device="cuda")
+        keys, counters = torch.full_like(ids, -7), torch.full((nq, 4), -7, dtype=torch.int32, device="cuda")
+        call = lambda: ann.ann_search(h, qt, 10, itopk, width, 200, out_ids=ids, out_dists=keys, counters=counters, routes=routes)
+        assert ("cluster_search_kernel" in kernels_of(torch, call)) == (team == 0)
+        torch.cuda.synchronize()
+        got.append((ids, keys, counters[:, :3]))
+    ann.ann_free(h)
+    assert all(torch.equal(a, b) for a, b in zip(*got))
+    dirty = (routes == 1).cpu().numpy()
+    assert (got[0][0].cpu().numpy()[dirty] >= n - 2_000).any()           # some of them did leave
