@@ -894,17 +894,27 @@ int cluster_region_words(const ann_index_t* h, const Plan& plan) {
 //     The making of the keys has to be worth the rounds that get shorter: d 256, m 3707, l 32, w 2: 67 | 72; d 128, m 7674, l 64, w 8: 43 | 43,
 //     against d 128, m 7542, l 100, w 4: 101 | 74 and d 128, m 7720, l 256, w 4: 145 | 96.  Workgroups have to be resident all at once (2 387,
 //     d 128, m 7486: 197 | 392).
+//     Every query streams its whole cluster, where one that gathers reads part of it: up to 100 MB, and 4 MB more per round, for the whole
+//     call.  d 128, m 6103 (781 KB), 3.2 GB, l 184 and 100, w 4: 300 queries 155 | 122 and 106 | 99, 600 160 | 151 and 109 | 127, 1 000 165 | 193 and
+//     113 | 170, on four streams at once 51 | 124 and 36 | 120; m 2000, 2.1 GB: 1 000 145 | 112 and 99 | 90, on four streams 40 | 44 and 29 | 41,
+//     2 000 156 | 155 and 107 | 130, 56 | 85 and 56 | 80; m 6103 in the caches (31 MB), l 184: 600 129 | 89, on four streams 35 | 51, 1 000 132 | 107, 39 | 86.
 //   * More queries: four or eight to a workgroup, grouped by cluster.  Eight make the keys for less, four wait less for the
 //     slowest of them: 44 027, d 144, m 748, l 160, w 2: 1 221 | - / 812 / 884; 9 180, d 256, m 753, l 160, w 1: 448 | - / 273 / 334; 16 893, d 128,
 //     m 931, l 64, w 2: 192 | - / 122 / 125; 40 653, d 128, m 1054, l 64, w 2: 506 | - / 315 / 306; 34 070, d 144, m 1877, l 112, w 4: 671 | - / 480 / 450;
 //     28 938, d 96, m 1839, l 64, w 8: 353 | - / 352 / 326; but 2 298, d 256, m 1646, l 64, w 6: 107 | - / 62 / 83.
-//   * Where edges leave the clusters, some queries are searched anew; 128-byte rows, list of 184, w 4, expected of them in a call
-//     [and share of the queries].  All of a batch of few queries wait for one such: 1 000 queries, m 1000: 115 | 76 with none, 90 [0.0006] 0.6,
-//     150 [0.006] 6, 165 [0.6] 600; 100: 106 | 59 none, 75 [0.006] 0.6, 105 [0.018] 1.8, 130 [0.6] 60.  Large batches hide it up to a share:
-//     100 000, m 2000: 2 037 | 1 626 none, 1 740 [0.006], 1 858 [0.018], 2 178 [0.06], 3 520 [0.6]; 40 000, m 1000: 742 | 438 none, 509 [0.006],
-//     521 [0.018], 576 [0.06], 861 [0.6].
-//     Twelve wavefronts of a compute unit have to find room in LDS: 34 594, d 128, m 2676, l 256, w 8 (twelve): 1 010 | - / 727 / 953; 38 424, d 256,
-//     m 2939 (twelve): 1 225 | - / 995 / 1 255; 7 382, d 128, m 4745 (eight): 307 | - / 429 / -.
+//     What decides against gathering is [clusters read per query, over the share of its cluster that a query is expected to score].  Of 3 185
+//     calls over 60 indices (rows of 64 to 256 bytes, 100 to 6 000 a cluster, 1 MB to 2 GB) those below 0.76 took 0.6 to 0.85 of the gathering
+//     search's time, those above up to 2.2 times: d 128, m 2000, 2.1 GB, l 184, w 4: 5 000 199 | 330 [1.57], 10 000 368 | 469 [1.30], 20 000 606 | 667 [0.98],
+//     40 000 1 044 | 1 011 [0.71], 80 000 1 864 | 1 628 [0.36]; m 1000: 10 000 340 | 370 [1.22], 20 000 588 | 557 [1.01], 40 000 983 | 798 [0.76], 80 000 1 828 |
+//     1 320 [0.55]; m 129, 75 000 clusters, 3 967: 243 | 362 [1.0].  Twelve wavefronts of a compute unit have to find room in LDS (7 382, d 128, m 4745,
+//     eight: 307 | - / 429), and where no more do, the line is 0.45: d 128, l 256, w 4: 22 717, m 2972 831 | 1 072 [0.46], 18 332, m 2335 0.79 of the
+//     time [0.37]; l 184: 38 412, m 2780 888 | 932 [0.49].  Rows of 64 edges take their time to read in either search, 0.66: m 1948 0.55 of
+//     the time [0.57], m 2336 0.75 [0.65], m 2967 1.55 times [1.19].
+//   * Where edges leave the clusters, some queries are searched anew.  Few queries all wait for one of them, large batches hide up to one
+//     in a hundred: time with none | [share of the queries] and number expected, d 128, l 184, w 4: 1 000 queries, m 1000: 115 | 76 none, 90 [0.0006] 0.6,
+//     150 [0.006] 6, 165 [0.6] 600; 100: 106 | 59 none, 75 [0.006] 0.6, 105 [0.018] 1.8, 130 [0.6] 60; 100 000, m 2000: 2 037 | 1 626 none, 1 740 [0.006],
+//     1 858 [0.018], 2 178 [0.06], 3 520 [0.6]; 40 000, m 1000: 742 | 438 none, 509 [0.006], 521 [0.018], 576 [0.06], 861 [0.6]; 10 000, m 2000: 333 | 307 none,
+//     375 [0.006].
 void search_by_clusters(const ann_index_t* h, int64_t nq, int itopk, int width, int max_iters, Way* way) {
     if (!h->by_clusters || nq < 1 || nq > 2147483647ll) return;
     // options that ask for a search of another kind
@@ -920,11 +930,13 @@ void search_by_clusters(const ann_index_t* h, int64_t nq, int itopk, int width, 
     // far until the list is full
     const int64_t parents = (int64_t)width * max_iters < itopk ? (int64_t)width * max_iters : itopk;
     const double anew = h->leaving * (double)(parents * h->d.degree) + h->far * (double)(itopk + width * h->d.degree);
+    const double cluster_bytes = (double)(h->d.n / h->d.n_clusters) * h->row_bytes;
     // matrix instructions that the keys of up to sixteen queries take
     const int64_t products = (h->d.n / h->d.n_clusters + 15) / 16 * ((h->row_bytes + 63) / 64), per_cluster = nq / h->d.n_clusters;
     if (nq < 1000 || (nq < 3000 && per_cluster < 5)) {
         const size_t graph = ((size_t)h->longest_cluster * h->d.degree + 1) / 2 * sizeof(uint32_t), each = head + region + stages;
         if (products > 50 * rounds || each * (size_t)((nq + 255) / 256) > kLdsBytes || anew * (double)nq > 0.5) return;
+        if ((double)nq * cluster_bytes > 1e6 * (100.0 + 4.0 * (double)rounds)) return;
         way->group = 1;
         way->waves = nq <= 384 ? kMaxClusterGroup : 4;
         // a small cluster's graph rows fit beside the table (100 queries, m 100, degree 32: 33.7 without, 31.1 with; 40 KB and more
@@ -935,7 +947,13 @@ void search_by_clusters(const ann_index_t* h, int64_t nq, int itopk, int width, 
     if (anew > 1.0 / 128 || products > 45 * rounds * (per_cluster < 1 ? 1 : per_cluster < 4 ? per_cluster : 4)) return;
     const size_t fours = 4 * (kLdsBytes / (head + 4 * region)), eights = 8 * (kLdsBytes / (head + 8 * region));
     if (fours < 12) return;
-    way->group = way->waves = products > 4 * rounds && nq >= 4096 && per_cluster >= 8 && eights >= fours ? 8 : 4;
+    const int group = products > 4 * rounds && nq >= 4096 && per_cluster >= 8 && eights >= fours ? 8 : 4;
+    // clusters that the workgroups read in all: each of those that have queries once, and one more wherever a workgroup begins
+    const double met = h->d.n_clusters * (1.0 - std::exp(-(double)nq / h->d.n_clusters)), runs = met + (double)nq / group;
+    double most = fours > 12 ? 0.8 : h->d.degree < 48 ? 0.45 : 0.66;
+    if (anew * (double)nq > 0.5) most *= 0.6;  // the searches that some queries need afterwards
+    if (runs > most * scored_share(h, parents, h->d.n / h->d.n_clusters) * (double)nq) return;
+    way->group = way->waves = group;
 }
 
 // Checks the arguments of a search and launches it; `route` is null for uniform entries.

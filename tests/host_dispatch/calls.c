@@ -239,11 +239,35 @@ static void searched_anew(void) {
     }
 }
 
+/* Whole clusters are read where that costs no more than the rows that a query would gather. */
+static void bytes_read(void) {
+    const struct { int dim, mean, clusters, degree, nq, itopk, width, group; } calls[] = {
+        {128, 6103, 16384, 32, 1000, 184, 4, 0}, {128, 6103, 16384, 32, 100, 184, 4, 1}, {128, 6103, 40, 32, 999, 184, 4, 0}, {128, 100, 100, 32, 100, 64, 1, 1},
+        {128, 1000, 1000, 32, 1000, 184, 4, 1}, {128, 2000, 8192, 32, 2000, 184, 4, 0}, {256, 2500, 2048, 32, 2000, 100, 4, 0},
+        {128, 2000, 8192, 32, 5000, 184, 4, 0}, {128, 2000, 8192, 32, 20000, 184, 4, 0}, {128, 2000, 8192, 32, 500000, 184, 4, 8},
+        {128, 1000, 16384, 32, 10000, 100, 4, 0}, {128, 1000, 16384, 32, 100000, 184, 4, 4}, {128, 1000, 1000, 32, 10000, 128, 4, 4}, {96, 2500, 8192, 32, 80000, 64, 1, 0},
+        {128, 1000, 1000, 32, 4000, 184, 4, 4}, {96, 129, 74596, 64, 3967, 128, 2, 0}, {128, 2972, 736, 32, 22717, 256, 4, 0}, {128, 2300, 60, 64, 9000, 256, 4, 4}};
+    int32_t *routes = device(500000 * 4), *ids = device(500000 * 4), *keys = device(500000 * 4);
+    void* q = device((size_t)500000 * 256);
+    for (unsigned i = 0; i < sizeof(calls) / sizeof(calls[0]); ++i) {
+        ann_index_desc_t d = index_of(ANN_U8, calls[i].dim, calls[i].mean, calls[i].clusters, calls[i].degree, 1);
+        ann_index_t* h = load(&d);
+        launched[0] = 0;
+        CHECK(ann_search_routed(h, q, calls[i].nq, routes, 1, calls[i].itopk, calls[i].width, 200, ids, keys, NULL, NULL) == ANN_OK);
+        const int whole = ran("cluster_search_kernel"), group = !whole ? 0 : !ran("cluster_order_kernel") && !ran("cluster_scatter_kernel") ? 1 : (int)threads / 64;
+        if (group != calls[i].group) printf("call %u: %d\n", i, group);
+        CHECK(group == calls[i].group);
+        ann_free(h);
+        release((void*)d.vectors), release((void*)d.graph);
+    }
+}
+
 int main(int argc, char** argv) {
     const char* what = argc > 1 ? argv[1] : "";
     if (!strcmp(what, "scratch")) scratch();
     else if (!strcmp(what, "stand_ins")) stand_ins();
     else if (!strcmp(what, "searched_anew")) searched_anew();
+    else if (!strcmp(what, "bytes_read")) bytes_read();
     else return 2;
     printf("%s ok\n", what);
     return 0;
