@@ -1560,3 +1560,55 @@ def test_queries_that_cannot_end_in_their_cluster_are_searched_anew(torch_cuda, 
     assert all(torch.equal(a, b) for a, b in zip(*got))
     dirty = (routes == 1).cpu().numpy()
     assert (got[0][0].cpu().numpy()[dirty] >= n - 2_000).any()           # some of them did leave
+
+
+@pytest.mark.parametrize("nq", [100, 5_000])
+def test_search_by_whole_clusters_of_padded_rows_captured_static_and_on_two_streams(torch_cuda, nq):
+    """Vectors with a row stride; ann_search_static; replays of a captured call, alone and between eager calls; calls of one handle
+    on two streams at once: the results of the gathering search each time."""
+    from paper_2512_02278_amd import ann
+
+    torch = torch_cuda
+    rng = np.random.default_rng(nq)
+    x, cen, off, lab, g = uint8_clusters(torch, rng, 96, (700, 900, 1_000, 640, 801), 32, pad=48)
+    to = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    vectors = to(x)
+    h = ann.ann_index_load(vectors[:, :96], to(g), n_entry=32, entry_mode=1, seed=4, centroids=to(cen), cluster_offsets=to(off), route_c=1)
+    q = to(np.clip(np.rint(x[rng.integers(0, len(x), 2 * nq), :96] + 9.0 * rng.standard_normal((2 * nq, 96))), 0, 255).astype(np.uint8))
+    halves = (q[:nq].contiguous(), q[nq:].contiguous())
+    empty = lambda: (torch.full((nq, 10), -7, dtype=torch.int32, device="cuda"), torch.full((nq, 10), -7, dtype=torch.int32, device="cuda"))
+    how = (10, 128, 4, 200)
+    ann.ann_index_set_option(h, ann.ANN_OPT_WAVEFRONTS_PER_QUERY, 1)
+    want = [ann.ann_search(h, half, *how) for half in halves]
+    ann.ann_index_set_option(h, ann.ANN_OPT_WAVEFRONTS_PER_QUERY, 0)
+    torch.cuda.synchronize()
+    same = lambda got, half=0: torch.equal(got[0], want[half][0]) and torch.equal(got[1], want[half][1])
+
+    got = empty()
+    assert "cluster_search_kernel" in kernels_of(torch, lambda: ann.ann_search(h, halves[0], *how, *got))
+    assert same(got)
+    got = empty()
+    assert "cluster_search_kernel" in kernels_of(torch, lambda: ann.ann_search_static(h, halves[0], *how, *got))
+    assert same(got)
+    for search in (ann.ann_search, ann.ann_search_static):  # (a captured ann_search of several queries to a workgroup gathers)
+        got = empty()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            search(h, halves[0], *how, *got)
+        for _ in range(3):
+            got[0].fill_(-7), got[1].fill_(-7)
+            graph.replay()
+            torch.cuda.synchronize()
+            assert same(got)
+            assert same(ann.ann_search(h, halves[1], *how), 1)
+            torch.cuda.synchronize()
+        del graph
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    out = [[empty() for _ in range(6)] for _ in range(2)]
+    torch.cuda.synchronize()
+    for i in range(6):
+        for s in range(2):
+            ann.ann_search(h, halves[s], *how, *out[s][i], stream=streams[s])
+    torch.cuda.synchronize()
+    ann.ann_free(h)
+    assert all(same(got, s) for s in range(2) for got in out[s])
