@@ -15,13 +15,13 @@
 //
 // What a word cannot hold ends the search of that query here: a graph edge that leaves the cluster (or the part of it that
 // the table covers), and a key too far from the cluster's smallest that would have to enter a list that is not full.  The
-// wavefront then searches the query anew with BeamSearch, which gathers rows.  ann_index_load looks at a sample of the
-// index for how often that is to be expected (sample_clusters).
+// wavefront then searches the query anew with BeamSearch, which gathers rows.  ann_index_load counts how often that is to be
+// expected (sample_clusters_kernel), and a call of which too many queries would is searched by gathering.
 //
 // Everything is exact integer arithmetic: ids, keys, rounds and counters are those of the gathering search.
 //
-// Measured (before: beam_search_kernel): 500 000 queries, clusters of 1 953 rows of 128 bytes, list of 184: 7.3 ms (9.35), 5 600 vector
-// instructions a query (11 400); 10 000 queries, clusters of 1 000: 115 us (187); 100 queries, clusters of 100: 26 us (43).  What bounds it
+// Measured (before: beam_search_kernel): 500 000 queries, clusters of 1 953 rows of 128 bytes, list of 184: 7.3 ms (9.35), 5 360 vector
+// instructions a query (11 400); 10 000 queries, clusters of 1 000: 116 us (187); 100 queries, clusters of 100: 25 us (43).  What bounds it
 // now: sixteen wavefronts of a compute unit find room in LDS with clusters of two thousand rows, and a round is a chain of two LDS round trips,
 // one graph row from L2 and some 70 vector and 65 scalar instructions; the vector ALUs are 0.6 busy.  Tables of 16 bits per row
 // (twice the wavefronts) need a second pass over the cluster for the smallest key, which cost what they saved (7.9 ms); loads of the

@@ -31,8 +31,8 @@ namespace {
 
 constexpr int kNodesPerWave = 32;
 // Nodes per workgroup of in_edges_kernel (at most 256).  Small on purpose: the fewer nodes an XCD has in
-// flight, the fewer target lists are half-written in its L2 at a time, and the more of their 8-byte words
-// merge into whole lines before they are written back (22.5 ms per 25M nodes with 256, 9.5 ms with 8).
+// flight, the fewer target lists are half-written in its L2 at a time, and the more of their words of 4 bytes (8 where position and
+// source do not fit) merge into whole lines before they are written back (25M nodes of 32 edges: 21.8 ms with 256, 9.3 with 32, 8.3 with 8).
 constexpr int kChunkNodes = 8;
 constexpr int kScanChunk = 4096;  // elements per workgroup of the scan kernels: 256 threads x 16
 
@@ -79,8 +79,8 @@ __device__ __forceinline__ uint32_t slot_of(uint32_t id, int shift) { return (id
 // An entry y of rank rr in the row of the neighbour of rank i is a detour of the edge x -> y of rank j if y is in x's row
 // and j is above both i and rr: eight table reads are in flight per lane (and where the ids do not lie close together, eight
 // reads of the ids at those ranks).  What the entry is needs no test: an absent one equals no id of x's row, and a rank of d_in - 1
-// is below no other.  1M nodes 64 -> 32: 1.19 ms (1.48 ms with the second read everywhere), 524 vector and 145 LDS instructions per
-// node (590, 211); 250 000 nodes 128 -> 64: 1.29 ms (1.63), 1 969 and 555 (2 261, 815).  Bound by LDS: its units are 0.85 and 0.76 busy, half of
+// is below no other.  1M nodes 64 -> 32: 1.2 to 1.3 ms from machine to machine (1.48 ms with the second read everywhere), 524 vector and 145 LDS instructions per
+// node (590, 211); 250 000 nodes 128 -> 64: 1.3 to 1.4 ms (1.63), 1 969 and 555 (2 261, 815).  Bound by LDS: its units are 0.85 and 0.77 busy, half of
 // that with bank conflicts of random byte reads; the vector ALUs 0.72 and 0.62.
 template <int R, bool VEC>
 __global__ void __launch_bounds__(64) graph_prune_kernel(const int32_t* __restrict__ knn, int64_t n, int d_in, int d_out,
@@ -370,14 +370,6 @@ __global__ void __launch_bounds__(1024) count_in_edges_kernel(const int32_t* __r
     }
 }
 
-// Chunk of kChunkNodes nodes a workgroup of the edge kernel works on: like the node runs above, the chunks
-// are dealt so that an XCD walks a contiguous eighth of the ids; the edges of neighbouring nodes point
-// into the same few clusters, and their words then meet in one L2 before they are written back.
-__device__ __forceinline__ int64_t chunk_of(int64_t b, int64_t chunks_per_xcd) { return (b & 7) * chunks_per_xcd + (b >> 3); }
-
-// Chunk c covers the kChunkNodes nodes from kChunkNodes * c on: element t of their rows is node
-// kChunkNodes * c + t / d, position t % d, with t / d == (t * d_inv) >> 22 for t < 256 * d, d <= 64
-// (d_inv = ceil(2^22 / d)).
 // Exclusive scan of indeg[0..n) into off[0..n] (64-bit), in three launches: per-chunk sums, a scan of
 // those by one workgroup, then every chunk scans itself on top of its prefix.
 __global__ void __launch_bounds__(256) chunk_sums_kernel(const uint32_t* __restrict__ deg, int64_t n, int64_t* sums) {
@@ -451,7 +443,16 @@ __device__ __forceinline__ Word edge_word(int position, int64_t source, int sour
     return sizeof(Word) == 8 ? (Word)(((uint64_t)(uint32_t)position << 32) | (uint32_t)source) : (Word)((uint32_t)position << source_bits | (uint32_t)source);
 }
 
+// Chunk of kChunkNodes nodes a workgroup of the edge kernel works on: like the node runs above, the chunks
+// are dealt so that an XCD walks a contiguous eighth of the ids; the edges of neighbouring nodes point
+// into the same few clusters, and their words then meet in one L2 before they are written back.
+__device__ __forceinline__ int64_t chunk_of(int64_t b, int64_t chunks_per_xcd) { return (b & 7) * chunks_per_xcd + (b >> 3); }
+
 // pairs[off[y] + slot[e]] <- the word of every edge e into y
+//
+// Chunk c covers the kChunkNodes nodes from kChunkNodes * c on: element t of their rows is node
+// kChunkNodes * c + t / d, position t % d, with t / d == (t * d_inv) >> 22 for t < 256 * d, d <= 64
+// (d_inv = ceil(2^22 / d)).
 template <class Word>
 __global__ void __launch_bounds__(256) in_edges_kernel(const int32_t* __restrict__ g, int64_t n, int d, uint32_t d_inv,
                                                        const int64_t* __restrict__ off, const uint32_t* __restrict__ slot,
