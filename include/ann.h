@@ -84,10 +84,10 @@ typedef struct {
  * the centroids are known to be device memory and there is room, and not while a stream is captured that the default stream waits for,
  * else they are routed without; for 128-byte
  * uint8 rows about 140, the centroids in the order the routing reads them) is allocated and filled on the
- * default stream, which is synchronised before returning; with route_c == 1, for float rows of 256 bytes and more and uint8
- * rows of at most 256, cluster_offsets is read back on that stream, and for the latter, where all three arrays are known to be whole in
- * device memory, a sample of graph rows and vectors is
- * looked at; nothing else touches the device.
+ * default stream, which is synchronised before returning; with route_c == 1, for float rows of 256 bytes and more
+ * cluster_offsets is read back on that stream, and for uint8 rows of at most 256 a kernel reads cluster_offsets, up to
+ * 16 million edges of graph and some thousand vectors, where all three arrays are known to be whole in device memory (and no
+ * stream is captured that the default stream waits for; else such an index is searched by gathering); nothing else touches the device.
  * Must be called with the device that owns the arrays current.
  * Errors: ANN_EINVAL, ANN_EUNSUPPORTED, ANN_ENOMEM, ANN_EHIP.
  */
@@ -144,7 +144,7 @@ int ann_index_set_option(ann_index_t* handle, int option, int64_t value);
  * ANN_OPT_VISITED_WINDOW_BITS = 0 and ANN_OPT_WAVEFRONTS_PER_QUERY != 0 asks for a search that has none: the search then
  * gathers the rows, with the same results, and keeps no memory.  Batches over uint8 rows of at most 256 bytes (route_c == 1, graph
  * edges within the clusters) are searched by whole clusters held in LDS where that pays, from 1000 queries or so on grouped by cluster
- * (the nq + n_clusters int32 of scratch; not under stream capture); the same options and ANN_OPT_VISITED_HASH_BITS_BIAS != 0 ask for the gathering search, with the
+ * (the nq + n_clusters int32 of scratch; not under stream capture, nor where that memory is not to be had); the same options and ANN_OPT_VISITED_HASH_BITS_BIAS != 0 ask for the gathering search, with the
  * same results.  Calls on
  * different streams may share a handle.  A route id outside [0, n_clusters) (only possible
  * through ann_search_routed) names no cluster: it gives no entries, and a query whose routes
