@@ -595,8 +595,8 @@ def prune_roofline(workload: str, sha: str, n: int, d_in: int, degree: int, prun
                             "frac": round(traffic / prune_ms / 1e6 / HBM_PEAK_GBPS, 4)},
                     "note": "achieved / peak: vector instructions issued x 64 lanes / time against 4 cycles per instruction on every SIMD, the "
                             "nearest counted resource.  What binds is LDS: "
-                            "every id of a neighbour's row costs a random byte read and a dependent read of an id, a dozen cycles per 64 "
-                            "lanes each.  Neighbours' rows are re-read from L2 (XCD-local walk), so the algorithmic bytes do not bind "
+                            "every id of a neighbour's row costs a random byte read, and where a row's ids do not lie close together a dependent "
+                            "read of an id, a dozen cycles per 64 lanes each.  Neighbours' rows are re-read from L2 (XCD-local walk), so the algorithmic bytes do not bind "
                             "(see hbm)"})
     else:
         out.update({"bound": "lds", "achieved": None, "peak": round(VALU_PEAK_TOPS, 2), "unit": "TOP/s", "frac": None, "traffic": None})
