@@ -15,6 +15,7 @@
 #include "combine.h"
 #include "graph_build.h"
 #include "key_table.h"
+#include "rank_search.h"
 #include "route_mfma.h"
 #include "route_mfma_u8.h"
 #include "schedule.h"
@@ -71,6 +72,7 @@ constexpr int kDefaultWindowBits = 8192, kMaxWindowBits = 1 << 17;
 // From this batch size on, a routed batch is executed grouped by cluster (schedule.hip).
 constexpr int64_t kMinQueriesForClusterOrder = 16384;
 constexpr int64_t kTableBytes = 1ll << 30;
+constexpr unsigned kLeftOverGrid = 2048;  // workgroups that go through the queries a search by rank leaves, mostly none
 
 }  // namespace ann
 
@@ -281,7 +283,7 @@ static __global__ void __launch_bounds__(64) sample_clusters_kernel(ann_index_de
                 }
             }
         }
-        if (run >= kFarRows) continue;
+        if (run >= kFarRows || d.dtype != ANN_U8) continue;
         lo = __builtin_amdgcn_readfirstlane(lo);
         const int size = __builtin_amdgcn_readfirstlane(hi) - lo;
         if (size > kMaxClusterRows) continue;  // a row of none
@@ -389,7 +391,7 @@ hipError_t look_at_clusters(ann_index_t* h, ClusterSample* sample) {
     if (e == hipSuccess) e = hipMemcpy(&got, sample, sizeof(got), hipMemcpyDeviceToHost);
     if (e != hipSuccess) return e;
     h->longest_cluster = (int64_t)got.longest;
-    h->by_clusters = got.longest <= (unsigned long long)kMaxClusterRows;
+    h->by_clusters = h->d.dtype == ANN_U8 && got.longest <= (unsigned long long)kMaxClusterRows;
     h->leaving = got.leaving / (64.0 * (double)runs * h->d.degree);
     h->far = got.far / (64.0 * (double)(runs < kFarRows ? runs : kFarRows));
     return hipSuccess;
@@ -444,12 +446,13 @@ extern "C" int ann_index_load(const ann_index_desc_t* desc, ann_index_t** out_ha
     h->route_bias = nullptr;
     h->longest_cluster = d.n;
     h->by_clusters = false;
-    h->leaving = h->far = 0.0;
+    h->leaving = 1.0;
+    h->far = 0.0;
     const bool mfma_route = d.entry_mode == ANN_ENTRY_ROUTED;
     // A search by whole clusters is a choice: arrays that are not known to be in place on a device (a handle that only routes may have
     // stand-ins) are not looked at, and are searched by gathering.  Loading an index of 10 000 rows takes 40 us with that look, 22
     // without; with the offsets read back, an allocation of its own and two more copies it took 79.
-    const bool look = mfma_route && d.route_c == 1 && d.dtype == ANN_U8 && row_bytes <= kMaxClusterRowBytes &&
+    const bool look = mfma_route && ((d.route_c == 1 && d.dtype == ANN_U8 && row_bytes <= kMaxClusterRowBytes) || may_use_table(h)) &&
                       on_device(d.vectors, (size_t)(d.n - 1) * d.row_stride_bytes + row_bytes) &&
                       on_device(d.graph, (size_t)d.n * d.degree * sizeof(int32_t)) &&
                       on_device(d.cluster_offsets, ((size_t)d.n_clusters + 1) * sizeof(int64_t)) && may_allocate_more(nullptr);
@@ -465,8 +468,9 @@ extern "C" int ann_index_load(const ann_index_desc_t* desc, ann_index_t** out_ha
             e = launch_route_bias(d.dtype, d.metric, static_cast<const uint8_t*>(d.centroids), d.n_clusters,
                                   (int)row_bytes, h->route_bias, nullptr);
         bool listing = true;
-        if (e == hipSuccess) e = look ? look_at_clusters(h, sample_behind(h->route_bias, route_mfma_bias_bytes(d.n_clusters)))
-                              : settled_routing(h) ? norms_allow_listing(h, &listing) : hipStreamSynchronize(nullptr);
+        if (e == hipSuccess && look) e = look_at_clusters(h, sample_behind(h->route_bias, route_mfma_bias_bytes(d.n_clusters)));
+        if (e == hipSuccess && settled_routing(h)) e = norms_allow_listing(h, &listing);
+        else if (e == hipSuccess && !look) e = hipStreamSynchronize(nullptr);
         if (e != hipSuccess || !listing) {
             if (h->route_bias) (void)hipFree(h->route_bias);
             h->route_bias = nullptr;
@@ -491,7 +495,7 @@ extern "C" int ann_index_load(const ann_index_desc_t* desc, ann_index_t** out_ha
                         hipGetErrorString(e));
         }
     }
-    if (may_use_table(h)) find_longest_cluster(h);
+    if (may_use_table(h) && h->longest_cluster == d.n) find_longest_cluster(h);  // not looked at
     *out_handle = h;
     return ANN_OK;
 }
@@ -874,6 +878,43 @@ int table_stride(const ann_index_t* h, int64_t nq, int itopk, int width, int max
     return may_allocate_more(stream) ? (int)stride : 0;
 }
 
+// Whether a search with a key table ranks the clusters' rows (rank_search.h): those of the longest cluster, and the ranks that it settles.
+//
+// Of 50 calls over 8 to 400 clusters (300 to 2 900 rows of 200 to 1 536 bytes, lists of 32 to 256, 16 to 512 neighbours a round) the whole call
+// without / with ranks, and [rounds x (64 x registers of the list + 2 x neighbours - 200) over the rows of a cluster]: 0.92 [2.1], 0.95 [3.4], 0.96 [3.1],
+// 0.97 [2.9], 0.98 [3.5], 0.94 [below 0: a list and a round of 64 at most], 1.09 [5.0], 1.07 [6.0], 1.18 [6.5], 1.07 [7.7], 1.10 [14], 1.19 [28], 1.25 [36]; with few
+// queries, where a round's latency counts, up to 1.45.
+void rank_rows(const ann_index_t* h, int64_t nq, int itopk, int width, int max_iters, int stride, SearchParams* p) {
+    const int64_t parents = (int64_t)width * max_iters < itopk ? (int64_t)width * max_iters : itopk;
+    // queries that meet an edge that leaves their cluster: a small batch would wait for one of them
+    const double anew = h->leaving * (double)(parents * h->d.degree);
+    if (anew > 1.0 / 128 || (nq < kMinQueriesForClusterOrder && anew * (double)nq > 0.5)) return;
+    const int64_t mean = h->d.n / h->d.n_clusters, longest = h->longest_cluster < stride ? h->longest_cluster : stride;
+    if (mean > kMaxRankRows) return;
+    // Ranking costs as much as there are rows; it saves, a round, what the list and the neighbours cost beyond the search for
+    // bits that are set.
+    const int64_t rounds = (parents + width - 1) / width;
+    if (2 * rounds * (64 * ((itopk + 63) / 64) + 2 * width * h->d.degree - 200) < 9 * mean) return;
+    p->rank_rows = (int)(longest < kMaxRankRows ? longest : kMaxRankRows);
+    // The search expands what its list holds at the end, and at first the best of its entries.  Of n entries drawn at random fewer than
+    // `width` are among the nearest share f of the rows with the probability summed up here: in one of fifty calls for some query.
+    const double n = h->d.n_entry, rare = 0.02 / (double)nq;
+    double f = 0.0, fewer = 1.0;
+    while (fewer > rare && f < 0.99) {
+        f += 0.02;
+        double term = std::pow(1.0 - f, n);
+        fewer = 0.0;
+        for (int i = 0; i < width; ++i) {
+            fewer += term;
+            term *= (n - i) / (i + 1) * f / (1.0 - f);
+        }
+    }
+    if (f >= 0.99) f = 1.0;
+    const int group = kRankTiles * kRankTile, most = (p->rank_rows + group - 1) / group * group;
+    const double want = std::fmax(f * (double)longest, 2.0 * itopk + 64.0) + kRankHalo;
+    p->rank_places = want >= most ? most : ((int)want + group - 1) / group * group;
+}
+
 constexpr size_t kLdsBytes = 160 * 1024;  // of a compute unit; one workgroup may have all of it
 
 // LDS words per query of a search by whole clusters: the table, or the gathering search that may follow.
@@ -999,13 +1040,14 @@ int search_impl(ann_index_t* h, const void* queries, int64_t nq, const int32_t* 
     int64_t per_launch = kMaxQueriesPerLaunch;
     TableBlocks::Block* block = nullptr;
     if (stride > 0 && order) {
-        int64_t most = kTableBytes / (4 * (int64_t)stride);
+        // a query's keys, and its place in the list of those that the search by rank leaves
+        int64_t most = (kTableBytes - 4) / (4 * ((int64_t)stride + 1));
         if (most > 512) most = most / 512 * 512;
         const int64_t launches = (nq + most - 1) / most, even = (nq + launches - 1) / launches;
         per_launch = (even + 511) / 512 * 512;
         if (per_launch > most) per_launch = most;
         if (per_launch > nq) per_launch = nq;
-        block = h->tables.take(4 * (size_t)stride * (size_t)per_launch, stream);
+        block = h->tables.take(4 * ((size_t)stride + 1) * (size_t)per_launch + 4, stream);
         if (!block) per_launch = kMaxQueriesPerLaunch;  // no memory: gather every row
     }
     uint32_t* const table = block ? static_cast<uint32_t*>(block->memory) : nullptr;
@@ -1046,6 +1088,10 @@ int search_impl(ann_index_t* h, const void* queries, int64_t nq, const int32_t* 
         p.order = order;
         p.table = table;
         p.table_stride = table ? stride : 0;
+        p.rank_rows = p.rank_places = 0;
+        p.again = nullptr;
+        if (table) rank_rows(h, nq, itopk, width, max_iters, stride, &p);
+        if (p.rank_rows > 0) p.again = reinterpret_cast<int32_t*>(table + (size_t)stride * (size_t)per_launch);
         size_t lds_bytes = plan.lds_bytes;
         if (way.group > 0) {
             ClusterParams c;
@@ -1086,6 +1132,7 @@ int search_impl(ann_index_t* h, const void* queries, int64_t nq, const int32_t* 
             if (t.slice_rows < 128) t.slice_rows = 128;
             t.slices = (stride + t.slice_rows - 1) / t.slice_rows;
             t.table = table;
+            t.none = p.again;
             e = launch_key_table(h->d.dtype, h->d.metric, h->variant->g, h->variant->nch, t, stream);
             if (e != hipSuccess) break;
             const int64_t longest = (h->longest_cluster + 31) / 32 * 32;
@@ -1094,7 +1141,13 @@ int search_impl(ann_index_t* h, const void* queries, int64_t nq, const int32_t* 
                 p.window_bits = (int)longest;
             }
         }
-        e = h->variant->search(p, plan.list_variant, team, (unsigned)(8 * p.q_per_xcd), lds_bytes, stream);
+        unsigned grid = (unsigned)(8 * p.q_per_xcd);
+        if (p.again) {
+            e = launch_rank_search(p, kListVariants[plan.list_variant][1], grid, (size_t)rank_lds_bytes(p.rank_rows, p.rank_places), stream);
+            if (e != hipSuccess) break;
+            if (grid > kLeftOverGrid) grid = kLeftOverGrid;
+        }
+        e = h->variant->search(p, plan.list_variant, team, grid, lds_bytes, stream);
     }
     if (block) h->tables.give_back(block, stream);
     if (e != hipSuccess) return fail(ANN_EHIP, "ann_search: launch failed: %s", hipGetErrorString(e));

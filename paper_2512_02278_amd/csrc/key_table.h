@@ -32,6 +32,7 @@ struct KeyTableParams {
     int32_t stride;                  // keys per query, a multiple of 32: rows beyond it are left to the search
     int32_t slices, slice_rows;      // slices of a cluster's rows, slice_rows (a multiple of 64) rows each
     uint32_t* table;
+    int32_t* none;                   // a counter that is set to zero, or null
 };
 
 template <int Q>

@@ -59,6 +59,7 @@ __global__ void __launch_bounds__(256) key_table_kernel(const KeyTableParams p) 
     constexpr int NCH = Row::NCH, Q = key_table_set(Row::NCH);
     const int lane = lane_id();
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    if (p.none && blockIdx.x == 0 && threadIdx.x == 0) *p.none = 0;
     KeyTableRuns<Q> run;
     run.begin(p, lane);
     while (run.next(p, lane)) {

@@ -26,16 +26,6 @@ enum { kL2 = 0, kIP = 1 };
 typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-__device__ __forceinline__ uint32_t float_to_ordered(float f) {
-    f = f + 0.0f;  // -0 becomes +0, so equal keys have equal bits
-    uint32_t u = __builtin_bit_cast(uint32_t, f);
-    return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-}
-__device__ __forceinline__ float ordered_to_float(uint32_t u) {
-    u = (u & 0x80000000u) ? (u & 0x7fffffffu) : ~u;
-    return __builtin_bit_cast(float, u);
-}
-
 // a - b of the low (H = 0) or high halves, rounded once to fp32: what converting both and subtracting gives, in one
 // instruction instead of three (an fp16 L2 key is 4 instructions per pair of elements, from 8).
 template <int H>

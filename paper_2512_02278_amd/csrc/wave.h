@@ -59,6 +59,17 @@ __device__ __forceinline__ uint64_t xor_lane64(uint64_t v, int lane) {
     return ((uint64_t)hi << 32) | lo;
 }
 
+// Float keys as words that compare like them.
+__device__ __forceinline__ uint32_t float_to_ordered(float f) {
+    f = f + 0.0f;  // -0 becomes +0, so equal keys have equal bits
+    uint32_t u = __builtin_bit_cast(uint32_t, f);
+    return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+}
+__device__ __forceinline__ float ordered_to_float(uint32_t u) {
+    u = (u & 0x80000000u) ? (u & 0x7fffffffu) : ~u;
+    return __builtin_bit_cast(float, u);
+}
+
 // Butterfly sum over groups of G consecutive lanes; every lane of a group ends up
 // with the same value, and the order of additions is the same for every group.
 template <int MASK>
@@ -80,6 +91,22 @@ __device__ __forceinline__ T group_sum(T v, int lane) {
     } else {
         return v;
     }
+}
+
+// Sum over this lane and those below it.
+__device__ __forceinline__ uint32_t wave_inclusive_sum(uint32_t v) {
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, false);  // row_shr:1, 0 where a row begins
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, false);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, false);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, false);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false);  // row_bcast:15 into the odd rows
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false);  // row_bcast:31 into the upper half
+    return v;
+}
+
+// The next lane's v; `last` in lane 63.
+__device__ __forceinline__ uint32_t next_lane(uint32_t v, uint32_t last) {
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)last, (int)v, 0x130, 0xf, 0xf, false);  // wave_shl:1
 }
 
 // Sums of Q values (a power of two) over groups of G lanes, in group_sum's order: every lane ends up with the sum

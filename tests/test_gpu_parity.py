@@ -1421,6 +1421,64 @@ def kernels_of(torch, call):
     return " ".join(e.name for e in prof.events())
 
 
+@pytest.mark.parametrize("dt,dim,metric,sizes,k,itopk,width,degree,n_entry,iters,kind", [
+    ("f32", 96, 0, (500, 1, 64, 63, 65, 900, 1_408, 1_409), 10, 128, 4, 32, 32, 100, "plain"),   # three clusters of more rows than the table holds
+    ("f32", 96, 0, (3_072, 3_073, 2_950), 100, 512, 8, 64, 32, 100, "plain"),                   # the most rows that are ranked, and one more
+    ("f16", 768, 1, (300, 700, 410), 70, 70, 4, 48, 64, 100, "plain"),
+    ("f32", 100, 1, (500, 260, 900), 10, 100, 6, 27, 5, 100, "plain"),
+    ("f16", 128, 0, (256, 257, 288, 300), 256, 256, 8, 64, 32, 40, "plain"),
+    ("f32", 128, 0, (280, 301), 128, 128, 2, 33, 1, 100, "plain"),
+    ("f32", 96, 0, (700, 900), 10, 128, 4, 32, 32, 100, "copies"),       # equal keys, in buckets of two and of fifty
+    ("f32", 96, 0, (700, 900), 10, 128, 4, 32, 32, 100, "outlier"),      # nearly all rows in few buckets
+    ("f32", 96, 0, (700, 900), 10, 128, 4, 32, 32, 100, "infinite"),     # no buckets
+    ("f32", 96, 0, (700, 900, 800), 10, 128, 4, 32, 32, 100, "far"),     # edges that leave a cluster
+    ("f32", 96, 0, (700, 900), 100, 128, 4, 32, 32, 100, "sparse"),      # searches that end with less than k rows
+])
+def test_search_by_rank_gives_the_bits_of_the_gathering_search(torch_cuda, dt, dim, metric, sizes, k, itopk, width, degree, n_entry, iters, kind):
+    """Searches with a key table rank the rows of a cluster first.  Results and counters have the bits of the search that gathers
+    every row (a fixed team size asks for that one), also where a query is left to another search."""
+    from paper_2512_02278_amd import ann
+
+    torch, dev, nq = torch_cuda, "cuda:0", 4_200
+    rng = np.random.default_rng(dim + len(sizes) + len(kind))
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    n, nc = int(off[-1]), len(sizes)
+    cen = rng.standard_normal((nc, dim))
+    lab = np.repeat(np.arange(nc), sizes)
+    x = (cen[lab] + 0.7 * rng.standard_normal((n, dim))).astype(NP_DT[dt])
+    g = rng.integers(off[lab][:, None], off[lab + 1][:, None], (n, degree)).astype(np.int32)
+    g[rng.random((n, degree)) > 0.97] = -1
+    g[rng.random((n, degree)) > 0.99] = n
+    if kind == "copies":
+        x[1:300:2] = x[0:300:2]
+        x[off[1]:off[1] + 50] = x[off[1]]
+    if kind == "outlier":
+        x[5] = 1e4
+    if kind == "infinite":
+        x[5, 3] = np.inf
+    if kind == "sparse":
+        g[rng.random((n, degree)) > 0.04] = -1
+    q = (x[rng.integers(6, n, nq)].astype(np.float64) + 0.1 * rng.standard_normal((nq, dim))).astype(NP_DT[dt])
+    to = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(dev)
+    gt = to(g)
+    h = ann.ann_index_load(to(x), gt, metric=metric, n_entry=n_entry, entry_mode=1, seed=4, centroids=to(cen.astype(NP_DT[dt])),
+                           cluster_offsets=to(off), route_c=1)
+    if kind == "far":  # behind the load's back: with a share like this it would not have them ranked
+        gt[off[1]:off[1] + 30, 3] = 0
+    qt, routes = to(q), to(rng.integers(-1, nc, nq).astype(np.int32))
+    got = []
+    for team in (0, 1):
+        ann.ann_index_set_option(h, ann.ANN_OPT_WAVEFRONTS_PER_QUERY, team)
+        ids = torch.full((nq, k), -7, dtype=torch.int32, device=dev)
+        keys = torch.empty((nq, k), dtype=torch.float32, device=dev)
+        counters = torch.full((nq, 4), -7, dtype=torch.int32, device=dev)
+        names = kernels_of(torch, lambda: ann.ann_search(h, qt, k, itopk, width, iters, out_ids=ids, out_dists=keys, counters=counters, routes=routes))
+        assert ("rank_search_kernel" in names) == (team == 0), names
+        got.append((ids, keys.view(torch.int32), counters[:, :3]))
+    ann.ann_free(h)
+    assert all(torch.equal(a, b) for a, b in zip(*got))
+
+
 @pytest.mark.parametrize("metric", [0, 1])
 @pytest.mark.parametrize("dim,sizes,itopk,width,degree,n_entry,nq,far", [
     (128, (100, 1, 0, 15, 16, 17, 111, 64), 64, 1, 32, 32, 100, 0.0),        # one query per workgroup, graph rows in LDS
