@@ -212,7 +212,9 @@ int ann_free(ann_index_t* handle);
 const char* ann_last_error(void);
 
 /* Bytes of LDS one query's wavefront uses in a search that gathers rows, or a
- * negative error code; lets callers reason about occupancy. */
+ * negative error code; lets callers reason about occupancy.  (Searches with
+ * ANN_ENTRY_UNIFORM may use more, for a larger visited hash, where a compute
+ * unit has it to spare.) */
 int64_t ann_lds_bytes(ann_index_t* handle, int itopk, int width);
 
 /*

@@ -544,7 +544,7 @@ int make_plan(const ann_index* h, int itopk, int width, Plan* plan, const char* 
     // words: round scratch (keys + ids, or a copy of the list), parents, window table, bitmap, hash
     const size_t scratch = 3 * (size_t)plan->cap > 128 * (size_t)kListVariants[lv][0] ? 3 * (size_t)plan->cap
                                                                                    : 128 * (size_t)kListVariants[lv][0];
-    plan->lds_bytes = sizeof(uint32_t) * (scratch + 64 + 32 + 8 + (size_t)h->window_bits / 32 + (size_t(1) << bits));
+    plan->lds_bytes = sizeof(uint32_t) * (scratch + 64 + 32 + 8 + (size_t)hash_at(h->window_bits) + (size_t(1) << bits));
     return ANN_OK;
 }
 
@@ -997,6 +997,27 @@ void search_by_clusters(const ann_index_t* h, int64_t nq, int itopk, int width, 
     way->group = way->waves = group;
 }
 
+// Entries drawn over the whole index: everything that a search scores is remembered in the hash, which has LDS to spare where registers
+// or the batch bound the queries in flight (a compute unit holds 16 to 20 wavefronts over float rows, 28 over short uint8 rows).  Twice
+// the ids that may come, so that it need not be emptied - rows are scored again after that - and insertions seldom meet.  With buckets
+// in place of single words (hash_insert), us before / now, 100, 1 000, 3 000, 20 000 queries: 400-byte fp16 rows, list of 100, 81 neighbours a
+// round 329/246, 430/318, 793/592, 3 365/2 888; 1 536 bytes, 64, 128 453/314, 804/524, 2 096/1 467, (10 000) 6 464/5 104; 128-byte uint8 rows, 64, 32
+// 250/164, 295/193, 348/260, 1 165/867; 512-byte fp32 rows, 160, 96 467/347, 525/401, 1 033/891, (30 000) 9 262/9 159.  Single words in the
+// larger hash were slower than in the small one here and there (384 bytes, 256, 256, 1 000 queries 616/663).
+void enlarge_hash(const ann_index_t* h, int64_t nq, int itopk, Plan* plan) {
+    if (h->d.entry_mode != ANN_ENTRY_UNIFORM || h->hash_bits_bias != 0) return;
+    const int64_t visits = (int64_t)itopk * h->d.degree + h->d.n_entry, resident = (nq + 255) / 256;
+    size_t room = kLdsBytes / (size_t)resident;
+    const size_t least = h->d.dtype == ANN_U8 ? 5800 : 8192;
+    if (room < least) room = least;
+    while (plan->hash_bits < 13 && (int64_t(1) << plan->hash_bits) < 2 * visits) {
+        const size_t more = sizeof(uint32_t) << plan->hash_bits;
+        if (plan->lds_bytes + more > room) break;
+        plan->lds_bytes += more;
+        ++plan->hash_bits;
+    }
+}
+
 // Checks the arguments of a search and launches it; `route` is null for uniform entries.
 int search_impl(ann_index_t* h, const void* queries, int64_t nq, const int32_t* route, bool route_given, int k,
                 int itopk, int width, int max_iters, int32_t* out_ids, void* out_dists, int32_t* out_counters,
@@ -1011,6 +1032,7 @@ int search_impl(ann_index_t* h, const void* queries, int64_t nq, const int32_t* 
     const int rc = make_plan(h, itopk, width, &plan, "ann_search");
     if (rc != ANN_OK) return rc;
     if (nq == 0) return ANN_OK;
+    enlarge_hash(h, nq, itopk, &plan);
     if (!queries || !out_ids || !out_dists || (route_given && !route)) return fail(ANN_EINVAL, "ann_search: null argument");
     if (!aligned16(queries)) return fail(ANN_EINVAL, "ann_search: queries not 16-byte aligned");
 
@@ -1135,9 +1157,9 @@ int search_impl(ann_index_t* h, const void* queries, int64_t nq, const int32_t* 
             t.none = p.again;
             e = launch_key_table(h->d.dtype, h->d.metric, h->variant->g, h->variant->nch, t, stream);
             if (e != hipSuccess) break;
-            const int64_t longest = (h->longest_cluster + 31) / 32 * 32;
+            const int64_t longest = (h->longest_cluster + 127) / 128 * 128;
             if (longest < p.window_bits) {
-                lds_bytes -= sizeof(uint32_t) * (size_t)((p.window_bits - longest) / 32);
+                lds_bytes -= sizeof(uint32_t) * (size_t)(hash_at(p.window_bits) - hash_at((int)longest));
                 p.window_bits = (int)longest;
             }
         }

@@ -32,16 +32,45 @@ namespace ann {
 
 constexpr uint32_t kEmptySlot = 0xffffffffu;
 
+// Words of the visited bitmap, to where the hash begins.
+__host__ __device__ constexpr int hash_at(int window_bits) { return ((window_bits >> 5) + 3) & ~3; }
+
 // True if `id` was not in the hash (and now is).  The hash is never full.
+//
+// Buckets of W = 2 or 4 words, read with one instruction: what a wavefront waits for is the longest of 64 searches, and slot by slot
+// (an atomic each) that took a dozen LDS round trips a round even where the hash was two fifths full.  Lanes with one id
+// see the same bucket, choose the same word and find each other there; those with different ids mostly choose different words.
+template <int W>
 __device__ __forceinline__ bool hash_insert(uint32_t* table, int hash_bits, uint32_t id) {
+    typedef uint32_t words_t __attribute__((ext_vector_type(W)));
     const uint32_t mask = (1u << hash_bits) - 1u;
     uint32_t h = (id * 0x9E3779B1u) >> (32 - hash_bits);
-    for (;;) {
-        const uint32_t old = atomicCAS(&table[h], kEmptySlot, id);
-        if (old == kEmptySlot) return true;
-        if (old == id) return false;
-        h = (h + 1) & mask;
-    }
+    const uint32_t first = h & (W - 1);
+    h &= ~(uint32_t)(W - 1);
+    // 0: new, 1: seen, 2: look on
+    int found;
+    do {
+        const words_t v = *reinterpret_cast<const volatile words_t*>(table + h);
+        uint32_t at_first = v[0], word = W;
+        bool there = false;
+#pragma unroll
+        for (int i = W - 1; i >= 0; --i) {
+            there |= v[i] == id;
+            at_first = first == (uint32_t)i ? v[i] : at_first;
+            word = v[i] == kEmptySlot ? (uint32_t)i : word;
+        }
+        word = at_first == kEmptySlot ? first : word;
+        found = there ? 1 : 2;
+        if (!there) {
+            if (word < (uint32_t)W) {
+                const uint32_t old = atomicCAS(&table[h + word], kEmptySlot, id);
+                found = old == kEmptySlot ? 0 : old == id ? 1 : 2;  // another lane's id, or a bucket that has changed
+            } else {
+                h = (h + W) & mask;
+            }
+        }
+    } while (found == 2);
+    return found == 0;
 }
 
 // TEAM wavefronts serve one query (one workgroup of 64 * TEAM lanes).  Wavefront 0, the leader, owns
@@ -65,6 +94,7 @@ struct BeamSearch {
     static constexpr int UP = U <= 1 ? 1 : U <= 2 ? 2 : U <= 4 ? 4 : 8;                                // U or the next power of two
     static constexpr int BR = LPL >= 2 ? 2 : 1;                       // registers of a sort batch
     static constexpr int kInsertMax = 8;                // at most this many new keys are inserted one by one
+    static constexpr int HW = Row::kDtype == kU8 ? 2 : 4;  // words of a hash bucket; four take registers that the small uint8 variants do not have
 
     const SearchParams& p;
     int lane;
@@ -103,7 +133,7 @@ struct BeamSearch {
         wtab = parents + 64;
         team = wtab + 32;
         bitmap = team + kTeamWords;
-        table = bitmap + (p.window_bits >> 5);
+        table = bitmap + hash_at(p.window_bits);
         n_windows = n_table = n_dist = n_parents = n_resets = 0;
         w0_lo = w0_size = n_keys = 0;
     }
@@ -147,7 +177,7 @@ struct BeamSearch {
             const uint32_t m = 1u << (bit & 31);
             return (atomicOr(&bitmap[bit >> 5], m) & m) ? 0 : 1;
         }
-        return hash_insert(table, p.hash_bits, id) ? 2 : 0;
+        return hash_insert<HW>(table, p.hash_bits, id) ? 2 : 0;
     }
 
     // Empties the hash and puts back the list's ids that no window covers.
@@ -158,7 +188,7 @@ struct BeamSearch {
         for (int r = 0; r < LPL; ++r) {
             const uint32_t id = (uint32_t)L[r] >> 1;
             const bool put = L[r] != kInfKey && window_bit(id) < 0;
-            if (put) hash_insert(table, p.hash_bits, id);
+            if (put) hash_insert<HW>(table, p.hash_bits, id);
             n_table += __builtin_popcountll(__ballot(put));
         }
         ++n_resets;

@@ -252,6 +252,33 @@ def test_small_visited_hash_forces_resets(oracle, torch_cuda, team):
     assert gc[:, 3].max() >= 1 and (gc[:, 1] > oc["n_dist"]).any()
 
 
+@pytest.mark.parametrize("team", [1, 2])
+@pytest.mark.parametrize("dt,dim,itopk,width,degree,nq", [
+    ("u8", 128, 64, 4, 16, 40),      # buckets of two words, a hash that is never emptied
+    ("u8", 96, 256, 4, 32, 3_000),   # and one that is
+    ("f16", 200, 100, 3, 27, 40),    # of four
+    ("f32", 100, 128, 8, 32, 3_000),
+])
+def test_visited_hash_knows_every_id_once(oracle, torch_cuda, dt, dim, itopk, width, degree, nq, team):
+    """Entries over the whole index: what has been scored is in the hash alone.  As long as it is not emptied a row is scored once,
+    also where the graph names it several times in a round.  Small whole numbers: float keys are exact."""
+    from paper_2512_02278_amd import ann
+
+    rng = np.random.default_rng(dim)
+    n = 5_000
+    x = rng.integers(0, 9, (n, dim)).astype(NP_DT[dt])
+    g = rng.integers(0, n, (n, degree)).astype(np.int32)
+    g[:, 1::3] = g[:, 0:1]                          # an id several times in a row
+    g[:, 2] = rng.integers(0, 40, n)                # and in many rows
+    g[rng.random((n, degree)) > 0.95] = -1
+    q = rng.integers(0, 9, (nq, dim)).astype(NP_DT[dt])
+    gc, oc = check_exact(oracle, torch_cuda, x, g, q, 10, itopk, width, 200, n_entry=32, seed=3,
+                         options={ann.ANN_OPT_WAVEFRONTS_PER_QUERY: team})
+    kept = gc[:, 3] == 0
+    assert np.array_equal(gc[kept, 1], oc["n_dist"][kept])
+    assert kept.all() if nq == 40 else True
+
+
 @pytest.mark.parametrize("window_bits,route_c", [(8192, 1), (8192, 3), (512, 2), (96, 1)])
 def test_visited_bitmap_windows(oracle, torch_cuda, window_bits, route_c):
     """The visited bitmap covers the routed clusters' id ranges; ids beyond it (other
