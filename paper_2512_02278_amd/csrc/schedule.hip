@@ -11,6 +11,7 @@
 #include <hip/hip_runtime.h>
 
 #include "schedule.h"
+#include "wave.h"
 
 namespace ann {
 
@@ -61,27 +62,27 @@ __global__ void __launch_bounds__(256) cluster_scatter_kernel(const int32_t* rou
 }
 
 // The same in one launch for batches and cluster counts that one workgroup gets through in about the time that the
-// four launches' own latencies add up to, a counter per cluster in LDS: 7 us for 5 000 queries (four launches: 19 us),
-// 21 us for 20 000 (27 us).
+// four launches' own latencies add up to, a counter per cluster in LDS.  What the count returns is a query's place in its cluster, and
+// both stay in the thread's registers until the scan is done: 5 000 queries 5.4 us (7.2 with the routes read and counted
+// a second time), 10 000 7.9 (13.0), 20 000 14.4 (21.1; four launches: 27).  U: queries of a thread, all their routes in flight.
 constexpr int kSmallOrderQueries = 24576, kSmallOrderClusters = 8192;
+template <int U>
 __global__ void __launch_bounds__(1024) small_cluster_order_kernel(const int32_t* __restrict__ route, int route_c, int nq,
                                                                    int n_clusters, int32_t* __restrict__ order) {
     __shared__ int32_t counts[kSmallOrderClusters];
     __shared__ int32_t wave_sums[16];
-    constexpr int U = 8;  // routes in flight per thread
     const int t = threadIdx.x;
+    uint32_t at[U];  // a query's cluster, and then its place among those of the cluster (16 bits each)
+#pragma unroll
+    for (int u = 0; u < U; ++u) at[u] = (uint32_t)route[(uint32_t)min(u * 1024 + t, nq - 1) * (uint32_t)route_c];
     for (int c = t; c < n_clusters; c += 1024) counts[c] = 0;
     __syncthreads();
-    for (int q0 = 0; q0 < nq; q0 += 1024 * U) {
-        int32_t b[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int q = q0 + u * 1024 + t;
-            b[u] = q < nq ? bucket_of(route[(int64_t)q * route_c], n_clusters) : -1;
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-            if (b[u] >= 0) atomicAdd(&counts[b[u]], 1);
+    for (int u = 0; u < U; ++u) {
+        const uint32_t b = (uint32_t)bucket_of((int32_t)at[u], n_clusters);
+        uint32_t place = 0;
+        if (u * 1024 + t < nq) place = (uint32_t)__hip_atomic_fetch_add(&counts[b], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        at[u] = b << 16 | place;
     }
     __syncthreads();
     // exclusive scan: every thread's run of clusters, the wavefront's threads, the wavefronts
@@ -89,11 +90,7 @@ __global__ void __launch_bounds__(1024) small_cluster_order_kernel(const int32_t
     const int lo = min(t * per, n_clusters), hi = min(lo + per, n_clusters);
     int32_t sum = 0;
     for (int c = lo; c < hi; ++c) sum += counts[c];
-    int32_t upto = sum;
-    for (int d = 1; d < 64; d <<= 1) {
-        const int32_t below = __shfl_up(upto, d);
-        if ((t & 63) >= d) upto += below;
-    }
+    const int32_t upto = (int32_t)wave_inclusive_sum((uint32_t)sum);
     if ((t & 63) == 63) wave_sums[t >> 6] = upto;
     __syncthreads();
     int32_t run = upto - sum;
@@ -104,23 +101,17 @@ __global__ void __launch_bounds__(1024) small_cluster_order_kernel(const int32_t
         run += n;
     }
     __syncthreads();
-    for (int q0 = 0; q0 < nq; q0 += 1024 * U) {
-        int32_t b[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int q = q0 + u * 1024 + t;
-            b[u] = q < nq ? bucket_of(route[(int64_t)q * route_c], n_clusters) : -1;
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-            if (b[u] >= 0) order[atomicAdd(&counts[b[u]], 1)] = q0 + u * 1024 + t;
-    }
+    for (int u = 0; u < U; ++u)
+        if (u * 1024 + t < nq) order[counts[at[u] >> 16] + (int)(at[u] & 0xffffu)] = u * 1024 + t;
 }
 
 hipError_t launch_cluster_order(const int32_t* route, int route_c, int64_t nq, int n_clusters, int32_t* counts,
                                 int32_t* order, hipStream_t stream) {
     if (nq <= kSmallOrderQueries && n_clusters <= kSmallOrderClusters) {
-        hipLaunchKernelGGL(small_cluster_order_kernel, dim3(1), dim3(1024), 0, stream, route, route_c, (int)nq, n_clusters, order);
+        const auto kernel = nq <= 4 * 1024 ? small_cluster_order_kernel<4> : nq <= 12 * 1024 ? small_cluster_order_kernel<12>
+                                                                                          : small_cluster_order_kernel<kSmallOrderQueries / 1024>;
+        hipLaunchKernelGGL(kernel, dim3(1), dim3(1024), 0, stream, route, route_c, (int)nq, n_clusters, order);
         return hipGetLastError();
     }
     const unsigned blocks = (unsigned)((nq + 255) / 256 < 4096 ? (nq + 255) / 256 : 4096);

@@ -965,6 +965,34 @@ def test_key_table_gives_the_bits_of_the_gathering_search(torch_cuda, dt, dim, m
     ann.ann_free(h)
 
 
+@pytest.mark.parametrize("nq", [1, 1_023, 4_096, 4_097, 12_288, 12_289, 24_576, 24_577])
+@pytest.mark.parametrize("n_clusters", [1, 1_023, 8_192, 8_193])
+def test_execution_order_of_small_batches_names_every_query_once(torch_cuda, nq, n_clusters):
+    """At the edges of the order kernels' variants, with routes that name no cluster: a query that the order left out would keep
+    what its result held before."""
+    from paper_2512_02278_amd import ann
+
+    torch, dev, dim = torch_cuda, "cuda:0", 8
+    g = torch.Generator(device=dev).manual_seed(nq + n_clusters)
+    n = 2 * n_clusters
+    x = torch.randn((n, dim), generator=g, device=dev)
+    graph = torch.randint(0, n, (n, 2), generator=g, device=dev, dtype=torch.int32)
+    off = 2 * torch.arange(n_clusters + 1, device=dev)
+    h = ann.ann_index_load(x, graph, n_entry=2, entry_mode=1, seed=2, centroids=x[:n_clusters].contiguous(), cluster_offsets=off, route_c=1)
+    q = torch.randn((nq, dim), generator=g, device=dev)
+    routes = torch.randint(-1, n_clusters + 1, (nq,), generator=g, device=dev, dtype=torch.int32)
+    got = []
+    for least in (-1, 0):
+        ann.ann_index_set_option(h, ann.ANN_OPT_CLUSTER_ORDER_MIN_QUERIES, least)
+        ids = torch.full((nq, 2), -7, dtype=torch.int32, device=dev)
+        keys = torch.full((nq, 2), -7.0, device=dev)
+        ann.ann_search(h, q, 2, 4, 1, 2, out_ids=ids, out_dists=keys, routes=routes)
+        got.append((ids, keys.view(torch.int32)))
+    torch.cuda.synchronize()
+    ann.ann_free(h)
+    assert all(torch.equal(a, b) for a, b in zip(*got)) and not bool((got[1][0] == -7).any())
+
+
 @pytest.mark.parametrize("metric", [0, 1])
 @pytest.mark.parametrize("n_clusters,nq,levels", [
     (4096, 66_000, 256),    # one slice of whole tiles
