@@ -634,6 +634,15 @@ struct BeamSearch {
         }
     }
 
+    // A barrier after which the team sees what this wavefront has left in LDS.  The wait is written out: before a barrier at the head
+    // of a loop the compiler leaves out the one that __syncthreads stands for (the LDS writes of publish() were still under way when
+    // the others read what it had published; with other kernels on the compute unit one call in five hundred scored an earlier
+    // round's ids, or whatever had been in LDS before).
+    __device__ __forceinline__ static void team_barrier() {
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __syncthreads();
+    }
+
     // Two workgroup barriers per round: before the scoring step (the leader has left the round's ids, their
     // count and the list's worst key in LDS) and after it (every wavefront's keys are in ckey).  Between the
     // second barrier and the next first one only the leader works: merge, parents, graph rows, visited filter.
@@ -647,12 +656,12 @@ struct BeamSearch {
             publish(m, 0);
         }
         for (;;) {
-            __syncthreads();
+            team_barrier();
             const int m = (int)team[kTeamM];
             if (team[kTeamDone] != 0u) break;
             worst = ((uint64_t)team[kTeamWorst + 1] << 32) | team[kTeamWorst];
             score(m);
-            __syncthreads();
+            team_barrier();
             if (leader) {
                 n_dist += m;
                 merge_all((int)team[kTeamKept]);
