@@ -289,42 +289,49 @@ struct RankSearch {
         for (; iters < p.max_iters; ++iters) {
             const uint64_t scored = *reinterpret_cast<const uint64_t*>(bits + 2 * lane);
             const uint64_t open = scored & ~done;
-            const int count = __builtin_popcountll(scored);
-            const int upto = (int)wave_inclusive_sum((uint32_t)count);
-            uint64_t lanes = __ballot(open != 0);
-            // the list ends with bit `cut` of lane `edge`
-            const uint64_t beyond = __ballot(upto >= p.itopk);
-            int edge = 64;
-            uint64_t in_edge = ~0ull;
-            if (beyond) {
+            const uint64_t any_open = __ballot(open != 0);
+            // The first `width` open entries.  A rank below itopk is in the list whatever has been scored; where the last one taken
+            // lies beyond, the list's end is looked for and they are taken again.
+            bool again = false;
+            int np, last, edge = 64;  // the list ends with the bits in_edge of lane `edge`
+            uint64_t in_edge = ~0ull, closed;
+            for (;;) {  // uniform, twice at most
+                uint64_t lanes = edge < 64 ? any_open & (2ull * (1ull << edge) - 1ull) : any_open;
+                np = last = 0;
+                closed = done;
+                while (lanes) {
+                    const int l = __builtin_ctzll(lanes);
+                    lanes &= lanes - 1;
+                    const uint64_t word = lane_word(open, l) & (l == edge ? in_edge : ~0ull);
+                    const int at = rank_below(word, np);
+                    const uint64_t taken = __ballot(at < p.width) & word;
+                    if (__builtin_amdgcn_inverse_ballot_w64(taken)) parents[at] = (uint32_t)(2 * (l * 64 + lane));
+                    if (taken) last = l * 64 + 63 - __builtin_clzll(taken);
+                    closed |= lane == l ? taken : 0ull;
+                    np += __builtin_popcountll(taken);
+                    if (np >= p.width) break;
+                }
+                if (last < p.itopk || edge < 64) break;
+                const int count = __builtin_popcountll(scored);
+                const int upto = (int)wave_inclusive_sum((uint32_t)count);
+                const uint64_t beyond = __ballot(upto >= p.itopk);
+                if (!beyond) break;
                 edge = __builtin_ctzll(beyond);
                 const int left = p.itopk - (__builtin_amdgcn_readlane(upto, edge) - __builtin_amdgcn_readlane(count, edge));
                 const uint64_t word = lane_word(scored, edge);
                 const uint64_t cut = __ballot(rank_below(word) == left - 1) & word;  // one bit
                 in_edge = cut | (cut - 1);
-                lanes &= 2ull * (1ull << edge) - 1ull;
+                if (last <= edge * 64 + __builtin_ctzll(cut)) break;
+                again = true;
             }
-            // the first `width` open entries
-            int np = 0, last = 0;
-            while (lanes) {  // uniform
-                const int l = __builtin_ctzll(lanes);
-                lanes &= lanes - 1;
-                const uint64_t word = lane_word(open, l) & (l == edge ? in_edge : ~0ull);
-                const int at = rank_below(word, np);
-                const uint64_t taken = __ballot(at < p.width) & word;
-                if (__builtin_amdgcn_inverse_ballot_w64(taken)) parents[at] = (uint32_t)(2 * (l * 64 + lane));
-                if (taken) last = l * 64 + 63 - __builtin_clzll(taken);
-                done |= lane == l ? taken : 0ull;
-                np += __builtin_popcountll(taken);
-                if (np >= p.width) break;
-            }
+            done = closed;
             if (np == 0) break;
             if (last >= near) return false;
             n_parents += np;
             lds_order();
-            if (iters == 0) {
-                // Lanes without a parent read for one that has been expanded before, which marks nothing new: from the second round
-                // on that is what their places hold.
+            if (iters == 0 || again) {
+                // Lanes without a parent read for one that is expanded anyhow, which marks nothing new: their places hold those of earlier
+                // rounds, unless there was none or more had been taken at first.
                 const uint32_t first = parents[0];
                 if (lane >= np) parents[lane] = first;
                 lds_order();
