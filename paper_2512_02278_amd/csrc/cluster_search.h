@@ -236,8 +236,7 @@ struct ClusterSearch {
                 if (r == 0 || total < p.width) {  // uniform
                     const uint64_t b = __ballot((L[r] & 1u) == 0u) & listed[r];
                     const int rank = rank_below(b, total);
-                    // (a lane below the mask's last bit may be outside it)
-                    const bool take = ((L[r] & 1u) == 0u) && rank < p.width && r * 64 + lane < p.itopk;
+                    const bool take = __builtin_amdgcn_inverse_ballot_w64(__ballot(rank < p.width) & b);
                     if (take) parents[rank] = (L[r] >> 1) & row_mask;
                     L[r] |= take ? 1u : 0u;
                     total += __builtin_popcountll(b);
@@ -247,8 +246,13 @@ struct ClusterSearch {
             const int np = total < p.width ? total : p.width;
             n_parents += np;
             lds_order();
-            // a place of `parents` beyond np holds a row of an earlier round, or row 0
-            const int nref = np * p.degree;
+            // Lanes without a parent read for one that has been expanded before, whose neighbours' words are gone: from the second round
+            // on that is what the places of `parents` beyond np hold.
+            if (iters == 0) {
+                const uint32_t first = parents[0];
+                if (lane >= np) parents[lane] = first;
+                lds_order();
+            }
             uint64_t foreign = 0;
             uint32_t at[CPL];
 #pragma unroll
@@ -257,19 +261,19 @@ struct ClusterSearch {
 #pragma unroll
                 for (int t = 0; t < CPL; ++t) rel[t] = graph[at[t]];
 #pragma unroll
-                for (int t = 0; t < CPL; ++t) {
-                    foreign |= __ballot(rel[t] == 0xfffeu) & __ballot(t * 64 + lane < nref);
-                    rel[t] = t * 64 + lane < nref ? rel[t] : kNone;
-                }
+                for (int t = 0; t < CPL; ++t) foreign |= __ballot(rel[t] == 0xfffeu);
             } else {
-                uint32_t id[CPL];
+                uint32_t most = 0;
 #pragma unroll
-                for (int t = 0; t < CPL; ++t) id[t] = *reinterpret_cast<const uint32_t*>(rows + at[t] * 4u);
+                for (int t = 0; t < CPL; ++t) rel[t] = *reinterpret_cast<const uint32_t*>(rows + at[t] * 4u);
 #pragma unroll
                 for (int t = 0; t < CPL; ++t) {
-                    id[t] = t * 64 + lane < nref ? id[t] : kNone;
-                    rel[t] = id[t] - (uint32_t)lo;
-                    foreign |= __ballot(rel[t] >= size) & __ballot(id[t] < (uint32_t)p.n);
+                    rel[t] -= (uint32_t)lo;
+                    most = max(most, rel[t]);
+                }
+                if (__any(most >= size)) {
+#pragma unroll
+                    for (int t = 0; t < CPL; ++t) foreign |= __ballot(rel[t] >= size) & __ballot(rel[t] + (uint32_t)lo < (uint32_t)p.n);
                 }
             }
             if (!score(rel, foreign)) return false;
