@@ -890,7 +890,7 @@ void rank_rows(const ann_index_t* h, int64_t nq, int itopk, int width, int max_i
     const double anew = h->leaving * (double)(parents * h->d.degree);
     if (anew > 1.0 / 128 || (nq < kMinQueriesForClusterOrder && anew * (double)nq > 0.5)) return;
     const int64_t mean = h->d.n / h->d.n_clusters, longest = h->longest_cluster < stride ? h->longest_cluster : stride;
-    if (mean > kMaxRankRows) return;
+    if (mean > kMaxRankRows || stride % 64 != 0) return;  // a query's keys are read 64 at a time (a window option may cut the stride)
     // Ranking costs as much as there are rows; it saves, a round, what the list and the neighbours cost beyond the search for
     // bits that are set.
     const int64_t rounds = (parents + width - 1) / width;

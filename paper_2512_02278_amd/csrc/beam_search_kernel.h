@@ -80,7 +80,8 @@ __device__ __forceinline__ bool hash_insert(uint32_t* table, int hash_bits, uint
 //
 // TABLE: the keys of a query against the first table_stride rows of its (only) window have been computed beforehand
 // (key_table.h), so a new id among them costs one 4-byte read instead of a row gather and its arithmetic.
-// Other ids are gathered as ever, and the visited set is the same as without a table.  Such a search takes 0.27 ms for 5 000
+// Other ids are gathered as ever, and the visited set is the same as without a table.  (Most queries with a table are searched by rank,
+// rank_search.h; this is for those that search leaves, and for calls that it would not make faster.)  Such a search takes 0.27 ms for 5 000
 // queries over 1536-byte rows (512 neighbours a round) that took 1.98 ms with gathers, and 0.82 ms for 20 000 over 384-byte rows
 // instead of 1.33 ms.  0.44 and 0.64 of the vector-ALU issue slots are used then; the rest waits for graph rows and LDS.
 //

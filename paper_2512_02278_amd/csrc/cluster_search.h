@@ -20,10 +20,11 @@
 //
 // Everything is exact integer arithmetic: ids, keys, rounds and counters are those of the gathering search.
 //
-// Measured (before: beam_search_kernel): 500 000 queries, clusters of 1 953 rows of 128 bytes, list of 184: 7.3 ms (9.35), 5 360 vector
-// instructions a query (11 400); 10 000 queries, clusters of 1 000: 116 us (187); 100 queries, clusters of 100: 25 us (43).  What bounds it
+// Measured (before: beam_search_kernel): 500 000 queries, clusters of 1 953 rows of 128 bytes, list of 184: 7.1 ms (9.35), 5 080 vector
+// instructions a query (11 400); 10 000 queries, clusters of 1 000: 100 to 116 us (187); 100 queries, clusters of 100: 25 us (43).  What bounds it
 // now: sixteen wavefronts of a compute unit find room in LDS with clusters of two thousand rows, and a round is a chain of two LDS round trips,
-// one graph row from L2 and some 70 vector and 65 scalar instructions; the vector ALUs are 0.6 busy.  Tables of 16 bits per row
+// one graph row from L2 and some 65 vector and 60 scalar instructions; the vector ALUs are 0.6 busy.  The making of the keys is 28 % of
+// a wavefront's time (three or four tiles of rows in flight instead of two change nothing), waiting for the slowest of eight queries 10 %.  Tables of 16 bits per row
 // (twice the wavefronts) need a second pass over the cluster for the smallest key, which cost what they saved (7.9 ms); loads of the
 // rows in the order of the matrix operand, without the stage, kept the address units busy with 16 bytes at a time (1.7 ms for the
 // making of the keys, 2.5 without).

@@ -19,9 +19,9 @@
 // One wavefront per query.
 //
 // Measured (before: beam_search_kernel with the table): 20 000 queries, clusters of 2 441 rows, list of 256, 256 neighbours a round: 0.506 ms (0.82; 0.52
-// with the list's end looked for in every round), some 8 300 vector instructions a query (15 200); 5 000 queries, clusters of 2 441, 512 neighbours:
+// with the list's end looked for in every round), 7 900 vector instructions a query (15 200); 5 000 queries, clusters of 2 441, 512 neighbours:
 // 0.163 ms (0.265).  Of a query's time a third is the ranking; a round is a chain of five LDS round trips and a graph row from L2 or the memory-side
-// cache.  Vector ALUs 0.6 busy, LDS 0.47.  With all places settled and the rows of all ranks in LDS thirteen wavefronts of a compute unit found
+// cache.  Vector ALUs 0.54 busy, LDS 0.47, half of that with bank conflicts.  With all places settled and the rows of all ranks in LDS thirteen wavefronts of a compute unit found
 // room instead of eighteen (0.69 ms); as a first part of beam_search_kernel its registers were those of both (0.60 ms).
 #pragma once
 
