@@ -685,25 +685,28 @@ template <class Row, int LPL, int CPL, int TEAM, bool TABLE>
 __global__ void __launch_bounds__(64 * TEAM, (TEAM == 1 && Row::kDtype == kU8 && Row::G * Row::NCH <= 16 && LPL <= 4 && CPL <= 2) ? 7 : 1)
     beam_search_kernel(const SearchParams p) {
     extern __shared__ uint32_t lds[];
-    if constexpr (TABLE) {
-        if (p.again) {
-            // only the queries that the search by rank (rank_search.h) has left
-            for (int i = (int)blockIdx.x; i < p.again[0]; i += (int)gridDim.x) {
-                const int32_t local = p.again[1 + i];
-                BeamSearch<Row, LPL, CPL, 1, true> s(p, lds, lane_id(), 0);
-                s.keys = p.table + (int64_t)local * p.table_stride;
-                s.run(p.order[p.q_base + local]);
-                s.lds_sync();
-            }
-            return;
-        }
-    }
     const int64_t b = blockIdx.x;
     const int64_t local = (b & 7) * p.q_per_xcd + (b >> 3);
     if (local >= p.q_count) return;  // the whole workgroup
     BeamSearch<Row, LPL, CPL, TEAM, TABLE> s(p, lds, lane_id(), TEAM == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)));
     if constexpr (TABLE) s.keys = p.table + local * p.table_stride;
     s.run(p.order ? (int64_t)p.order[p.q_base + local] : p.q_base + local);
+}
+
+// The queries that the search by rank (rank_search.h) has left, any number of them to a workgroup.  A kernel of its own: the loop keeps what
+// it can in registers from query to query, 12 to 41 more of them, which would take the search with a table a wavefront or two per SIMD.
+template <class Row, int LPL, int CPL>
+__global__ void __launch_bounds__(64) left_over_search_kernel(const SearchParams p) {
+    extern __shared__ uint32_t lds[];
+    for (int i = (int)blockIdx.x; i < p.again[0]; i += (int)gridDim.x) {
+        const int32_t local = p.again[1 + i];
+        int lane = lane_id();
+        asm volatile("" : "+v"(lane));  // another one for each query: nothing that depends on it is kept
+        BeamSearch<Row, LPL, CPL, 1, true> s(p, lds, lane, 0);
+        s.keys = p.table + (int64_t)local * p.table_stride;
+        s.run(p.order[p.q_base + local]);
+        s.lds_sync();
+    }
 }
 
 }  // namespace ann

@@ -31,7 +31,11 @@ hipError_t launch_route(const RouteParams& p, hipStream_t stream);
 #define ANN_LAUNCH_LIST(LPL, CPL)                                                                                                \
     if constexpr (Row::kDtype != kU8) { /* no uint8 index has a table */                                                         \
         if (p.table) {                                                                                                           \
-            hipLaunchKernelGGL((beam_search_kernel<Row, LPL, CPL, 1, true>), dim3(grid), dim3(64), lds_bytes, stream, p);        \
+            if (p.again) { /* a round of 64 neighbours at most is not ranked */                                                  \
+                if constexpr (CPL > 1) hipLaunchKernelGGL((left_over_search_kernel<Row, LPL, CPL>), dim3(grid), dim3(64), lds_bytes, stream, p); \
+            } else {                                                                                                             \
+                hipLaunchKernelGGL((beam_search_kernel<Row, LPL, CPL, 1, true>), dim3(grid), dim3(64), lds_bytes, stream, p);    \
+            }                                                                                                                    \
             break;                                                                                                               \
         }                                                                                                                        \
     }                                                                                                                            \
