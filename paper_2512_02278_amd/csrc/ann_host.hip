@@ -244,7 +244,7 @@ static __global__ void __launch_bounds__(64) sample_clusters_kernel(ann_index_de
     const int lane = lane_id();
     const int64_t* const off = static_cast<const int64_t*>(d.cluster_offsets);
     const unsigned long long longest = sample->longest;
-    if (longest > (unsigned long long)kMaxClusterRows) return;
+    if (d.dtype == ANN_U8 && longest > (unsigned long long)kMaxClusterRows) return;  // not searched by whole clusters whatever is found
     uint32_t leaving = 0;
     for (int64_t run = blockIdx.x; run < runs; run += gridDim.x) {
         const int64_t row = run * step + lane;

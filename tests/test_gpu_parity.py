@@ -1534,6 +1534,37 @@ def test_search_by_rank_gives_the_bits_of_the_gathering_search(torch_cuda, dt, d
     assert all(torch.equal(a, b) for a, b in zip(*got))
 
 
+@pytest.mark.parametrize("leaving", [False, True])
+def test_edges_that_leave_are_counted_beside_a_long_cluster(torch_cuda, leaving):
+    """One cluster of 9 000 rows among a thousand of 1 300: the load counts the edges that leave their clusters all the same, and queries
+    that would meet them are not ranked."""
+    from paper_2512_02278_amd import ann
+
+    torch, dev, nq, degree = torch_cuda, "cuda:0", 20_000, 64
+    gen = torch.Generator(device=dev).manual_seed(12)
+    sizes = torch.full((1_001,), 1_300, dtype=torch.int64, device=dev)
+    sizes[77] = 9_000
+    off = torch.cat([torch.zeros(1, dtype=torch.int64, device=dev), sizes.cumsum(0)])
+    n = int(off[-1])
+    lab = torch.repeat_interleave(torch.arange(sizes.numel(), device=dev), sizes)
+    cen = torch.randn((sizes.numel(), 64), generator=gen, device=dev)
+    x = cen[lab] + 0.7 * torch.randn((n, 64), generator=gen, device=dev)
+    g = off[lab, None] + (torch.rand((n, degree), generator=gen, device=dev) * sizes[lab, None]).long()
+    if leaving:
+        g[:, 0] = torch.randint(0, n, (n,), generator=gen, device=dev)
+    q = x[torch.randint(0, n, (nq,), generator=gen, device=dev)] + 0.1 * torch.randn((nq, 64), generator=gen, device=dev)
+    h = ann.ann_index_load(x, g.int(), n_entry=32, entry_mode=1, seed=4, centroids=cen, cluster_offsets=off, route_c=1)
+    routes = torch.randint(0, sizes.numel(), (nq,), generator=gen, device=dev, dtype=torch.int32)
+    got = []
+    for team in (0, 1):
+        ann.ann_index_set_option(h, ann.ANN_OPT_WAVEFRONTS_PER_QUERY, team)
+        names = kernels_of(torch, lambda: got.append(ann.ann_search(h, q, 10, 256, 4, 100, routes=routes)))
+        assert ("rank_search_kernel" in names) == (team == 0 and not leaving), names
+        assert ("key_table_kernel" in names) == (team == 0), names
+    ann.ann_free(h)
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1].view(torch.int32), got[1][1].view(torch.int32))
+
+
 @pytest.mark.parametrize("metric", [0, 1])
 @pytest.mark.parametrize("dim,sizes,itopk,width,degree,n_entry,nq,far", [
     (128, (100, 1, 0, 15, 16, 17, 111, 64), 64, 1, 32, 32, 100, 0.0),        # one query per workgroup, graph rows in LDS
