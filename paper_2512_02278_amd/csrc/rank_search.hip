@@ -9,32 +9,46 @@ template <int CPL>
 struct RankSearch {
     static constexpr int kHalo = kRankHalo, kTile = kRankTile;
     static constexpr uint32_t kNobody = 128u << 7;
+    // A row on its way to its place is tagged with the last bits of its bucket.  Neighbours with one tag are of one bucket, or their
+    // buckets are sixteen or more apart: then their keys are in order, and nothing comes of taking them for one.
+    static constexpr int kTag = 12;
+    static constexpr uint32_t kTagged = (1u << kTag) - 1u;
+    static constexpr uint32_t kMostCrowded = kRankBitWords + 64 - 1;  // what the words of bits and parents hold
+    static_assert(kMaxRankRows <= 1 << kTag, "a row and a place fit in front of the tag");
 
     const SearchParams& p;
     const uint32_t* const keys;  // of rows lo .. lo + size - 1
     const int lane;
     uint32_t* const bits;        // a bit per rank
     uint32_t* const parents;     // twice their ranks
+    float* const begins;         // where bits are later: the bucket that a cell's first key falls into
+    uint32_t* const list;        // where bits and parents are later: how many buckets are crowded, then (first place << 8 | rows) of each
     uint16_t* const by_rank;     // row of a rank below `near`
     uint16_t* const code_of;     // rank of a row, as (rank / 32) << 7 | rank % 32
     uint8_t* const buckets;      // where code_of is later
     int64_t lo;
     int size;
     int near;                    // ranks from here on are in the order of the buckets only
-    float scale, shift;          // bucket = key * scale + shift
+    float least, scale;          // the smallest key; cells of the range of the keys
 
     __device__ __forceinline__ RankSearch(const SearchParams& p_, uint32_t* lds, const uint32_t* keys_, int lane_)
-        : p(p_), keys(keys_), lane(lane_), bits(lds), parents(lds + kRankBitWords), by_rank(reinterpret_cast<uint16_t*>(parents + 64)),
-          code_of(by_rank + 2 * rank_row_words(p_.rank_places)), buckets(reinterpret_cast<uint8_t*>(code_of)) {}
+        : p(p_), keys(keys_), lane(lane_), bits(lds), parents(lds + kRankBitWords), begins(reinterpret_cast<float*>(lds)), list(lds),
+          by_rank(reinterpret_cast<uint16_t*>(parents + 64)), code_of(by_rank + 2 * rank_row_words(p_.rank_places)), buckets(reinterpret_cast<uint8_t*>(code_of)) {}
 
     __device__ __forceinline__ static void lds_order() {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     }
-    __device__ __forceinline__ uint32_t bucket_of(float key) const {
-        // one rounding: monotonous
-        return (uint32_t)__builtin_amdgcn_fmed3f(__builtin_fmaf(key, scale, shift), 0.0f, (float)(kRankBuckets - 1));
+    // A key's cell and, behind the point, its place in it: 0 up to and without kRankCells.
+    __device__ __forceinline__ float cell_of(float key) const {
+        return __builtin_amdgcn_fmed3f((key - least) * scale, 0.0f, (float)kRankCells - 0x1p-17f);
+    }
+    // Every step rounds once, and the last one of a cell ends at most where the next cell's buckets begin: monotonous.
+    __device__ __forceinline__ uint32_t bucket_at(float cell) const {
+        const float* const at = begins + (uint32_t)cell;
+        const float first = at[0], buckets = at[1] - first;
+        return (uint32_t)__builtin_fmaf(__builtin_amdgcn_fractf(cell), buckets, first);
     }
     // Chunks of 512 rows, a register of 64 each; `work(first register, lane)` for those that there are.  (With a copy of the lane number
     // that the compiler cannot see through: it would keep the 48 row numbers in registers from chunk to chunk.)
@@ -50,6 +64,69 @@ struct RankSearch {
             }
     }
 
+    // Buckets of more rows than the tiles settle (kHalo + 1: a row of such a bucket passes kHalo others at most).  `words`: in a byte each, where a lane's buckets begin among its rows.
+    __device__ __forceinline__ void list_crowded(const uint32_t* words, uint32_t first, uint32_t rows, uint32_t stored) {
+#pragma unroll 1
+        for (int i = 0; i < 16; ++i) {
+            uint32_t from = words[lane * 16 + i];
+            const uint32_t after = i < 15 ? words[lane * 16 + i + 1] : rows;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const uint32_t start = from & 0xffu, end = (j < 3 ? from >> 8 : after) & 0xffu;
+                if (end - start > (uint32_t)(kHalo + 1) && first + start < stored) {
+                    const uint32_t at = __hip_atomic_fetch_add(list, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                    if (at < kMostCrowded) list[1 + at] = (first + start) << 8 | (end - start);
+                }
+                from >>= 8;
+            }
+        }
+    }
+    // Puts their rows in order, each by counting those below it, before the tiles are gone through.
+    __device__ __forceinline__ void settle_crowded(int stored) {
+        const uint32_t n = (uint32_t)__builtin_amdgcn_readfirstlane((int)list[0]);
+        for (uint32_t i = 0; i < n; ++i) {
+            const uint32_t which = (uint32_t)__builtin_amdgcn_readfirstlane((int)list[1 + i]);
+            const int start = (int)(which >> 8), rows = (int)(which & 0xffu);
+            if (start + rows > stored) {  // the last one, which not all places are kept of
+                near = start;
+                continue;
+            }
+            uint32_t row[4];
+            uint64_t at[4];
+            int below[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                row[c] = by_rank[start + min(c * 64 + lane, rows - 1)];
+                below[c] = 0;
+            }
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                if (c * 64 < rows) at[c] = (uint64_t)keys[row[c] & kTagged] << 32 | row[c];
+            if (rows <= 64) {
+                // copies of one row mostly are in order
+                const uint64_t next = (uint64_t)next_lane((uint32_t)(at[0] >> 32), 0xffffffffu) << 32 | next_lane((uint32_t)at[0], 0xffffffffu);
+                if (!__any(lane < rows - 1 && next < at[0])) continue;
+            }
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+#pragma unroll 1
+                for (int l = 0; l < min(rows - c * 64, 64); ++l) {
+                    const uint64_t other = lane_word(at[c], l);
+#pragma unroll
+                    for (int o = 0; o < 4; ++o)
+                        if (o * 64 < rows) below[o] += other < at[o] ? 1 : 0;
+                }
+            lds_order();
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                if (c * 64 + lane < rows) {
+                    by_rank[start + below[c]] = (uint16_t)row[c];
+                    code_of[row[c] & kTagged] = code(start + below[c]);  // `near` may come to lie among them
+                }
+            lds_order();
+        }
+    }
+
     __device__ __forceinline__ bool rank() {
         uint32_t key[kChunk * kChunks];  // of row 64 t + lane
         each_chunk([&](int t0, int lane) {
@@ -57,27 +134,44 @@ struct RankSearch {
             for (int t = t0; t < t0 + kChunk; ++t)
                 if (t * 64 < size) key[t] = keys[t * 64 + lane];  // a query's row of the table is whole 64s
         });
-        // buckets
-        const float k0 = ordered_to_float((uint32_t)__builtin_amdgcn_readfirstlane((int)key[0]));  // (beyond the rows: anything)
-        float sum = 0.0f, squares = 0.0f;
+        // the range of the keys, in cells
+        const uint32_t some = (uint32_t)__builtin_amdgcn_readfirstlane((int)key[0]);
+        uint32_t lowest = some, highest = some;
         each_chunk([&](int t0, int lane) {
 #pragma unroll
             for (int t = t0; t < t0 + kChunk; ++t) {
-                key[t] = __builtin_bit_cast(uint32_t, ordered_to_float(key[t]));
-                const float d = lane < size - t * 64 ? __builtin_bit_cast(float, key[t]) - k0 : 0.0f;
-                sum += d;
-                squares = __builtin_fmaf(d, d, squares);
+                const uint32_t of_row = lane < size - t * 64 ? key[t] : some;
+                lowest = min(lowest, of_row);
+                highest = max(highest, of_row);
             }
         });
-        sum = group_sum<64>(sum, lane);
-        squares = group_sum<64>(squares, lane);
-        const float n = (float)size, mean = sum / n, deviation = __builtin_sqrtf(squares / n - mean * mean);
-        scale = (float)kRankBuckets / (6.5f * deviation);
-        shift = 0.5f * (float)kRankBuckets - (k0 + mean) * scale;
+        least = ordered_to_float(~wave_max(~lowest));
+        const float range = ordered_to_float(wave_max(highest)) - least;
+        scale = (float)kRankCells / range;
         // (also keys that are no numbers, or all the same)
-        if (!(__builtin_fabsf(shift) < 1e30f && scale > 0.0f && scale < 1e30f)) return false;
+        if (!(range < 1e30f && scale < 1e30f)) return false;
+        uint32_t* const counts = bits;
+        reinterpret_cast<uint2*>(counts)[lane] = make_uint2(0u, 0u);
+        lds_order();
+        each_chunk([&](int t0, int lane) {
+#pragma unroll
+            for (int t = t0; t < t0 + kChunk; ++t) {
+                const float cell = cell_of(ordered_to_float(key[t]));
+                key[t] = __builtin_bit_cast(uint32_t, cell);
+                if (lane < size - t * 64) __hip_atomic_fetch_add(&counts[(uint32_t)cell], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            }
+        });
+        lds_order();
+        {
+            const uint2 held = reinterpret_cast<const uint2*>(counts)[lane];
+            const uint32_t upto = wave_inclusive_sum(held.x + held.y);
+            const float each = (float)(kRankBuckets - 1) / (float)size;
+            reinterpret_cast<float2*>(begins)[lane] = make_float2((float)(upto - held.y - held.x) * each, (float)(upto - held.y) * each);
+            if (lane == 63) begins[kRankCells] = (float)upto * each;
+        }
+        lds_order();
 
-        // how many rows every bucket holds; the key gives way to the bucket
+        // how many rows every bucket holds; the cell gives way to the bucket
 #pragma unroll
         for (int i = 0; i < kRankBuckets / 1024; ++i) reinterpret_cast<uint4*>(buckets)[i * 64 + lane] = make_uint4(0, 0, 0, 0);
         lds_order();
@@ -85,7 +179,7 @@ struct RankSearch {
         each_chunk([&](int t0, int lane) {
 #pragma unroll
             for (int t = t0; t < t0 + kChunk; ++t) {
-                key[t] = bucket_of(__builtin_bit_cast(float, key[t]));
+                key[t] = bucket_at(__builtin_bit_cast(float, key[t]));
                 if (lane < size - t * 64)
                     __hip_atomic_fetch_add(&words[key[t] >> 2], 1u << (8u * key[t] & 31u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             }
@@ -101,6 +195,11 @@ struct RankSearch {
             w[4 * i + 2] = v.z;
             w[4 * i + 3] = v.w;
         }
+        uint32_t crowded = 0;  // the high bit of a byte of more than kHalo + 1 rows (and now and then of the one above it)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) crowded |= w[i] | (w[i] + 0x01010101u * (127u - (kHalo + 1)));
+        const bool any_crowded = __any((crowded & 0x80808080u) != 0u);
+        if (any_crowded && lane == 0) list[0] = 0u;
         uint32_t before = 0, rows = 0;  // the rows so far, in every byte; their number
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
@@ -113,10 +212,16 @@ struct RankSearch {
         const uint32_t upto = wave_inclusive_sum(rows);
         if (__ballot(rows > 255u) || __builtin_amdgcn_readlane((int)upto, 63) != size) return false;
         const uint32_t first = upto - rows;
+        const int stored = min(size, p.rank_places + kHalo);
 #pragma unroll
         for (int i = 0; i < 4; ++i) reinterpret_cast<uint4*>(buckets)[lane * 4 + i] = make_uint4(w[4 * i], w[4 * i + 1], w[4 * i + 2], w[4 * i + 3]);
         lds_order();
-        // rows in the order of their buckets; the bucket gives way to the place
+        if (any_crowded) {
+            list_crowded(words, first, rows, (uint32_t)stored);
+            lds_order();
+            if ((uint32_t)__builtin_amdgcn_readfirstlane((int)list[0]) > kMostCrowded) return false;
+        }
+        // rows in the order of their buckets; the bucket gives way to the place, and a tag
         each_chunk([&](int t0, int lane) {
             constexpr int U = 4;
 #pragma unroll
@@ -132,25 +237,27 @@ struct RankSearch {
                 }
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
-                    key[t1 + u] = base[u] + __builtin_amdgcn_ubfe(old[u], 8u * key[t1 + u] & 31u, 8);
+                    const uint32_t b = key[t1 + u];
+                    key[t1 + u] = b << kTag | (base[u] + __builtin_amdgcn_ubfe(old[u], 8u * b & 31u, 8));
                     asm volatile("" : "+v"(key[t1 + u]));  // here, not at its use: there it would keep three registers
                 }
             }
         });
         lds_order();
-        const int stored = min(size, p.rank_places + kHalo);
         each_chunk([&](int t0, int lane) {
 #pragma unroll
             for (int t = t0; t < t0 + kChunk; ++t) {
                 if (lane < size - t * 64) {
-                    const int row = t * 64 + lane;
-                    code_of[row] = code((int)key[t]);
-                    if ((int)key[t] < stored) by_rank[key[t]] = (uint16_t)row;
+                    const uint32_t row = (uint32_t)(t * 64 + lane), at = key[t] & kTagged;
+                    code_of[row] = code((int)at);
+                    if ((int)at < stored) by_rank[at] = (uint16_t)((key[t] & ~kTagged) | row);
                 }
             }
         });
         if (lane == 0) code_of[size] = (uint16_t)kNobody;
         lds_order();
+        near = size;
+        if (any_crowded) settle_crowded(stored);
         // Tiles of places.  The middle lanes of a tile see all places that a row may have to pass.  Tiles are read before those in front
         // of them are written.
         constexpr int N = kRankTiles;
@@ -159,11 +266,10 @@ struct RankSearch {
 #pragma unroll
             for (int u = 0; u < N; ++u) next_row[u] = by_rank[min(max((t0 + u) * kTile - kHalo + lane, 0), stored - 1)];
 #pragma unroll
-            for (int u = 0; u < N; ++u) next_key[u] = keys[next_row[u]];
+            for (int u = 0; u < N; ++u) next_key[u] = keys[next_row[u] & kTagged];
         };
         read(0);
         const int places = min(size, p.rank_places);
-        near = size;
         for (int t0 = 0; t0 * kTile < places; t0 += N) {
             uint32_t row[N], at_key[N], other[N];
             uint64_t same[N], run[N], more = 0;
@@ -178,13 +284,13 @@ struct RankSearch {
 #pragma unroll
             for (int u = 0; u < N; ++u) {
                 const int at = (t0 + u) * kTile - kHalo + lane;
-                const uint32_t b = at >= 0 && at < stored ? bucket_of(ordered_to_float(at_key[u])) : 0x80000000u + (uint32_t)lane;
+                const uint32_t b = at >= 0 && at < stored ? row[u] >> kTag : 0x80000000u + (uint32_t)lane;
                 same[u] = run[u] = __ballot(b == next_lane(b, 0xffffffffu));  // as the next lane's
                 more |= run[u];
                 move[u] = 0;
             }
             for (int d = 1; more; ++d) {  // uniform
-                if (d > kHalo) return false;
+                if (d > kHalo) break;  // a crowded bucket, which is in order
                 uint64_t swap[N], equal[N], ties = 0;
 #pragma unroll
                 for (int u = 0; u < N; ++u) {
@@ -212,12 +318,12 @@ struct RankSearch {
             if (size > places && (t0 + N) * kTile >= places) {
                 // the last tile ends where a bucket does
                 const uint64_t begins = ~(same[N - 1] << 1) & ((1ull << (64 - kHalo)) - 1ull);
-                near = (t0 + N - 1) * kTile - kHalo + 63 - __builtin_clzll(begins);
+                near = min(near, (t0 + N - 1) * kTile - kHalo + 63 - __builtin_clzll(begins));
             }
 #pragma unroll
             for (int u = 0; u < N; ++u) {
                 const int at = (t0 + u) * kTile - kHalo + lane;
-                if (lane >= kHalo && lane < 64 - kHalo && at < near) by_rank[at + move[u]] = (uint16_t)row[u];
+                if (lane >= kHalo && lane < 64 - kHalo && at < near) by_rank[at + move[u]] = (uint16_t)(row[u] & kTagged);
             }
         }
         lds_order();

@@ -1470,10 +1470,18 @@ def test_routing_chunks_of_both_lengths(torch_cuda, dt, row_bytes, nq):
 
 def kernels_of(torch, call):
     """Names of the kernels that `call` launches."""
+    return " ".join(kernel_times(torch, call))
+
+
+def kernel_times(torch, call):
+    """Names of the kernels that `call` launches, and their time in microseconds."""
     with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as prof:
         call()
         torch.cuda.synchronize()
-    return " ".join(e.name for e in prof.events())
+    times = {}
+    for e in prof.events():
+        times[e.name] = times.get(e.name, 0.0) + e.device_time_total
+    return times
 
 
 @pytest.mark.parametrize("dt,dim,metric,sizes,k,itopk,width,degree,n_entry,iters,kind", [
@@ -1484,14 +1492,21 @@ def kernels_of(torch, call):
     ("f16", 128, 0, (256, 257, 288, 300), 256, 256, 8, 64, 32, 40, "plain"),
     ("f32", 128, 0, (280, 301), 128, 128, 2, 33, 1, 100, "plain"),
     ("f32", 96, 0, (700, 900), 10, 128, 4, 32, 32, 100, "copies"),       # equal keys, in buckets of two and of fifty
-    ("f32", 96, 0, (700, 900), 10, 128, 4, 32, 32, 100, "outlier"),      # nearly all rows in few buckets
+    ("f32", 96, 0, (2_900, 3_000), 10, 256, 4, 64, 32, 100, "many copies"),  # crowded buckets, some where the settled places end
+    ("f32", 96, 0, (1_900, 1_500), 10, 128, 4, 64, 32, 100, "many copies"),
+    ("f16", 128, 1, (900, 1_000), 70, 100, 4, 64, 5, 100, "many copies"),    # in all places
+    ("f32", 96, 0, (2_441, 2_000, 2_200), 10, 256, 4, 64, 32, 100, "groups"),  # rows near the query, far from the others
+    ("f16", 768, 1, (2_441, 1_900), 100, 256, 8, 64, 32, 100, "groups"),
+    ("f32", 96, 0, (2_441, 2_300), 10, 256, 4, 64, 32, 100, "tight groups"),   # three, and narrow
+    ("f32", 96, 0, (2_441, 2_300), 10, 256, 4, 64, 32, 100, "alone"),          # one row far nearer than all others
+    ("f32", 96, 0, (700, 900), 10, 128, 4, 32, 32, 100, "outlier"),      # nearly all rows in one cell
     ("f32", 96, 0, (700, 900), 10, 128, 4, 32, 32, 100, "infinite"),     # no buckets
     ("f32", 96, 0, (700, 900, 800), 10, 128, 4, 32, 32, 100, "far"),     # edges that leave a cluster
     ("f32", 96, 0, (700, 900), 100, 128, 4, 32, 32, 100, "sparse"),      # searches that end with less than k rows
 ])
 def test_search_by_rank_gives_the_bits_of_the_gathering_search(torch_cuda, dt, dim, metric, sizes, k, itopk, width, degree, n_entry, iters, kind):
     """Searches with a key table rank the rows of a cluster first.  Results and counters have the bits of the search that gathers
-    every row (a fixed team size asks for that one), also where a query is left to another search."""
+    every row (a fixed team size asks for that one), also where a query is left to another search, which is where it has to be only."""
     from paper_2512_02278_amd import ann
 
     torch, dev, nq = torch_cuda, "cuda:0", 4_200
@@ -1507,13 +1522,26 @@ def test_search_by_rank_gives_the_bits_of_the_gathering_search(torch_cuda, dt, d
     if kind == "copies":
         x[1:300:2] = x[0:300:2]
         x[off[1]:off[1] + 50] = x[off[1]]
+    if kind == "many copies":
+        for c in range(nc):
+            at = int(off[c])
+            for rows in (100, 14, 13, 15, 64, 65, 30) * 2:
+                if at + rows < off[c + 1]:
+                    x[at:at + rows] = x[at]
+                at += rows + 3
+            x[off[c]:off[c + 1]] = x[off[c] + rng.permutation(sizes[c])]
+    if kind == "groups" or kind == "tight groups":
+        of, own = (50, 0.5) if kind == "groups" else (3, 0.2)
+        middle = rng.standard_normal((nc * of, dim))
+        x = (cen[lab] + 0.7 * ((1 - own ** 2) ** 0.5 * middle[lab * of + rng.integers(0, of, n)] + own * rng.standard_normal((n, dim)))).astype(NP_DT[dt])
     if kind == "outlier":
         x[5] = 1e4
     if kind == "infinite":
         x[5, 3] = np.inf
     if kind == "sparse":
         g[rng.random((n, degree)) > 0.04] = -1
-    q = (x[rng.integers(6, n, nq)].astype(np.float64) + 0.1 * rng.standard_normal((nq, dim))).astype(NP_DT[dt])
+    near = rng.integers(6, n, nq)
+    q = (x[near].astype(np.float64) + (0.001 if kind == "alone" else 0.1) * rng.standard_normal((nq, dim))).astype(NP_DT[dt])
     to = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(dev)
     gt = to(g)
     h = ann.ann_index_load(to(x), gt, metric=metric, n_entry=n_entry, entry_mode=1, seed=4, centroids=to(cen.astype(NP_DT[dt])),
@@ -1521,14 +1549,22 @@ def test_search_by_rank_gives_the_bits_of_the_gathering_search(torch_cuda, dt, d
     if kind == "far":  # behind the load's back: with a share like this it would not have them ranked
         gt[off[1]:off[1] + 30, 3] = 0
     qt, routes = to(q), to(rng.integers(-1, nc, nq).astype(np.int32))
+    if kind.endswith("groups") or kind == "alone":
+        routes = to(lab[near].astype(np.int32))  # the cluster that the query is in
     got = []
     for team in (0, 1):
         ann.ann_index_set_option(h, ann.ANN_OPT_WAVEFRONTS_PER_QUERY, team)
         ids = torch.full((nq, k), -7, dtype=torch.int32, device=dev)
         keys = torch.empty((nq, k), dtype=torch.float32, device=dev)
         counters = torch.full((nq, 4), -7, dtype=torch.int32, device=dev)
-        names = kernels_of(torch, lambda: ann.ann_search(h, qt, k, itopk, width, iters, out_ids=ids, out_dists=keys, counters=counters, routes=routes))
+        times = kernel_times(torch, lambda: ann.ann_search(h, qt, k, itopk, width, iters, out_ids=ids, out_dists=keys, counters=counters, routes=routes))
+        names = " ".join(times)
         assert ("rank_search_kernel" in names) == (team == 0), names
+        if team == 0:
+            # without queries the launch that goes through those left ends at once
+            ranked, left = (sum(t for name, t in times.items() if what in name) for what in ("rank_search_kernel", "left_over_search_kernel"))
+            longest = min((n // nc * 3 // 2 + 127) // 64 * 64, 3_072)
+            assert (left > 12.0 + 0.15 * ranked) == (max(sizes) > longest or kind in ("outlier", "infinite", "far", "sparse")), (ranked, left)
         got.append((ids, keys.view(torch.int32), counters[:, :3]))
     ann.ann_free(h)
     assert all(torch.equal(a, b) for a, b in zip(*got))
