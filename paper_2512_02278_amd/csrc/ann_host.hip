@@ -72,6 +72,7 @@ constexpr int kDefaultWindowBits = 8192, kMaxWindowBits = 1 << 17;
 // From this batch size on, a routed batch is executed grouped by cluster (schedule.hip).
 constexpr int64_t kMinQueriesForClusterOrder = 16384;
 constexpr int64_t kTableBytes = 1ll << 30;
+constexpr int64_t kMinQueriesToLeaveSome = 20000;  // see rank_rows
 constexpr unsigned kLeftOverGrid = 2048;  // workgroups that go through the queries a search by rank leaves, mostly none
 
 }  // namespace ann
@@ -200,6 +201,7 @@ struct ann_index {
     int64_t longest_cluster;  // rows of the longest cluster, or a bound on it
     bool by_clusters;         // whether searches by whole clusters (cluster_search.h) were looked at and fit
     double leaving, far;      // shares of graph edges that leave their cluster, and of keys that are too far, if so
+    double in_long;           // share of the rows in clusters too long for the search by rank
 };
 
 using namespace ann;
@@ -224,18 +226,24 @@ struct ClusterSample {
     unsigned long long longest;  // rows of the longest cluster
     uint32_t leaving;            // sampled graph edges that leave the cluster
     uint32_t far;                // sampled keys that are too far above the smallest for a word of cluster_search.h
+    unsigned long long in_long;  // rows in clusters that are too long for the search by rank
 };
 
-// One workgroup: the longest cluster, and zeros for what sample_clusters_kernel adds up.
-static __global__ void __launch_bounds__(1024) longest_cluster_kernel(const int64_t* off, int n_clusters, ClusterSample* out) {
-    __shared__ unsigned long long longest;
-    if (threadIdx.x == 0) longest = 0;
+// One workgroup: the longest cluster, the rows in those of more than `most_ranked`, and zeros for what sample_clusters_kernel adds up.
+static __global__ void __launch_bounds__(1024) longest_cluster_kernel(const int64_t* off, int n_clusters, ClusterSample* out, int64_t most_ranked) {
+    __shared__ unsigned long long longest, in_long;
+    if (threadIdx.x == 0) longest = in_long = 0;
     __syncthreads();
-    int64_t most = 0;
-    for (int c = (int)threadIdx.x; c < n_clusters; c += 1024) most = max(most, off[c + 1] - off[c]);
+    int64_t most = 0, rows = 0;
+    for (int c = (int)threadIdx.x; c < n_clusters; c += 1024) {
+        const int64_t size = off[c + 1] - off[c];
+        most = max(most, size);
+        rows += size > most_ranked ? size : 0;
+    }
     atomicMax(&longest, (unsigned long long)most);
+    if (rows) atomicAdd(&in_long, (unsigned long long)rows);
     __syncthreads();
-    if (threadIdx.x == 0) *out = ClusterSample{longest, 0u, 0u};
+    if (threadIdx.x == 0) *out = ClusterSample{longest, 0u, 0u, in_long};
 }
 
 // A workgroup takes runs of 64 rows, `step` rows from start to start, and counts the graph edges that leave their cluster.  The first
@@ -342,6 +350,14 @@ extern "C" const char* ann_last_error(void) { return g_error; }
 
 namespace {
 
+// Keys per query of a key table, unless the visited bitmap is shorter: half as long again as the mean cluster; rows beyond are gathered.
+int64_t table_rows(const ann_index_t* h) {
+    const int64_t mean = h->d.n / h->d.n_clusters;
+    return (mean + mean / 2 + 127) / 64 * 64;
+}
+// Rows of the longest cluster that a search with such a table ranks.
+int64_t most_ranked(const ann_index_t* h) { return table_rows(h) < kMaxRankRows ? table_rows(h) : kMaxRankRows; }
+
 // Whether any call on the handle can search with a key table (table_stride).
 bool may_use_table(const ann_index_t* h) {
     return h->d.entry_mode == ANN_ENTRY_ROUTED && h->d.route_c == 1 && h->d.dtype != ANN_U8 && h->row_bytes >= 256 && h->d.n / h->d.n_clusters >= 256;
@@ -384,7 +400,7 @@ hipError_t norms_allow_listing(const ann_index_t* h, bool* allow) {
 hipError_t look_at_clusters(ann_index_t* h, ClusterSample* sample) {
     const int64_t most = kSampledEdges / (64 * (int64_t)h->d.degree), all = (h->d.n + 63) / 64;
     const int64_t runs = all <= most ? all : most, step = all <= most ? 64 : h->d.n / runs;
-    hipLaunchKernelGGL(longest_cluster_kernel, dim3(1), dim3(1024), 0, nullptr, static_cast<const int64_t*>(h->d.cluster_offsets), h->d.n_clusters, sample);
+    hipLaunchKernelGGL(longest_cluster_kernel, dim3(1), dim3(1024), 0, nullptr, static_cast<const int64_t*>(h->d.cluster_offsets), h->d.n_clusters, sample, most_ranked(h));
     hipLaunchKernelGGL(sample_clusters_kernel, dim3((unsigned)(runs < 8192 ? runs : 8192)), dim3(64), 0, nullptr, h->d, h->row_bytes, runs, step, sample);
     ClusterSample got;
     hipError_t e = hipGetLastError();
@@ -394,6 +410,7 @@ hipError_t look_at_clusters(ann_index_t* h, ClusterSample* sample) {
     h->by_clusters = h->d.dtype == ANN_U8 && got.longest <= (unsigned long long)kMaxClusterRows;
     h->leaving = got.leaving / (64.0 * (double)runs * h->d.degree);
     h->far = got.far / (64.0 * (double)(runs < kFarRows ? runs : kFarRows));
+    h->in_long = (double)got.in_long / (double)h->d.n;
     return hipSuccess;
 }
 
@@ -447,7 +464,7 @@ extern "C" int ann_index_load(const ann_index_desc_t* desc, ann_index_t** out_ha
     h->longest_cluster = d.n;
     h->by_clusters = false;
     h->leaving = 1.0;
-    h->far = 0.0;
+    h->far = h->in_long = 0.0;
     const bool mfma_route = d.entry_mode == ANN_ENTRY_ROUTED;
     // A search by whole clusters is a choice: arrays that are not known to be in place on a device (a handle that only routes may have
     // stand-ins) are not looked at, and are searched by gathering.  Loading an index of 10 000 rows takes 40 us with that look, 22
@@ -872,8 +889,7 @@ int table_stride(const ann_index_t* h, int64_t nq, int itopk, int width, int max
     const int64_t gathered = 8 * parents < mean ? 8 * parents : mean;
     const int64_t twice_products = (int64_t)h->d.dim * (h->d.dtype == ANN_F16 && h->d.metric == ANN_IP ? 1 : 4);
     if (10 * gathered * h->row_bytes < 4 * twice_products * mean || scored_share(h, parents, mean) < table_share(h, nq, parents, width)) return 0;
-    // half as long again as the mean cluster: rows beyond are gathered
-    int64_t stride = (mean + mean / 2 + 127) / 64 * 64;
+    int64_t stride = table_rows(h);
     if (stride > h->window_bits) stride = h->window_bits;
     return may_allocate_more(stream) ? (int)stride : 0;
 }
@@ -886,11 +902,18 @@ int table_stride(const ann_index_t* h, int64_t nq, int itopk, int width, int max
 // queries, where a round's latency counts, up to 1.45.
 void rank_rows(const ann_index_t* h, int64_t nq, int itopk, int width, int max_iters, int stride, SearchParams* p) {
     const int64_t parents = (int64_t)width * max_iters < itopk ? (int64_t)width * max_iters : itopk;
-    // queries that meet an edge that leaves their cluster: a small batch would wait for one of them
+    // Queries that are left to another search: those that meet an edge that leaves their cluster, after they have been ranked, and those in long
+    // clusters.  That search comes after this one, and a query alone takes as long as a small batch: 8 000 queries of 96 fp32 elements 407 us
+    // with none in long clusters, 626 [share of the queries 0.016], 633 [0.05], 631 [0.35], without ranks 545 to 608; 5 000 of 768 fp16 elements
+    // 493, 689, 705, 744, without 587 to 696.  In a large batch they may be many: 20 000 queries 780, 1 100 [0.016], 1 118 [0.05], 1 148 [0.15], 1 202 [0.35], without
+    // 1 103, 1 105, 1 174, 1 198, 1 181; 768 elements 1 269, 1 531, 1 621, 1 936, 2 084, without 1 575, 1 622, 1 788, 2 246, 2 052.  Between them 18 000
+    // queries with one long cluster in four hundred: 1 037, without 1 014.
     const double anew = h->leaving * (double)(parents * h->d.degree);
-    if (anew > 1.0 / 128 || (nq < kMinQueriesForClusterOrder && anew * (double)nq > 0.5)) return;
+    if (anew > 1.0 / 128 || h->in_long > 0.2 || (nq < kMinQueriesToLeaveSome && (anew + h->in_long) * (double)nq > 0.5)) return;
     const int64_t mean = h->d.n / h->d.n_clusters, longest = h->longest_cluster < stride ? h->longest_cluster : stride;
-    if (mean > kMaxRankRows || stride % 64 != 0) return;  // a query's keys are read 64 at a time (a window option may cut the stride)
+    // (an option may cut the visited bitmap, and with it the table's rows: a query's keys are read 64 at a time, and how many clusters are too long
+    // then has not been looked at)
+    if (mean > kMaxRankRows || stride % 64 != 0 || (stride < table_rows(h) && stride < h->longest_cluster)) return;
     // Ranking costs as much as there are rows; it saves, a round, what the list and the neighbours cost beyond the search for
     // bits that are set.
     const int64_t rounds = (parents + width - 1) / width;

@@ -22,6 +22,7 @@ static int host_reads; /* copies from memory that is no device memory */
 static struct { dim3 grid, block; size_t lds; hipStream_t stream; } config;
 static uint32_t sample_result[2]; /* what the kernel that looks at a sample of an index finds: edges that leave, keys too far */
 static unsigned threads; /* of the last launch's workgroups */
+static size_t most_async; /* largest hipMallocAsync */
 static int sampled, default_stream_free = 1;
 
 static int find(const void* p) {
@@ -70,10 +71,13 @@ hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3 block, void** args, si
         strcat(launched, " ");
         if (strstr(kernels[i].name, "longest_cluster_kernel")) {
             const int64_t* off = *(const int64_t**)args[0];
-            uint64_t longest = 0;
-            for (int c = 0; c < *(int*)args[1]; ++c)
+            uint64_t longest = 0, in_long = 0;
+            for (int c = 0; c < *(int*)args[1]; ++c) {
                 if ((uint64_t)(off[c + 1] - off[c]) > longest) longest = off[c + 1] - off[c];
+                if (off[c + 1] - off[c] > *(int64_t*)args[3]) in_long += off[c + 1] - off[c];
+            }
             memcpy(*(char**)args[2], &longest, sizeof(longest));
+            memcpy(*(char**)args[2] + 16, &in_long, sizeof(in_long));
         }
         if (strstr(kernels[i].name, "sample_clusters_kernel")) {
             sampled = 1;
@@ -89,6 +93,7 @@ hipError_t hipMallocAsync(void** p, size_t bytes, hipStream_t s) {
     (void)s;
     *p = NULL;
     if (bytes > async_limit) return hipErrorOutOfMemory;
+    if (bytes > most_async) most_async = bytes;
     *p = device(bytes);
     return hipSuccess;
 }
@@ -262,12 +267,44 @@ static void bytes_read(void) {
     }
 }
 
+/* Rows are ranked where few queries will have to be searched otherwise: of a small batch none. */
+static void ranked(void) {
+    const struct { int nq; uint32_t leaving; int long_clusters, window_bits, width, ranks; } calls[] = {
+        /* 16 777 216 edges, 256 * 64 of them a query */
+        {8000, 0, 0, 0, 4, 1}, {8000, 1, 0, 0, 4, 0}, {20000, 0, 0, 0, 4, 1}, {20000, 8, 0, 0, 4, 1}, {20000, 9, 0, 0, 4, 0},
+        {20000, 1u << 24, 0, 0, 4, 0},
+        /* clusters of 3 300 rows among 400 of 2 000 */
+        {8000, 0, 1, 0, 4, 0}, {19999, 0, 1, 0, 4, 0}, {20000, 0, 1, 0, 4, 1}, {20000, 0, 40, 0, 4, 1}, {20000, 0, 60, 0, 4, 0}, {20000, 9, 1, 0, 4, 0},
+        /* a visited bitmap that cuts the rows of the table: the longest cluster fits, does so in rows that are not whole 64s, does not fit */
+        {8000, 0, 0, 2048, 4, 1}, {8000, 0, 0, 2016, 4, 0}, {8000, 0, 0, 1024, 4, 0}, {20000, 0, 1, 3200, 4, 1}, {20000, 0, 1, 3008, 4, 0},
+        /* rounds of few neighbours */
+        {20000, 0, 0, 0, 1, 1}, {20000, 0, 0, 0, 8, 1}};
+    void* q = device((size_t)20000 * 384);
+    int32_t *routes = device(20000 * 4), *ids = device(20000 * 40), *keys = device(20000 * 40);
+    ann_index_desc_t d = index_of(ANN_F32, 96, 2000, 400, 64, 1);
+    for (unsigned i = 0; i < sizeof(calls) / sizeof(calls[0]); ++i) {
+        int64_t* off = (int64_t*)d.cluster_offsets;
+        for (int c = 0; c < 400; ++c) off[c + 1] = off[c] + (c < calls[i].long_clusters ? 3300 : c < 2 * calls[i].long_clusters ? 700 : 2000);
+        sample_result[0] = calls[i].leaving, sample_result[1] = 0;
+        ann_index_t* h = load(&d);
+        if (calls[i].window_bits) CHECK(ann_index_set_option(h, ANN_OPT_VISITED_WINDOW_BITS, calls[i].window_bits) == ANN_OK);
+        launched[0] = 0, most_async = 0;
+        CHECK(ann_search_routed(h, q, calls[i].nq, routes, 10, 256, calls[i].width, 200, ids, keys, NULL, NULL) == ANN_OK);
+        if (ran("rank_search_kernel") != calls[i].ranks) printf("call %u\n", i);
+        CHECK(ran("key_table_kernel") && ran("rank_search_kernel") == calls[i].ranks && ran("left_over_search_kernel") == calls[i].ranks);
+        const size_t stride = calls[i].window_bits && calls[i].window_bits < 3072 ? (size_t)calls[i].window_bits : 3072;
+        CHECK(most_async >= 4 * (stride + 1) * (size_t)calls[i].nq + 4); /* keys, and the list of those that are left */
+        ann_free(h);
+    }
+}
+
 int main(int argc, char** argv) {
     const char* what = argc > 1 ? argv[1] : "";
     if (!strcmp(what, "scratch")) scratch();
     else if (!strcmp(what, "stand_ins")) stand_ins();
     else if (!strcmp(what, "searched_anew")) searched_anew();
     else if (!strcmp(what, "bytes_read")) bytes_read();
+    else if (!strcmp(what, "ranked")) ranked();
     else return 2;
     printf("%s ok\n", what);
     return 0;

@@ -1485,10 +1485,10 @@ def kernel_times(torch, call):
 
 
 @pytest.mark.parametrize("dt,dim,metric,sizes,k,itopk,width,degree,n_entry,iters,kind", [
-    ("f32", 96, 0, (500, 1, 64, 63, 65, 900, 1_408, 1_409), 10, 128, 4, 32, 32, 100, "plain"),   # three clusters of more rows than the table holds
-    ("f32", 96, 0, (3_072, 3_073, 2_950), 100, 512, 8, 64, 32, 100, "plain"),                   # the most rows that are ranked, and one more
+    ("f32", 96, 0, (500, 1, 64, 63, 65, 900, 1_408, 1_409) + (520,) * 40, 10, 128, 4, 32, 32, 100, "plain"),   # three clusters of more rows than the table holds
+    ("f32", 96, 0, (3_072, 3_073, 2_950, 3_000, 3_001, 2_999), 100, 512, 8, 64, 32, 100, "plain"),                   # the most rows that are ranked, and one more
     ("f16", 768, 1, (300, 700, 410), 70, 70, 4, 48, 64, 100, "plain"),
-    ("f32", 100, 1, (500, 260, 900), 10, 100, 6, 27, 5, 100, "plain"),
+    ("f32", 100, 1, (500, 260, 900) + (530,) * 8, 10, 100, 6, 27, 5, 100, "plain"),
     ("f16", 128, 0, (256, 257, 288, 300), 256, 256, 8, 64, 32, 40, "plain"),
     ("f32", 128, 0, (280, 301), 128, 128, 2, 33, 1, 100, "plain"),
     ("f32", 96, 0, (700, 900), 10, 128, 4, 32, 32, 100, "copies"),       # equal keys, in buckets of two and of fifty
@@ -1509,7 +1509,8 @@ def test_search_by_rank_gives_the_bits_of_the_gathering_search(torch_cuda, dt, d
     every row (a fixed team size asks for that one), also where a query is left to another search, which is where it has to be only."""
     from paper_2512_02278_amd import ann
 
-    torch, dev, nq = torch_cuda, "cuda:0", 4_200
+    longest = min((sum(sizes) // len(sizes) * 3 // 2 + 127) // 64 * 64, 3_072)  # that is ranked
+    torch, dev, nq = torch_cuda, "cuda:0", 4_200 if max(sizes) <= longest else 20_000  # only large batches are ranked beside longer ones
     rng = np.random.default_rng(dim + len(sizes) + len(kind))
     off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
     n, nc = int(off[-1]), len(sizes)
@@ -1563,7 +1564,6 @@ def test_search_by_rank_gives_the_bits_of_the_gathering_search(torch_cuda, dt, d
         if team == 0:
             # without queries the launch that goes through those left ends at once
             ranked, left = (sum(t for name, t in times.items() if what in name) for what in ("rank_search_kernel", "left_over_search_kernel"))
-            longest = min((n // nc * 3 // 2 + 127) // 64 * 64, 3_072)
             assert (left > 12.0 + 0.15 * ranked) == (max(sizes) > longest or kind in ("outlier", "infinite", "far", "sparse")), (ranked, left)
         got.append((ids, keys.view(torch.int32), counters[:, :3]))
     ann.ann_free(h)
