@@ -73,7 +73,6 @@ constexpr int kDefaultWindowBits = 8192, kMaxWindowBits = 1 << 17;
 constexpr int64_t kMinQueriesForClusterOrder = 16384;
 constexpr int64_t kTableBytes = 1ll << 30;
 constexpr int64_t kMinQueriesToLeaveSome = 20000;  // see rank_rows
-constexpr unsigned kLeftOverGrid = 2048;  // workgroups that go through the queries a search by rank leaves, mostly none
 
 }  // namespace ann
 
@@ -1190,7 +1189,10 @@ int search_impl(ann_index_t* h, const void* queries, int64_t nq, const int32_t* 
         if (p.again) {
             e = launch_rank_search(p, kListVariants[plan.list_variant][1], grid, (size_t)rank_lds_bytes(p.rank_rows, p.rank_places), stream);
             if (e != hipSuccess) break;
-            if (grid > kLeftOverGrid) grid = kLeftOverGrid;
+            // (2 048 workgroups, eight of the twelve to twenty-eight that a compute unit holds, where 0.15 and 0.35 of the queries were left:
+            // 1 300 and 1 439 us instead of 1 148 and 1 202, 20 000 queries; without any 4 us in either case)
+            const size_t resident = 256 * (kLdsBytes / lds_bytes < 20 ? kLdsBytes / lds_bytes : 20);
+            if (grid > resident) grid = (unsigned)resident;
         }
         e = h->variant->search(p, plan.list_variant, team, grid, lds_bytes, stream);
     }

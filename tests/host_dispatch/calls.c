@@ -22,6 +22,7 @@ static int host_reads; /* copies from memory that is no device memory */
 static struct { dim3 grid, block; size_t lds; hipStream_t stream; } config;
 static uint32_t sample_result[2]; /* what the kernel that looks at a sample of an index finds: edges that leave, keys too far */
 static unsigned threads; /* of the last launch's workgroups */
+static unsigned blocks;  /* how many */
 static size_t most_async; /* largest hipMallocAsync */
 static int sampled, default_stream_free = 1;
 
@@ -63,8 +64,8 @@ hipError_t __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* lds, hipSt
     return hipSuccess;
 }
 hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3 block, void** args, size_t lds, hipStream_t s) {
-    (void)grid, (void)lds, (void)s;
-    threads = block.x;
+    (void)lds, (void)s;
+    threads = block.x, blocks = grid.x;
     for (int i = 0; i < n_kernels; ++i) {
         if (kernels[i].host != f) continue;
         strcat(launched, kernels[i].name);
@@ -294,6 +295,7 @@ static void ranked(void) {
         CHECK(ran("key_table_kernel") && ran("rank_search_kernel") == calls[i].ranks && ran("left_over_search_kernel") == calls[i].ranks);
         const size_t stride = calls[i].window_bits && calls[i].window_bits < 3072 ? (size_t)calls[i].window_bits : 3072;
         CHECK(most_async >= 4 * (stride + 1) * (size_t)calls[i].nq + 4); /* keys, and the list of those that are left */
+        if (calls[i].ranks) CHECK(blocks >= 256 * 12 && blocks <= 256 * 28); /* as many as a chip holds */
         ann_free(h);
     }
 }
