@@ -24,6 +24,7 @@ static uint32_t sample_result[2]; /* what the kernel that looks at a sample of a
 static unsigned threads; /* of the last launch's workgroups */
 static unsigned blocks;  /* how many */
 static size_t most_async; /* largest hipMallocAsync */
+static size_t lds_used;  /* by the last launch's workgroups */
 static int sampled, default_stream_free = 1;
 
 static int find(const void* p) {
@@ -64,8 +65,8 @@ hipError_t __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* lds, hipSt
     return hipSuccess;
 }
 hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3 block, void** args, size_t lds, hipStream_t s) {
-    (void)lds, (void)s;
-    threads = block.x, blocks = grid.x;
+    (void)s;
+    threads = block.x, blocks = grid.x, lds_used = lds;
     for (int i = 0; i < n_kernels; ++i) {
         if (kernels[i].host != f) continue;
         strcat(launched, kernels[i].name);
@@ -300,6 +301,27 @@ static void ranked(void) {
     }
 }
 
+/* With entries drawn over the whole index the visited hash has room for twice what a search will visit. */
+static void hash(void) {
+    const struct { int dtype, dim, nq, itopk, width, rounds; size_t more; } calls[] = {
+        /* bytes of LDS beyond those of the smallest hash, 512 and 256 words */
+        {ANN_F16, 200, 100, 100, 3, 200, 4 * (8192 - 512)}, {ANN_F16, 200, 100, 100, 3, 10, 4 * (2048 - 512)},
+        {ANN_F16, 200, 100, 100, 3, 3, 4 * (1024 - 512)}, {ANN_F16, 200, 100, 100, 3, 0, 0},
+        {ANN_U8, 128, 100, 64, 1, 200, 4 * (8192 - 256)}, {ANN_U8, 128, 100, 64, 1, 16, 4 * (2048 - 256)}, {ANN_U8, 128, 100, 64, 1, 2, 0}};
+    void* q = device((size_t)100 * 400);
+    int32_t *ids = device(100 * 40), *keys = device(100 * 40);
+    for (unsigned i = 0; i < sizeof(calls) / sizeof(calls[0]); ++i) {
+        ann_index_desc_t d = index_of(calls[i].dtype, calls[i].dim, 1000, 100, calls[i].dtype == ANN_U8 ? 32 : 27, 1);
+        d.entry_mode = ANN_ENTRY_UNIFORM;
+        ann_index_t* h = load(&d);
+        CHECK(ann_search(h, q, calls[i].nq, 10, calls[i].itopk, calls[i].width, calls[i].rounds, ids, keys, NULL) == ANN_OK);
+        const size_t more = lds_used - (size_t)ann_lds_bytes(h, calls[i].itopk, calls[i].width);
+        if (more != calls[i].more) printf("call %u: %zu\n", i, more);
+        CHECK(more == calls[i].more);
+        ann_free(h);
+    }
+}
+
 int main(int argc, char** argv) {
     const char* what = argc > 1 ? argv[1] : "";
     if (!strcmp(what, "scratch")) scratch();
@@ -307,6 +329,7 @@ int main(int argc, char** argv) {
     else if (!strcmp(what, "searched_anew")) searched_anew();
     else if (!strcmp(what, "bytes_read")) bytes_read();
     else if (!strcmp(what, "ranked")) ranked();
+    else if (!strcmp(what, "hash")) hash();
     else return 2;
     printf("%s ok\n", what);
     return 0;

@@ -21,7 +21,7 @@ def program(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("scenario", ["scratch", "stand_ins", "searched_anew", "bytes_read", "ranked"])
+@pytest.mark.parametrize("scenario", ["scratch", "stand_ins", "searched_anew", "bytes_read", "ranked", "hash"])
 def test_dispatch(program, scenario):
     r = subprocess.run([str(program), scenario], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0 and f"{scenario} ok" in r.stdout, r.stdout + r.stderr
