@@ -1026,6 +1026,12 @@ void search_by_clusters(const ann_index_t* h, int64_t nq, int itopk, int width, 
 // round 329/246, 430/318, 793/592, 3 365/2 888; 1 536 bytes, 64, 128 453/314, 804/524, 2 096/1 467, (10 000) 6 464/5 104; 128-byte uint8 rows, 64, 32
 // 250/164, 295/193, 348/260, 1 165/867; 512-byte fp32 rows, 160, 96 467/347, 525/401, 1 033/891, (30 000) 9 262/9 159.  Single words in the
 // larger hash were slower than in the small one here and there (384 bytes, 256, 256, 1 000 queries 616/663).
+// Batches on other streams share the compute units: of short rows four find room.  us a batch with the small hash / with all of the LDS for one batch / now,
+// one, four and eight streams: 128-byte uint8 rows, 128, 128: 1 000 queries 344/286/345, 94/144/90, 93/139/85, 2 000 367/313/351, 115/171/108, 107/167/101; 64, 32: 1 000
+// 439/318/374, 125/171/98, 121/158/99; 96 bytes, 192, 256: 500 508/458/446, 148/187/139, 145/180/133, 1 000 514/466/494, 177/367/163, 171/354/157; 384 bytes, 128, 128: 4 000
+// 970/862/959, 575/609/573, 607/619/605.  Of float rows fewer are in flight, and they may have all of it but where a thousand would take 40 KB each: 384 bytes, 64, 64
+// 274/198/225, 106/115/86, 125/122/105; 256 bytes, 256, 256 575/495/518, 405/413/340, 397/405/336; 400 bytes, 100, 81 478/340/365, 198/169/147, 193/165/143.  Of longer rows
+// all: 512 bytes, 192, 192, 1 000 588/459, 430/315, 415/299; 1 536 bytes, 128, 256 1 219/822, 1 133/729, 1 141/741; 768 bytes of uint8, 128, 128 520/424, 272/242, 267/231.
 // Searches of few rounds visit few ids, and a large hash takes time to clear: three rounds, 100 queries of 384 bytes 15.6 us, with a hash for the
 // whole list 17.2, 1 000 on four streams 12.0 and 18.1.
 void enlarge_hash(const ann_index_t* h, int64_t nq, int itopk, int width, int max_iters, Plan* plan) {
@@ -1033,6 +1039,8 @@ void enlarge_hash(const ann_index_t* h, int64_t nq, int itopk, int width, int ma
     const int64_t parents = (int64_t)width * max_iters < itopk ? (int64_t)width * max_iters : itopk;
     const int64_t visits = parents * h->d.degree + h->d.n_entry, resident = (nq + 255) / 256;
     size_t room = kLdsBytes / (size_t)resident;
+    if (h->d.dtype == ANN_U8 && h->row_bytes < 512) room /= 4;
+    else if (h->row_bytes < 512 && resident > 2 && room > 32 * 1024) room = 32 * 1024;
     const size_t least = h->d.dtype == ANN_U8 ? 5800 : 8192;
     if (room < least) room = least;
     while (plan->hash_bits < 13 && (int64_t(1) << plan->hash_bits) < 2 * visits) {

@@ -307,9 +307,11 @@ static void hash(void) {
         /* bytes of LDS beyond those of the smallest hash, 512 and 256 words */
         {ANN_F16, 200, 100, 100, 3, 200, 4 * (8192 - 512)}, {ANN_F16, 200, 100, 100, 3, 10, 4 * (2048 - 512)},
         {ANN_F16, 200, 100, 100, 3, 3, 4 * (1024 - 512)}, {ANN_F16, 200, 100, 100, 3, 0, 0},
-        {ANN_U8, 128, 100, 64, 1, 200, 4 * (8192 - 256)}, {ANN_U8, 128, 100, 64, 1, 16, 4 * (2048 - 256)}, {ANN_U8, 128, 100, 64, 1, 2, 0}};
-    void* q = device((size_t)100 * 400);
-    int32_t *ids = device(100 * 40), *keys = device(100 * 40);
+        {ANN_U8, 128, 100, 64, 1, 200, 4 * (8192 - 256)}, {ANN_U8, 128, 100, 64, 1, 16, 4 * (2048 - 256)}, {ANN_U8, 128, 100, 64, 1, 2, 0},
+        /* a thousand queries: what leaves room for other batches */
+        {ANN_U8, 128, 1000, 64, 1, 200, 4 * (2048 - 256)}, {ANN_F16, 200, 1000, 100, 3, 200, 4 * (4096 - 512)}, {ANN_F16, 256, 1000, 100, 3, 200, 4 * (8192 - 512)}};
+    void* q = device((size_t)1000 * 512);
+    int32_t *ids = device(1000 * 40), *keys = device(1000 * 40);
     for (unsigned i = 0; i < sizeof(calls) / sizeof(calls[0]); ++i) {
         ann_index_desc_t d = index_of(calls[i].dtype, calls[i].dim, 1000, 100, calls[i].dtype == ANN_U8 ? 32 : 27, 1);
         d.entry_mode = ANN_ENTRY_UNIFORM;
