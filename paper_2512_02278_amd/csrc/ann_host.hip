@@ -804,25 +804,25 @@ namespace {
 // Wavefronts per query when the caller has not fixed them.  A team pays where a round's gathers are the long pole (rows of 256
 // bytes and more: a wavefront covers few of them per instruction and has a bounded number of loads in flight) and the chip is
 // not full anyway: up to 1 024 queries its 1 024 SIMDs hold all wavefronts of teams of four at once.
-// 1 / 2 / 4 wavefronts per query, us, uniform entries, list of 100, 81 neighbours a round:
+// 1 / 2 / 4 wavefronts per query, us, uniform entries, list of 100, 81 neighbours a round, 200 000 fp16 rows in clusters of 1 000:
 //     queries     50             1 000             1 500             3 001             6 000
-//   256 bytes   335/291/262    438/383/342       455/409/369       561/508/618       702/747/1 019
-//   384         328/299/270    452/419/378       462/425/463       571/655/745       962/921/1 183
-//   400         467/377/307    697/560/466       699/575/575       796/781/840     1 237/1 153/1 373
-//   512         433/343/282    573/463/390       587/487/546       771/705/762     1 238/1 156/1 263
-//   768         574/442/356    893/666/542       905/687/584     1 105/959/952     1 781/1 653/1 594
-//   1 024       943/667/506  1 015/726/572     1 040/789/675   1 329/1 178/1 148   2 167/2 171/2 082
-//   1 536       672/488/385  1 034/816/713     1 181/989/929   1 789/1 594/1 542   3 080/2 963/2 878
+//   256 bytes   122/120/116    166/157/150       167/158/151       184/173/253       267/335/521
+//   384         175/147/128    231/201/181       231/201/251       248/285/364       454/496/699
+//   400         145/126/112    216/197/181       226/204/254       259/325/393       536/517/699
+//   512         143/121/108    190/166/153       200/180/249       239/295/362       527/511/681
+//   768         251/186/145    293/220/187       339/270/227       443/364/349       718/704/738
+//   1 024       244/189/153    304/238/199       303/249/221       429/408/413       946/910/856
+//   1 536       254/187/145    301/245/216       346/314/358       615/609/576     1 313/1 260/1 208
 // In a routed search most neighbours have been seen, and a round has fewer rows to gather.  List of 128, 128 neighbours a
 // round, 1 000 and 1 500 queries: 384 bytes 105/107/105 and 111/115/174, 400 bytes 167/155/147 and 174/167/222, 768 bytes
 // 168/142/130 and 178/160/155, 1 536 bytes 210/196/195 and 261/267/309 (6 000: 914/910/903).  List of 64, 32 neighbours: 256
 // bytes 115/126/126, 384 bytes 119/132/131, 400 bytes 180/178/175, 1 536 bytes 196/189/186 (6 000: 762/765/819).  256 neighbours, 4 400
 // queries: 1 024 bytes 521/517/539, 1 536 bytes 781/764/751; 512 neighbours, 3 465 queries: 1 024 bytes 728/-/653.
-// Rounds of few neighbours leave a team little to share: 16 neighbours, uniform entries, 1 000 queries: 256 bytes 548/597/600, 512
-// bytes 581/626/614, 768 bytes 715/648/618; 32 neighbours, 6 000 queries, 1 024 bytes 878/946/1 316 (17 MB of rows) and 1 998/1 943/2 124
+// Rounds of few neighbours leave a team little to share: 16 neighbours, uniform entries, 1 000 queries: 256 bytes 181/200/201, 512
+// bytes 203/213/210, 768 bytes 258/231/220; 32 neighbours, 6 000 queries, 1 024 bytes 491/491/691 (17 MB of rows) and 674/683/803
 // (200 MB).  Teams that are not all resident wait for each other's places: 384 neighbours, 1 400 and 2 400 queries: 256 bytes
-// 418/345/490 and 457/581/721, 400 bytes 595/453/575 and 664/790/849, 768 bytes 740/537/676 and 872/1 060/1 009.
-// Large batches of long rows are bound by bytes in flight again: 50 000 queries over 1 536 bytes 33 819 / - / 33 323.
+// 256/224/316 and 369/426/515, 400 bytes 384/299/362 and 685/643/651, 768 bytes 614/422/470 and 1 034/948/880.
+// Large batches of long rows are bound by bytes in flight again: 50 000 queries over 1 536 bytes 9 665 / - / 9 187.
 int default_team(const ann_index_t* h, int64_t nq, int width) {
     const int bytes = h->row_bytes;
     const int64_t round = (int64_t)width * h->d.degree;
@@ -1021,10 +1021,10 @@ void search_by_clusters(const ann_index_t* h, int64_t nq, int itopk, int width, 
 
 // Entries drawn over the whole index: everything that a search scores is remembered in the hash, which has LDS to spare where registers
 // or the batch bound the queries in flight (a compute unit holds 16 to 20 wavefronts over float rows, 28 over short uint8 rows).  Twice
-// the ids that may come, so that it need not be emptied - rows are scored again after that - and insertions seldom meet.  With buckets
-// in place of single words (hash_insert), us before / now, 100, 1 000, 3 000, 20 000 queries: 400-byte fp16 rows, list of 100, 81 neighbours a
-// round 329/246, 430/318, 793/592, 3 365/2 888; 1 536 bytes, 64, 128 453/314, 804/524, 2 096/1 467, (10 000) 6 464/5 104; 128-byte uint8 rows, 64, 32
-// 250/164, 295/193, 348/260, 1 165/867; 512-byte fp32 rows, 160, 96 467/347, 525/401, 1 033/891, (30 000) 9 262/9 159.  Single words in the
+// the ids that may come, so that it need not be emptied - rows are scored again after that - and insertions seldom meet.  With single words in place of buckets
+// (hash_insert) and the smallest hash / now, us, 100, 1 000, 2 000, 4 000 queries, indices of 200 000 rows in clusters of 1 000 with a third of their edges anywhere:
+// 400-byte fp16 rows, list of 100, 81 neighbours a round 349/245, 478/365, 593/469, 936/745; 1 536 bytes (100 000 rows), 128, 256 504/360, 1 219/823, 2 345/1 703, 4 642/4 642;
+// 512-byte fp32 rows, 192, 192 445/354, 588/459, 945/745, 1 982/1 963; 128-byte uint8 rows, 64, 32 344/233, 439/374, 437/401, 492/408.  Single words in the
 // larger hash were slower than in the small one here and there (384 bytes, 256, 256, 1 000 queries 616/663).
 // Batches on other streams share the compute units: of short rows four find room.  us a batch with the small hash / with all of the LDS for one batch / now,
 // one, four and eight streams: 128-byte uint8 rows, 128, 128: 1 000 queries 344/286/345, 94/144/90, 93/139/85, 2 000 367/313/351, 115/171/108, 107/167/101; 64, 32: 1 000
