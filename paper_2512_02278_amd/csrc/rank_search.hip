@@ -15,13 +15,14 @@ struct RankSearch {
     static constexpr uint32_t kTagged = (1u << kTag) - 1u;
     static constexpr uint32_t kMostCrowded = kRankBitWords + 64 - 1;  // what the words of bits and parents hold
     static_assert(kMaxRankRows <= 1 << kTag, "a row and a place fit in front of the tag");
+    static_assert(kRankBitWords + 64 + rank_row_words(kRankTiles * kRankTile) >= 2 * kRankCells, "room for `begins` in front of the buckets");
 
     const SearchParams& p;
     const uint32_t* const keys;  // of rows lo .. lo + size - 1
     const int lane;
     uint32_t* const bits;        // a bit per rank
     uint32_t* const parents;     // twice their ranks
-    float* const begins;         // where bits are later: the bucket that a cell's first key falls into
+    float2* const begins;        // where bits, parents and the first of by_rank are later: a cell's first bucket, and how many it has
     uint32_t* const list;        // where bits and parents are later: how many buckets are crowded, then (first place << 8 | rows) of each
     uint16_t* const by_rank;     // row of a rank below `near`
     uint16_t* const code_of;     // rank of a row, as (rank / 32) << 7 | rank % 32
@@ -32,7 +33,7 @@ struct RankSearch {
     float least, scale;          // the smallest key; cells of the range of the keys
 
     __device__ __forceinline__ RankSearch(const SearchParams& p_, uint32_t* lds, const uint32_t* keys_, int lane_)
-        : p(p_), keys(keys_), lane(lane_), bits(lds), parents(lds + kRankBitWords), begins(reinterpret_cast<float*>(lds)), list(lds),
+        : p(p_), keys(keys_), lane(lane_), bits(lds), parents(lds + kRankBitWords), begins(reinterpret_cast<float2*>(lds)), list(lds),
           by_rank(reinterpret_cast<uint16_t*>(parents + 64)), code_of(by_rank + 2 * rank_row_words(p_.rank_places)), buckets(reinterpret_cast<uint8_t*>(code_of)) {}
 
     __device__ __forceinline__ static void lds_order() {
@@ -46,9 +47,8 @@ struct RankSearch {
     }
     // Every step rounds once, and the last one of a cell ends at most where the next cell's buckets begin: monotonous.
     __device__ __forceinline__ uint32_t bucket_at(float cell) const {
-        const float* const at = begins + (uint32_t)cell;
-        const float first = at[0], buckets = at[1] - first;
-        return (uint32_t)__builtin_fmaf(__builtin_amdgcn_fractf(cell), buckets, first);
+        const float2 at = begins[(uint32_t)cell];
+        return (uint32_t)__builtin_fmaf(__builtin_amdgcn_fractf(cell), at.y, at.x);
     }
     // Chunks of 512 rows, a register of 64 each; `work(first register, lane)` for those that there are.  (With a copy of the lane number
     // that the compiler cannot see through: it would keep the 48 row numbers in registers from chunk to chunk.)
@@ -138,11 +138,14 @@ struct RankSearch {
         const uint32_t some = (uint32_t)__builtin_amdgcn_readfirstlane((int)key[0]);
         uint32_t lowest = some, highest = some;
         each_chunk([&](int t0, int lane) {
+            if ((t0 + kChunk) * 64 > size) {  // uniform
+#pragma unroll
+                for (int t = t0; t < t0 + kChunk; ++t) key[t] = lane < size - t * 64 ? key[t] : some;
+            }
 #pragma unroll
             for (int t = t0; t < t0 + kChunk; ++t) {
-                const uint32_t of_row = lane < size - t * 64 ? key[t] : some;
-                lowest = min(lowest, of_row);
-                highest = max(highest, of_row);
+                lowest = min(lowest, key[t]);
+                highest = max(highest, key[t]);
             }
         });
         least = ordered_to_float(~wave_max(~lowest));
@@ -166,8 +169,8 @@ struct RankSearch {
             const uint2 held = reinterpret_cast<const uint2*>(counts)[lane];
             const uint32_t upto = wave_inclusive_sum(held.x + held.y);
             const float each = (float)(kRankBuckets - 1) / (float)size;
-            reinterpret_cast<float2*>(begins)[lane] = make_float2((float)(upto - held.y - held.x) * each, (float)(upto - held.y) * each);
-            if (lane == 63) begins[kRankCells] = (float)upto * each;
+            const float first = (float)(upto - held.y - held.x) * each, second = (float)(upto - held.y) * each, end = (float)upto * each;
+            reinterpret_cast<float4*>(begins)[lane] = make_float4(first, second - first, second, end - second);
         }
         lds_order();
 
