@@ -200,7 +200,7 @@ struct ann_index {
     int64_t longest_cluster;  // rows of the longest cluster, or a bound on it
     bool by_clusters;         // whether searches by whole clusters (cluster_search.h) were looked at and fit
     double leaving, far;      // shares of graph edges that leave their cluster, and of keys that are too far, if so
-    double in_long;           // share of the rows in clusters too long for the search by rank
+    double in_long, copied;   // shares of the rows in clusters too long for the search by rank, and of rows of which there are many copies
 };
 
 using namespace ann;
@@ -216,7 +216,7 @@ static const RowVariant* pick_variant(int dtype, int metric, int64_t row_bytes, 
     return best;
 }
 
-constexpr int kMaxClusterRowBytes = 256, kFarRows = 1024;
+constexpr int kMaxClusterRowBytes = 256, kFarRows = 1024, kCopiedRows = 128, kManyCopies = 12;
 constexpr int64_t kSampledEdges = 1ll << 24;
 constexpr float kMostNormRatio = 8.0f;  // largest |c|^2 to their mean
 
@@ -224,7 +224,8 @@ constexpr float kMostNormRatio = 8.0f;  // largest |c|^2 to their mean
 struct ClusterSample {
     unsigned long long longest;  // rows of the longest cluster
     uint32_t leaving;            // sampled graph edges that leave the cluster
-    uint32_t far;                // sampled keys that are too far above the smallest for a word of cluster_search.h
+    uint32_t far;                // uint8: sampled keys that are too far above the smallest for a word of cluster_search.h
+    uint32_t copied;             // others: sampled rows of which a cluster holds kManyCopies or more
     unsigned long long in_long;  // rows in clusters that are too long for the search by rank
 };
 
@@ -242,11 +243,11 @@ static __global__ void __launch_bounds__(1024) longest_cluster_kernel(const int6
     atomicMax(&longest, (unsigned long long)most);
     if (rows) atomicAdd(&in_long, (unsigned long long)rows);
     __syncthreads();
-    if (threadIdx.x == 0) *out = ClusterSample{longest, 0u, 0u, in_long};
+    if (threadIdx.x == 0) *out = ClusterSample{longest, 0u, 0u, 0u, in_long};
 }
 
 // A workgroup takes runs of 64 rows, `step` rows from start to start, and counts the graph edges that leave their cluster.  The first
-// kFarRows workgroups also look at the keys of 64 rows of a cluster as seen from another of its rows.
+// kFarRows workgroups also look at the keys of 64 rows of a cluster as seen from another of its rows (uint8).
 static __global__ void __launch_bounds__(64) sample_clusters_kernel(ann_index_desc_t d, int row_bytes, int64_t runs, int64_t step, ClusterSample* sample) {
     const int lane = lane_id();
     const int64_t* const off = static_cast<const int64_t*>(d.cluster_offsets);
@@ -313,6 +314,41 @@ static __global__ void __launch_bounds__(64) sample_clusters_kernel(ann_index_de
     }
     for (int s = 1; s < 64; s <<= 1) leaving += __shfl_xor(leaving, s);
     if (leaving && lane == 0) atomicAdd(&sample->leaving, leaving);
+}
+
+// A workgroup looks for the copies of a row in its cluster (by the first 16 bytes, 16 in the middle and the last 16), kCopiedRows of them spread
+// over all.
+static __global__ void __launch_bounds__(512) copied_rows_kernel(ann_index_desc_t d, int row_bytes, ClusterSample* sample) {
+    constexpr int U = 6;  // rows of a thread, all loads in flight: 3 072 of a workgroup
+    static_assert(512 * U >= kMaxRankRows, "a workgroup holds a cluster that is ranked");
+    __shared__ int copies;
+    const int64_t* const off = static_cast<const int64_t*>(d.cluster_offsets);
+    const char* const vectors = static_cast<const char*>(d.vectors);
+    const auto piece = [&](int64_t r, int at) { return *reinterpret_cast<const uint4*>(vectors + r * d.row_stride_bytes + at); };
+    const auto equal = [](const uint4& a, const uint4& b) { return a.x == b.x && a.y == b.y && a.z == b.z && a.w == b.w; };
+    const int64_t row = d.n * blockIdx.x / gridDim.x;
+    int at = 0, end = d.n_clusters;  // the last cluster that starts at or before the row
+    while (end - at > 1) {
+        const int mid = at + (end - at) / 2;
+        if (off[mid] <= row) at = mid;
+        else end = mid;
+    }
+    const int64_t lo = off[at], size = off[at + 1] - lo;
+    if (lo < 0 || lo > row || size < 1 || lo + size > d.n || lo + size <= row || size > kMaxRankRows) return;  // (the whole workgroup)
+    if (threadIdx.x == 0) copies = 0;
+    __syncthreads();
+    const int middle = row_bytes / 32 * 16, last = row_bytes - 16;
+    uint4 y[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) y[u] = piece(lo + min(u * 512 + (int)threadIdx.x, (int)size - 1), 0);
+    const uint4 x0 = piece(row, 0), x1 = piece(row, middle), x2 = piece(row, last);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int r = u * 512 + (int)threadIdx.x;
+        if (r < size && equal(y[u], x0) && equal(piece(lo + r, middle), x1) && equal(piece(lo + r, last), x2)) atomicAdd(&copies, 1);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0 && copies >= kManyCopies) atomicAdd(&sample->copied, 1u);
 }
 
 // Whether HIP knows these bytes as device memory; clears the error if it does not.
@@ -401,6 +437,7 @@ hipError_t look_at_clusters(ann_index_t* h, ClusterSample* sample) {
     const int64_t runs = all <= most ? all : most, step = all <= most ? 64 : h->d.n / runs;
     hipLaunchKernelGGL(longest_cluster_kernel, dim3(1), dim3(1024), 0, nullptr, static_cast<const int64_t*>(h->d.cluster_offsets), h->d.n_clusters, sample, most_ranked(h));
     hipLaunchKernelGGL(sample_clusters_kernel, dim3((unsigned)(runs < 8192 ? runs : 8192)), dim3(64), 0, nullptr, h->d, h->row_bytes, runs, step, sample);
+    if (h->d.dtype != ANN_U8) hipLaunchKernelGGL(copied_rows_kernel, dim3(kCopiedRows), dim3(512), 0, nullptr, h->d, h->row_bytes, sample);
     ClusterSample got;
     hipError_t e = hipGetLastError();
     if (e == hipSuccess) e = hipMemcpy(&got, sample, sizeof(got), hipMemcpyDeviceToHost);
@@ -409,6 +446,7 @@ hipError_t look_at_clusters(ann_index_t* h, ClusterSample* sample) {
     h->by_clusters = h->d.dtype == ANN_U8 && got.longest <= (unsigned long long)kMaxClusterRows;
     h->leaving = got.leaving / (64.0 * (double)runs * h->d.degree);
     h->far = got.far / (64.0 * (double)(runs < kFarRows ? runs : kFarRows));
+    h->copied = got.copied / (double)kCopiedRows;
     h->in_long = (double)got.in_long / (double)h->d.n;
     return hipSuccess;
 }
@@ -463,11 +501,11 @@ extern "C" int ann_index_load(const ann_index_desc_t* desc, ann_index_t** out_ha
     h->longest_cluster = d.n;
     h->by_clusters = false;
     h->leaving = 1.0;
-    h->far = h->in_long = 0.0;
+    h->far = h->in_long = h->copied = 0.0;
     const bool mfma_route = d.entry_mode == ANN_ENTRY_ROUTED;
     // A search by whole clusters is a choice: arrays that are not known to be in place on a device (a handle that only routes may have
     // stand-ins) are not looked at, and are searched by gathering.  Loading an index of 10 000 rows takes 40 us with that look, 22
-    // without; with the offsets read back, an allocation of its own and two more copies it took 79.
+    // without; with the offsets read back, an allocation of its own and two more copies it took 79.  A million float rows with 64 edges: 107, 44 without.
     const bool look = mfma_route && ((d.route_c == 1 && d.dtype == ANN_U8 && row_bytes <= kMaxClusterRowBytes) || may_use_table(h)) &&
                       on_device(d.vectors, (size_t)(d.n - 1) * d.row_stride_bytes + row_bytes) &&
                       on_device(d.graph, (size_t)d.n * d.degree * sizeof(int32_t)) &&
@@ -913,6 +951,9 @@ void rank_rows(const ann_index_t* h, int64_t nq, int itopk, int width, int max_i
     // (an option may cut the visited bitmap, and with it the table's rows: a query's keys are read 64 at a time, and how many clusters are too long
     // then has not been looked at)
     if (mean > kMaxRankRows || stride % 64 != 0 || (stride < table_rows(h) && stride < h->longest_cluster)) return;
+    // Copies of a row meet in one bucket, whose rows are put in order one by one: where all rows have two copies 0.77 of the time without ranks, eight 1.02,
+    // twenty 1.32, fifty 1.46.
+    if (h->copied > 0.5) return;
     // Ranking costs as much as there are rows; it saves, a round, what the list and the neighbours cost beyond the search for
     // bits that are set.
     const int64_t rounds = (parents + width - 1) / width;

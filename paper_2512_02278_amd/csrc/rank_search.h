@@ -23,7 +23,8 @@
 // 880 us (1 175; 871 with buckets of one width); where a cluster consists of 50 groups, own noise 0.8, 0.7, 0.3 of the whole, 150 of 0.7, 8 of 0.3, 3 of 0.2:
 // 907, 933, 1 002, 885, 948, 905 (1 178, 1 174, 1 121, 1 161, 1 076, 1 112; with buckets of one width, which left most queries to the other search, 1 264, 2 185,
 // 2 071, 1 577, 1 818, 2 065); 5 000 queries of 768 fp16 elements, 512 neighbours, in the same order: 552 (645) and 566, 569, 591, 555, 577, 567 (649, 645, 641, 642, 621, 629).
-// Copies of rows make crowded buckets: two of each row 910 us (1 185), eight 1 171 (1 145), twenty 1 667 (1 262), fifty 1 949 (1 335).
+// Copies of rows make crowded buckets: two of each row 910 us (1 185), eight 1 171 (1 145), twenty 1 667 (1 262), fifty 1 949 (1 335);
+// where more than half of the rows have a dozen copies nothing is ranked.
 // Of a query's time a third is the ranking; a round is a chain of five LDS round trips and a graph row from L2 or the memory-side
 // cache.  With all places settled and the rows of all ranks in LDS thirteen wavefronts of a compute unit found
 // room instead of eighteen (0.69 ms instead of 0.52 for the search alone); as a first part of beam_search_kernel its registers were those of both (0.60 ms).

@@ -20,7 +20,7 @@ static size_t async_limit = (size_t)1 << 40; /* hipMallocAsync refuses more */
 static char launched[1 << 16];
 static int host_reads; /* copies from memory that is no device memory */
 static struct { dim3 grid, block; size_t lds; hipStream_t stream; } config;
-static uint32_t sample_result[2]; /* what the kernel that looks at a sample of an index finds: edges that leave, keys too far */
+static uint32_t sample_result[3]; /* what the kernel that looks at a sample of an index finds: edges that leave, keys too far, rows with many copies */
 static unsigned threads; /* of the last launch's workgroups */
 static unsigned blocks;  /* how many */
 static size_t most_async; /* largest hipMallocAsync */
@@ -79,12 +79,12 @@ hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3 block, void** args, si
                 if (off[c + 1] - off[c] > *(int64_t*)args[3]) in_long += off[c + 1] - off[c];
             }
             memcpy(*(char**)args[2], &longest, sizeof(longest));
-            memcpy(*(char**)args[2] + 16, &in_long, sizeof(in_long));
+            memcpy(*(char**)args[2] + 24, &in_long, sizeof(in_long));
         }
         if (strstr(kernels[i].name, "sample_clusters_kernel")) {
             sampled = 1;
             char* sample = *(char**)args[4]; /* rows of the longest cluster (8 bytes), then the counts */
-            memcpy(sample + 8, sample_result, sizeof(uint32_t) * 2);
+            memcpy(sample + 8, sample_result, sizeof(sample_result));
         }
     }
     return hipSuccess;
@@ -236,7 +236,7 @@ static void searched_anew(void) {
     void* q = device(40000 * 128);
     int32_t *routes = device(40000 * 4), *ids = device(40000 * 40), *keys = device(40000 * 40);
     for (unsigned i = 0; i < sizeof(calls) / sizeof(calls[0]); ++i) {
-        sample_result[0] = calls[i].leaving, sample_result[1] = calls[i].far;
+        sample_result[0] = calls[i].leaving, sample_result[1] = calls[i].far, sample_result[2] = 0;
         ann_index_t* h = load(&d);
         launched[0] = 0;
         CHECK(ann_search_routed(h, q, calls[i].nq, routes, 10, 184, 4, 200, ids, keys, NULL, NULL) == ANN_OK);
@@ -271,7 +271,7 @@ static void bytes_read(void) {
 
 /* Rows are ranked where few queries will have to be searched otherwise: of a small batch none. */
 static void ranked(void) {
-    const struct { int nq; uint32_t leaving; int long_clusters, window_bits, width, ranks; } calls[] = {
+    const struct { int nq; uint32_t leaving; int long_clusters, window_bits, width, ranks; uint32_t copied; } calls[] = {
         /* 16 777 216 edges, 256 * 64 of them a query */
         {8000, 0, 0, 0, 4, 1}, {8000, 1, 0, 0, 4, 0}, {20000, 0, 0, 0, 4, 1}, {20000, 8, 0, 0, 4, 1}, {20000, 9, 0, 0, 4, 0},
         {20000, 1u << 24, 0, 0, 4, 0},
@@ -279,6 +279,8 @@ static void ranked(void) {
         {8000, 0, 1, 0, 4, 0}, {19999, 0, 1, 0, 4, 0}, {20000, 0, 1, 0, 4, 1}, {20000, 0, 40, 0, 4, 1}, {20000, 0, 60, 0, 4, 0}, {20000, 9, 1, 0, 4, 0},
         /* a visited bitmap that cuts the rows of the table: the longest cluster fits, does so in rows that are not whole 64s, does not fit */
         {8000, 0, 0, 2048, 4, 1}, {8000, 0, 0, 2016, 4, 0}, {8000, 0, 0, 1024, 4, 0}, {20000, 0, 1, 3200, 4, 1}, {20000, 0, 1, 3008, 4, 0},
+        /* 128 rows, of some of which there are copies */
+        {8000, 0, 0, 0, 4, 1, 64}, {8000, 0, 0, 0, 4, 0, 65}, {20000, 0, 0, 0, 4, 0, 128},
         /* rounds of few neighbours */
         {20000, 0, 0, 0, 1, 1}, {20000, 0, 0, 0, 8, 1}};
     void* q = device((size_t)20000 * 384);
@@ -287,7 +289,7 @@ static void ranked(void) {
     for (unsigned i = 0; i < sizeof(calls) / sizeof(calls[0]); ++i) {
         int64_t* off = (int64_t*)d.cluster_offsets;
         for (int c = 0; c < 400; ++c) off[c + 1] = off[c] + (c < calls[i].long_clusters ? 3300 : c < 2 * calls[i].long_clusters ? 700 : 2000);
-        sample_result[0] = calls[i].leaving, sample_result[1] = 0;
+        sample_result[0] = calls[i].leaving, sample_result[1] = 0, sample_result[2] = calls[i].copied;
         ann_index_t* h = load(&d);
         if (calls[i].window_bits) CHECK(ann_index_set_option(h, ANN_OPT_VISITED_WINDOW_BITS, calls[i].window_bits) == ANN_OK);
         launched[0] = 0, most_async = 0;

@@ -1527,7 +1527,7 @@ def test_search_by_rank_gives_the_bits_of_the_gathering_search(torch_cuda, dt, d
     if kind == "many copies":
         for c in range(nc):
             at = int(off[c])
-            for rows in (100, 14, 13, 15, 64, 65, 30) * 2:
+            for rows in (100, 14, 13, 15, 64, 65, 30) * (2 if sizes[c] > 1_000 else 1):
                 if at + rows < off[c + 1]:
                     x[at:at + rows] = x[at]
                 at += rows + 3
@@ -1597,6 +1597,31 @@ def test_edges_that_leave_are_counted_beside_a_long_cluster(torch_cuda, leaving)
         ann.ann_index_set_option(h, ann.ANN_OPT_WAVEFRONTS_PER_QUERY, team)
         names = kernels_of(torch, lambda: got.append(ann.ann_search(h, q, 10, 256, 4, 100, routes=routes)))
         assert ("rank_search_kernel" in names) == (team == 0 and not leaving), names
+        assert ("key_table_kernel" in names) == (team == 0), names
+    ann.ann_free(h)
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1].view(torch.int32), got[1][1].view(torch.int32))
+
+
+@pytest.mark.parametrize("dt,copies,ranked", [("f32", 2, True), ("f32", 11, True), ("f32", 12, False), ("f16", 40, False)])
+def test_rows_of_many_copies_are_not_ranked(torch_cuda, dt, copies, ranked):
+    """The load looks for copies of sampled rows, which the search by rank would have to put in order one by one."""
+    from paper_2512_02278_amd import ann
+
+    torch, dev, dim, nc, size, degree = torch_cuda, "cuda:0", 128, 20, 840, 48
+    gen = torch.Generator(device=dev).manual_seed(13)
+    rows = torch.randint(-3, 4, (nc, -(-size // copies), dim), generator=gen, device=dev).to(torch.float32 if dt == "f32" else torch.float16)
+    rows[:, :, :40] = 0  # rows that are no copies differ late
+    x = rows.repeat_interleave(copies, 1)[:, :size].reshape(nc * size, dim)
+    x = x.reshape(nc, size, dim)[:, torch.randperm(size, generator=torch.Generator().manual_seed(1)).to(dev)].reshape(nc * size, dim).contiguous()
+    off = torch.arange(nc + 1, device=dev) * size
+    g = (off[:-1].repeat_interleave(size)[:, None] + torch.randint(0, size, (nc * size, degree), generator=gen, device=dev)).int()
+    h = ann.ann_index_load(x, g, n_entry=32, entry_mode=1, seed=4, centroids=x[:nc].contiguous(), cluster_offsets=off, route_c=1)
+    routes = torch.randint(0, nc, (4_200,), generator=gen, device=dev, dtype=torch.int32)
+    q, got = x[torch.randint(0, nc * size, (4_200,), generator=gen, device=dev)], []
+    for team in (0, 1):
+        ann.ann_index_set_option(h, ann.ANN_OPT_WAVEFRONTS_PER_QUERY, team)
+        names = kernels_of(torch, lambda: got.append(ann.ann_search(h, q, 10, 128, 4, 100, routes=routes)))
+        assert ("rank_search_kernel" in names) == (team == 0 and ranked), names
         assert ("key_table_kernel" in names) == (team == 0), names
     ann.ann_free(h)
     assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1].view(torch.int32), got[1][1].view(torch.int32))
